@@ -135,6 +135,58 @@ static void launch_flat_variant(uint32_t v, dim3 g, dim3 b, hipStream_t s, const
     else launch_flat_sp<PACK, false>(v, g, b, s, a, mur);
 }
 
+template <bool PACK, bool NTL, int SP>
+static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, hipStream_t s, const CopyArgs &a, uint32_t x, uint32_t n_tiles) {
+    if (flat) hipLaunchKernelGGL((kvl_any_flat_kernel<PACK, NTL, SP>), g, b, 0, s, a, x);
+    else if (walk) hipLaunchKernelGGL((kvl_any_tile_kernel<PACK, NTL, SP, true>), g, b, 0, s, a, x, n_tiles);
+    else hipLaunchKernelGGL((kvl_any_tile_kernel<PACK, NTL, SP, false>), g, b, 0, s, a, x, n_tiles);
+}
+
+// Rows or addresses that are not multiples of 16 bytes (the planes of a launch have one row size).
+//   flat or tiled: a descriptor of up to kAnyFlatWindows vectors leaves too much of its last 256-lane tile
+//     idle (300 MB hops: 132-byte rows by 16, 133 vectors, 250 -> 220 us flat; 260 by 16, 261 vectors, two
+//     tiles, 309 -> 225); beyond it a tile per 256 lanes is the better (132 by 64, 530 vectors: 215 against
+//     245 flat).  A flat workgroup has 1024 lanes (1026-byte rows by 1: 361 us at 256, 329 at 512, 324), a
+//     tile of a descriptor below two 256-lane tiles 128 (1026 by 4: 377 us at 256, 286 at 128).
+//   cache policy: a layer that the on-die cache can hold between the gather and the scatter is written
+//     with sc1 stores and read back with plain loads (132 by 64, hop of 80 MB: 65 us against 74 with
+//     non-temporal accesses throughout; 1026 by 16, 120 MB: 82 against 95), a larger one passes it by (300 MB:
+//     226 -> 214 and 268 -> 251 us; 800 MB of 657-byte rows: 647 -> 634).
+static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uint32_t planes, bool far_host,
+                       hipStream_t stream) {
+    const uint64_t unit_bytes = (uint64_t)plan->max_unit_rows * a.row_elems[a.plane_begin];
+    const uint64_t windows = (unit_bytes + 30) / 16;       // 16-byte windows a span of that size can touch
+    const bool flat = windows <= kAnyFlatWindows;
+    uint32_t threads = plan->tuning.block_threads;
+    if (!plan->threads_chosen) threads = flat ? 1024 : unit_bytes + 127 <= 2 * 256 * 16 ? 128 : 256;
+    uint64_t cap = plan->tuning.max_groups;
+    if (!cap && far_host) cap = 2 * kHostSideGroups;       // (one vector per lane: see kHostSideGroups)
+    const uint64_t per_unit = (unit_bytes + 127 + 16ull * threads - 1) / (16ull * threads);
+    uint64_t per_launch = flat ? ((1ull << 32) - threads) / windows : (uint64_t)INT32_MAX / per_unit;
+    if (flat && plan->tuning.max_groups)
+        per_launch = std::min<uint64_t>(per_launch, (uint64_t)plan->tuning.max_groups * threads / windows);
+    per_launch = std::max<uint64_t>(1, per_launch);
+    const bool kept = plan->payload_bytes <= kCachedLayerBytes;
+    for (uint64_t first = 0; first < a.n_units; first += per_launch) {
+        CopyArgs part = a;
+        part.unit_begin = a.unit_begin + (uint32_t)first;
+        part.n_units = (uint32_t)std::min<uint64_t>(per_launch, a.n_units - first);
+        const uint64_t tiles = part.n_units * per_unit;
+        bool walk = false;
+        const uint32_t groups = flat ? (uint32_t)((part.n_units * windows + threads - 1) / threads)
+                                     : launch_groups(tiles, threads, (uint32_t)cap, &walk);
+        const uint32_t x = (uint32_t)(flat ? windows : per_unit);
+        dim3 grid(groups, planes), block(threads);
+        if (pack) {
+            if (kept) launch_any_one<true, true, 2>(flat, walk, grid, block, stream, part, x, (uint32_t)tiles);
+            else launch_any_one<true, true, 1>(flat, walk, grid, block, stream, part, x, (uint32_t)tiles);
+        } else {
+            if (kept) launch_any_one<false, false, 3>(flat, walk, grid, block, stream, part, x, (uint32_t)tiles);
+            else launch_any_one<false, true, 1>(flat, walk, grid, block, stream, part, x, (uint32_t)tiles);
+        }
+    }
+}
+
 int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_t unit_end,
                  uint32_t plane_begin, uint32_t plane_end,
                  void *const *pool_planes, const uintptr_t *xfer_plane, hipStream_t stream, bool far_host) {
@@ -205,16 +257,7 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
     }
     dim3 block(threads);
     if (!vec) {
-        // one workgroup per descriptor; a launch holds fewer than 2^32 lanes
-        const uint64_t per_launch = kMaxLanesPerLaunch / threads;
-        for (uint64_t first = 0; first < a.n_units; first += per_launch) {
-            CopyArgs part = a;
-            part.unit_begin = a.unit_begin + (uint32_t)first;
-            part.n_units = (uint32_t)std::min<uint64_t>(per_launch, a.n_units - first);
-            dim3 grid(part.n_units, plane_end - plane_begin);
-            if (pack) hipLaunchKernelGGL(kvl_bytes_kernel<true>, grid, block, 0, stream, part);
-            else hipLaunchKernelGGL(kvl_bytes_kernel<false>, grid, block, 0, stream, part);
-        }
+        launch_any(plan, pack, a, plane_end - plane_begin, far_host, stream);
     } else if (v & 128u) {
         // lane indices are 32 bits: split the descriptors over launches where they would not fit
         // (tuning.max_groups, if given, lowers the workgroups per launch further)
