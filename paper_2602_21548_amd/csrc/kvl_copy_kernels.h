@@ -28,21 +28,20 @@
 //   flat    (code bit 7, with ntl and sp only) no tiles: lane g of the launch takes vector
 //           g mod m of descriptor g div m, m = vectors of the largest descriptor; for
 //           descriptors far smaller than a workgroup (token-granular pools)
-// The default is the tiled form, or the flat one when the largest descriptor fills less
-// than half a workgroup: on 2 M single-token blocks of 1152 bytes the tiled form leaves
-// 72 % of its lanes idle and the flat one keeps all of them busy (gather 3.2 -> 5.3 TB/s;
-// the scatter stays at 3.3-3.7 TB/s in every form: random 1152-byte writes are the
-// memory's limit there, 1 KiB ones reach 4.5-4.7).
+// The default is the tiled form, or the row-map form (kvl_rows_kernel, for plans that have a
+// map) where takes_row_map says so; without a map, descriptors of less than half a workgroup
+// go flat: on single-token blocks of 1152 bytes the tiled form leaves 72 % of its lanes idle.
 // Measured on MI355X (5.2 GB of 72 KiB blocks in random order), the tiled form
 // with one vector per lane and 256-lane workgroups is the fastest: it leaves no
 // dependency between a lane's memory operations and lets the hardware fill the
 // memory system with resident wavefronts.  Cache policies, measured with gather
 // and scatter alternating as they do in use: the gather (random reads,
 // sequential writes) runs best with non-temporal loads and sc1 stores; the
-// scatter (sequential reads, random writes) with sc1+nt stores, and with
-// non-temporal loads only if the rows are multiples of 128 bytes (otherwise
-// neighbouring wavefronts share source lines, and a non-temporal load fetches
-// the shared line twice).  Together the policies are worth 5-15 % over plain
+// scatter (sequential reads, random writes) with sc1+nt stores and non-temporal
+// loads, plain ones where rows that are not multiples of 128 bytes make neighbouring
+// wavefronts share source lines and the layer is small enough for the on-die cache
+// still to hold them (kPlainReadBackBytes), or so large that nothing of it is held
+// (kPassByBytes; the gather's stores are sc1+nt there).  Together the policies are worth 5-15 % over plain
 // loads and stores.  With rows that are not multiples of 128 bytes the tiles are
 // also lined up with the destination's cache lines (worth 5-9 % on 656-byte rows).
 #pragma once
@@ -53,6 +52,7 @@ namespace kvl {
 
 // default variant codes (see the list above) and the plain copy's policies
 constexpr uint32_t kDefaultPackCode = 2u | 4u | (2u << 3);   // tile x1, nt loads, sc1 stores
+constexpr uint32_t kDefaultPackCodePassBy = 2u | 4u | (3u << 3);  // tile x1, nt loads, sc1+nt stores
 constexpr uint32_t kDefaultUnpackCode = 2u | 4u | (3u << 3);    // tile x1, nt loads, sc1+nt stores
 constexpr uint32_t kDefaultUnpackCodeOddRows = 2u | (3u << 3);  // tile x1, plain loads, sc1+nt stores
 constexpr uint32_t kFlatPackCode = 128u | 4u | (2u << 3);       // flat, nt loads, sc1 stores
@@ -363,6 +363,54 @@ __global__ void __launch_bounds__(1024) kvl_flat_kernel(const CopyArgs a, uint32
     gsrc_t src = (gsrc_t)((PACK ? a.pool[p] : a.xfer[p]) + (uint64_t)(PACK ? u.pool_row : u.xfer_row) * row * 16u);
     gdst_t dst = (gdst_t)((PACK ? a.xfer[p] : a.pool[p]) + (uint64_t)(PACK ? u.xfer_row : u.pool_row) * row * 16u);
     store16<SP>(dst + off, load16<NTL>(src + off));
+}
+
+// Row-map form for descriptors of a few rows: the transfer side is dense, so the launch is laid out over it
+// (lane g moves vector g of the range, lined up with the transfer buffer's 128-byte lines) and each row's
+// place in the pool comes from a table with one entry per row, made from the descriptors when they are
+// uploaded.  However ragged the descriptors are, no lane idles.  A wavefront's 64 vectors lie in at most K
+// rows: their entries are fetched through the scalar cache and each lane picks its own (K == 0, for rows below
+// 256 bytes: a vector load per lane).  A million single-row blocks of 1152 bytes, 1.17 GB a layer, gather + scatter:
+// 1122 us (tiled, because one chance pair of neighbours made the largest descriptor two rows, + flat) -> 763 us (6.1 TB/s).
+typedef const uint32_t __attribute__((address_space(4))) *cmap_t;
+
+template <bool PACK, bool NTL, int SP, int K>
+__global__ void __launch_bounds__(1024) kvl_rows_kernel(const CopyArgs a, const uint32_t *row_map, uint32_t row_begin,
+                                                        uint32_t n_vecs) {
+    const uint32_t p = a.plane_begin + blockIdx.y;
+    const uint32_t row = a.row_elems[p];
+    const uintptr_t xfer = a.xfer[p] + (uint64_t)row_begin * row * 16u;
+    const uint32_t lead = (uint32_t)(xfer >> 4) & 7u;
+    const uint32_t pos = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t g = pos - lead;
+    if (pos < lead || g >= n_vecs) return;
+    cmap_t map = (cmap_t)(uintptr_t)(row_map + row_begin);
+    uint32_t pool_row, off;             // the lane's row in the pool and its vector inside that row
+    if (K == 0) {
+        const uint32_t r = g / row;
+        off = g - r * row;
+        pool_row = map[r];
+    } else {
+        const uint32_t first = __builtin_amdgcn_readfirstlane(g);       // of the wavefront's lanes with work
+        const uint32_t r = first / row;
+        uint32_t entry[K > 0 ? K : 1];
+#pragma unroll
+        for (int k = 0; k < K; ++k) entry[k] = map[r + k];              // (the table is padded by 8 entries)
+        off = g - r * row;
+        pool_row = entry[0];
+        uint32_t skip = 0;
+#pragma unroll
+        for (int k = 1; k < K; ++k) {
+            const bool past = off >= (uint32_t)k * row;
+            pool_row = past ? entry[k] : pool_row;
+            skip = past ? (uint32_t)k * row : skip;
+        }
+        off -= skip;
+    }
+    const uintptr_t pool = a.pool[p] + ((uint64_t)pool_row * row + off) * 16u;
+    gsrc_t src = (gsrc_t)(PACK ? pool : xfer + (uint64_t)g * 16u);
+    gdst_t dst = (gdst_t)(PACK ? xfer + (uint64_t)g * 16u : pool);
+    store16<SP>(dst, load16<NTL>(src));
 }
 
 // Rows or addresses that are not multiples of 16 bytes.  The vector unit takes 16-byte accesses at any

@@ -26,6 +26,12 @@ struct kvl_plan_s {
     std::vector<uint32_t> block_row_lo, block_row_hi;   // with it: rows [lo, hi) of each block that the plan moves
     kvl_unit_t *d_units = nullptr;               // device copy (absent for KVL_HOST_ONLY)
     size_t d_units_capacity = 0;                 // bytes of the cached buffer d_units lives in
+    uint32_t *d_row_map = nullptr;               // behind the descriptors in the same buffer, where they are small
+                                                 // (see kvl_rows_kernel): the pool row of every transfer row
+    mutable hipEvent_t map_event = nullptr;      // with it: recorded after the kernel that makes the map,
+    mutable bool map_pending = false;            // whether that kernel may still have to run, and the stream (any
+    mutable hipStream_t map_waited = nullptr;    // while map_stream_known) that has been made to wait for it last
+    mutable bool map_stream_known = false;
     int device = -1;
     // One event per stream on which kernels that read d_units were enqueued (the caller's streams and
     // the lanes), re-recorded after every such launch: once all of them have fired no kernel reads the
@@ -76,6 +82,44 @@ inline uint32_t launch_groups(uint64_t work, uint32_t threads, uint32_t cap, boo
     return (uint32_t)(*walk ? most : work);
 }
 
+// Rows that are no multiple of a 128-byte line: up to this payload the scatter reads the transfer buffer with plain
+// loads (the on-die cache still has it), beyond it with non-temporal ones (64-token blocks of 656-byte rows, hop:
+// 100 MB 63 us against 73; 140 MB 107 against 104; 1 GB 771 against 748; 576-byte rows, 1 GB, 745 against 702).
+// From some GB up the plain loads, with a gather that stores past the cache, are ahead again (12 GB: 7469 us, with
+// such a gather 7432, against 7493; 5 GB 3452 against 3470; 1 GB 752 against 745).
+constexpr uint64_t kPlainReadBackBytes = 112u << 20, kPassByBytes = 4ull << 30;
+
+// Tiles of a launch by descriptors: the default workgroup, halved where that leaves clearly fewer lanes without
+// work (32-token blocks of 656-byte rows are 5.1 tiles of 256 lanes: 5.1 TB/s; 10.3 tiles of 128 lanes: 5.8).
+inline uint32_t tile_threads(uint64_t unit_vecs) {
+    auto idle = [&](uint64_t t) { return 1.0 - (double)unit_vecs / (double)((unit_vecs + t - 1) / t * t); };
+    return idle(kDefaultBlockThreads) - idle(kDefaultBlockThreads / 2) > 0.07 ? kDefaultBlockThreads / 2 : kDefaultBlockThreads;
+}
+
+// Whether a launch over planes of this row size is laid out over the transfer rows (kvl_rows_kernel) instead of over
+// the descriptors' tiles, which have the size of the largest descriptor's.  Measured on hops of one plane, us a hop,
+// tiles / rows:
+//  - tiles that would leave lanes idle, and descriptors of less than a workgroup.  1 GB layers: 1152-byte rows by 1
+//    (72 vectors) 747 / 579, by 4 (1.1 tiles) 630 / 580, by 6 634 / 576, by 8 (2.25 tiles) 577 / 575, by 10 569 / 574;
+//    2048 by 1 779 / 667, by 2 (one full tile) 660 / 666; 576 by 64 (9 tiles and the line-up) 706 / 666.  The scatter
+//    into rows that are no multiple of a line writes them in halves this way (a tile begins on a line) and wants a
+//    worse filled tile before it gains: scatter alone, 656 by 32 (85 % busy) +2 %, 272 by 16 (53 %) -2 %.
+//  - a scatter whose layer is about the size of the on-die cache, tiles / rows: 656 by 64, 100 MB 63 / 65 (plain
+//    loads), 140 MB 103 / 95, 300 MB 194 / 172, 400 MB 295 / 292, 600 MB 404 / 416; 2048 by 64, 240 MB 142 / 141,
+//    300 MB 162 / 155, 400 MB 239 / 227, 600 MB 343 / 331, 1 GB 604 / 602.
+inline bool takes_row_map(const kvl_plan_s *plan, uint32_t row_bytes, bool pack) {
+    if (plan->paired || !plan->vec16 || plan->units.empty() || plan->max_unit_rows > 4096) return false;
+    const bool lines = row_bytes % 128 == 0;
+    const uint64_t row = row_bytes / 16, largest = plan->max_unit_rows * row;
+    const uint64_t t = tile_threads(largest), tiles = (largest + (lines ? 0 : 7) + t - 1) / t;
+    const double average = (double)plan->hit_tokens * (double)row / (double)plan->units.size();
+    const double busy = average / (double)(tiles * t);
+    if (average < 200 || busy < (pack || lines ? 0.91 : 0.80)) return true;
+    if (pack || row_bytes < 48) return false;
+    const uint64_t mb = plan->payload_bytes >> 20;
+    return lines ? mb >= 256 && mb < 576 : plan->payload_bytes > kPlainReadBackBytes && mb < 432;
+}
+
 // Cut [0, n_units) of one plane into chunks of at most chunk_bytes.
 int make_chunks(const kvl_plan_t *plan, uint64_t chunk_bytes, std::vector<kvl_chunk_t> &out);
 
@@ -92,6 +136,8 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
 bool is_host_memory(const kvl_plan_t *plan, const void *ptr);
 
 int upload_units(kvl_plan_t *plan);
+// whether a launch on `stream` may read plan->d_row_map; orders the stream after the map's making if that is needed
+bool row_map_ready(const kvl_plan_t *plan, hipStream_t stream);
 // a kernel reading the plan's descriptors has just been enqueued on `stream`
 void mark_launch(const kvl_plan_t *plan, hipStream_t stream);
 void drop_stream_events(const kvl_plan_t *plan);

@@ -136,6 +136,16 @@ static void launch_flat_variant(uint32_t v, dim3 g, dim3 b, hipStream_t s, const
 }
 
 template <bool PACK, bool NTL, int SP>
+static void launch_rows(dim3 g, dim3 b, hipStream_t s, const CopyArgs &a, const uint32_t *map, uint32_t row_begin,
+                        uint32_t n_vecs) {
+    const uint32_t row = a.row_elems[a.plane_begin];
+    if (row >= 64) hipLaunchKernelGGL((kvl_rows_kernel<PACK, NTL, SP, 2>), g, b, 0, s, a, map, row_begin, n_vecs);
+    else if (row >= 32) hipLaunchKernelGGL((kvl_rows_kernel<PACK, NTL, SP, 3>), g, b, 0, s, a, map, row_begin, n_vecs);
+    else if (row >= 16) hipLaunchKernelGGL((kvl_rows_kernel<PACK, NTL, SP, 5>), g, b, 0, s, a, map, row_begin, n_vecs);
+    else hipLaunchKernelGGL((kvl_rows_kernel<PACK, NTL, SP, 0>), g, b, 0, s, a, map, row_begin, n_vecs);
+}
+
+template <bool PACK, bool NTL, int SP>
 static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, hipStream_t s, const CopyArgs &a, uint32_t x, uint32_t n_tiles) {
     if (flat) hipLaunchKernelGGL((kvl_any_flat_kernel<PACK, NTL, SP>), g, b, 0, s, a, x);
     else if (walk) hipLaunchKernelGGL((kvl_any_tile_kernel<PACK, NTL, SP, true>), g, b, 0, s, a, x, n_tiles);
@@ -233,8 +243,9 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         bool rows_128 = true;       // every span starts on a 128-byte line of the transfer buffer
         for (uint32_t p = plane_begin; p < plane_end; ++p)
             rows_128 = rows_128 && plan->layout.row_bytes[p] % 128 == 0;
-        if (pack) v = kDefaultPackCode;
-        else v = rows_128 ? kDefaultUnpackCode : kDefaultUnpackCodeOddRows;
+        const uint64_t n = plan->payload_bytes;
+        if (pack) v = rows_128 || n < kPassByBytes ? kDefaultPackCode : kDefaultPackCodePassBy;
+        else v = rows_128 || (n > kPlainReadBackBytes && n < kPassByBytes) ? kDefaultUnpackCode : kDefaultUnpackCodeOddRows;
         // across the host link: two vectors per lane, so that the few workgroups of the thin
         // form (kHostSideGroups) keep enough bytes in flight
         if (far_host) v |= 3u;
@@ -243,20 +254,30 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
     uint32_t widest = 0;        // vectors of the largest descriptor, over the planes of this launch
     for (uint32_t p = plane_begin; p < plane_end; ++p) widest = std::max(widest, a.row_elems[p]);
     const uint64_t unit_vecs = (uint64_t)plan->max_unit_rows * widest;
-    // Descriptors that fill their last tile badly: with the default workgroup size, halve it where that
-    // leaves clearly fewer lanes without work (32-token blocks of 656-byte rows are 5.1 tiles of 256 lanes:
-    // 5.1 TB/s; 10.3 tiles of 128 lanes: 5.8).
-    if (vec && !plan->threads_chosen && !plan->tuning.variant && threads == kDefaultBlockThreads) {
-        auto idle = [&](uint64_t t) { return 1.0 - (double)unit_vecs / (double)((unit_vecs + t - 1) / t * t); };
-        if (idle(threads) - idle(threads / 2) > 0.07) threads /= 2;
-    }
+    if (vec && !plan->threads_chosen && !plan->tuning.variant) threads = tile_threads(unit_vecs);
     // descriptors that fill less than half a workgroup: deal the lanes out without tiles
     if (vec && !plan->tuning.variant && unit_vecs * 2 <= plan->tuning.block_threads) {
         v = pack ? kFlatPackCode : kFlatUnpackCode;
         threads = plan->tuning.block_threads;
     }
     dim3 block(threads);
-    if (!vec) {
+    const kvl_unit_t &u_first = plan->units[unit_begin], &u_last = plan->units[unit_end - 1];
+    if (vec && !plan->tuning.variant && !plan->tuning.max_groups && !far_host && plan->d_row_map &&
+        takes_row_map(plan, plan->layout.row_bytes[plane_begin], pack) && row_map_ready(plan, stream)) {
+        // the launch is laid out over the transfer rows of these descriptors; its lanes are numbered with 32 bits
+        if (!plan->threads_chosen) threads = kDefaultBlockThreads;
+        const uint64_t rows = (uint64_t)u_last.xfer_row + u_last.n_rows - u_first.xfer_row;
+        const uint64_t per_launch = std::max<uint64_t>(1, ((1ull << 32) - threads - 8) / widest);
+        const bool lines = plan->layout.row_bytes[plane_begin] % 128 == 0;
+        for (uint64_t first = 0; first < rows; first += per_launch) {
+            const uint32_t n = (uint32_t)(std::min<uint64_t>(per_launch, rows - first) * widest);
+            const uint32_t row_begin = (uint32_t)(u_first.xfer_row + first);
+            dim3 grid((uint32_t)(((uint64_t)n + 7 + threads - 1) / threads), plane_end - plane_begin);
+            if (pack) launch_rows<true, true, 2>(grid, dim3(threads), stream, a, plan->d_row_map, row_begin, n);
+            else if (lines) launch_rows<false, true, 3>(grid, dim3(threads), stream, a, plan->d_row_map, row_begin, n);
+            else launch_rows<false, true, 1>(grid, dim3(threads), stream, a, plan->d_row_map, row_begin, n);
+        }
+    } else if (!vec) {
         launch_any(plan, pack, a, plane_end - plane_begin, far_host, stream);
     } else if (v & 128u) {
         // lane indices are 32 bits: split the descriptors over launches where they would not fit

@@ -59,6 +59,7 @@ struct CachedBuffer {
 struct RetiredBuffer {
     CachedBuffer buf;
     std::vector<hipEvent_t> events;     // all fired: no kernel reads the buffer any more
+    hipEvent_t map_event;               // (or null) fired: the kernel that wrote the row map into it has finished
 };
 struct PooledLane {
     hipStream_t stream;
@@ -68,6 +69,7 @@ std::mutex g_cache_mutex;               // guards everything below
 std::vector<CachedBuffer> g_cache;
 std::vector<RetiredBuffer> g_retired;
 std::vector<std::pair<hipEvent_t, int>> g_events;       // spare events, with their device
+std::vector<std::pair<hipEvent_t, int>> g_map_events;   // spare events that other streams wait on (row maps)
 std::vector<PooledLane> g_lanes;
 constexpr size_t kCacheEntries = 16;
 constexpr size_t kCacheBytes = 256u << 20;      // never keep more than this much idle
@@ -82,28 +84,31 @@ size_t round_capacity(size_t bytes) {
 }
 
 // with g_cache_mutex held and `device` current
-hipEvent_t take_event(int device) {
-    for (size_t i = 0; i < g_events.size(); ++i) {
-        if (g_events[i].second == device) {
-            hipEvent_t e = g_events[i].first;
-            g_events.erase(g_events.begin() + (long)i);
+hipEvent_t take_event(int device, bool map = false) {
+    auto &spare = map ? g_map_events : g_events;
+    for (size_t i = 0; i < spare.size(); ++i) {
+        if (spare[i].second == device) {
+            hipEvent_t e = spare[i].first;
+            spare.erase(spare.begin() + (long)i);
             return e;
         }
     }
     // The events only say "the kernels before this point have finished": no timing, and no
-    // system-scope cache flush when they fire (nothing is read back through them).
+    // system-scope cache flush when they fire (nothing is read back through them; a map's
+    // event is followed by kernels that read the map).
     hipEvent_t e = nullptr;
-    if (hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
+    if (hipEventCreateWithFlags(&e, hipEventDisableTiming | (map ? 0u : hipEventDisableSystemFence)) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
     }
     return e;
 }
 
-void give_event(hipEvent_t e, int device) {
-    if (g_events.size() < kSpareEvents) {
+void give_event(hipEvent_t e, int device, bool map = false) {
+    auto &spare = map ? g_map_events : g_events;
+    if (spare.size() < kSpareEvents) {
         try {
-            g_events.emplace_back(e, device);
+            spare.emplace_back(e, device);
             return;
         } catch (const std::bad_alloc &) {
         }
@@ -130,19 +135,20 @@ void reap_retired(bool wait) {
     for (size_t i = 0; i < g_retired.size();) {
         RetiredBuffer &r = g_retired[i];
         bool done = true;
-        for (hipEvent_t e : r.events) {
+        auto pending = [wait](hipEvent_t e) {
             const hipError_t q = wait ? hipEventSynchronize(e) : hipEventQuery(e);
-            if (q == hipErrorNotReady) {
-                done = false;
-                break;
-            }
+            if (q == hipErrorNotReady) return true;
             if (q != hipSuccess) (void)hipGetLastError();       // a broken event cannot hold the buffer for ever
-        }
+            return false;
+        };
+        if (r.map_event) done = !pending(r.map_event);
+        for (size_t k = 0; k < r.events.size() && done; ++k) done = !pending(r.events[k]);
         if (!done) {
             ++i;
             continue;
         }
         for (hipEvent_t e : r.events) give_event(e, r.buf.device);
+        if (r.map_event) give_event(r.map_event, r.buf.device, true);
         keep_or_free(r.buf);
         g_retired.erase(g_retired.begin() + (long)i);
     }
@@ -250,9 +256,11 @@ static hipError_t descriptor_alloc(void **out, size_t bytes, size_t *capacity, i
 // The plan is going away: its descriptor array may be reused once the events recorded after its
 // launches have fired.  No stream is touched here.
 static void descriptor_release(const kvl_plan_t *plan) {
-    RetiredBuffer r{CachedBuffer{plan->d_units, plan->d_units_capacity, plan->device}, {}};
-    if (plan->flags & KVL_CALLER_SYNCS) {
+    RetiredBuffer r{CachedBuffer{plan->d_units, plan->d_units_capacity, plan->device}, {}, plan->map_event};
+    if (plan->flags & KVL_CALLER_SYNCS) {               // (its map was waited for when it was made)
         std::lock_guard<std::mutex> lock(g_cache_mutex);
+        if (plan->map_event) give_event(plan->map_event, plan->device, true);
+        plan->map_event = nullptr;
         keep_or_free(r.buf);
         return;
     }
@@ -268,10 +276,13 @@ static void descriptor_release(const kvl_plan_t *plan) {
                 tracked = false;
             }
         }
-        if (r.buf.ptr)
+        if (r.buf.ptr) {
             for (const auto &se : plan->stream_events) give_event(se.second, plan->device);
+            if (plan->map_event) give_event(plan->map_event, plan->device, true);
+        }
     }
     plan->stream_events.clear();
+    plan->map_event = nullptr;
     if (r.buf.ptr) {
         // some launch could not be followed: fall back to what a device free would have done
         int current = plan->device;
@@ -305,6 +316,7 @@ bool is_host_memory(const kvl_plan_t *plan, const void *ptr) {
 namespace {
 struct Uploader {
     hipStream_t stream = nullptr;
+    hipStream_t map_stream = nullptr;   // row maps are made here, behind nobody's copies
     void *bounce = nullptr;         // pinned
     size_t capacity = 0;
 };
@@ -313,11 +325,94 @@ Uploader g_uploaders[64];
 constexpr size_t kBounceLimit = 64u << 20;      // larger descriptor arrays are copied from pageable memory
 }  // namespace
 
+// The row map (see kvl_rows_kernel), made on the device out of the descriptors just uploaded: 16 lanes write a
+// descriptor's entries.  A million single-row descriptors take about 10 us.
+__global__ void __launch_bounds__(256) kvl_row_map_kernel(const kvl_unit_t *units, uint32_t n_units, uint32_t *row_map) {
+    const uint64_t t = (uint64_t)blockIdx.x * 256u + threadIdx.x;
+    if ((t >> 4) >= n_units) return;
+    const kvl_unit_t u = units[t >> 4];
+    for (uint32_t i = t & 15u; i < u.n_rows; i += 16) row_map[u.xfer_row + i] = u.pool_row + i;
+}
+
+// (The bounds keep its launch below 2^32 lanes and the table below 1 GiB.)
+static bool wants_row_map(const kvl_plan_t *plan) {
+    if (plan->units.size() >= (1u << 28) || plan->hit_tokens >= (1u << 28)) return false;
+    for (uint32_t p = 0; p < plan->layout.n_planes; ++p) {
+        const uint32_t row = plan->layout.row_bytes[p];
+        if ((plan->flags & KVL_GATHER) && takes_row_map(plan, row, true)) return true;
+        if ((plan->flags & KVL_SCATTER) && takes_row_map(plan, row, false)) return true;
+    }
+    return false;
+}
+
+// Enqueue the making of the plan's row map; its first user waits for it (row_map_ready).  The call does not: beside
+// a busy device the kernel takes its turn, and a plan is made under the kernels of the batch before.  If anything
+// fails the plan goes without a map.
+static void start_row_map(kvl_plan_t *plan, hipStream_t &stream) {
+    if (!stream && hipStreamCreateWithFlags(&stream, hipStreamNonBlocking) != hipSuccess) {
+        stream = nullptr;
+        (void)hipGetLastError();
+        return;
+    }
+    hipEvent_t ev;
+    {
+        std::lock_guard<std::mutex> lock(g_cache_mutex);
+        ev = take_event(plan->device, true);
+    }
+    if (!ev) return;
+    const uint32_t n = (uint32_t)plan->units.size();
+    uint32_t *map = reinterpret_cast<uint32_t *>(plan->d_units + n);
+    hipLaunchKernelGGL(kvl_row_map_kernel, dim3((uint32_t)(((uint64_t)n * 16 + 255) / 256)), dim3(256), 0, stream,
+                       plan->d_units, n, map);
+    bool ok = hipGetLastError() == hipSuccess;
+    ok = hipEventRecord(ev, stream) == hipSuccess && ok;
+    // a plan whose caller answers for its lifetime may be dropped before its first launch
+    if (!ok || (plan->flags & KVL_CALLER_SYNCS)) ok = hipStreamSynchronize(stream) == hipSuccess && ok;
+    if (ok) {
+        plan->d_row_map = map;
+        plan->map_event = ev;
+        plan->map_pending = !(plan->flags & KVL_CALLER_SYNCS);
+    } else {
+        (void)hipGetLastError();
+        std::lock_guard<std::mutex> lock(g_cache_mutex);
+        give_event(ev, plan->device, true);
+    }
+}
+
+bool row_map_ready(const kvl_plan_t *plan, hipStream_t stream) {
+    if (!plan->map_pending) return true;
+    if (plan->map_stream_known && plan->map_waited == stream) return true;
+    // an event from outside may not be waited for in a capture: such a launch goes without the map
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (hipEventQuery(plan->map_event) == hipSuccess) {
+        plan->map_pending = false;
+        return true;
+    }
+    (void)hipGetLastError();
+    if (hipStreamWaitEvent(stream, plan->map_event, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    plan->map_waited = stream;
+    plan->map_stream_known = true;
+    return true;
+}
+
 int upload_units(kvl_plan_t *plan) {
     hipError_t e = hipGetDevice(&plan->device);
     if (e == hipSuccess && !plan->units.empty()) {
         const size_t bytes = plan->units.size() * sizeof(kvl_unit_t);
-        e = descriptor_alloc((void **)&plan->d_units, bytes, &plan->d_units_capacity, plan->device);
+        size_t map_bytes = wants_row_map(plan) ? (plan->hit_tokens + 8) * sizeof(uint32_t) : 0;
+        e = descriptor_alloc((void **)&plan->d_units, bytes + map_bytes, &plan->d_units_capacity, plan->device);
+        if (e != hipSuccess && map_bytes) {             // no room for the table: the descriptors alone will do
+            (void)hipGetLastError();
+            map_bytes = 0;
+            e = descriptor_alloc((void **)&plan->d_units, bytes, &plan->d_units_capacity, plan->device);
+        }
         if (e == hipSuccess && plan->device >= 0 && plan->device < 64) {
             std::lock_guard<std::mutex> lock(g_upload_mutex);
             Uploader &u = g_uploaders[plan->device];
@@ -339,6 +434,7 @@ int upload_units(kvl_plan_t *plan) {
                 }
                 e = hipMemcpyAsync(plan->d_units, from, bytes, hipMemcpyHostToDevice, u.stream);
                 if (e == hipSuccess) e = hipStreamSynchronize(u.stream);
+                if (e == hipSuccess && map_bytes) start_row_map(plan, u.map_stream);
             }
         } else if (e == hipSuccess) {
             e = hipMemcpy(plan->d_units, plan->units.data(), bytes, hipMemcpyHostToDevice);
@@ -772,13 +868,14 @@ int kvl_check_buffer(const void *ptr, uint64_t bytes, int allow_host) {
 void kvl_release_cached_memory(void) {
     std::vector<kvl::CachedBuffer> drop;
     std::vector<kvl::PooledLane> lanes;
-    std::vector<std::pair<hipEvent_t, int>> events;
+    std::vector<std::pair<hipEvent_t, int>> events, map_events;
     {
         std::lock_guard<std::mutex> lock(kvl::g_cache_mutex);
         kvl::reap_retired(true);                    // waits for the kernels of destroyed plans, nothing else
         drop.swap(kvl::g_cache);
         lanes.swap(kvl::g_lanes);
         events.swap(kvl::g_events);
+        map_events.swap(kvl::g_map_events);
     }
     for (const kvl::CachedBuffer &b : drop) (void)hipFree(b.ptr);
     for (const kvl::PooledLane &l : lanes) {
@@ -786,11 +883,13 @@ void kvl_release_cached_memory(void) {
         (void)hipStreamDestroy(l.stream);
     }
     for (const auto &e : events) (void)hipEventDestroy(e.first);
+    for (const auto &e : map_events) (void)hipEventDestroy(e.first);
     // the upload streams and their pinned staging buffers come back on the next plan
     std::lock_guard<std::mutex> lock(kvl::g_upload_mutex);
     for (kvl::Uploader &u : kvl::g_uploaders) {
         if (u.bounce) (void)hipHostFree(u.bounce);
         if (u.stream) (void)hipStreamDestroy(u.stream);
+        if (u.map_stream) (void)hipStreamDestroy(u.map_stream);
         u = kvl::Uploader{};
     }
 }

@@ -61,3 +61,53 @@ def test_rows_and_addresses_off_the_16_byte_grid(bs, row, x_off, pool_off):
 @pytest.mark.parametrize("bs,row", [(1, 57), (16, 132), (64, 132)])
 def test_odd_rows_split_over_launches_and_walked(bs, row, tuning):
     hop_at(W.tiny(940 + row, 5, bs, (row, row, 16), 120, 20 * bs), 3, 1, **tuning)
+
+
+# rows of 1, 15, 16, 31, 32, 63, 64, 65 and 72 vectors (how many rows a wavefront's 64 vectors can touch changes at
+# 16, 32 and 64), one to a few to a block, with and without chance neighbours merged into longer descriptors
+@pytest.mark.parametrize("row", [16, 240, 256, 496, 512, 1008, 1024, 1040, 1152])
+@pytest.mark.parametrize("bs,kind", [(1, "runs"), (1, "random"), (3, "fragmented"), (7, "runs")])
+@pytest.mark.parametrize("x_off", [0, 48])
+def test_small_descriptors_by_the_row_map(row, bs, kind, x_off):
+    hop_at(W.tiny(960 + row + bs, 7, bs, (row, 64, row), 400, 50 * bs, kind=kind), x_off)
+    hop_at(W.tiny(970 + row + bs, 5, bs, (row,), 300, 50 * bs, kind=kind), x_off, block_threads=64)
+
+
+@pytest.mark.parametrize("row,mb", [(656, 118), (1152, 280)])
+def test_layers_about_the_size_of_the_on_die_cache(row, mb):
+    """Whole blocks whose scatter takes the row map for the size of the layer."""
+    tokens = (mb << 20) // row // 3
+    hop_at(_uniform(3, tokens, 64, row))
+
+
+def _uniform(requests, tokens, bs, row):
+    w = W.tiny(981, requests, bs, (row,), requests * (tokens // bs + 4), tokens, allow_zero_hit=False)
+    w.hit[:] = [tokens - 5 * r for r in range(requests)]
+    w.app[:] = 3
+    nb = [(int(h) + 3 + bs - 1) // bs for h in w.hit]
+    for side, seed in ((w.src, 1), (w.dst, 2)):
+        side.tables = W.make_tables(nb, side.pool_blocks, "random", np.random.Generator(np.random.PCG64(seed)))
+    return w
+
+
+@pytest.mark.parametrize("chunk,slots", [(4096, 1), (65536, 3)])
+def test_row_map_through_the_staging_slots(chunk, slots):
+    """Chunks launch parts of the descriptors, with the transfer rows shifted into a staging slot."""
+    w = W.tiny(990, 9, 1, (1152, 272), 3000, 300)
+    bs, rows = w.layout.block_tokens, w.layout.row_bytes
+    x = W.random_payload(w, 0, oracle.payload_bytes(w.hit, rows))
+    want = W.sentinel_pool(w, "dst")
+    oracle.unpack(bs, rows, w.hit, w.dst.tables, x, want)
+    plan = dev_plan(w, "dst", K.KVL_SCATTER | K.KVL_GATHER)
+    host = torch.from_numpy(x).pin_memory()
+    back = torch.empty_like(host).pin_memory()
+    staging = torch.zeros(chunk * slots, dtype=torch.uint8, device="cuda")
+    pool = planes_to_dev(W.sentinel_pool(w, "dst"))
+    torch.cuda.synchronize()
+    cs, ks = torch.cuda.Stream(), torch.cuda.Stream()
+    K.kvl_h2d_unpack_layer(plan, host, staging, chunk, pool, cs, ks)
+    K.kvl_d2h_pack_layer(plan, pool, staging, chunk, back, ks, cs)
+    torch.cuda.synchronize()
+    for a, b in zip(pool, want):
+        assert same_bytes(to_host(a), b)
+    assert same_bytes(back.numpy(), x)
