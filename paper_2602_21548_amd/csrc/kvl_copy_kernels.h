@@ -503,58 +503,60 @@ struct FullBlockArgs {
     uintptr_t blocks;                          // base of the Full-Block buffer
     uint64_t fb_elems;                         // elements per Full Block
     uint64_t layer_plane_off[KVL_MAX_PLANES];  // element offset of (layer, plane) inside a Full Block
+    uint32_t tile_end[KVL_MAX_PLANES];         // tiles of a descriptor up to and with this plane
 };
 
-// A tile is VPT * blockDim elements of a descriptor; lane t takes elements t, t + blockDim, ...
-// of it, all loads before the first store.
-template <bool TO_POOL, bool VEC, int VPT>
+// A tile is VPT * blockDim vectors of a descriptor's plane; lane t takes vectors t, t + blockDim, ...  of it, all loads
+// before the first store.  VEC: whole 16-byte vectors; else any byte addresses, one vector per lane (copy_any).
+// Bound by memory: the policies are those of the copy kernels with the same direction through the on-die cache (into
+// the pool nt loads and sc1 stores, which leave the layer there for whoever reads it next; out of it nt loads and
+// sc1+nt stores).  Both directions in turn, 64-token blocks of 61 layers, us a layer, against plain loads with sc1+nt
+// stores one way and nt loads with plain stores the other: 1152-byte rows, 101 MB a layer, 89 -> 63; 221 MB 185 -> 142;
+// 1.8 GB 1388 -> 1305; 656-byte rows, 58 MB, 59 -> 46.  Across the host link the old ones stay (the link is the bound).
+template <bool TO_POOL, bool VEC, int VPT, bool NTL, int SP>
 __device__ __forceinline__ void fullblock_tile(const FullBlockArgs &a, uint32_t tiles_per_unit, uint32_t tile_index) {
     const uint32_t u_idx = tile_index / tiles_per_unit;
-    const uint32_t tile = tile_index - u_idx * tiles_per_unit;
-    const kvl_unit_t u = a.units[u_idx];
-    const uint32_t p = blockIdx.y;
-    const uint32_t row = a.row_elems[p];
-    const uint32_t n = u.n_rows * row;
+    uint32_t tile = tile_index - u_idx * tiles_per_unit;
+    const cunits_t u = (cunits_t)(uintptr_t)a.units + u_idx;
+    // a descriptor's tiles are those of its planes one after the other, each plane its own number of them
+    uint32_t p = 0;
+#pragma unroll
+    for (uint32_t q = 0; q + 1 < KVL_MAX_PLANES; ++q) p += tile >= a.tile_end[q] ? 1u : 0u;
+    tile -= p ? a.tile_end[p - 1] : 0u;
+    const uint32_t row = a.row_elems[p], pool_row = u->pool_row;
+    const uint32_t n = u->n_rows * row;
     const uint32_t first = tile * (blockDim.x * VPT) + threadIdx.x;
-    if (first >= n) return;
-    const uint32_t within = u.pool_row % a.block_tokens;
-    const uint64_t in_pool = (uint64_t)u.pool_row * row;
-    const uint64_t in_blocks = (uint64_t)u.block_index * a.fb_elems + a.layer_plane_off[p] + (uint64_t)within * row;
+    const uint32_t within = pool_row % a.block_tokens;
+    const uint64_t in_pool = (uint64_t)pool_row * row;
+    const uint64_t in_blocks = (uint64_t)u->block_index * a.fb_elems + a.layer_plane_off[p] + (uint64_t)within * row;
     if (VEC) {
+        if (first >= n) return;
         gsrc_t src = TO_POOL ? (gsrc_t)a.blocks + in_blocks : (gsrc_t)a.pool[p] + in_pool;
         gdst_t dst = TO_POOL ? (gdst_t)a.pool[p] + in_pool : (gdst_t)a.blocks + in_blocks;
         v4u v[VPT];
 #pragma unroll
         for (int k = 0; k < VPT; ++k) {
             const uint32_t i = first + k * blockDim.x;
-            if (i < n) v[k] = TO_POOL ? load16<false>(src + i) : load16<true>(src + i);
+            if (i < n) v[k] = load16<NTL>(src + i);
         }
 #pragma unroll
         for (int k = 0; k < VPT; ++k) {
             const uint32_t i = first + k * blockDim.x;
-            if (i < n) {
-                if (TO_POOL) store16<3>(dst + i, v[k]);
-                else store16<0>(dst + i, v[k]);
-            }
+            if (i < n) store16<SP>(dst + i, v[k]);
         }
     } else {
-        uint8_t *pool = reinterpret_cast<uint8_t *>(a.pool[p]) + in_pool;
-        uint8_t *blocks = reinterpret_cast<uint8_t *>(a.blocks) + in_blocks;
-        for (int k = 0; k < VPT; ++k) {
-            const uint32_t i = first + k * blockDim.x;
-            if (i >= n) break;
-            if (TO_POOL) pool[i] = blocks[i];
-            else blocks[i] = pool[i];
-        }
+        const uintptr_t pool = a.pool[p] + in_pool, blocks = a.blocks + in_blocks;
+        const uintptr_t dst = TO_POOL ? pool : blocks;
+        copy_any<NTL, SP>(TO_POOL ? blocks : pool, dst, n, (uint32_t)dst & 127u, first);
     }
 }
 
 // gridDim.x workgroups walk over the n_tiles tiles (one tile each when there are as many).
-template <bool TO_POOL, bool VEC, int VPT>
+template <bool TO_POOL, bool VEC, int VPT, bool NTL, int SP>
 __global__ void __launch_bounds__(256) kvl_fullblock_kernel(const FullBlockArgs a, uint32_t tiles_per_unit,
                                                             uint32_t n_tiles) {
     for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x)
-        fullblock_tile<TO_POOL, VEC, VPT>(a, tiles_per_unit, t);
+        fullblock_tile<TO_POOL, VEC, VPT, NTL, SP>(a, tiles_per_unit, t);
 }
 
 // Reference streams for measuring what the memory can do (kvl_ceiling_kernel): the tiled form

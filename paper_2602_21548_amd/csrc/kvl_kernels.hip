@@ -375,33 +375,39 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
     a.blocks = base;
     a.fb_elems = block_pitch / e;
     uint64_t plane_off = 0;
-    uint32_t max_row = 0;
     for (uint32_t p = 0; p < P; ++p) {
         a.row_elems[p] = (uint32_t)(plan->layout.row_bytes[p] / e);
         a.pool[p] = reinterpret_cast<uintptr_t>(pool_planes[p]);
         a.layer_plane_off[p] = (layer_off + plane_off) / e;
         plane_off += bs * plan->layout.row_bytes[p];
-        max_row = std::max(max_row, a.row_elems[p]);
     }
     const uint32_t threads = 256;
-    // across the host link: two elements per lane on few workgroups (as the copy kernels do, see launch_units)
-    const uint32_t vpt = far_host ? 2 : 1;
-    const uint64_t per_tile = (uint64_t)threads * vpt;
-    const uint64_t tpu = ((uint64_t)plan->max_unit_rows * max_row + per_tile - 1) / per_tile;
+    // across the host link: two vectors per lane on few workgroups (as the copy kernels do, see launch_units)
+    const uint32_t vpt = far_host && vec ? 2 : 1;
+    const uint64_t per_tile = (uint64_t)threads * vpt * (vec ? 1 : 16);
+    // (a span off the 16-byte grid is laid out from the 128-byte line below its start)
+    uint64_t tpu = 0;
+    for (uint32_t p = 0; p < KVL_MAX_PLANES; ++p) {
+        if (p < P) tpu += ((uint64_t)plan->max_unit_rows * a.row_elems[p] + (vec ? 0 : 127) + per_tile - 1) / per_tile;
+        a.tile_end[p] = (uint32_t)std::min<uint64_t>(tpu, UINT32_MAX);
+    }
     const uint64_t wgs = (uint64_t)a.n_units * tpu;
-    if (tpu == 0 || wgs > (uint64_t)INT32_MAX) return KVL_ERANGE;
-    const uint32_t cap = plan->tuning.max_groups ? plan->tuning.max_groups : (far_host ? kHostSideGroups : 0u);
+    if (wgs > (uint64_t)INT32_MAX) return KVL_ERANGE;
+    const uint32_t cap = plan->tuning.max_groups ? plan->tuning.max_groups
+                                                 : (far_host ? (vec ? kHostSideGroups : 2 * kHostSideGroups) : 0u);
     const uint32_t n_tiles = (uint32_t)wgs;
     bool walk = false;
-    dim3 grid(launch_groups(wgs, threads, cap, &walk), P), block(threads);
-#define KVL_FB_LAUNCH(TP, VE, VP) \
-    hipLaunchKernelGGL((kvl_fullblock_kernel<TP, VE, VP>), grid, block, 0, stream, a, (uint32_t)tpu, n_tiles)
+    dim3 grid(launch_groups(wgs, threads, cap, &walk)), block(threads);
+#define KVL_FB_LAUNCH(...) \
+    hipLaunchKernelGGL((kvl_fullblock_kernel<__VA_ARGS__>), grid, block, 0, stream, a, (uint32_t)tpu, n_tiles)
     if (to_pool) {
-        if (vec) { if (vpt == 2) KVL_FB_LAUNCH(true, true, 2); else KVL_FB_LAUNCH(true, true, 1); }
-        else { if (vpt == 2) KVL_FB_LAUNCH(true, false, 2); else KVL_FB_LAUNCH(true, false, 1); }
+        if (!vec) KVL_FB_LAUNCH(true, false, 1, true, 2);
+        else if (far_host) KVL_FB_LAUNCH(true, true, 2, false, 3);
+        else KVL_FB_LAUNCH(true, true, 1, true, 2);
     } else {
-        if (vec) { if (vpt == 2) KVL_FB_LAUNCH(false, true, 2); else KVL_FB_LAUNCH(false, true, 1); }
-        else { if (vpt == 2) KVL_FB_LAUNCH(false, false, 2); else KVL_FB_LAUNCH(false, false, 1); }
+        if (!vec) KVL_FB_LAUNCH(false, false, 1, true, 3);
+        else if (far_host) KVL_FB_LAUNCH(false, true, 2, true, 0);
+        else KVL_FB_LAUNCH(false, true, 1, true, 3);
     }
 #undef KVL_FB_LAUNCH
     KVL_HIP(hipGetLastError());

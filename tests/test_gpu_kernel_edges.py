@@ -111,3 +111,35 @@ def test_row_map_through_the_staging_slots(chunk, slots):
     for a, b in zip(pool, want):
         assert same_bytes(to_host(a), b)
     assert same_bytes(back.numpy(), x)
+
+
+# one and several planes of unlike rows (their tiles are numbered one plane after the other), on and off the 16-byte
+# grid, spans around one and two tiles
+@pytest.mark.parametrize("bs,rows", [(64, (64,)), (64, (1024, 128)), (16, (16, 656, 64)), (8, (512, 16, 520, 1024)), (64, (132,)),
+                                     (3, (5, 7)), (16, (255, 256, 257, 31)), (1, (4095, 1)), (1, (4096, 8208))])
+@pytest.mark.parametrize("off", [0, 5])
+@pytest.mark.parametrize("where", ["device", "pinned"])
+def test_full_blocks_planes_and_tiles(bs, rows, off, where):
+    L, layer = 2, 1
+    w = W.tiny(1020 + bs + len(rows), 5, bs, rows, 120, 9 * bs, kind="runs", n_layers=L)
+    g, s = dev_plan(w, "src", K.KVL_GATHER | K.KVL_NO_MERGE), dev_plan(w, "dst", K.KVL_SCATTER | K.KVL_NO_MERGE)
+    fb, count = g.fullblock_geometry()
+    n = fb * count
+    first = np.zeros_like(w.hit)
+    src = W.fill_pool(w, layer, "src")
+    want = np.full(n, 0x5A, dtype=np.uint8)
+    oracle.pool_to_fullblocks(bs, L, rows, first, w.hit, w.src.tables, layer, src, want)
+    want_pool = W.sentinel_pool(w, "dst")
+    oracle.fullblocks_to_pool(bs, L, rows, first, w.hit, w.dst.tables, layer, want, want_pool)
+    buf = torch.full((n + off + GUARD,), 0x5A, dtype=torch.uint8)
+    buf = buf.cuda() if where == "device" else buf.pin_memory()
+    d_src, d_dst = planes_to_dev(src), planes_to_dev(W.sentinel_pool(w, "dst"))
+    torch.cuda.synchronize()
+    K.kvl_pool_to_fullblocks_layer(g, d_src, layer, buf[off:off + n])
+    K.kvl_fullblocks_to_pool_layer(s, buf[off:off + n], layer, d_dst)
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy()
+    assert same_bytes(got[off:off + n], want), "persist differs from the oracle"
+    assert np.all(got[:off] == 0x5A) and np.all(got[off + n:] == 0x5A)
+    for a, b in zip(d_dst, want_pool):
+        assert same_bytes(to_host(a), b), "load differs from the oracle"
