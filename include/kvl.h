@@ -78,9 +78,8 @@ extern "C" {
 #define KVL_NO_MERGE   8u  /* do not merge physically adjacent blocks into one run */
 #define KVL_NO_POINTER_CHECKS 64u  /* skip kvl_check_buffer on every call made with this plan */
 #define KVL_CALLER_SYNCS 128u      /* the caller promises that everything enqueued with the plan has finished
-                                      by the time it destroys the plan: launches are then not followed by an
-                                      event each (about 3 us per launch, which only shows on layers of a few
-                                      MB), and kvl_plan_destroy hands the descriptor array on at once */
+                                      by the time it destroys the plan: launches then carry no event each
+                                      (about 2 us per launch, which only shows on layers of a few MB), and kvl_plan_destroy hands the descriptor array on at once */
 /* Which token rows of each request the plan moves.  Default: the hit prefix
  * [0, hit).  The other two serve the step after a layer's computation
  * (Section 4.1): the decode-engine read path sends on only the miss tokens'
@@ -149,8 +148,8 @@ int kvl_plan(const kvl_layout_t *layout, const kvl_request_t *requests, uint32_t
 int kvl_plan_tuned(const kvl_layout_t *layout, const kvl_request_t *requests, uint32_t n_req,
                    uint32_t flags, const kvl_tuning_t *tuning, kvl_plan_t **out);
 /* Frees the plan.  The call does not wait for the device: kernels enqueued with the
- * plan may still be running or queued.  Every launch made with a plan is followed by
- * an event on its stream (one event per stream, recorded again after each launch);
+ * plan may still be running or queued.  Every launch made with a plan carries
+ * an event (one per stream, that of the stream's last launch);
  * the plan's device descriptor array is retired with those events and goes back to a
  * small cache inside the library (at most 16 buffers / 256 MiB, from which later
  * plans are served without a device allocation) only when they have fired.  The

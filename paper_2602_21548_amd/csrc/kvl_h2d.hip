@@ -446,7 +446,7 @@ int kvl_plan_set_lane_cu_mask(kvl_plan_t *plan, const uint32_t *mask, uint32_t n
     for (hipStream_t s : plan->lanes) {
         hipError_t e = hipStreamSynchronize(s);
         if (first == hipSuccess) first = e;
-        // (the event recorded after the lane's last launch has fired by now and stays with the plan)
+        // (the event of the lane's last launch has fired by now and stays with the plan)
         if (poolable) {
             kvl::return_lane(s, plan->device);
         } else {

@@ -34,7 +34,7 @@ struct kvl_plan_s {
     mutable bool map_stream_known = false;
     int device = -1;
     // One event per stream on which kernels that read d_units were enqueued (the caller's streams and
-    // the lanes), re-recorded after every such launch: once all of them have fired no kernel reads the
+    // the lanes), taken along by every such launch: once all of them have fired no kernel reads the
     // buffer any more and it may be handed to another plan.  Recorded at launch time because a stream
     // of the caller's may be gone by the time the plan is destroyed.
     mutable std::vector<std::pair<hipStream_t, hipEvent_t>> stream_events;
@@ -138,8 +138,8 @@ bool is_host_memory(const kvl_plan_t *plan, const void *ptr);
 int upload_units(kvl_plan_t *plan);
 // whether a launch on `stream` may read plan->d_row_map; orders the stream after the map's making if that is needed
 bool row_map_ready(const kvl_plan_t *plan, hipStream_t stream);
-// a kernel reading the plan's descriptors has just been enqueued on `stream`
-void mark_launch(const kvl_plan_t *plan, hipStream_t stream);
+// the event that a launch reading the plan's descriptors is to take with it on `stream` (null: it is not followed)
+hipEvent_t launch_event(const kvl_plan_t *plan, hipStream_t stream);
 void drop_stream_events(const kvl_plan_t *plan);
 // lanes come from, and go back to, a small pool shared by all plans
 hipStream_t take_pooled_lane(int device);

@@ -3,6 +3,8 @@
 #include <algorithm>
 #include <cstdio>
 
+#include <hip/hip_ext.h>
+
 #include "kvl_copy_kernels.h"
 
 namespace kvl {
@@ -25,14 +27,27 @@ int check_device(const kvl_plan_t *plan) {
     return dev == plan->device ? KVL_OK : KVL_EINVAL;
 }
 
+// Where a kernel goes, and the event that is to fire when it has finished (or null).  The event rides on the
+// dispatch itself: recorded on its own behind it, it costs another packet for the host to write and the queue to
+// wait for (launches of a 3 us kernel in a row: 7.5 us each recorded, 4.5 us riding, 2.8 us without; host 8 / 2.5).
+struct On {
+    hipStream_t stream;
+    hipEvent_t done;
+};
+#define KVL_LAUNCH(kernel, grid, block, on, ...)                                                                  \
+    do {                                                                                                          \
+        if ((on).done) hipExtLaunchKernelGGL(kernel, grid, block, 0, (on).stream, nullptr, (on).done, 0, __VA_ARGS__); \
+        else hipLaunchKernelGGL(kernel, grid, block, 0, (on).stream, __VA_ARGS__);                                \
+    } while (0)
+
 template <bool PACK, bool WAVE, int U, bool NTL, int SP>
-static void launch_one(dim3 grid, dim3 block, hipStream_t s, const CopyArgs &a) {
-    if (PACK) hipLaunchKernelGGL((kvl_pack_kernel<WAVE, U, NTL, SP>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((kvl_unpack_kernel<WAVE, U, NTL, SP>), grid, block, 0, s, a);
+static void launch_one(dim3 grid, dim3 block, const On &s, const CopyArgs &a) {
+    if (PACK) KVL_LAUNCH((kvl_pack_kernel<WAVE, U, NTL, SP>), grid, block, s, a);
+    else KVL_LAUNCH((kvl_unpack_kernel<WAVE, U, NTL, SP>), grid, block, s, a);
 }
 
 template <bool PACK, bool WAVE, int U, bool NTL>
-static void launch_sp(uint32_t v, dim3 g, dim3 b, hipStream_t s, const CopyArgs &a) {
+static void launch_sp(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a) {
     switch ((v >> 3) & 3u) {
         case 0: launch_one<PACK, WAVE, U, NTL, 0>(g, b, s, a); break;
         case 1: launch_one<PACK, WAVE, U, NTL, 1>(g, b, s, a); break;
@@ -42,13 +57,13 @@ static void launch_sp(uint32_t v, dim3 g, dim3 b, hipStream_t s, const CopyArgs 
 }
 
 template <bool PACK, bool WAVE, int U>
-static void launch_nt(uint32_t v, dim3 g, dim3 b, hipStream_t s, const CopyArgs &a) {
+static void launch_nt(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a) {
     if (v & 4u) launch_sp<PACK, WAVE, U, true>(v, g, b, s, a);
     else launch_sp<PACK, WAVE, U, false>(v, g, b, s, a);
 }
 
 template <bool PACK>
-static void launch_span_variant(uint32_t v, dim3 g, dim3 b, hipStream_t s, const CopyArgs &a) {
+static void launch_span_variant(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a) {
     const bool wave = (v & 3u) == 1u, deep = (v & 32u) != 0;
     if (wave) {
         if (deep) launch_nt<PACK, true, 8>(v, g, b, s, a);
@@ -61,15 +76,15 @@ static void launch_span_variant(uint32_t v, dim3 g, dim3 b, hipStream_t s, const
 
 // n_tiles != 0: the launch has fewer workgroups than tiles and they walk over them
 template <bool PACK, int VPT, bool NTL, int SP>
-static void launch_tile_one(dim3 g, dim3 b, hipStream_t s, const CopyArgs &a, uint32_t tpu, uint32_t al,
+static void launch_tile_one(dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t tpu, uint32_t al,
                             uint32_t n_tiles) {
-    if (n_tiles) hipLaunchKernelGGL((kvl_tile_walk_kernel<PACK, VPT, NTL, SP>), g, b, 0, s, a, tpu, al, n_tiles);
-    else if (PACK) hipLaunchKernelGGL((kvl_pack_tile_kernel<VPT, NTL, SP>), g, b, 0, s, a, tpu, al);
-    else hipLaunchKernelGGL((kvl_unpack_tile_kernel<VPT, NTL, SP>), g, b, 0, s, a, tpu, al);
+    if (n_tiles) KVL_LAUNCH((kvl_tile_walk_kernel<PACK, VPT, NTL, SP>), g, b, s, a, tpu, al, n_tiles);
+    else if (PACK) KVL_LAUNCH((kvl_pack_tile_kernel<VPT, NTL, SP>), g, b, s, a, tpu, al);
+    else KVL_LAUNCH((kvl_unpack_tile_kernel<VPT, NTL, SP>), g, b, s, a, tpu, al);
 }
 
 template <bool PACK, int VPT, bool NTL>
-static void launch_tile_sp(uint32_t v, dim3 g, dim3 b, hipStream_t s, const CopyArgs &a, uint32_t tpu,
+static void launch_tile_sp(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t tpu,
                            uint32_t al, uint32_t n_tiles) {
     switch ((v >> 3) & 3u) {
         case 0: launch_tile_one<PACK, VPT, NTL, 0>(g, b, s, a, tpu, al, n_tiles); break;
@@ -80,25 +95,25 @@ static void launch_tile_sp(uint32_t v, dim3 g, dim3 b, hipStream_t s, const Copy
 }
 
 template <bool PACK, int VPT>
-static void launch_tile_variant(uint32_t v, dim3 g, dim3 b, hipStream_t s, const CopyArgs &a, uint32_t tpu,
+static void launch_tile_variant(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t tpu,
                                 uint32_t al, uint32_t n_tiles) {
     if (v & 4u) launch_tile_sp<PACK, VPT, true>(v, g, b, s, a, tpu, al, n_tiles);
     else launch_tile_sp<PACK, VPT, false>(v, g, b, s, a, tpu, al, n_tiles);
 }
 
 template <bool PACK, bool NTL>
-static void launch_pipe_sp(uint32_t v, dim3 g, dim3 b, hipStream_t s, const CopyArgs &a, uint32_t tpu, uint32_t al,
+static void launch_pipe_sp(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t tpu, uint32_t al,
                            uint32_t n_tiles) {
     switch ((v >> 3) & 3u) {
-        case 0: hipLaunchKernelGGL((kvl_tile_pipe_kernel<PACK, NTL, 0>), g, b, 0, s, a, tpu, al, n_tiles); break;
-        case 1: hipLaunchKernelGGL((kvl_tile_pipe_kernel<PACK, NTL, 1>), g, b, 0, s, a, tpu, al, n_tiles); break;
-        case 2: hipLaunchKernelGGL((kvl_tile_pipe_kernel<PACK, NTL, 2>), g, b, 0, s, a, tpu, al, n_tiles); break;
-        default: hipLaunchKernelGGL((kvl_tile_pipe_kernel<PACK, NTL, 3>), g, b, 0, s, a, tpu, al, n_tiles); break;
+        case 0: KVL_LAUNCH((kvl_tile_pipe_kernel<PACK, NTL, 0>), g, b, s, a, tpu, al, n_tiles); break;
+        case 1: KVL_LAUNCH((kvl_tile_pipe_kernel<PACK, NTL, 1>), g, b, s, a, tpu, al, n_tiles); break;
+        case 2: KVL_LAUNCH((kvl_tile_pipe_kernel<PACK, NTL, 2>), g, b, s, a, tpu, al, n_tiles); break;
+        default: KVL_LAUNCH((kvl_tile_pipe_kernel<PACK, NTL, 3>), g, b, s, a, tpu, al, n_tiles); break;
     }
 }
 
 template <bool PACK>
-static void launch_pipe_variant(uint32_t v, dim3 g, dim3 b, hipStream_t s, const CopyArgs &a, uint32_t tpu,
+static void launch_pipe_variant(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t tpu,
                                 uint32_t al, uint32_t n_tiles) {
     if (v & 4u) launch_pipe_sp<PACK, true>(v, g, b, s, a, tpu, al, n_tiles);
     else launch_pipe_sp<PACK, false>(v, g, b, s, a, tpu, al, n_tiles);
@@ -120,36 +135,36 @@ static int compute_units(int device) {
 }
 
 template <bool PACK, bool NTL>
-static void launch_flat_sp(uint32_t v, dim3 g, dim3 b, hipStream_t s, const CopyArgs &a, uint32_t mur) {
+static void launch_flat_sp(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t mur) {
     switch ((v >> 3) & 3u) {
-        case 0: hipLaunchKernelGGL((kvl_flat_kernel<PACK, NTL, 0>), g, b, 0, s, a, mur); break;
-        case 1: hipLaunchKernelGGL((kvl_flat_kernel<PACK, NTL, 1>), g, b, 0, s, a, mur); break;
-        case 2: hipLaunchKernelGGL((kvl_flat_kernel<PACK, NTL, 2>), g, b, 0, s, a, mur); break;
-        default: hipLaunchKernelGGL((kvl_flat_kernel<PACK, NTL, 3>), g, b, 0, s, a, mur); break;
+        case 0: KVL_LAUNCH((kvl_flat_kernel<PACK, NTL, 0>), g, b, s, a, mur); break;
+        case 1: KVL_LAUNCH((kvl_flat_kernel<PACK, NTL, 1>), g, b, s, a, mur); break;
+        case 2: KVL_LAUNCH((kvl_flat_kernel<PACK, NTL, 2>), g, b, s, a, mur); break;
+        default: KVL_LAUNCH((kvl_flat_kernel<PACK, NTL, 3>), g, b, s, a, mur); break;
     }
 }
 
 template <bool PACK>
-static void launch_flat_variant(uint32_t v, dim3 g, dim3 b, hipStream_t s, const CopyArgs &a, uint32_t mur) {
+static void launch_flat_variant(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t mur) {
     if (v & 4u) launch_flat_sp<PACK, true>(v, g, b, s, a, mur);
     else launch_flat_sp<PACK, false>(v, g, b, s, a, mur);
 }
 
 template <bool PACK, bool NTL, int SP>
-static void launch_rows(dim3 g, dim3 b, hipStream_t s, const CopyArgs &a, const uint32_t *map, uint32_t row_begin,
+static void launch_rows(dim3 g, dim3 b, const On &s, const CopyArgs &a, const uint32_t *map, uint32_t row_begin,
                         uint32_t n_vecs) {
     const uint32_t row = a.row_elems[a.plane_begin];
-    if (row >= 64) hipLaunchKernelGGL((kvl_rows_kernel<PACK, NTL, SP, 2>), g, b, 0, s, a, map, row_begin, n_vecs);
-    else if (row >= 32) hipLaunchKernelGGL((kvl_rows_kernel<PACK, NTL, SP, 3>), g, b, 0, s, a, map, row_begin, n_vecs);
-    else if (row >= 16) hipLaunchKernelGGL((kvl_rows_kernel<PACK, NTL, SP, 5>), g, b, 0, s, a, map, row_begin, n_vecs);
-    else hipLaunchKernelGGL((kvl_rows_kernel<PACK, NTL, SP, 0>), g, b, 0, s, a, map, row_begin, n_vecs);
+    if (row >= 64) KVL_LAUNCH((kvl_rows_kernel<PACK, NTL, SP, 2>), g, b, s, a, map, row_begin, n_vecs);
+    else if (row >= 32) KVL_LAUNCH((kvl_rows_kernel<PACK, NTL, SP, 3>), g, b, s, a, map, row_begin, n_vecs);
+    else if (row >= 16) KVL_LAUNCH((kvl_rows_kernel<PACK, NTL, SP, 5>), g, b, s, a, map, row_begin, n_vecs);
+    else KVL_LAUNCH((kvl_rows_kernel<PACK, NTL, SP, 0>), g, b, s, a, map, row_begin, n_vecs);
 }
 
 template <bool PACK, bool NTL, int SP>
-static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, hipStream_t s, const CopyArgs &a, uint32_t x, uint32_t n_tiles) {
-    if (flat) hipLaunchKernelGGL((kvl_any_flat_kernel<PACK, NTL, SP>), g, b, 0, s, a, x);
-    else if (walk) hipLaunchKernelGGL((kvl_any_tile_kernel<PACK, NTL, SP, true>), g, b, 0, s, a, x, n_tiles);
-    else hipLaunchKernelGGL((kvl_any_tile_kernel<PACK, NTL, SP, false>), g, b, 0, s, a, x, n_tiles);
+static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t x, uint32_t n_tiles) {
+    if (flat) KVL_LAUNCH((kvl_any_flat_kernel<PACK, NTL, SP>), g, b, s, a, x);
+    else if (walk) KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, true>), g, b, s, a, x, n_tiles);
+    else KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, false>), g, b, s, a, x, n_tiles);
 }
 
 // Rows or addresses that are not multiples of 16 bytes (the planes of a launch have one row size).
@@ -163,7 +178,7 @@ static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, hipStream_t s, 
 //     non-temporal accesses throughout; 1026 by 16, 120 MB: 82 against 95), a larger one passes it by (300 MB:
 //     226 -> 214 and 268 -> 251 us; 800 MB of 657-byte rows: 647 -> 634).
 static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uint32_t planes, bool far_host,
-                       hipStream_t stream) {
+                       const On &on) {
     const uint64_t unit_bytes = (uint64_t)plan->max_unit_rows * a.row_elems[a.plane_begin];
     const uint64_t windows = (unit_bytes + 30) / 16;       // 16-byte windows a span of that size can touch
     const bool flat = windows <= kAnyFlatWindows;
@@ -188,11 +203,11 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
         const uint32_t x = (uint32_t)(flat ? windows : per_unit);
         dim3 grid(groups, planes), block(threads);
         if (pack) {
-            if (kept) launch_any_one<true, true, 2>(flat, walk, grid, block, stream, part, x, (uint32_t)tiles);
-            else launch_any_one<true, true, 1>(flat, walk, grid, block, stream, part, x, (uint32_t)tiles);
+            if (kept) launch_any_one<true, true, 2>(flat, walk, grid, block, on, part, x, (uint32_t)tiles);
+            else launch_any_one<true, true, 1>(flat, walk, grid, block, on, part, x, (uint32_t)tiles);
         } else {
-            if (kept) launch_any_one<false, false, 3>(flat, walk, grid, block, stream, part, x, (uint32_t)tiles);
-            else launch_any_one<false, true, 1>(flat, walk, grid, block, stream, part, x, (uint32_t)tiles);
+            if (kept) launch_any_one<false, false, 3>(flat, walk, grid, block, on, part, x, (uint32_t)tiles);
+            else launch_any_one<false, true, 1>(flat, walk, grid, block, on, part, x, (uint32_t)tiles);
         }
     }
 }
@@ -261,6 +276,7 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         threads = plan->tuning.block_threads;
     }
     dim3 block(threads);
+    const On on{stream, launch_event(plan, stream)};
     const kvl_unit_t &u_first = plan->units[unit_begin], &u_last = plan->units[unit_end - 1];
     if (vec && !plan->tuning.variant && !plan->tuning.max_groups && !far_host && plan->d_row_map &&
         takes_row_map(plan, plan->layout.row_bytes[plane_begin], pack) && row_map_ready(plan, stream)) {
@@ -273,12 +289,12 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
             const uint32_t n = (uint32_t)(std::min<uint64_t>(per_launch, rows - first) * widest);
             const uint32_t row_begin = (uint32_t)(u_first.xfer_row + first);
             dim3 grid((uint32_t)(((uint64_t)n + 7 + threads - 1) / threads), plane_end - plane_begin);
-            if (pack) launch_rows<true, true, 2>(grid, dim3(threads), stream, a, plan->d_row_map, row_begin, n);
-            else if (lines) launch_rows<false, true, 3>(grid, dim3(threads), stream, a, plan->d_row_map, row_begin, n);
-            else launch_rows<false, true, 1>(grid, dim3(threads), stream, a, plan->d_row_map, row_begin, n);
+            if (pack) launch_rows<true, true, 2>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n);
+            else if (lines) launch_rows<false, true, 3>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n);
+            else launch_rows<false, true, 1>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n);
         }
     } else if (!vec) {
-        launch_any(plan, pack, a, plane_end - plane_begin, far_host, stream);
+        launch_any(plan, pack, a, plane_end - plane_begin, far_host, on);
     } else if (v & 128u) {
         // lane indices are 32 bits: split the descriptors over launches where they would not fit
         // (tuning.max_groups, if given, lowers the workgroups per launch further)
@@ -292,8 +308,8 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
             part.n_units = (uint32_t)std::min<uint64_t>(per_launch, a.n_units - first);
             const uint64_t lanes = (uint64_t)part.n_units * unit_vecs;
             dim3 grid((uint32_t)((lanes + threads - 1) / threads), plane_end - plane_begin);
-            if (pack) launch_flat_variant<true>(v, grid, block, stream, part, plan->max_unit_rows);
-            else launch_flat_variant<false>(v, grid, block, stream, part, plan->max_unit_rows);
+            if (pack) launch_flat_variant<true>(v, grid, block, on, part, plan->max_unit_rows);
+            else launch_flat_variant<false>(v, grid, block, on, part, plan->max_unit_rows);
         }
     } else if ((v & 3u) >= 2u) {
         const uint32_t vpt = (v & 3u) == 3u ? 2 : 1;
@@ -319,11 +335,10 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
             uint64_t groups = cap ? cap : std::max<uint64_t>(1, resident / (plane_end - plane_begin));
             groups = std::min<uint64_t>(groups, blocks);
             dim3 grid((uint32_t)groups, plane_end - plane_begin);
-            if (pack) launch_pipe_variant<true>(v, grid, block, stream, a, (uint32_t)tpu, al, (uint32_t)blocks);
-            else launch_pipe_variant<false>(v, grid, block, stream, a, (uint32_t)tpu, al, (uint32_t)blocks);
+            if (pack) launch_pipe_variant<true>(v, grid, block, on, a, (uint32_t)tpu, al, (uint32_t)blocks);
+            else launch_pipe_variant<false>(v, grid, block, on, a, (uint32_t)tpu, al, (uint32_t)blocks);
             KVL_HIP(hipGetLastError());
-            mark_launch(plan, stream);
-            return KVL_OK;
+                    return KVL_OK;
         }
         // one workgroup per tile, unless a cap was asked for or the launch would not fit
         bool walk = false;
@@ -331,21 +346,20 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         const uint32_t n_tiles = walk ? (uint32_t)blocks : 0u;
         dim3 grid(groups, plane_end - plane_begin);
         if (pack) {
-            if (vpt == 2) launch_tile_variant<true, 2>(v, grid, block, stream, a, (uint32_t)tpu, al, n_tiles);
-            else launch_tile_variant<true, 1>(v, grid, block, stream, a, (uint32_t)tpu, al, n_tiles);
+            if (vpt == 2) launch_tile_variant<true, 2>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles);
+            else launch_tile_variant<true, 1>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles);
         } else {
-            if (vpt == 2) launch_tile_variant<false, 2>(v, grid, block, stream, a, (uint32_t)tpu, al, n_tiles);
-            else launch_tile_variant<false, 1>(v, grid, block, stream, a, (uint32_t)tpu, al, n_tiles);
+            if (vpt == 2) launch_tile_variant<false, 2>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles);
+            else launch_tile_variant<false, 1>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles);
         }
     } else {
         const uint32_t per_wg = (v & 3u) == 1u ? threads / 64 : 1;
         if ((uint64_t)((a.n_units + per_wg - 1) / per_wg) * threads > kMaxLanesPerLaunch) return KVL_ERANGE;
         dim3 grid((a.n_units + per_wg - 1) / per_wg, plane_end - plane_begin);
-        if (pack) launch_span_variant<true>(v, grid, block, stream, a);
-        else launch_span_variant<false>(v, grid, block, stream, a);
+        if (pack) launch_span_variant<true>(v, grid, block, on, a);
+        else launch_span_variant<false>(v, grid, block, on, a);
     }
     KVL_HIP(hipGetLastError());
-    mark_launch(plan, stream);
     return KVL_OK;
 }
 
@@ -398,8 +412,9 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
     const uint32_t n_tiles = (uint32_t)wgs;
     bool walk = false;
     dim3 grid(launch_groups(wgs, threads, cap, &walk)), block(threads);
+    const On on{stream, launch_event(plan, stream)};
 #define KVL_FB_LAUNCH(...) \
-    hipLaunchKernelGGL((kvl_fullblock_kernel<__VA_ARGS__>), grid, block, 0, stream, a, (uint32_t)tpu, n_tiles)
+    KVL_LAUNCH((kvl_fullblock_kernel<__VA_ARGS__>), grid, block, on, a, (uint32_t)tpu, n_tiles)
     if (to_pool) {
         if (!vec) KVL_FB_LAUNCH(true, false, 1, true, 2);
         else if (far_host) KVL_FB_LAUNCH(true, true, 2, false, 3);
@@ -411,7 +426,6 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
     }
 #undef KVL_FB_LAUNCH
     KVL_HIP(hipGetLastError());
-    mark_launch(plan, stream);
     return KVL_OK;
 }
 

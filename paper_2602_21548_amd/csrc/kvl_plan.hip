@@ -46,8 +46,8 @@ int make_chunks(const kvl_plan_t *plan, uint64_t chunk_bytes, std::vector<kvl_ch
 // Descriptor arrays come from a small per-process cache, so that a caller who builds a plan
 // per batch pays neither a device allocation nor a device free (both synchronise the device,
 // and a free can stall the next launch for tens of milliseconds).  A destroyed plan's array is
-// retired, not freed: every launch that reads it is followed by an event on its stream (one event
-// per stream, recorded again after each launch), and the array goes back to the cache only when
+// retired, not freed: every launch that reads it takes an event with it (one per stream, which
+// fires when the stream's last such launch has finished), and the array goes back to the cache only when
 // those events have fired.  Nothing here waits for the device; only kvl_release_cached_memory
 // blocks (on the retired arrays' own events).
 namespace {
@@ -155,48 +155,37 @@ void reap_retired(bool wait) {
 }
 }  // namespace
 
-void mark_launch(const kvl_plan_t *plan, hipStream_t stream) {
-    if (plan->flags & KVL_CALLER_SYNCS) return;            // the caller answers for the plan's lifetime
+// (An event that no launch ever took with it counts as fired.)
+hipEvent_t launch_event(const kvl_plan_t *plan, hipStream_t stream) {
+    if (plan->flags & KVL_CALLER_SYNCS) return nullptr;    // the caller answers for the plan's lifetime
     // a launch that is being captured into a graph runs whenever the graph is replayed: not ours to follow
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
         (void)hipGetLastError();
         plan->untracked_use = true;
-        return;
+        return nullptr;
     }
     if (capture != hipStreamCaptureStatusNone) {
         plan->untracked_use = true;
-        return;
+        return nullptr;
     }
-    hipEvent_t ev = nullptr;
     for (const auto &se : plan->stream_events)
-        if (se.first == stream) ev = se.second;
-    if (!ev) {
-        if (plan->stream_events.size() >= kTrackedStreams) {
-            plan->untracked_use = true;
-            return;
-        }
-        {
-            std::lock_guard<std::mutex> lock(g_cache_mutex);
-            ev = take_event(plan->device);
-        }
-        if (!ev) {
-            plan->untracked_use = true;
-            return;
-        }
-        try {
-            plan->stream_events.emplace_back(stream, ev);
-        } catch (const std::bad_alloc &) {
-            std::lock_guard<std::mutex> lock(g_cache_mutex);
-            give_event(ev, plan->device);
-            plan->untracked_use = true;
-            return;
+        if (se.first == stream) return se.second;
+    hipEvent_t ev = nullptr;
+    if (plan->stream_events.size() < kTrackedStreams) {
+        std::lock_guard<std::mutex> lock(g_cache_mutex);
+        ev = take_event(plan->device);
+        if (ev) {
+            try {
+                plan->stream_events.emplace_back(stream, ev);
+            } catch (const std::bad_alloc &) {
+                give_event(ev, plan->device);
+                ev = nullptr;
+            }
         }
     }
-    if (hipEventRecord(ev, stream) != hipSuccess) {
-        (void)hipGetLastError();
-        plan->untracked_use = true;
-    }
+    if (!ev) plan->untracked_use = true;
+    return ev;
 }
 
 void drop_stream_events(const kvl_plan_t *plan) {
@@ -253,8 +242,8 @@ static hipError_t descriptor_alloc(void **out, size_t bytes, size_t *capacity, i
     return hipMalloc(out, want);
 }
 
-// The plan is going away: its descriptor array may be reused once the events recorded after its
-// launches have fired.  No stream is touched here.
+// The plan is going away: its descriptor array may be reused once its launches' events
+// have fired.  No stream is touched here.
 static void descriptor_release(const kvl_plan_t *plan) {
     RetiredBuffer r{CachedBuffer{plan->d_units, plan->d_units_capacity, plan->device}, {}, plan->map_event};
     if (plan->flags & KVL_CALLER_SYNCS) {               // (its map was waited for when it was made)
