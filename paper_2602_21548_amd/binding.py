@@ -176,8 +176,16 @@ def _check(rc: int, what: str) -> None:
         raise KvlError(rc, what)
 
 
+# The current stream's handle without the Stream object that torch.cuda.current_stream() makes
+# (2.8 us of a 13 us call; 0.2 us this way), where this torch has the two accessors.
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
+        if _current_raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _current_raw_stream(_current_device()) or None
         return int(torch.cuda.current_stream().cuda_stream) or None
     if isinstance(stream, int):
         return stream or None
@@ -185,7 +193,7 @@ def _stream_handle(stream) -> Optional[int]:
 
 
 def _nbytes(t: torch.Tensor) -> int:
-    return t.numel() * t.element_size()
+    return t.nbytes
 
 
 def _dev(t: torch.Tensor, what: str) -> int:
@@ -201,6 +209,11 @@ class Plan:
         self._h = C.c_void_p(handle)
         self.layout = layout
         self.flags = flags
+        # asked for on every call
+        self.n_planes = int(layout.n_planes)
+        self._plane_bytes = tuple(int(layout.pool_blocks) * int(layout.block_tokens) * int(layout.row_bytes[p])
+                                  for p in range(self.n_planes))
+        self._pointers = C.c_void_p * self.n_planes
 
     def destroy(self) -> None:
         if self._h:
@@ -226,12 +239,8 @@ class Plan:
             raise ValueError("plan destroyed")
         return self._h
 
-    @property
-    def n_planes(self) -> int:
-        return int(self.layout.n_planes)
-
     def plane_bytes(self, p: int) -> int:
-        return int(self.layout.pool_blocks) * int(self.layout.block_tokens) * int(self.layout.row_bytes[p])
+        return self._plane_bytes[p]
 
     @property
     def payload_bytes(self) -> int:
@@ -333,13 +342,14 @@ def kvl_plan(layout: kvl_layout_t, hit, app, tables: Sequence[np.ndarray], flags
 
 
 def _plane_ptrs(plan: Plan, planes: Sequence[torch.Tensor], what: str):
-    if len(planes) != plan.n_planes:
-        raise ValueError(f"{what}: expected {plan.n_planes} planes")
-    arr = (C.c_void_p * plan.n_planes)()
+    need = plan._plane_bytes
+    if len(planes) != len(need):
+        raise ValueError(f"{what}: expected {len(need)} planes")
+    arr = plan._pointers()
     for p, t in enumerate(planes):
         arr[p] = _dev(t, what)
-        if _nbytes(t) < plan.plane_bytes(p):
-            raise ValueError(f"{what}: plane {p} holds {_nbytes(t)} bytes, pool needs {plan.plane_bytes(p)}")
+        if t.nbytes < need[p]:
+            raise ValueError(f"{what}: plane {p} holds {t.nbytes} bytes, pool needs {need[p]}")
     return arr
 
 
@@ -360,20 +370,20 @@ def kvl_plan_pair(gather: Plan, scatter: Plan) -> Plan:
     _check(_lib.kvl_plan_pair(gather.handle, scatter.handle, C.byref(out)), "kvl_plan_pair")
     p = Plan(out.value, gather.layout, gather.flags)
     p.dst_layout = scatter.layout
+    p._dst_plane_bytes = scatter._plane_bytes
     return p
 
 
 def kvl_move_layer(paired: Plan, src_pool_planes: Sequence[torch.Tensor],
                    dst_pool_planes: Sequence[torch.Tensor], stream=None) -> None:
     src = _plane_ptrs(paired, src_pool_planes, "kvl_move_layer source pool")
-    dl = paired.dst_layout
     if len(dst_pool_planes) != paired.n_planes:
         raise ValueError("kvl_move_layer: wrong number of destination planes")
-    dst = (C.c_void_p * paired.n_planes)()
+    dst = paired._pointers()
     for p, t in enumerate(dst_pool_planes):
-        need = int(dl.pool_blocks) * int(dl.block_tokens) * int(dl.row_bytes[p])
-        if _nbytes(t) < need:
-            raise ValueError(f"kvl_move_layer: destination plane {p} holds {_nbytes(t)} bytes, pool needs {need}")
+        need = paired._dst_plane_bytes[p]
+        if t.nbytes < need:
+            raise ValueError(f"kvl_move_layer: destination plane {p} holds {t.nbytes} bytes, pool needs {need}")
         dst[p] = _dev(t, "kvl_move_layer destination pool")
     _check(_lib.kvl_move_layer(paired.handle, src, dst, _stream_handle(stream)), "kvl_move_layer")
 
