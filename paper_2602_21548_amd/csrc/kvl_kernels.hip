@@ -191,7 +191,7 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
     if (flat && plan->tuning.max_groups)
         per_launch = std::min<uint64_t>(per_launch, (uint64_t)plan->tuning.max_groups * threads / windows);
     per_launch = std::max<uint64_t>(1, per_launch);
-    const bool kept = plan->payload_bytes <= kCachedLayerBytes;
+    const bool kept = plan->payload_bytes <= kCachedLayerBytes && !plan->paired;
     for (uint64_t first = 0; first < a.n_units; first += per_launch) {
         CopyArgs part = a;
         part.unit_begin = a.unit_begin + (uint32_t)first;
@@ -259,7 +259,8 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         for (uint32_t p = plane_begin; p < plane_end; ++p)
             rows_128 = rows_128 && plan->layout.row_bytes[p] % 128 == 0;
         const uint64_t n = plan->payload_bytes;
-        if (pack) v = rows_128 || n < kPassByBytes ? kDefaultPackCode : kDefaultPackCodePassBy;
+        if (plan->paired) v = kMoveCode;
+        else if (pack) v = rows_128 || n < kPassByBytes ? kDefaultPackCode : kDefaultPackCodePassBy;
         else v = rows_128 || (n > kPlainReadBackBytes && n < kPassByBytes) ? kDefaultUnpackCode : kDefaultUnpackCodeOddRows;
         // across the host link: two vectors per lane, so that the few workgroups of the thin
         // form (kHostSideGroups) keep enough bytes in flight
@@ -269,11 +270,12 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
     uint32_t widest = 0;        // vectors of the largest descriptor, over the planes of this launch
     for (uint32_t p = plane_begin; p < plane_end; ++p) widest = std::max(widest, a.row_elems[p]);
     const uint64_t unit_vecs = (uint64_t)plan->max_unit_rows * widest;
-    if (vec && !plan->threads_chosen && !plan->tuning.variant) threads = tile_threads(unit_vecs);
+    if (vec && !plan->threads_chosen && !plan->tuning.variant)
+        threads = plan->paired ? (plan->layout.row_bytes[plane_begin] % 128 == 0 ? 64u : 128u) : tile_threads(unit_vecs);
     // descriptors that fill less than half a workgroup: deal the lanes out without tiles
     if (vec && !plan->tuning.variant && unit_vecs * 2 <= plan->tuning.block_threads) {
-        v = pack ? kFlatPackCode : kFlatUnpackCode;
-        threads = plan->tuning.block_threads;
+        v = plan->paired ? kFlatMoveCode : pack ? kFlatPackCode : kFlatUnpackCode;
+        threads = plan->paired && !plan->threads_chosen ? 1024u : plan->tuning.block_threads;
     }
     dim3 block(threads);
     const On on{stream, launch_event(plan, stream)};

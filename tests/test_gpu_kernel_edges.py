@@ -143,3 +143,21 @@ def test_full_blocks_planes_and_tiles(bs, rows, off, where):
     assert np.all(got[:off] == 0x5A) and np.all(got[off + n:] == 0x5A)
     for a, b in zip(d_dst, want_pool):
         assert same_bytes(to_host(a), b), "load differs from the oracle"
+
+
+# a move's own workgroups: 64 lanes, 128, and 1024 flat; descriptors around one wavefront and one workgroup
+@pytest.mark.parametrize("bs,rows", [(1, (16,)), (1, (1152,)), (1, (656, 128)), (2, (1024,)), (1, (2048,)), (1, (2064,)), (16, (1152, 656)),
+                                     (64, (656,)), (3, (37,)), (64, (132, 132))])
+def test_move_launch_shapes(bs, rows):
+    w = W.tiny(1080 + bs + sum(rows), 6, bs, rows, 200, 20 * bs, kind="runs" if bs % 2 else "random")
+    src = W.fill_pool(w, 0, "src")
+    x = oracle.pack(bs, rows, w.hit, w.src.tables, src)
+    want = W.sentinel_pool(w, "dst")
+    oracle.unpack(bs, rows, w.hit, w.dst.tables, x, want)
+    g, s = dev_plan(w, "src", K.KVL_GATHER), dev_plan(w, "dst", K.KVL_SCATTER)
+    pair = K.kvl_plan_pair(g, s)
+    d_src, d_dst = planes_to_dev(src), planes_to_dev(W.sentinel_pool(w, "dst"))
+    K.kvl_move_layer(pair, d_src, d_dst)
+    torch.cuda.synchronize()
+    for a, b in zip(d_dst, want):
+        assert same_bytes(to_host(a), b)
