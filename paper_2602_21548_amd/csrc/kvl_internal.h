@@ -35,9 +35,11 @@ struct kvl_plan_s {
     int device = -1;
     // One event per stream on which kernels that read d_units were enqueued (the caller's streams and
     // the lanes), taken along by every such launch: once all of them have fired no kernel reads the
-    // buffer any more and it may be handed to another plan.  Recorded at launch time because a stream
-    // of the caller's may be gone by the time the plan is destroyed.
+    // buffer any more and it may be handed to another plan.  They go with the launches because a stream
+    // of the caller's may be gone by the time the plan is destroyed; the default stream may not, and
+    // gets its event afterwards.
     mutable std::vector<std::pair<hipStream_t, hipEvent_t>> stream_events;
+    mutable bool null_stream_use = false;        // launched on the default stream (which carries no events)
     mutable bool untracked_use = false;          // a launch could not be followed (too many streams, a stream
                                                  // under capture, a failed record): wait for the device instead
     kvl_tuning_t tuning{};                       // resolved (no zero fields)

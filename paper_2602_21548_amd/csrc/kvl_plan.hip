@@ -60,6 +60,7 @@ struct RetiredBuffer {
     CachedBuffer buf;
     std::vector<hipEvent_t> events;     // all fired: no kernel reads the buffer any more
     hipEvent_t map_event;               // (or null) fired: the kernel that wrote the row map into it has finished
+    bool null_stream;                   // used on the default stream, and no event recorded there yet
 };
 struct PooledLane {
     hipStream_t stream;
@@ -130,10 +131,43 @@ void keep_or_free(const CachedBuffer &b) {
     (void)hipFree(b.ptr);
 }
 
+// An event for what the default stream of the buffer's device holds now, among which are the buffer's last launches:
+// false if none could be recorded (a capture forbids it).  That stream cannot go away, so its launches carry no event
+// each; one is recorded when the buffer is looked at again.
+bool record_null_stream(RetiredBuffer &r, bool wait) {
+    int current = r.buf.device;
+    (void)hipGetDevice(&current);
+    if (current != r.buf.device) (void)hipSetDevice(r.buf.device);
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    hipEvent_t e = nullptr;
+    if (hipStreamIsCapturing(nullptr, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone)
+        e = take_event(r.buf.device);
+    bool ok = e && hipEventRecord(e, nullptr) == hipSuccess;
+    if (ok) {
+        try {
+            r.events.push_back(e);
+        } catch (const std::bad_alloc &) {
+            ok = false;
+        }
+    }
+    if (!ok) {
+        (void)hipGetLastError();
+        if (e) give_event(e, r.buf.device);
+        if (wait) ok = hipStreamSynchronize(nullptr) == hipSuccess;
+    }
+    if (current != r.buf.device) (void)hipSetDevice(current);
+    if (ok) r.null_stream = false;
+    return ok;
+}
+
 // move the retired buffers whose events have all fired to the cache; `wait`: block for them
 void reap_retired(bool wait) {
     for (size_t i = 0; i < g_retired.size();) {
         RetiredBuffer &r = g_retired[i];
+        if (r.null_stream && !record_null_stream(r, wait)) {
+            ++i;
+            continue;
+        }
         bool done = true;
         auto pending = [wait](hipEvent_t e) {
             const hipError_t q = wait ? hipEventSynchronize(e) : hipEventQuery(e);
@@ -167,6 +201,10 @@ hipEvent_t launch_event(const kvl_plan_t *plan, hipStream_t stream) {
     }
     if (capture != hipStreamCaptureStatusNone) {
         plan->untracked_use = true;
+        return nullptr;
+    }
+    if (!stream) {                                         // see record_null_stream
+        plan->null_stream_use = true;
         return nullptr;
     }
     for (const auto &se : plan->stream_events)
@@ -245,7 +283,8 @@ static hipError_t descriptor_alloc(void **out, size_t bytes, size_t *capacity, i
 // The plan is going away: its descriptor array may be reused once its launches' events
 // have fired.  No stream is touched here.
 static void descriptor_release(const kvl_plan_t *plan) {
-    RetiredBuffer r{CachedBuffer{plan->d_units, plan->d_units_capacity, plan->device}, {}, plan->map_event};
+    RetiredBuffer r{CachedBuffer{plan->d_units, plan->d_units_capacity, plan->device}, {}, plan->map_event,
+                    plan->null_stream_use};
     if (plan->flags & KVL_CALLER_SYNCS) {               // (its map was waited for when it was made)
         std::lock_guard<std::mutex> lock(g_cache_mutex);
         if (plan->map_event) give_event(plan->map_event, plan->device, true);

@@ -161,3 +161,45 @@ def test_move_launch_shapes(bs, rows):
     torch.cuda.synchronize()
     for a, b in zip(d_dst, want):
         assert same_bytes(to_host(a), b)
+
+
+def test_a_plan_used_on_the_default_stream_keeps_its_descriptors_until_they_are_read():
+    """Launches on the default stream carry no event: a plan destroyed while its kernel is still queued there must
+    not hand its descriptors (or its row map) to the plans made next; they come back once the stream has passed."""
+    w = W.tiny(1120, 9, 1, (1152,), 6000, 500)
+    other = W.tiny(1120, 9, 1, (1152,), 6000, 500)
+    other.src.tables = [t[::-1].copy() for t in other.src.tables]
+    bs, rows = w.layout.block_tokens, w.layout.row_bytes
+    src = W.fill_pool(w, 0, "src")
+    want = [oracle.pack(bs, rows, v.hit, v.src.tables, src) for v in (w, other)]
+    d_src = planes_to_dev(src)
+    x = [torch.zeros(want[0].size, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    side = torch.cuda.Stream()
+    K.kvl_release_cached_memory()
+    for _ in range(3):
+        torch.cuda.synchronize()
+        g = dev_plan(w, "src", K.KVL_GATHER)
+        torch.cuda._sleep(40_000_000)                       # tens of milliseconds on the default stream
+        K.kvl_pack_layer(g, d_src, x[0])
+        g.destroy()
+        plans = [dev_plan(other, "src", K.KVL_GATHER) for _ in range(4)]
+        for p in plans:
+            K.kvl_pack_layer(p, d_src, x[1], stream=side)
+        torch.cuda.synchronize()
+        assert same_bytes(to_host(x[0]), want[0]), "a descriptor array was reused before its kernel had run"
+        assert same_bytes(to_host(x[1]), want[1])
+        for p in plans:
+            p.destroy()
+        for t in x:
+            t.zero_()
+    torch.cuda.synchronize()
+    K.kvl_release_cached_memory()
+    free0, _ = torch.cuda.mem_get_info()
+    for _ in range(100):
+        p = dev_plan(w, "src", K.KVL_GATHER)
+        K.kvl_pack_layer(p, d_src, x[0])
+        p.destroy()
+    torch.cuda.synchronize()
+    K.kvl_release_cached_memory()
+    free1, _ = torch.cuda.mem_get_info()
+    assert free0 - free1 < (8 << 20), f"{(free0 - free1) >> 20} MiB of device memory gone"
