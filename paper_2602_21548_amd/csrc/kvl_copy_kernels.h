@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(1024) kvl_rows_kernel(const CopyArgs a, const 
 // stick out over an end are pushed inside the span, where they move some bytes a second time (the same
 // bytes to the same place).  Nothing is conditional but the lanes without work.  Bound by memory like the
 // forms above: a 280 MB layer of 132-byte rows in 64-token blocks, gather + scatter, 618 us byte by byte
-// (1.8 TB/s), 207 us now (5.4 TB/s).
+// (1.8 TB/s), 205 us now (5.5 TB/s).
 typedef v4u __attribute__((aligned(1))) v4u_any;
 typedef const v4u_any __attribute__((address_space(1))) *gsrc_any_t;
 typedef v4u_any __attribute__((address_space(1))) *gdst_any_t;
@@ -445,7 +445,7 @@ __device__ __forceinline__ void store16_any(uintptr_t p, v4u v) {
     else store16<SP>((gdst_t)p, v);          // written out as an instruction: no alignment is assumed
 }
 
-// Vector `k` of a span of n bytes, vectors counted from `lead` bytes below its first destination byte.
+// Vector `k` of a span of n bytes, vectors counted from `lead` bytes below its first byte.
 template <bool NTL, int SP>
 __device__ __forceinline__ void copy_any(uintptr_t src, uintptr_t dst, uint32_t n, uint32_t lead, uint32_t k) {
     int64_t at = (int64_t)((uint64_t)k * 16u) - (int64_t)lead;
@@ -475,7 +475,11 @@ __global__ void __launch_bounds__(1024) kvl_any_tile_kernel(const CopyArgs a, ui
         const uintptr_t pool = pool_base + (uint64_t)u->pool_row * row;
         const uintptr_t xfer = xfer_base + (uint64_t)u->xfer_row * row;
         const uintptr_t dst = PACK ? xfer : pool;
-        copy_any<NTL, SP>(PACK ? pool : xfer, dst, u->n_rows * row, (uint32_t)dst & 127u,
+        // tiles start on a line of the destination, or, where a gather's stores pass the cache by (SP == 1), of the
+        // source (300 MB and 1 GB of 1026-byte rows, hop, 236 -> 233 and 706 -> 693 us; 657-byte rows, 180 MB, 135 -> 131;
+        // for the scatter, and with stores that stay in the cache, the source's lines lose 2-10 %)
+        const uintptr_t line = PACK && SP == 1 ? pool : dst;
+        copy_any<NTL, SP>(PACK ? pool : xfer, dst, u->n_rows * row, (uint32_t)line & 127u,
                           tile * blockDim.x + threadIdx.x);
         if (!WALK) return;
     }

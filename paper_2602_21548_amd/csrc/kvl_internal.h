@@ -67,9 +67,9 @@ constexpr uint32_t kDefaultUnitBytes = 128u << 10;
 constexpr uint32_t kDefaultBlockThreads = 256;
 constexpr uint32_t kHostSideGroups = 64;    // workgroups of a kernel whose far side is host memory (see kvl_tile_walk_kernel)
 constexpr uint32_t kAnyFlatWindows = 288;   // rows that are no multiple of 16 bytes: largest descriptor, in vectors, dealt out flat
-// A layer's payload that the 256 MB on-die cache can carry from the gather's stores to the scatter's loads
-// (what else passes through it in between takes the rest).
-constexpr uint64_t kCachedLayerBytes = 192u << 20;
+// Rows that are no multiple of 16 bytes: up to this payload the on-die cache holds the layer from the gather's stores to
+// the scatter's loads, beside what else passes through it.
+constexpr uint64_t kCachedLayerBytes = 64u << 20;
 constexpr uint32_t kNumVariants = 512;       // explicit variants are 1 .. kNumVariants
 bool valid_block_threads(uint32_t t);
 

@@ -173,10 +173,10 @@ static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, co
 //     tiles, 309 -> 225); beyond it a tile per 256 lanes is the better (132 by 64, 530 vectors: 215 against
 //     245 flat).  A flat workgroup has 1024 lanes (1026-byte rows by 1: 361 us at 256, 329 at 512, 324), a
 //     tile of a descriptor below two 256-lane tiles 128 (1026 by 4: 377 us at 256, 286 at 128).
-//   cache policy: a layer that the on-die cache can hold between the gather and the scatter is written
-//     with sc1 stores and read back with plain loads (132 by 64, hop of 80 MB: 65 us against 74 with
-//     non-temporal accesses throughout; 1026 by 16, 120 MB: 82 against 95), a larger one passes it by (300 MB:
-//     226 -> 214 and 268 -> 251 us; 800 MB of 657-byte rows: 647 -> 634).
+//   cache policy: a layer that the on-die cache holds from the gather to the scatter is written with sc1 stores
+//     and read back with plain loads (132-byte rows by 64, three layers in turn, hop of 40 MB: 29.4 us against 33.0
+//     with non-temporal accesses throughout), a larger one passes it by (100 MB 76.7 -> 72.0, 180 MB 131.6 -> 123.2,
+//     1 GB 710 -> 704).  Across the host link the former (741-byte rows, 80 MB in and out, 2857 us against 2987).
 static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uint32_t planes, bool far_host,
                        const On &on) {
     const uint64_t unit_bytes = (uint64_t)plan->max_unit_rows * a.row_elems[a.plane_begin];
@@ -191,7 +191,7 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
     if (flat && plan->tuning.max_groups)
         per_launch = std::min<uint64_t>(per_launch, (uint64_t)plan->tuning.max_groups * threads / windows);
     per_launch = std::max<uint64_t>(1, per_launch);
-    const bool kept = plan->payload_bytes <= kCachedLayerBytes && !plan->paired;
+    const bool kept = far_host || (plan->payload_bytes <= kCachedLayerBytes && !plan->paired);
     for (uint64_t first = 0; first < a.n_units; first += per_launch) {
         CopyArgs part = a;
         part.unit_begin = a.unit_begin + (uint32_t)first;
