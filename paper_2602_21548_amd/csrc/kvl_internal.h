@@ -29,9 +29,7 @@ struct kvl_plan_s {
     uint32_t *d_row_map = nullptr;               // behind the descriptors in the same buffer, where they are small
                                                  // (see kvl_rows_kernel): the pool row of every transfer row
     mutable hipEvent_t map_event = nullptr;      // with it: recorded after the kernel that makes the map,
-    mutable bool map_pending = false;            // whether that kernel may still have to run, and the stream (any
-    mutable hipStream_t map_waited = nullptr;    // while map_stream_known) that has been made to wait for it last
-    mutable bool map_stream_known = false;
+    mutable bool map_pending = false;            // and whether that kernel may still have to run
     int device = -1;
     // One event per stream on which kernels that read d_units were enqueued (the caller's streams and
     // the lanes), taken along by every such launch: once all of them have fired no kernel reads the

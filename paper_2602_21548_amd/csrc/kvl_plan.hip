@@ -353,13 +353,15 @@ Uploader g_uploaders[64];
 constexpr size_t kBounceLimit = 64u << 20;      // larger descriptor arrays are copied from pageable memory
 }  // namespace
 
-// The row map (see kvl_rows_kernel), made on the device out of the descriptors just uploaded: 16 lanes write a
-// descriptor's entries.  A million single-row descriptors take about 10 us.
-__global__ void __launch_bounds__(256) kvl_row_map_kernel(const kvl_unit_t *units, uint32_t n_units, uint32_t *row_map) {
+// The row map (see kvl_rows_kernel), made on the device out of the descriptors just uploaded: 2^lanes_log2 lanes write
+// a descriptor's entries, 16 or, where two rows are the average, one (a million single-row descriptors: 33 us with 16, 9 with one).
+__global__ void __launch_bounds__(256) kvl_row_map_kernel(const kvl_unit_t *units, uint32_t n_units, uint32_t lanes_log2,
+                                                          uint32_t *row_map) {
     const uint64_t t = (uint64_t)blockIdx.x * 256u + threadIdx.x;
-    if ((t >> 4) >= n_units) return;
-    const kvl_unit_t u = units[t >> 4];
-    for (uint32_t i = t & 15u; i < u.n_rows; i += 16) row_map[u.xfer_row + i] = u.pool_row + i;
+    if ((t >> lanes_log2) >= n_units) return;
+    const kvl_unit_t u = units[t >> lanes_log2];
+    const uint32_t lanes = 1u << lanes_log2;
+    for (uint32_t i = (uint32_t)t & (lanes - 1u); i < u.n_rows; i += lanes) row_map[u.xfer_row + i] = u.pool_row + i;
 }
 
 // (The bounds keep its launch below 2^32 lanes and the table below 1 GiB.)
@@ -390,8 +392,9 @@ static void start_row_map(kvl_plan_t *plan, hipStream_t &stream) {
     if (!ev) return;
     const uint32_t n = (uint32_t)plan->units.size();
     uint32_t *map = reinterpret_cast<uint32_t *>(plan->d_units + n);
-    hipLaunchKernelGGL(kvl_row_map_kernel, dim3((uint32_t)(((uint64_t)n * 16 + 255) / 256)), dim3(256), 0, stream,
-                       plan->d_units, n, map);
+    const uint32_t lanes_log2 = plan->hit_tokens <= 2ull * n ? 0 : 4;
+    hipLaunchKernelGGL(kvl_row_map_kernel, dim3((uint32_t)((((uint64_t)n << lanes_log2) + 255) / 256)), dim3(256), 0, stream,
+                       plan->d_units, n, lanes_log2, map);
     bool ok = hipGetLastError() == hipSuccess;
     ok = hipEventRecord(ev, stream) == hipSuccess && ok;
     // a plan whose caller answers for its lifetime may be dropped before its first launch
@@ -409,7 +412,6 @@ static void start_row_map(kvl_plan_t *plan, hipStream_t &stream) {
 
 bool row_map_ready(const kvl_plan_t *plan, hipStream_t stream) {
     if (!plan->map_pending) return true;
-    if (plan->map_stream_known && plan->map_waited == stream) return true;
     // an event from outside may not be waited for in a capture: such a launch goes without the map
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
@@ -425,9 +427,7 @@ bool row_map_ready(const kvl_plan_t *plan, hipStream_t stream) {
         (void)hipGetLastError();
         return false;
     }
-    plan->map_waited = stream;
-    plan->map_stream_known = true;
-    return true;
+    return true;        // (asked again on every launch until it has fired: a stream's handle may be a new stream's by then)
 }
 
 int upload_units(kvl_plan_t *plan) {
@@ -917,7 +917,10 @@ void kvl_release_cached_memory(void) {
     for (kvl::Uploader &u : kvl::g_uploaders) {
         if (u.bounce) (void)hipHostFree(u.bounce);
         if (u.stream) (void)hipStreamDestroy(u.stream);
-        if (u.map_stream) (void)hipStreamDestroy(u.map_stream);
+        if (u.map_stream) {
+            (void)hipStreamSynchronize(u.map_stream);       // a map or two, for their plans' events
+            (void)hipStreamDestroy(u.map_stream);
+        }
         u = kvl::Uploader{};
     }
 }
