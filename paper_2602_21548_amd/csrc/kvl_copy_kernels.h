@@ -56,10 +56,9 @@ constexpr uint32_t kDefaultPackCodePassBy = 2u | 4u | (3u << 3);  // tile x1, nt
 constexpr uint32_t kDefaultUnpackCode = 2u | 4u | (3u << 3);    // tile x1, nt loads, sc1+nt stores
 constexpr uint32_t kDefaultUnpackCodeOddRows = 2u | (3u << 3);  // tile x1, plain loads, sc1+nt stores
 // A move reads one pool and writes another, both in hops, and nobody reads the result at once: it writes past the caches,
-// in workgroups of one wavefront where every descriptor begins on a line, of two elsewhere.  600 MB of 64-token blocks,
-// us: 1152-byte rows 218 as the gather does it, 206 with its workgroups of 256, 199; 656-byte rows 213, 196, 195 (203
-// with 64 lanes); 2 and 3 GB 667 / 635 / 616 and 1142 / 1074 / 1068.  Single-token blocks, flat: 1152 bytes, 600 MB,
-// 267 -> 227 with 1024 lanes and nt stores, 656 bytes, 300 MB, 145 -> 109.
+// in workgroups as move_threads says.  64-token blocks, us, as the gather does it / this way: 1152-byte rows, 600 MB,
+// 218 / 199 (206 with 256 lanes), 2 GB 667 / 616; 656-byte rows, 600 MB, 213 / 196, 3 GB 1142 / 1074.  Single-token
+// blocks, flat: 1152 bytes, 600 MB, 267 -> 227 with 1024 lanes and nt stores, 656 bytes, 300 MB, 145 -> 109.
 constexpr uint32_t kMoveCode = 2u | 4u | (3u << 3);             // tile x1, nt loads, sc1+nt stores
 constexpr uint32_t kFlatMoveCode = 128u | 4u | (1u << 3);       // flat, nt loads, nt stores
 constexpr uint32_t kFlatPackCode = 128u | 4u | (2u << 3);       // flat, nt loads, sc1 stores

@@ -96,6 +96,18 @@ inline uint32_t tile_threads(uint64_t unit_vecs) {
     return idle(kDefaultBlockThreads) - idle(kDefaultBlockThreads / 2) > 0.07 ? kDefaultBlockThreads / 2 : kDefaultBlockThreads;
 }
 
+// Lanes of a move's workgroups: one wavefront where the descriptors are alike and begin on lines, else as tile_threads
+// says.  A launch has the tiles of the largest descriptor for every one, and narrow workgroups make four times as many of
+// those that find nothing to do.  300 MB, us with 64 / 128 / 256 lanes: 1152-byte rows by 64, all alike, 92.1 / 94.9 /
+// 93.5; by 20 tokens at random (largest 1.4 times the average) 99.1 / 98.3 / 101.2; runs of 16-token blocks (1.9 times)
+// 121.6 / 104.6 / 100.1; 256-byte rows by 4 in runs (2.6 times) 178.8 / 165.2 / 117.0; 656-byte rows by 16 and 64, alike,
+// 99.5 / 105.8 / 99.8 and 97.7 / 95.3 / 95.1.
+inline uint32_t move_threads(const kvl_plan_s *plan, uint32_t row_bytes) {
+    const uint64_t largest = (uint64_t)plan->max_unit_rows * (row_bytes / 16);
+    const bool alike = 2ull * plan->max_unit_rows * plan->units.size() <= 3 * plan->hit_tokens;
+    return row_bytes % 128 == 0 && alike ? 64 : tile_threads(largest);
+}
+
 // Whether a launch over planes of this row size is laid out over the transfer rows (kvl_rows_kernel) instead of over
 // the descriptors' tiles, which have the size of the largest descriptor's.  Measured on hops of one plane, us a hop,
 // tiles / rows:

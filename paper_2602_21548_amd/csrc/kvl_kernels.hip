@@ -271,7 +271,7 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
     for (uint32_t p = plane_begin; p < plane_end; ++p) widest = std::max(widest, a.row_elems[p]);
     const uint64_t unit_vecs = (uint64_t)plan->max_unit_rows * widest;
     if (vec && !plan->threads_chosen && !plan->tuning.variant)
-        threads = plan->paired ? (plan->layout.row_bytes[plane_begin] % 128 == 0 ? 64u : 128u) : tile_threads(unit_vecs);
+        threads = plan->paired ? move_threads(plan, plan->layout.row_bytes[plane_begin]) : tile_threads(unit_vecs);
     // descriptors that fill less than half a workgroup: deal the lanes out without tiles
     if (vec && !plan->tuning.variant && unit_vecs * 2 <= plan->tuning.block_threads) {
         v = plan->paired ? kFlatMoveCode : pack ? kFlatPackCode : kFlatUnpackCode;

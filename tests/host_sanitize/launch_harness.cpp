@@ -1,0 +1,102 @@
+// What the library enqueues, and where, watched through a stand-in for the HIP runtime (fake_hip.h): launch shapes at
+// sizes that no test machine holds, waits, events and captures.  Built and run by tests/test_host_launches.py, one
+// check (named on the command line) to a process.
+#include <cstdio>
+#include <numeric>
+
+#include "fake_hip.h"
+#include "kvl_plan.hip"
+#include "kvl_kernels.hip"
+
+using fake::launches;
+
+#define REQUIRE(c) do { if (!(c)) { std::printf("%s failed at line %d\n", #c, __LINE__); return 1; } } while (0)
+
+static bool is(const fake::Launch &l, const char *kernel) { return l.kernel.find(kernel) != std::string::npos; }
+static uint64_t groups(const fake::Launch &l) { return (uint64_t)l.grid.x * l.grid.y * l.grid.z; }
+
+// A plan made without kvl_plan, for sizes that only the launcher sees: `n` descriptors of one row each but the last, of `last`.
+static kvl_plan_s made(uint64_t n, uint32_t last, uint32_t row, uint32_t planes = 1) {
+    kvl_plan_s p;
+    p.layout.n_layers = 1;
+    p.layout.block_tokens = 1;
+    p.layout.n_planes = planes;
+    for (uint32_t q = 0; q < planes; ++q) p.layout.row_bytes[q] = row;
+    p.layout.pool_blocks = p.dst_pool_blocks = n + last;
+    p.flags = KVL_GATHER | KVL_SCATTER | KVL_NO_POINTER_CHECKS;
+    p.hit_tokens = n - 1 + last;
+    p.payload_bytes = p.hit_tokens * row * planes;
+    p.blocks_touched = p.hit_tokens;
+    p.max_unit_rows = last;
+    p.vec16 = row % 16 == 0;
+    p.units.resize(n);
+    p.units.back() = kvl_unit_t{0, (uint32_t)(n - 1), last, 0};
+    static kvl_unit_t somewhere;
+    p.d_units = &somewhere;
+    p.device = 0;
+    p.tuning = kvl_tuning_t{kvl::kDefaultUnitBytes, kvl::kDefaultBlockThreads, 0, 0};
+    return p;
+}
+static void *const kPlanes[KVL_MAX_PLANES] = {(void *)(1ull << 40), (void *)(1ull << 41), (void *)(1ull << 42), (void *)(1ull << 43)};
+
+// kvl_plan over `tokens` single-token blocks in reverse order (no two merge)
+static kvl_plan_t *plan_of_single_tokens(uint32_t tokens, uint32_t row, uint32_t flags) {
+    std::vector<int32_t> table(tokens);
+    for (uint32_t i = 0; i < tokens; ++i) table[i] = (int32_t)(tokens - 1 - i);
+    kvl_layout_t lay{};
+    lay.n_layers = lay.block_tokens = lay.n_planes = 1;
+    lay.row_bytes[0] = row;
+    lay.pool_blocks = tokens;
+    kvl_request_t req{};
+    req.hit_tokens = req.n_blocks = tokens;
+    req.block_table = table.data();
+    kvl_plan_t *p = nullptr;
+    return kvl_plan(&lay, &req, 1, flags | KVL_NO_POINTER_CHECKS, &p) == KVL_OK ? p : nullptr;
+}
+
+// Moves: a launch has the largest descriptor's tiles for every descriptor, so narrow workgroups are for descriptors that
+// are alike.  Single rows with one long run among them keep the gather's shape, and its limit on tiles.
+static int check_move_shapes() {
+    for (uint64_t n : {1000000ull, 20000000ull}) {
+        kvl_plan_s p = made(n, 113, 1152);
+        p.paired = true;
+        uintptr_t to[KVL_MAX_PLANES] = {1ull << 44};
+        launches.clear();
+        REQUIRE(kvl::launch_units(&p, true, 0, (uint32_t)n, 0, 1, kPlanes, to, nullptr) == KVL_OK);
+        REQUIRE(launches.size() == 1 && launches[0].block.x == 256);
+        // 113 rows of 72 vectors are 32 tiles; beyond 2^32 lanes the workgroups walk
+        REQUIRE(groups(launches[0]) == std::min<uint64_t>(n * 32, kvl::kMaxLanesPerLaunch / 256));
+        p.d_units = nullptr;
+    }
+    kvl_plan_s p = made(1000, 1, 1152);
+    p.paired = true;
+    for (kvl_unit_t &u : p.units) u.n_rows = 64;
+    p.max_unit_rows = 64;
+    p.hit_tokens = 64 * 1000;
+    uintptr_t to[KVL_MAX_PLANES] = {1ull << 44};
+    launches.clear();
+    REQUIRE(kvl::launch_units(&p, true, 0, 1000, 0, 1, kPlanes, to, nullptr) == KVL_OK);
+    REQUIRE(launches.size() == 1 && launches[0].block.x == 64 && launches[0].grid.x == 1000 * 72);
+    p.layout.row_bytes[0] = 656;            // off the lines: as tile_threads says
+    launches.clear();
+    REQUIRE(kvl::launch_units(&p, true, 0, 1000, 0, 1, kPlanes, to, nullptr) == KVL_OK);
+    REQUIRE(launches.size() == 1 && launches[0].block.x == kvl::tile_threads(64 * 41));
+    p.d_units = nullptr;
+    return 0;
+}
+
+//CHECKS
+
+int main(int argc, char **argv) {
+    const std::map<std::string, int (*)()> checks = {
+        {"move_shapes", check_move_shapes},
+//TABLE
+    };
+    if (argc != 2 || !checks.count(argv[1])) {
+        for (const auto &c : checks) std::printf("%s\n", c.first.c_str());
+        return argc == 1 ? 0 : 2;
+    }
+    const int rc = checks.at(argv[1])();
+    if (rc == 0) std::printf("ok\n");
+    return rc;
+}

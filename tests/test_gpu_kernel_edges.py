@@ -203,3 +203,25 @@ def test_a_plan_used_on_the_default_stream_keeps_its_descriptors_until_they_are_
     K.kvl_release_cached_memory()
     free1, _ = torch.cuda.mem_get_info()
     assert free0 - free1 < (8 << 20), f"{(free0 - free1) >> 20} MiB of device memory gone"
+
+
+@pytest.mark.parametrize("row", [1152, 656])
+def test_a_move_of_single_rows_with_one_long_run(row):
+    """Descriptors that are unlike: every one has the largest one's tiles, most of them empty."""
+    n, run = 3000, 113
+    w = W.tiny(1100, 1, 1, (row,), n + 2 * run, n + run, allow_zero_hit=False)
+    rng = np.random.Generator(np.random.PCG64(4))
+    w.hit[:], w.app[:] = n + run, 0
+    for side, first in ((w.src, 0), (w.dst, run)):
+        single = np.setdiff1d(np.arange(side.pool_blocks), np.arange(first, first + run))
+        side.tables = [np.concatenate([rng.permutation(single)[:n], np.arange(first, first + run)]).astype(np.int32)]
+    bs, rows = w.layout.block_tokens, w.layout.row_bytes
+    src = W.fill_pool(w, 0, "src")
+    want = W.sentinel_pool(w, "dst")
+    oracle.unpack(bs, rows, w.hit, w.dst.tables, oracle.pack(bs, rows, w.hit, w.src.tables, src), want)
+    pair = K.kvl_plan_pair(dev_plan(w, "src", K.KVL_GATHER), dev_plan(w, "dst", K.KVL_SCATTER))
+    assert pair.units()[:, 2].max() > 1
+    d_src, d_dst = planes_to_dev(src), planes_to_dev(W.sentinel_pool(w, "dst"))
+    K.kvl_move_layer(pair, d_src, d_dst)
+    torch.cuda.synchronize()
+    assert same_bytes(to_host(d_dst[0]), want[0])
