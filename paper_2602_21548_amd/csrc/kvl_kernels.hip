@@ -402,29 +402,36 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
     const uint32_t vpt = far_host && vec ? 2 : 1;
     const uint64_t per_tile = (uint64_t)threads * vpt * (vec ? 1 : 16);
     // (a span off the 16-byte grid is laid out from the 128-byte line below its start)
-    uint64_t tpu = 0;
+    uint64_t tpu = 0, widest = 0;
     for (uint32_t p = 0; p < KVL_MAX_PLANES; ++p) {
-        if (p < P) tpu += ((uint64_t)plan->max_unit_rows * a.row_elems[p] + (vec ? 0 : 127) + per_tile - 1) / per_tile;
+        const uint64_t tiles = p < P ? ((uint64_t)plan->max_unit_rows * a.row_elems[p] + (vec ? 0 : 127) + per_tile - 1) / per_tile : 0;
+        widest = std::max(widest, tiles);
+        tpu += tiles;
         a.tile_end[p] = (uint32_t)std::min<uint64_t>(tpu, UINT32_MAX);
     }
-    const uint64_t wgs = (uint64_t)a.n_units * tpu;
-    if (wgs > (uint64_t)INT32_MAX) return KVL_ERANGE;
+    if (a.n_units * widest > (uint64_t)INT32_MAX || tpu > (uint64_t)INT32_MAX) return KVL_ERANGE;
     const uint32_t cap = plan->tuning.max_groups ? plan->tuning.max_groups
                                                  : (far_host ? (vec ? kHostSideGroups : 2 * kHostSideGroups) : 0u);
-    const uint32_t n_tiles = (uint32_t)wgs;
-    bool walk = false;
-    dim3 grid(launch_groups(wgs, threads, cap, &walk)), block(threads);
     const On on{stream, launch_event(plan, stream)};
+    // the tiles of all planes are numbered with 32 bits: descriptors that have more go in several launches
+    const uint32_t n_all = a.n_units, per_launch = (uint32_t)(INT32_MAX / tpu);
+    for (uint32_t first = 0; first < n_all; first += per_launch) {
+        a.n_units = std::min(per_launch, n_all - first);
+        const uint32_t n_tiles = a.n_units * (uint32_t)tpu;
+        bool walk = false;
+        dim3 grid(launch_groups(n_tiles, threads, cap, &walk)), block(threads);
 #define KVL_FB_LAUNCH(...) \
-    KVL_LAUNCH((kvl_fullblock_kernel<__VA_ARGS__>), grid, block, on, a, (uint32_t)tpu, n_tiles)
-    if (to_pool) {
-        if (!vec) KVL_FB_LAUNCH(true, false, 1, true, 2);
-        else if (far_host) KVL_FB_LAUNCH(true, true, 2, false, 3);
-        else KVL_FB_LAUNCH(true, true, 1, true, 2);
-    } else {
-        if (!vec) KVL_FB_LAUNCH(false, false, 1, true, 3);
-        else if (far_host) KVL_FB_LAUNCH(false, true, 2, true, 0);
-        else KVL_FB_LAUNCH(false, true, 1, true, 3);
+        KVL_LAUNCH((kvl_fullblock_kernel<__VA_ARGS__>), grid, block, on, a, (uint32_t)tpu, n_tiles)
+        if (to_pool) {
+            if (!vec) KVL_FB_LAUNCH(true, false, 1, true, 2);
+            else if (far_host) KVL_FB_LAUNCH(true, true, 2, false, 3);
+            else KVL_FB_LAUNCH(true, true, 1, true, 2);
+        } else {
+            if (!vec) KVL_FB_LAUNCH(false, false, 1, true, 3);
+            else if (far_host) KVL_FB_LAUNCH(false, true, 2, true, 0);
+            else KVL_FB_LAUNCH(false, true, 1, true, 3);
+        }
+        a.units += a.n_units;
     }
 #undef KVL_FB_LAUNCH
     KVL_HIP(hipGetLastError());

@@ -85,11 +85,29 @@ static int check_move_shapes() {
     return 0;
 }
 
+// Full Blocks: the limit on tiles is that of the widest plane, though the tiles of all planes are numbered through.
+static int check_full_block_planes() {
+    kvl_plan_s p = made(20000000, 1, 2048, 4);
+    p.layout.block_tokens = p.max_unit_rows = 64;           // ragged: blocks of one row, some of 64 (32 tiles a plane)
+    launches.clear();
+    REQUIRE(kvl::fullblock_launch(&p, true, 1ull << 44, 4 * 64 * 2048, 0, 0, 20000000, kPlanes, nullptr) == KVL_OK);
+    REQUIRE(launches.size() == 2);
+    for (const fake::Launch &l : launches) REQUIRE(is(l, "kvl_fullblock_kernel") && groups(l) * l.block.x <= kvl::kMaxLanesPerLaunch);
+    launches.clear();
+    REQUIRE(kvl::fullblock_launch(&p, true, 1ull << 44, 4 * 64 * 2048, 0, 5, 1005, kPlanes, nullptr) == KVL_OK);
+    REQUIRE(launches.size() == 1 && groups(launches[0]) == 1000 * 128);
+    p.max_unit_rows = 64 * 64;
+    REQUIRE(kvl::fullblock_launch(&p, true, 1ull << 44, 4 * 64 * 2048, 0, 0, 20000000, kPlanes, nullptr) == KVL_ERANGE);
+    p.d_units = nullptr;
+    return 0;
+}
+
 //CHECKS
 
 int main(int argc, char **argv) {
     const std::map<std::string, int (*)()> checks = {
         {"move_shapes", check_move_shapes},
+        {"full_block_planes", check_full_block_planes},
 //TABLE
     };
     if (argc != 2 || !checks.count(argv[1])) {
