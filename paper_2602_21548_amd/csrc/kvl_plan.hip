@@ -285,11 +285,25 @@ static hipError_t descriptor_alloc(void **out, size_t bytes, size_t *capacity, i
 static void descriptor_release(const kvl_plan_t *plan) {
     RetiredBuffer r{CachedBuffer{plan->d_units, plan->d_units_capacity, plan->device}, {}, plan->map_event,
                     plan->null_stream_use};
-    if (plan->flags & KVL_CALLER_SYNCS) {               // (its map was waited for when it was made)
+    if (plan->flags & KVL_CALLER_SYNCS) {
+        // the caller has waited for the launches; the map's kernel is the library's own and may still be to come, in a
+        // plan dropped before its first launch
         std::lock_guard<std::mutex> lock(g_cache_mutex);
-        if (plan->map_event) give_event(plan->map_event, plan->device, true);
+        bool retired = false;
+        if (plan->map_pending) {
+            r.null_stream = false;
+            try {
+                g_retired.push_back(r);
+                retired = true;
+            } catch (const std::bad_alloc &) {
+                (void)hipEventSynchronize(plan->map_event);
+            }
+        }
+        if (!retired) {
+            if (plan->map_event) give_event(plan->map_event, plan->device, true);
+            keep_or_free(r.buf);
+        }
         plan->map_event = nullptr;
-        keep_or_free(r.buf);
         return;
     }
     bool tracked = !plan->untracked_use;
@@ -397,14 +411,13 @@ static void start_row_map(kvl_plan_t *plan, hipStream_t &stream) {
                        plan->d_units, n, lanes_log2, map);
     bool ok = hipGetLastError() == hipSuccess;
     ok = hipEventRecord(ev, stream) == hipSuccess && ok;
-    // a plan whose caller answers for its lifetime may be dropped before its first launch
-    if (!ok || (plan->flags & KVL_CALLER_SYNCS)) ok = hipStreamSynchronize(stream) == hipSuccess && ok;
     if (ok) {
         plan->d_row_map = map;
         plan->map_event = ev;
-        plan->map_pending = !(plan->flags & KVL_CALLER_SYNCS);
+        plan->map_pending = true;
     } else {
         (void)hipGetLastError();
+        (void)hipStreamSynchronize(stream);
         std::lock_guard<std::mutex> lock(g_cache_mutex);
         give_event(ev, plan->device, true);
     }

@@ -102,12 +102,36 @@ static int check_full_block_planes() {
     return 0;
 }
 
+// kvl_plan enqueues the making of the row map and waits for nothing that runs on the device, whoever answers for the
+// plan's lifetime; the array of a plan dropped before its map was made comes back when the map's kernel has run.
+static int check_caller_syncs() {
+    for (uint32_t flags : {KVL_GATHER | KVL_CALLER_SYNCS, KVL_GATHER}) {
+        kvl_release_cached_memory();
+        launches.clear();
+        fake::mallocs = fake::waited = 0;
+        kvl_plan_t *p = plan_of_single_tokens(5000, 1152, flags);
+        REQUIRE(p && p->d_row_map && launches.size() == 1 && is(launches[0], "kvl_row_map_kernel"));
+        REQUIRE(fake::waited == 0 && fake::mallocs == 1);
+        const void *first = p->d_units;
+        kvl_plan_destroy(p);
+        p = plan_of_single_tokens(5000, 1152, flags);
+        REQUIRE(p && p->d_units != first && fake::mallocs == 2 && fake::waited == 0);
+        for (const fake::Launch &l : launches) fake::finish(l.stream);
+        kvl_plan_t *q = plan_of_single_tokens(5000, 1152, flags);
+        REQUIRE(q && q->d_units == first && fake::mallocs == 2 && fake::waited == 0);
+        kvl_plan_destroy(p);
+        kvl_plan_destroy(q);
+    }
+    return 0;
+}
+
 //CHECKS
 
 int main(int argc, char **argv) {
     const std::map<std::string, int (*)()> checks = {
         {"move_shapes", check_move_shapes},
         {"full_block_planes", check_full_block_planes},
+        {"caller_syncs", check_caller_syncs},
 //TABLE
     };
     if (argc != 2 || !checks.count(argv[1])) {
