@@ -423,24 +423,30 @@ static void start_row_map(kvl_plan_t *plan, hipStream_t &stream) {
     }
 }
 
+// (The map is lost only to a launch that is captured before the map has been made: an event from outside may not be
+// waited for in a capture.)
 bool row_map_ready(const kvl_plan_t *plan, hipStream_t stream) {
     if (!plan->map_pending) return true;
-    // an event from outside may not be waited for in a capture: such a launch goes without the map
+    // whether it has been made may be asked during a capture, this stream's or another's, by a thread that says so
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const hipError_t made = relaxed ? hipEventQuery(plan->map_event) : hipErrorNotReady;
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (made == hipSuccess) {
+        plan->map_pending = false;
+        return true;
+    }
+    (void)hipGetLastError();
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
         return false;
     }
-    if (hipEventQuery(plan->map_event) == hipSuccess) {
-        plan->map_pending = false;
-        return true;
-    }
-    (void)hipGetLastError();
     if (hipStreamWaitEvent(stream, plan->map_event, 0) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return true;        // (asked again on every launch until it has fired: a stream's handle may be a new stream's by then)
+    return true;        // (asked again on every launch until it has been made: a stream's handle may be a new stream's by then)
 }
 
 int upload_units(kvl_plan_t *plan) {

@@ -125,6 +125,46 @@ static int check_caller_syncs() {
     return 0;
 }
 
+static int pack(kvl_plan_t *p, hipStream_t s) {
+    return kvl_pack_layer(p, kPlanes, (void *)(1ull << 44), p->payload_bytes, s);
+}
+
+// A captured launch uses the row map if it has been made by then, also where no launch came before it; one that is
+// captured earlier goes without.  Neither does anything that a capture forbids, and no more does an eager launch beside one.
+static int check_row_map_under_capture() {
+    fake::Stream a, b;
+    kvl_plan_t *p = plan_of_single_tokens(5000, 1152, KVL_GATHER);
+    REQUIRE(p && p->d_row_map);
+    fake::Stream *map_stream = launches.back().stream;
+    fake::begin_capture(a);
+    REQUIRE(pack(p, fake::handle(a)) == KVL_OK && is(launches.back(), "kvl_flat_kernel"));
+    REQUIRE(pack(p, fake::handle(b)) == KVL_OK && is(launches.back(), "kvl_rows_kernel"));      // eager, beside it
+    REQUIRE(fake::waits.size() == 1 && fake::waits[0].first == &b);
+    fake::finish(map_stream);
+    REQUIRE(pack(p, fake::handle(a)) == KVL_OK && is(launches.back(), "kvl_rows_kernel"));
+    fake::end_capture(a);
+    REQUIRE(!fake::capture_broken && fake::waits.size() == 1);
+    kvl_plan_destroy(p);
+    return 0;
+}
+
+// Every stream that launches before the map has been made waits for it; none does afterwards.
+static int check_row_map_on_two_streams() {
+    fake::Stream a, b;
+    kvl_plan_t *p = plan_of_single_tokens(5000, 1152, KVL_GATHER);
+    fake::Stream *map_stream = launches.back().stream;
+    for (fake::Stream *s : {&a, &b, &fake::null_stream, &b}) {
+        fake::waits.clear();
+        REQUIRE(pack(p, s == &fake::null_stream ? nullptr : fake::handle(*s)) == KVL_OK);
+        REQUIRE(is(launches.back(), "kvl_rows_kernel") && fake::waits.size() == 1 && fake::waits[0].first == s);
+    }
+    fake::finish(map_stream);
+    fake::waits.clear();
+    REQUIRE(pack(p, fake::handle(a)) == KVL_OK && pack(p, fake::handle(b)) == KVL_OK && fake::waits.empty());
+    kvl_plan_destroy(p);
+    return 0;
+}
+
 //CHECKS
 
 int main(int argc, char **argv) {
@@ -132,6 +172,8 @@ int main(int argc, char **argv) {
         {"move_shapes", check_move_shapes},
         {"full_block_planes", check_full_block_planes},
         {"caller_syncs", check_caller_syncs},
+        {"row_map_under_capture", check_row_map_under_capture},
+        {"row_map_on_two_streams", check_row_map_on_two_streams},
 //TABLE
     };
     if (argc != 2 || !checks.count(argv[1])) {

@@ -1,5 +1,7 @@
 """The dispatch's edges: sizes at which a launch changes its kernel, its tile or its remainder, against the
 CPU oracle, bit for bit (the comparison is exact: bytes are moved, none is computed)."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -225,3 +227,75 @@ def test_a_move_of_single_rows_with_one_long_run(row):
     K.kvl_move_layer(pair, d_src, d_dst)
     torch.cuda.synchronize()
     assert same_bytes(to_host(d_dst[0]), want[0])
+
+
+@pytest.mark.parametrize("wait", [True, False], ids=["map-made", "at-once"])
+def test_a_plan_with_a_row_map_captured_without_an_eager_launch(wait):
+    """Its first launches are captured: the map is used if it has been made by then, and every replay is right."""
+    w = W.tiny(1130, 9, 1, (1152,), 3000, 300)
+    bs, rows = w.layout.block_tokens, w.layout.row_bytes
+    g, s = dev_plan(w, "src", K.KVL_GATHER), dev_plan(w, "dst", K.KVL_SCATTER)
+    d_src, d_dst = planes_to_dev(W.fill_pool(w, 0, "src")), planes_to_dev(W.sentinel_pool(w, "dst"))
+    x = torch.zeros(g.payload_bytes, dtype=torch.uint8, device="cuda")
+    st = torch.cuda.Stream()
+    if wait:
+        torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=st):
+        K.kvl_pack_layer(g, d_src, x, stream=st)
+        K.kvl_unpack_layer(s, x, d_dst, stream=st)
+    if wait:        # laid out over the transfer rows: as many lanes as there are vectors, and the line-up
+        vectors = int(w.hit.sum()) * rows[0] // 16
+        assert [grid for grid in _grids(graph)] == [(vectors + 7 + 255) // 256] * 2
+    graph.instantiate()
+    for rep in range(3):
+        fill = W.fill_pool(w, rep + 1, "src")
+        d_src[0].copy_(to_dev(fill[0]))
+        d_dst[0].fill_(0xA5)
+        x.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(st):
+            graph.replay()
+        st.synchronize()
+        want_x = oracle.pack(bs, rows, w.hit, w.src.tables, fill)
+        want = W.sentinel_pool(w, "dst")
+        oracle.unpack(bs, rows, w.hit, w.dst.tables, want_x, want)
+        assert same_bytes(to_host(x), want_x) and same_bytes(to_host(d_dst[0]), want[0]), f"replay {rep}"
+
+
+def _grids(graph):
+    """Workgroups along x of every kernel in a captured graph, in order."""
+    class Params(C.Structure):      # hipKernelNodeParams
+        _fields_ = [("block", C.c_uint32 * 3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", C.c_uint32 * 3),
+                    ("params", C.c_void_p), ("shared", C.c_uint32)]
+    hip, n = K.binding._lib, C.c_size_t()       # (the library brings the HIP runtime with it)
+    raw = C.c_void_p(graph.raw_cuda_graph())
+    assert hip.hipGraphGetNodes(raw, None, C.byref(n)) == 0
+    nodes = (C.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, C.byref(n)) == 0
+    out = []
+    for node in nodes:
+        p = Params()
+        assert hip.hipGraphKernelNodeGetParams(C.c_void_p(node), C.byref(p)) == 0
+        out.append(p.grid[0])
+    return out
+
+
+def test_a_row_map_awaited_by_two_streams():
+    """A plan's first launches on two streams at once: both wait for its map, whichever asks first."""
+    w = W.tiny(1140, 9, 1, (1152,), 6000, 500)
+    bs, rows = w.layout.block_tokens, w.layout.row_bytes
+    src = W.fill_pool(w, 0, "src")
+    want = oracle.pack(bs, rows, w.hit, w.src.tables, src)
+    d_src = planes_to_dev(src)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream(), None]
+    for _ in range(5):
+        x = [torch.zeros(want.size, dtype=torch.uint8, device="cuda") for _ in streams]
+        torch.cuda.synchronize()
+        g = dev_plan(w, "src", K.KVL_GATHER)
+        for s, t in zip(streams, x):
+            K.kvl_pack_layer(g, d_src, t, stream=s)
+        torch.cuda.synchronize()
+        for t in x:
+            assert same_bytes(to_host(t), want)
+        g.destroy()
