@@ -151,19 +151,20 @@ int kvl_plan_tuned(const kvl_layout_t *layout, const kvl_request_t *requests, ui
                    uint32_t flags, const kvl_tuning_t *tuning, kvl_plan_t **out);
 /* Frees the plan.  The call does not wait for the device: kernels enqueued with the
  * plan may still be running or queued.  Every launch made with a plan carries
- * an event (one per stream, that of the stream's last launch); the default stream,
- * which cannot go away, gets one when the library next looks at what was retired
- * (the next plan).  The plan's device descriptor array is retired with those events and
- * goes back to a small cache inside the library (at most 16 buffers / 256 MiB, from
- * which later plans are served without a device allocation) only when they have fired.
+ * an event (one per stream, that of the stream's last launch).  The plan's device descriptor
+ * array is retired with those events and goes back to a small cache inside the library (at most
+ * 16 buffers / 256 MiB, from which later plans are served without a device allocation) only when
+ * they have fired.  The default stream, which cannot go away, is followed by the next launch that
+ * the library makes there instead: that one carries an event for the arrays of all plans used there
+ * and destroyed before it, which go back when it has finished.
  * The streams themselves are not touched here and may be gone already.  Only the plan's
  * own lanes, if a host-buffer call left work on them that is not finished, are
  * waited for.  A plan whose launches were captured into a HIP graph cannot be followed
  * that way: destroying it waits for the device, and the graph must not be replayed
  * afterwards.  A plan made with KVL_CALLER_SYNCS is not followed at all (see there).
  * kvl_release_cached_memory empties the cache and the library's pool of lanes; it
- * waits for the kernels of destroyed plans, and for nothing else (on the default
- * stream: for what it holds by then). */
+ * waits for the kernels of destroyed plans, and for nothing else (of plans used on
+ * the default stream and not followed there yet: for what the stream holds). */
 void kvl_plan_destroy(kvl_plan_t *plan);
 void kvl_release_cached_memory(void);
 

@@ -34,8 +34,8 @@ struct kvl_plan_s {
     // One event per stream on which kernels that read d_units were enqueued (the caller's streams and
     // the lanes), taken along by every such launch: once all of them have fired no kernel reads the
     // buffer any more and it may be handed to another plan.  They go with the launches because a stream
-    // of the caller's may be gone by the time the plan is destroyed; the default stream may not, and
-    // gets its event afterwards.
+    // of the caller's may be gone by the time the plan is destroyed; the default stream may not (see
+    // DefaultStreamEvent).
     mutable std::vector<std::pair<hipStream_t, hipEvent_t>> stream_events;
     mutable bool null_stream_use = false;        // launched on the default stream (which carries no events)
     mutable bool untracked_use = false;          // a launch could not be followed (too many streams, a stream
@@ -150,8 +150,11 @@ bool is_host_memory(const kvl_plan_t *plan, const void *ptr);
 int upload_units(kvl_plan_t *plan);
 // whether a launch on `stream` may read plan->d_row_map; orders the stream after the map's making if that is needed
 bool row_map_ready(const kvl_plan_t *plan, hipStream_t stream);
-// the event that a launch reading the plan's descriptors is to take with it on `stream` (null: it is not followed)
-hipEvent_t launch_event(const kvl_plan_t *plan, hipStream_t stream);
+// The event that a launch reading the plan's descriptors is to take with it on `stream` (null: none).  Where *passes is
+// set, launched() is told afterwards whether the launch was made.
+struct DefaultStreamEvent;
+hipEvent_t launch_event(const kvl_plan_t *plan, hipStream_t stream, DefaultStreamEvent **passes);
+void launched(DefaultStreamEvent *passes, bool ok);
 void drop_stream_events(const kvl_plan_t *plan);
 // lanes come from, and go back to, a small pool shared by all plans
 hipStream_t take_pooled_lane(int device);

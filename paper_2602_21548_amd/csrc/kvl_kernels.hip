@@ -32,7 +32,21 @@ int check_device(const kvl_plan_t *plan) {
 // wait for (launches of a 3 us kernel in a row: 7.5 us each recorded, 4.5 us riding, 2.8 us without; host 8 / 2.5).
 struct On {
     hipStream_t stream;
+    DefaultStreamEvent *passes = nullptr;       // (made by the making of `done`)
     hipEvent_t done;
+    bool ok = false;
+    On(const kvl_plan_t *plan, hipStream_t s) : stream(s), done(launch_event(plan, s, &passes)) {}
+    ~On() {
+        if (passes) launched(passes, ok);
+    }
+    On(const On &) = delete;
+    On &operator=(const On &) = delete;
+    // the launches' result, once all have been made
+    int made() {
+        KVL_HIP(hipGetLastError());
+        ok = true;
+        return KVL_OK;
+    }
 };
 #define KVL_LAUNCH(kernel, grid, block, on, ...)                                                                  \
     do {                                                                                                          \
@@ -278,7 +292,7 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         threads = plan->paired && !plan->threads_chosen ? 1024u : plan->tuning.block_threads;
     }
     dim3 block(threads);
-    const On on{stream, launch_event(plan, stream)};
+    On on(plan, stream);
     const kvl_unit_t &u_first = plan->units[unit_begin], &u_last = plan->units[unit_end - 1];
     if (vec && !plan->tuning.variant && !plan->tuning.max_groups && !far_host && plan->d_row_map &&
         takes_row_map(plan, plan->layout.row_bytes[plane_begin], pack) && row_map_ready(plan, stream)) {
@@ -339,8 +353,7 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
             dim3 grid((uint32_t)groups, plane_end - plane_begin);
             if (pack) launch_pipe_variant<true>(v, grid, block, on, a, (uint32_t)tpu, al, (uint32_t)blocks);
             else launch_pipe_variant<false>(v, grid, block, on, a, (uint32_t)tpu, al, (uint32_t)blocks);
-            KVL_HIP(hipGetLastError());
-                    return KVL_OK;
+            return on.made();
         }
         // one workgroup per tile, unless a cap was asked for or the launch would not fit
         bool walk = false;
@@ -361,8 +374,7 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         if (pack) launch_span_variant<true>(v, grid, block, on, a);
         else launch_span_variant<false>(v, grid, block, on, a);
     }
-    KVL_HIP(hipGetLastError());
-    return KVL_OK;
+    return on.made();
 }
 
 // Launch the layout-converting kernel on descriptors [unit_begin, unit_end).  A
@@ -412,7 +424,7 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
     if (a.n_units * widest > (uint64_t)INT32_MAX || tpu > (uint64_t)INT32_MAX) return KVL_ERANGE;
     const uint32_t cap = plan->tuning.max_groups ? plan->tuning.max_groups
                                                  : (far_host ? (vec ? kHostSideGroups : 2 * kHostSideGroups) : 0u);
-    const On on{stream, launch_event(plan, stream)};
+    On on(plan, stream);
     // the tiles of all planes are numbered with 32 bits: descriptors that have more go in several launches
     const uint32_t n_all = a.n_units, per_launch = (uint32_t)(INT32_MAX / tpu);
     for (uint32_t first = 0; first < n_all; first += per_launch) {
@@ -434,8 +446,7 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
         a.units += a.n_units;
     }
 #undef KVL_FB_LAUNCH
-    KVL_HIP(hipGetLastError());
-    return KVL_OK;
+    return on.made();
 }
 
 // Bytes of one Layer Block (all planes of one block, one layer).

@@ -1,6 +1,7 @@
 // Host side of the library: batch validation, transfer-buffer layout and copy
 // descriptors (kvl_plan), plan inspection, error text.
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -50,6 +51,17 @@ int make_chunks(const kvl_plan_t *plan, uint64_t chunk_bytes, std::vector<kvl_ch
 // fires when the stream's last such launch has finished), and the array goes back to the cache only when
 // those events have fired.  Nothing here waits for the device; only kvl_release_cached_memory
 // blocks (on the retired arrays' own events).
+//
+// The default stream's launches carry no event each (hops of 19 MB, two planes, thousands in a row: 23 us each without
+// events, 31 with; a batch of 61 layers of 137 MB 4967 and 5060 us).  That stream cannot go away, so it is enough that a launch there which finds arrays
+// of destroyed plans waiting takes one event with it for all of them: whatever read them had been enqueued there before.
+// Nothing is put on the stream but the caller's own launches; arrays wait there until the next one, or the release.
+struct DefaultStreamEvent {
+    hipEvent_t event;
+    int device;
+    uint64_t before;        // for the arrays retired before this one of all retirements
+    unsigned arrays;        // that wait for it
+};
 namespace {
 struct CachedBuffer {
     void *ptr;
@@ -60,7 +72,9 @@ struct RetiredBuffer {
     CachedBuffer buf;
     std::vector<hipEvent_t> events;     // all fired: no kernel reads the buffer any more
     hipEvent_t map_event;               // (or null) fired: the kernel that wrote the row map into it has finished
-    bool null_stream;                   // used on the default stream, and no event recorded there yet
+    bool default_stream;                // used there as well, and
+    DefaultStreamEvent *passed;         // the event of a later launch there, once there has been one
+    uint64_t number;                    // of all retirements
 };
 struct PooledLane {
     hipStream_t stream;
@@ -72,6 +86,8 @@ std::vector<RetiredBuffer> g_retired;
 std::vector<std::pair<hipEvent_t, int>> g_events;       // spare events, with their device
 std::vector<std::pair<hipEvent_t, int>> g_map_events;   // spare events that other streams wait on (row maps)
 std::vector<PooledLane> g_lanes;
+uint64_t g_retirements = 0;
+std::atomic<unsigned> g_waiting{0};     // retired arrays with default_stream and without passed
 constexpr size_t kCacheEntries = 16;
 constexpr size_t kCacheBytes = 256u << 20;      // never keep more than this much idle
 constexpr size_t kSpareEvents = 256;
@@ -131,32 +147,14 @@ void keep_or_free(const CachedBuffer &b) {
     (void)hipFree(b.ptr);
 }
 
-// An event for what the default stream of the buffer's device holds now, among which are the buffer's last launches:
-// false if none could be recorded (a capture forbids it).  That stream cannot go away, so its launches carry no event
-// each; one is recorded when the buffer is looked at again.
-bool record_null_stream(RetiredBuffer &r, bool wait) {
-    int current = r.buf.device;
+// nobody reads on the default stream what it held so far
+bool wait_for_default_stream(int device) {
+    int current = device;
     (void)hipGetDevice(&current);
-    if (current != r.buf.device) (void)hipSetDevice(r.buf.device);
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    hipEvent_t e = nullptr;
-    if (hipStreamIsCapturing(nullptr, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone)
-        e = take_event(r.buf.device);
-    bool ok = e && hipEventRecord(e, nullptr) == hipSuccess;
-    if (ok) {
-        try {
-            r.events.push_back(e);
-        } catch (const std::bad_alloc &) {
-            ok = false;
-        }
-    }
-    if (!ok) {
-        (void)hipGetLastError();
-        if (e) give_event(e, r.buf.device);
-        if (wait) ok = hipStreamSynchronize(nullptr) == hipSuccess;
-    }
-    if (current != r.buf.device) (void)hipSetDevice(current);
-    if (ok) r.null_stream = false;
+    if (current != device) (void)hipSetDevice(device);
+    const bool ok = hipStreamSynchronize(nullptr) == hipSuccess;
+    if (!ok) (void)hipGetLastError();               // (a capture forbids it)
+    if (current != device) (void)hipSetDevice(current);
     return ok;
 }
 
@@ -164,24 +162,30 @@ bool record_null_stream(RetiredBuffer &r, bool wait) {
 void reap_retired(bool wait) {
     for (size_t i = 0; i < g_retired.size();) {
         RetiredBuffer &r = g_retired[i];
-        if (r.null_stream && !record_null_stream(r, wait)) {
-            ++i;
-            continue;
+        bool done = !r.default_stream || r.passed;
+        if (!done && wait && wait_for_default_stream(r.buf.device)) {
+            done = true;
+            r.default_stream = false;
+            --g_waiting;
         }
-        bool done = true;
         auto pending = [wait](hipEvent_t e) {
             const hipError_t q = wait ? hipEventSynchronize(e) : hipEventQuery(e);
             if (q == hipErrorNotReady) return true;
             if (q != hipSuccess) (void)hipGetLastError();       // a broken event cannot hold the buffer for ever
             return false;
         };
-        if (r.map_event) done = !pending(r.map_event);
+        if (done && r.passed) done = !pending(r.passed->event);
+        if (done && r.map_event) done = !pending(r.map_event);
         for (size_t k = 0; k < r.events.size() && done; ++k) done = !pending(r.events[k]);
         if (!done) {
             ++i;
             continue;
         }
         for (hipEvent_t e : r.events) give_event(e, r.buf.device);
+        if (r.passed && --r.passed->arrays == 0) {
+            give_event(r.passed->event, r.buf.device);
+            delete r.passed;
+        }
         if (r.map_event) give_event(r.map_event, r.buf.device, true);
         keep_or_free(r.buf);
         g_retired.erase(g_retired.begin() + (long)i);
@@ -190,7 +194,8 @@ void reap_retired(bool wait) {
 }  // namespace
 
 // (An event that no launch ever took with it counts as fired.)
-hipEvent_t launch_event(const kvl_plan_t *plan, hipStream_t stream) {
+hipEvent_t launch_event(const kvl_plan_t *plan, hipStream_t stream, DefaultStreamEvent **passes) {
+    *passes = nullptr;
     if (plan->flags & KVL_CALLER_SYNCS) return nullptr;    // the caller answers for the plan's lifetime
     // a launch that is being captured into a graph runs whenever the graph is replayed: not ours to follow
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -203,8 +208,20 @@ hipEvent_t launch_event(const kvl_plan_t *plan, hipStream_t stream) {
         plan->untracked_use = true;
         return nullptr;
     }
-    if (!stream) {                                         // see record_null_stream
+    if (!stream) {
         plan->null_stream_use = true;
+        if (g_waiting.load(std::memory_order_relaxed) == 0) return nullptr;
+        std::lock_guard<std::mutex> lock(g_cache_mutex);
+        for (const RetiredBuffer &r : g_retired) {
+            if (!r.default_stream || r.passed || r.buf.device != plan->device) continue;
+            DefaultStreamEvent *p = new (std::nothrow) DefaultStreamEvent{take_event(plan->device), plan->device, g_retirements, 0};
+            if (p && !p->event) {
+                delete p;
+                p = nullptr;
+            }
+            *passes = p;
+            return p ? p->event : nullptr;
+        }
         return nullptr;
     }
     for (const auto &se : plan->stream_events)
@@ -224,6 +241,21 @@ hipEvent_t launch_event(const kvl_plan_t *plan, hipStream_t stream) {
     }
     if (!ev) plan->untracked_use = true;
     return ev;
+}
+
+// (Not when the event is taken: until the launch is made it counts as fired.)
+void launched(DefaultStreamEvent *passes, bool ok) {
+    std::lock_guard<std::mutex> lock(g_cache_mutex);
+    for (RetiredBuffer &r : g_retired) {
+        if (!ok || !r.default_stream || r.passed || r.buf.device != passes->device || r.number >= passes->before) continue;
+        r.passed = passes;
+        ++passes->arrays;
+        --g_waiting;
+    }
+    if (passes->arrays == 0) {
+        give_event(passes->event, passes->device);
+        delete passes;
+    }
 }
 
 void drop_stream_events(const kvl_plan_t *plan) {
@@ -284,14 +316,14 @@ static hipError_t descriptor_alloc(void **out, size_t bytes, size_t *capacity, i
 // have fired.  No stream is touched here.
 static void descriptor_release(const kvl_plan_t *plan) {
     RetiredBuffer r{CachedBuffer{plan->d_units, plan->d_units_capacity, plan->device}, {}, plan->map_event,
-                    plan->null_stream_use};
+                    plan->null_stream_use, nullptr, 0};
     if (plan->flags & KVL_CALLER_SYNCS) {
         // the caller has waited for the launches; the map's kernel is the library's own and may still be to come, in a
         // plan dropped before its first launch
         std::lock_guard<std::mutex> lock(g_cache_mutex);
         bool retired = false;
         if (plan->map_pending) {
-            r.null_stream = false;
+            r.default_stream = false;
             try {
                 g_retired.push_back(r);
                 retired = true;
@@ -312,8 +344,11 @@ static void descriptor_release(const kvl_plan_t *plan) {
         if (tracked) {
             try {
                 for (const auto &se : plan->stream_events) r.events.push_back(se.second);
+                r.number = g_retirements;
                 g_retired.push_back(std::move(r));
                 r.buf.ptr = nullptr;
+                ++g_retirements;
+                if (r.default_stream) ++g_waiting;
             } catch (const std::bad_alloc &) {
                 tracked = false;
             }

@@ -9,6 +9,7 @@
 #include "kvl_kernels.hip"
 
 using fake::launches;
+using namespace kvl;
 
 #define REQUIRE(c) do { if (!(c)) { std::printf("%s failed at line %d\n", #c, __LINE__); return 1; } } while (0)
 
@@ -165,6 +166,62 @@ static int check_row_map_on_two_streams() {
     return 0;
 }
 
+// Plans used on the default stream: nothing is put there but the caller's launches, and an array goes back when a launch
+// made there after its plan's end has finished -- the first one, which alone carries an event for it.
+static int check_default_stream() {
+    auto plan = [] {
+        kvl_plan_t *p = plan_of_single_tokens(5000, 1152, KVL_GATHER);
+        fake::finish(launches.back().stream);          // (its map has been made)
+        return p;
+    };
+    kvl_release_cached_memory();
+    kvl_plan_t *a = plan(), *b = plan();
+    fake::records.clear();
+    fake::waited = fake::mallocs = 0;
+    launches.clear();
+    REQUIRE(pack(a, nullptr) == KVL_OK && pack(b, nullptr) == KVL_OK);
+    REQUIRE(!launches[0].event && !launches[1].event);
+    const void *mem_a = a->d_units;
+    kvl_plan_destroy(a);
+    const uint64_t queued = fake::null_stream.queued;
+    kvl_plan_t *c = plan();                             // looks at what was retired
+    REQUIRE(fake::null_stream.queued == queued && fake::mallocs == 1 && c->d_units != mem_a);
+    fake::finish(&fake::null_stream);
+    kvl_plan_t *d = plan();                             // a's launch has finished, but nothing there says so
+    REQUIRE(fake::null_stream.queued == queued && fake::mallocs == 2);
+    launches.clear();
+    REQUIRE(pack(b, nullptr) == KVL_OK && pack(b, nullptr) == KVL_OK && pack(c, nullptr) == KVL_OK);
+    REQUIRE(launches[0].event && !launches[1].event && !launches[2].event);
+    kvl_plan_t *e = plan();
+    REQUIRE(fake::mallocs == 3);                        // b's launch has not finished
+    fake::null_stream.done = fake::null_stream.queued - 2;
+    kvl_plan_t *f = plan();
+    REQUIRE(fake::mallocs == 3 && f->d_units == mem_a);
+    // a launch that is being made while a plan is destroyed does not speak for that plan's launches
+    kvl_plan_destroy(c);
+    DefaultStreamEvent *passes = nullptr;
+    hipEvent_t ev = launch_event(b, nullptr, &passes);
+    REQUIRE(ev && passes);
+    (void)fake::launch(nullptr, dim3(1), dim3(64), nullptr, ev);
+    REQUIRE(pack(d, nullptr) == KVL_OK);
+    kvl_plan_destroy(d);
+    launched(passes, true);
+    REQUIRE(g_retired.size() == 2 && g_waiting == 1 && !g_retired.back().passed);
+    // nor one that failed
+    ev = launch_event(b, nullptr, &passes);
+    REQUIRE(ev && passes);
+    launched(passes, false);
+    REQUIRE(g_waiting == 1);
+    REQUIRE(fake::waited == 0);
+    for (const auto &r : fake::records) REQUIRE(r.first != &fake::null_stream);
+    kvl_plan_destroy(b);
+    kvl_plan_destroy(e);
+    kvl_plan_destroy(f);
+    kvl_release_cached_memory();
+    REQUIRE(g_retired.empty() && g_waiting == 0 && fake::device_memory.empty());
+    return 0;
+}
+
 //CHECKS
 
 int main(int argc, char **argv) {
@@ -174,6 +231,7 @@ int main(int argc, char **argv) {
         {"caller_syncs", check_caller_syncs},
         {"row_map_under_capture", check_row_map_under_capture},
         {"row_map_on_two_streams", check_row_map_on_two_streams},
+        {"default_stream", check_default_stream},
 //TABLE
     };
     if (argc != 2 || !checks.count(argv[1])) {
