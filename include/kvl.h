@@ -153,7 +153,7 @@ int kvl_plan_tuned(const kvl_layout_t *layout, const kvl_request_t *requests, ui
  * plan may still be running or queued.  Every launch made with a plan carries
  * an event (one per stream, that of the stream's last launch).  The plan's device descriptor
  * array is retired with those events and goes back to a small cache inside the library (at most
- * 16 buffers / 256 MiB, from which later plans are served without a device allocation) only when
+ * 16 buffers / 1 GiB, from which later plans are served without a device allocation) only when
  * they have fired.  The default stream, which cannot go away, is followed by the next launch that
  * the library makes there instead: that one carries an event for the arrays of all plans used there
  * and destroyed before it, which go back when it has finished.

@@ -89,7 +89,7 @@ std::vector<PooledLane> g_lanes;
 uint64_t g_retirements = 0;
 std::atomic<unsigned> g_waiting{0};     // retired arrays with default_stream and without passed
 constexpr size_t kCacheEntries = 16;
-constexpr size_t kCacheBytes = 256u << 20;      // never keep more than this much idle
+constexpr size_t kCacheBytes = 1u << 30;        // never keep more than this much idle (see map_fits_cache)
 constexpr size_t kSpareEvents = 256;
 constexpr size_t kPooledLanes = 16;
 constexpr size_t kTrackedStreams = 24;
@@ -413,7 +413,7 @@ __global__ void __launch_bounds__(256) kvl_row_map_kernel(const kvl_unit_t *unit
     for (uint32_t i = (uint32_t)t & (lanes - 1u); i < u.n_rows; i += lanes) row_map[u.xfer_row + i] = u.pool_row + i;
 }
 
-// (The bounds keep its launch below 2^32 lanes and the table below 1 GiB.)
+// (The bounds keep its launch below 2^32 lanes.)
 static bool wants_row_map(const kvl_plan_t *plan) {
     if (plan->units.size() >= (1u << 28) || plan->hit_tokens >= (1u << 28)) return false;
     for (uint32_t p = 0; p < plan->layout.n_planes; ++p) {
@@ -422,6 +422,14 @@ static bool wants_row_map(const kvl_plan_t *plan) {
         if ((plan->flags & KVL_SCATTER) && takes_row_map(plan, row, false)) return true;
     }
     return false;
+}
+
+// Whether the cache still holds the arrays of a batch's two plans if they have maps: an array that it does not hold is
+// allocated and freed for every plan, which waits for the device.  (Beside descriptors that are few and long a map of very
+// many rows is most of the array; beside single rows it adds a quarter, which the rounding may double.)
+static bool map_fits_cache(size_t descriptor_bytes, size_t map_bytes) {
+    const size_t with = round_capacity(descriptor_bytes + map_bytes);
+    return with <= kCacheBytes / 2 || with == round_capacity(descriptor_bytes);
 }
 
 // Enqueue the making of the plan's row map; its first user waits for it (row_map_ready).  The call does not: beside
@@ -489,6 +497,7 @@ int upload_units(kvl_plan_t *plan) {
     if (e == hipSuccess && !plan->units.empty()) {
         const size_t bytes = plan->units.size() * sizeof(kvl_unit_t);
         size_t map_bytes = wants_row_map(plan) ? (plan->hit_tokens + 8) * sizeof(uint32_t) : 0;
+        if (!map_fits_cache(bytes, map_bytes)) map_bytes = 0;
         e = descriptor_alloc((void **)&plan->d_units, bytes + map_bytes, &plan->d_units_capacity, plan->device);
         if (e != hipSuccess && map_bytes) {             // no room for the table: the descriptors alone will do
             (void)hipGetLastError();

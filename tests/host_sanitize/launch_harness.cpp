@@ -40,20 +40,23 @@ static kvl_plan_s made(uint64_t n, uint32_t last, uint32_t row, uint32_t planes 
 }
 static void *const kPlanes[KVL_MAX_PLANES] = {(void *)(1ull << 40), (void *)(1ull << 41), (void *)(1ull << 42), (void *)(1ull << 43)};
 
-// kvl_plan over `tokens` single-token blocks in reverse order (no two merge)
-static kvl_plan_t *plan_of_single_tokens(uint32_t tokens, uint32_t row, uint32_t flags) {
-    std::vector<int32_t> table(tokens);
-    for (uint32_t i = 0; i < tokens; ++i) table[i] = (int32_t)(tokens - 1 - i);
+// kvl_plan over `blocks` whole blocks in reverse order (no two merge)
+static kvl_plan_t *plan_of_blocks(uint32_t blocks, uint32_t bs, uint32_t row, uint32_t flags) {
+    std::vector<int32_t> table(blocks);
+    for (uint32_t i = 0; i < blocks; ++i) table[i] = (int32_t)(blocks - 1 - i);
     kvl_layout_t lay{};
-    lay.n_layers = lay.block_tokens = lay.n_planes = 1;
+    lay.n_layers = lay.n_planes = 1;
+    lay.block_tokens = bs;
     lay.row_bytes[0] = row;
-    lay.pool_blocks = tokens;
+    lay.pool_blocks = blocks;
     kvl_request_t req{};
-    req.hit_tokens = req.n_blocks = tokens;
+    req.hit_tokens = blocks * bs;
+    req.n_blocks = blocks;
     req.block_table = table.data();
     kvl_plan_t *p = nullptr;
     return kvl_plan(&lay, &req, 1, flags | KVL_NO_POINTER_CHECKS, &p) == KVL_OK ? p : nullptr;
 }
+static kvl_plan_t *plan_of_single_tokens(uint32_t tokens, uint32_t row, uint32_t flags) { return plan_of_blocks(tokens, 1, row, flags); }
 
 // Moves: a launch has the largest descriptor's tiles for every descriptor, so narrow workgroups are for descriptors that
 // are alike.  Single rows with one long run among them keep the gather's shape, and its limit on tiles.
@@ -222,6 +225,34 @@ static int check_default_stream() {
     return 0;
 }
 
+// The arrays of a batch's two plans are kept for the next batch, whatever their row maps add to them.
+static int check_cached_arrays() {
+    for (uint32_t tokens : {5000u, 7000000u}) {
+        kvl_release_cached_memory();
+        fake::mallocs = fake::frees = 0;
+        for (int batch = 0; batch < 2; ++batch) {
+            kvl_plan_t *p[2];
+            for (kvl_plan_t *&q : p) {
+                q = plan_of_single_tokens(tokens, 1152, KVL_GATHER);
+                REQUIRE(q && q->d_row_map);
+                fake::finish(launches.back().stream);
+            }
+            for (kvl_plan_t *q : p) kvl_plan_destroy(q);
+        }
+        REQUIRE(fake::mallocs == 2 && fake::frees == 0);
+    }
+    kvl_release_cached_memory();
+    fake::mallocs = fake::frees = 0;
+    for (int batch = 0; batch < 2; ++batch) {               // 200 M rows in two million descriptors: no map of 800 MB beside 32
+        kvl_plan_t *p = plan_of_blocks(2000000, 100, 16, KVL_GATHER);
+        REQUIRE(p && !p->d_row_map);
+        kvl_plan_destroy(p);
+    }
+    REQUIRE(fake::mallocs == 1 && fake::frees == 0);
+    kvl_release_cached_memory();
+    return 0;
+}
+
 //CHECKS
 
 int main(int argc, char **argv) {
@@ -232,6 +263,7 @@ int main(int argc, char **argv) {
         {"row_map_under_capture", check_row_map_under_capture},
         {"row_map_on_two_streams", check_row_map_on_two_streams},
         {"default_stream", check_default_stream},
+        {"cached_arrays", check_cached_arrays},
 //TABLE
     };
     if (argc != 2 || !checks.count(argv[1])) {
