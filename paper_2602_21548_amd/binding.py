@@ -240,7 +240,8 @@ class Plan:
         return self._h
 
     def plane_bytes(self, p: int) -> int:
-        return self._plane_bytes[p]
+        """Bytes of plane p of a pool (0 for planes below KVL_MAX_PLANES that the layout does not have)."""
+        return int(self.layout.pool_blocks) * int(self.layout.block_tokens) * int(self.layout.row_bytes[p])
 
     @property
     def payload_bytes(self) -> int:

@@ -429,3 +429,11 @@ def test_piece_size_follows_the_batch_not_the_rare_adjacent_pair():
     p = K.kvl_plan(lay2, hit, app, tables, K.KVL_GATHER | K.KVL_HOST_ONLY)
     u = p.units()
     assert set(np.unique(u[:, 2]).tolist()) == {32} and p.n_units == 2 * R * per
+
+
+def test_plane_bytes_of_planes_a_layout_does_not_have():
+    lay = K.make_layout(2, 16, (1152, 64), 40)
+    p = K.kvl_plan(lay, [20], [3], [np.array([5, 9], dtype=np.int32)], K.KVL_GATHER | K.KVL_HOST_ONLY)
+    assert [p.plane_bytes(q) for q in range(4)] == [40 * 16 * 1152, 40 * 16 * 64, 0, 0]
+    with pytest.raises(IndexError):
+        p.plane_bytes(4)
