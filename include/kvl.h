@@ -479,7 +479,7 @@ int kvl_copy_linear(const void *src, void *dst, uint64_t bytes, void *stream);
 
 /* Reference streams for measuring what the memory can do, beside the kernels of the load path
  * (the benchmark's ceilings): plain device memory, the load/store instructions and cache policies
- * of the default gather and scatter, no descriptors.
+ * of the default gather and scatter of a layer of that size, no descriptors.
  *   block_bytes == 0: one linear stream of `bytes` bytes, src (+ skew_bytes) -> dst;
  *   block_bytes != 0: the access shape of a paged copy without its block tables: one side
  *     ("dense") is a linear stream, the other hops every block_bytes: block u of the dense

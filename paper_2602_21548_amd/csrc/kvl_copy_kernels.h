@@ -63,6 +63,11 @@ constexpr uint32_t kMoveCode = 2u | 4u | (3u << 3);             // tile x1, nt l
 constexpr uint32_t kFlatMoveCode = 128u | 4u | (1u << 3);       // flat, nt loads, nt stores
 constexpr uint32_t kFlatPackCode = 128u | 4u | (2u << 3);       // flat, nt loads, sc1 stores
 constexpr uint32_t kFlatUnpackCode = 128u | 4u | (1u << 3);     // flat, nt loads, nt stores
+// The tiled form's code for a plain gather or scatter; `lines`: every row begins on a 128-byte line.
+inline uint32_t default_tile_code(bool pack, bool lines, uint64_t payload) {
+    if (pack) return lines || payload < kPassByBytes ? kDefaultPackCode : kDefaultPackCodePassBy;
+    return lines || (payload > kPlainReadBackBytes && payload < kPassByBytes) ? kDefaultUnpackCode : kDefaultUnpackCodeOddRows;
+}
 constexpr bool kLinearNtLoad = true;
 constexpr int kLinearStorePolicy = 2;
 

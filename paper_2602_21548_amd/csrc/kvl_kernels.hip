@@ -272,10 +272,7 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         bool rows_128 = true;       // every span starts on a 128-byte line of the transfer buffer
         for (uint32_t p = plane_begin; p < plane_end; ++p)
             rows_128 = rows_128 && plan->layout.row_bytes[p] % 128 == 0;
-        const uint64_t n = plan->payload_bytes;
-        if (plan->paired) v = kMoveCode;
-        else if (pack) v = rows_128 || n < kPassByBytes ? kDefaultPackCode : kDefaultPackCodePassBy;
-        else v = rows_128 || (n > kPlainReadBackBytes && n < kPassByBytes) ? kDefaultUnpackCode : kDefaultUnpackCodeOddRows;
+        v = plan->paired ? kMoveCode : default_tile_code(pack, rows_128, plan->payload_bytes);
         // across the host link: two vectors per lane, so that the few workgroups of the thin
         // form (kHostSideGroups) keep enough bytes in flight
         if (far_host) v |= 3u;
@@ -628,17 +625,18 @@ int kvl_ceiling_kernel(const kvl_ceiling_t *c, const void *src, uint64_t src_byt
     // the multiplication finds the block of every workgroup index below 2^24 * tiles_per_block exactly
     if (groups > (1ull << 24) || groups * 256 > kMaxLanesPerLaunch) return KVL_ERANGE;
     const dim3 grid((uint32_t)groups), block(256);
-#define KVL_CEIL(M, G, N, S) hipLaunchKernelGGL((kvl_ceiling_pattern_kernel<M, G, N, S>), grid, block, 0, s, a)
-    // the cache policies of the default gather and scatter
-    if (gather) {
-        if (c->mode == KVL_CEILING_COPY) KVL_CEIL(0, true, true, 2);
-        else if (c->mode == KVL_CEILING_READ) KVL_CEIL(1, true, true, 2);
-        else KVL_CEIL(2, true, true, 2);
-    } else {
-        if (c->mode == KVL_CEILING_COPY) KVL_CEIL(0, false, false, 3);
-        else if (c->mode == KVL_CEILING_READ) KVL_CEIL(1, false, false, 3);
-        else KVL_CEIL(2, false, false, 3);
-    }
+#define KVL_CEIL(G, N, S)                                                                                              \
+    do {                                                                                                            \
+        if (c->mode == KVL_CEILING_COPY) hipLaunchKernelGGL((kvl_ceiling_pattern_kernel<0, G, N, S>), grid, block, 0, s, a); \
+        else if (c->mode == KVL_CEILING_READ) hipLaunchKernelGGL((kvl_ceiling_pattern_kernel<1, G, N, S>), grid, block, 0, s, a); \
+        else hipLaunchKernelGGL((kvl_ceiling_pattern_kernel<2, G, N, S>), grid, block, 0, s, a);                     \
+    } while (0)
+    // the cache policies of the default gather and scatter of such a layer
+    const uint32_t v = default_tile_code(gather, c->skew_bytes == 0 && c->block_bytes % 128 == 0, bytes);
+    if (gather && v == kDefaultPackCode) KVL_CEIL(true, true, 2);
+    else if (gather) KVL_CEIL(true, true, 3);
+    else if (v == kDefaultUnpackCode) KVL_CEIL(false, true, 3);
+    else KVL_CEIL(false, false, 3);
 #undef KVL_CEIL
     KVL_HIP(hipGetLastError());
     return KVL_OK;

@@ -253,6 +253,30 @@ static int check_cached_arrays() {
     return 0;
 }
 
+// The reference stream of a shape has the cache policies of the tiled kernels on that shape, on both sides of every line.
+static int check_ceiling_policies() {
+    for (uint32_t row : {656u, 1152u})
+        for (uint64_t payload : {100ull << 20, 200ull << 20, 5ull << 30})
+            for (bool gather : {true, false}) {
+                const uint32_t block = 64 * row, n = (uint32_t)(payload / block);
+                kvl_plan_s p = made(n, 64, row);
+                for (kvl_unit_t &u : p.units) u.n_rows = 64;
+                p.hit_tokens = 64ull * n;
+                p.payload_bytes = p.hit_tokens * row;
+                uintptr_t xfer[KVL_MAX_PLANES] = {1ull << 44};
+                launches.clear();
+                REQUIRE(launch_units(&p, gather, 0, n, 0, 1, kPlanes, xfer, nullptr) == KVL_OK);
+                const kvl_ceiling_t c{KVL_CEILING_COPY, block, gather ? 0u : 1u, row % 128 ? 16u : 0u, 18};
+                REQUIRE(kvl_ceiling_kernel(&c, kPlanes[0], 1ull << 40, kPlanes[1], 1ull << 40, p.payload_bytes, nullptr, nullptr) == KVL_OK);
+                // ..._tile_kernel<vectors per lane, nt loads, store policy>, kvl_ceiling_pattern_kernel<mode, gather, nt loads, store policy>
+                const std::string &tile = launches[0].kernel, &ceiling = launches[1].kernel;
+                const std::string policy = tile.substr(tile.find(", ") + 2, tile.find('>') - tile.find(", ") - 2);
+                REQUIRE(ceiling.find(std::string("<0, ") + (gather ? "true, " : "false, ") + policy + ">") != std::string::npos);
+                p.d_units = nullptr;
+            }
+    return 0;
+}
+
 //CHECKS
 
 int main(int argc, char **argv) {
@@ -264,6 +288,7 @@ int main(int argc, char **argv) {
         {"row_map_on_two_streams", check_row_map_on_two_streams},
         {"default_stream", check_default_stream},
         {"cached_arrays", check_cached_arrays},
+        {"ceiling_policies", check_ceiling_policies},
 //TABLE
     };
     if (argc != 2 || !checks.count(argv[1])) {
