@@ -35,6 +35,7 @@ struct Launch {
 static Stream null_stream;
 static std::vector<Launch> launches;
 static std::vector<std::pair<Stream *, Event *>> records, waits;        // hipEventRecord, hipStreamWaitEvent
+static void (*watch)(const Launch &, void **args);       // called with every launch, if set
 static std::map<const void *, std::string> kernels;
 static std::set<void *> device_memory;
 static uint64_t mallocs, frees, waited;     // allocations and frees of device memory; waits of the host for unfinished kernels
@@ -59,9 +60,10 @@ inline bool forbidden() {
     if (captures && mode != hipStreamCaptureModeRelaxed) capture_broken = true;
     return captures && mode != hipStreamCaptureModeRelaxed;
 }
-inline hipError_t launch(const void *f, dim3 grid, dim3 block, hipStream_t s, hipEvent_t stop) {
+inline hipError_t launch(const void *f, dim3 grid, dim3 block, void **args, hipStream_t s, hipEvent_t stop) {
     Stream *st = of(s);
     launches.push_back(Launch{kernels[f], st, grid, block, stop != nullptr});
+    if (watch) watch(launches.back(), args);
     if (!st->capturing) ++st->queued;
     if (stop) *of(stop) = Event{st, st->queued};
     return hipSuccess;
@@ -93,9 +95,9 @@ void __hipRegisterFunction(void **, const void *f, char *name, const char *, uns
     fake::kernels[f] = plain ? plain : name;
     std::free(plain);
 }
-hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **, size_t, hipStream_t s) { return fake::launch(f, g, b, s, nullptr); }
-hipError_t hipExtLaunchKernel(const void *f, dim3 g, dim3 b, void **, size_t, hipStream_t s, hipEvent_t, hipEvent_t stop, int) {
-    return fake::launch(f, g, b, s, stop);
+hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **a, size_t, hipStream_t s) { return fake::launch(f, g, b, a, s, nullptr); }
+hipError_t hipExtLaunchKernel(const void *f, dim3 g, dim3 b, void **a, size_t, hipStream_t s, hipEvent_t, hipEvent_t stop, int) {
+    return fake::launch(f, g, b, a, s, stop);
 }
 
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }

@@ -205,7 +205,7 @@ static int check_default_stream() {
     DefaultStreamEvent *passes = nullptr;
     hipEvent_t ev = launch_event(b, nullptr, &passes);
     REQUIRE(ev && passes);
-    (void)fake::launch(nullptr, dim3(1), dim3(64), nullptr, ev);
+    (void)fake::launch(nullptr, dim3(1), dim3(64), nullptr, nullptr, ev);
     REQUIRE(pack(d, nullptr) == KVL_OK);
     kvl_plan_destroy(d);
     launched(passes, true);
@@ -277,7 +277,37 @@ static int check_ceiling_policies() {
     return 0;
 }
 
-//CHECKS
+// Row-map launches beyond 2^32 lanes: in parts that follow one another and leave out no row.
+static uint64_t g_rows_covered;
+static bool g_rows_right;
+static int check_row_map_split() {
+    const uint32_t n = 23000000, row = 3040, vectors = row / 16;        // 4.4e9 vectors
+    kvl_plan_s p = made(n, 1, row);
+    static uint32_t map;
+    p.d_row_map = &map;
+    REQUIRE(takes_row_map(&p, row, true));
+    uintptr_t xfer[KVL_MAX_PLANES] = {(1ull << 44) + 112};              // the widest line-up
+    launches.clear();
+    g_rows_right = true;
+    fake::watch = [](const fake::Launch &l, void **args) {
+        const uint32_t begin = *(uint32_t *)args[2], vecs = *(uint32_t *)args[3];
+        g_rows_right = g_rows_right && begin == g_rows_covered && vecs % (3040 / 16) == 0 && vecs + 7ull <= (uint64_t)l.grid.x * l.block.x &&
+                       (uint64_t)l.grid.x * l.block.x <= kMaxLanesPerLaunch;
+        g_rows_covered += vecs / (3040 / 16);
+    };
+    for (uint32_t first : {0u, 5u}) {
+        p.units[first].xfer_row = first;
+        g_rows_covered = first;
+        launches.clear();
+        REQUIRE(launch_units(&p, true, first, n, 0, 1, kPlanes, xfer, nullptr) == KVL_OK);
+        REQUIRE(launches.size() == 2 && is(launches[0], "kvl_rows_kernel") && is(launches[1], "kvl_rows_kernel"));
+        REQUIRE(g_rows_right && g_rows_covered == n);
+    }
+    REQUIRE((uint64_t)n * vectors > (1ull << 32));
+    fake::watch = nullptr;
+    p.d_units = nullptr;
+    return 0;
+}
 
 int main(int argc, char **argv) {
     const std::map<std::string, int (*)()> checks = {
@@ -289,7 +319,7 @@ int main(int argc, char **argv) {
         {"default_stream", check_default_stream},
         {"cached_arrays", check_cached_arrays},
         {"ceiling_policies", check_ceiling_policies},
-//TABLE
+        {"row_map_split", check_row_map_split},
     };
     if (argc != 2 || !checks.count(argv[1])) {
         for (const auto &c : checks) std::printf("%s\n", c.first.c_str());

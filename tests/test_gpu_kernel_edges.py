@@ -65,6 +65,16 @@ def test_odd_rows_split_over_launches_and_walked(bs, row, tuning):
     hop_at(W.tiny(940 + row, 5, bs, (row, row, 16), 120, 20 * bs), 3, 1, **tuning)
 
 
+# layers beyond what the on-die cache holds from the gather to the scatter: other cache policies, and the gather's tiles
+# begin on the source's lines.  Tiled (one and several tiles, walked) and flat, both sides off their lines
+@pytest.mark.parametrize("bs,row,tuning", [(64, 132, {}), (64, 1026, {}), (64, 132, dict(max_groups=1000)), (16, 132, {}), (1, 8065, {}), (5, 1009, {})])
+@pytest.mark.parametrize("x_off,pool_off", [(0, 0), (13, 19)])
+def test_odd_rows_of_layers_that_pass_the_cache_by(bs, row, tuning, x_off, pool_off):
+    w = _uniform(3, (70 << 20) // row // 3, bs, row)
+    assert oracle.payload_bytes(w.hit, w.layout.row_bytes) > 64 << 20
+    hop_at(w, x_off, pool_off, **tuning)
+
+
 # rows of 1, 15, 16, 31, 32, 63, 64, 65 and 72 vectors (how many rows a wavefront's 64 vectors can touch changes at
 # 16, 32 and 64), one to a few to a block, with and without chance neighbours merged into longer descriptors
 @pytest.mark.parametrize("row", [16, 240, 256, 496, 512, 1008, 1024, 1040, 1152])
