@@ -900,6 +900,20 @@ def _time_launches(fn, stream, reps: int = 8, warm: int = 2) -> float:
     return float(np.mean(ms))
 
 
+def _time_in_turn(fns, stream, reps: int = 8, warm: int = 2):
+    """Average durations in ms of the launches of each of fns, made one after the other on `stream` without a pause,
+    as the gather and the scatter of a layer are in use (their cache policies are chosen for that)."""
+    import torch
+    marks = [torch.cuda.Event(enable_timing=True) for _ in range((reps + warm) * len(fns) + 1)]
+    marks[0].record(stream)
+    for i, mark in enumerate(marks[1:]):
+        fns[i % len(fns)]()
+        mark.record(stream)
+    stream.synchronize()
+    ms = [a.elapsed_time(b) for a, b in zip(marks, marks[1:])][warm * len(fns):]
+    return [float(np.mean(ms[i::len(fns)])) for i in range(len(fns))]
+
+
 def ceilings_leg(stream, roof_pack: dict, roof_unpack: dict, config_index: int) -> dict:
     """What the memory of this machine does on reference streams that use the load and store
     instructions and cache policies of the default kernels but no descriptors: a linear copy and
@@ -907,7 +921,8 @@ def ceilings_leg(stream, roof_pack: dict, roof_unpack: dict, config_index: int) 
     side dense, the other hopping every 41,984 bytes to a pseudo-random block, the two sides 16
     bytes apart in their 128-byte lines -- with the block's address computed, or read from a
     4-byte table entry through the scalar cache as a descriptor is; and that last form once more with
-    every hop kept within 16 neighbouring blocks, which shows what the distance of the hops costs."""
+    every hop kept within 16 neighbouring blocks, which shows what the distance of the hops costs.  The
+    gather and the scatter of that shape are timed in turn, as they are in use."""
     import torch
     import paper_2602_21548_amd as K
     dev = torch.device("cuda:0")
@@ -935,21 +950,18 @@ def ceilings_leg(stream, roof_pack: dict, roof_unpack: dict, config_index: int) 
     # the table holds the blocks the computed form would visit (u * odd constant mod 2^19)
     table = ((torch.arange(1 << k_dense, dtype=torch.int64, device=dev) * 0x9e3779b1) & ((1 << k_hop) - 1)).to(torch.int32)
     shape = {"block_bytes": block, "blocks": 1 << k_dense, "payload_bytes": payload, "skew_bytes": skew}
-    for side, name, src, dst in ((0, "gather", hop, dense), (1, "scatter", dense, hop)):
-        for tname, tab in (("computed_address", None), ("table_entry_per_block", table)):
-            ms = _time_launches(lambda: K.kvl_ceiling_kernel(K.KVL_CEILING_COPY, src, dst, payload, block_bytes=block,
-                                                             hopping_side=side, skew_bytes=skew, hop_blocks_log2=k_hop,
-                                                             block_table=tab, stream=stream), stream)
-            shape[f"{name}_{tname}"] = round(2.0 * payload / ms / 1e6, 1)
     # the same copy with the hops kept local: the blocks of every 16 consecutive ones (0.7 MB) are
     # permuted among themselves, so only how far a hop goes differs from the table above
     u = torch.arange(1 << k_dense, dtype=torch.int64, device=dev)
     near = ((u // 16) * 16 + (u % 16) * 5 % 16).to(torch.int32)
-    for side, name, src, dst in ((0, "gather", hop, dense), (1, "scatter", dense, hop)):
-        ms = _time_launches(lambda: K.kvl_ceiling_kernel(K.KVL_CEILING_COPY, src, dst, payload, block_bytes=block,
-                                                         hopping_side=side, skew_bytes=skew, hop_blocks_log2=k_hop,
-                                                         block_table=near, stream=stream), stream)
-        shape[f"{name}_table_entry_hops_within_16_blocks"] = round(2.0 * payload / ms / 1e6, 1)
+    for tname, tab in (("computed_address", None), ("table_entry_per_block", table),
+                       ("table_entry_hops_within_16_blocks", near)):
+        def copy(side, tab=tab):
+            K.kvl_ceiling_kernel(K.KVL_CEILING_COPY, dense if side else hop, hop if side else dense, payload,
+                                 block_bytes=block, hopping_side=side, skew_bytes=skew, hop_blocks_log2=k_hop,
+                                 block_table=tab, stream=stream)
+        for name, ms in zip(("gather", "scatter"), _time_in_turn((lambda: copy(0), lambda: copy(1)), stream)):
+            shape[f"{name}_{tname}"] = round(2.0 * payload / ms / 1e6, 1)
     del u, near
     out["shape_of_cfg4"] = shape
     if config_index == 4:
