@@ -109,27 +109,31 @@ inline uint32_t move_threads(const kvl_plan_s *plan, uint32_t row_bytes) {
 }
 
 // Whether a launch over planes of this row size is laid out over the transfer rows (kvl_rows_kernel) instead of over
-// the descriptors' tiles, which have the size of the largest descriptor's.  Measured on hops of one plane, us a hop,
-// tiles / rows:
-//  - tiles that would leave lanes idle, and descriptors of less than a workgroup.  1 GB layers: 1152-byte rows by 1
-//    (72 vectors) 747 / 579, by 4 (1.1 tiles) 630 / 580, by 6 634 / 576, by 8 (2.25 tiles) 577 / 575, by 10 569 / 574;
-//    2048 by 1 779 / 667, by 2 (one full tile) 660 / 666; 576 by 64 (9 tiles and the line-up) 706 / 666.  The scatter
-//    into rows that are no multiple of a line writes them in halves this way (a tile begins on a line) and wants a
-//    worse filled tile before it gains: scatter alone, 656 by 32 (85 % busy) +2 %, 272 by 16 (53 %) -2 %.
-//  - a scatter whose layer is about the size of the on-die cache, tiles / rows: 656 by 64, 100 MB 63 / 65 (plain
-//    loads), 140 MB 103 / 95, 300 MB 194 / 172, 400 MB 295 / 292, 600 MB 404 / 416; 2048 by 64, 240 MB 142 / 141,
-//    300 MB 162 / 155, 400 MB 239 / 227, 600 MB 343 / 331, 1 GB 604 / 602.
+// the descriptors' tiles, which have the size of the largest descriptor's.  Measured on hops of one plane, 16 requests of
+// uneven length, random tables, three layers each with its own plan and buffers in turn; us a hop, tiles / rows:
+//  - tiles that would leave lanes idle, and descriptors of less than a workgroup: by rows both ways.  1 GB, 1152-byte rows
+//    by 1 (72 vectors) 747 / 579, by 4 (1.1 tiles) 630 / 580, by 8 (2.25 tiles) 577 / 575, by 10 569 / 574; 2048 by 1 779 /
+//    667, by 2 (one full tile) 660 / 666; 910 MB, 64 by 64 904 / 644, 128 by 50 629 / 588, 80 by 256 649 / 610.  The
+//    scatter into rows that are no multiple of a line writes them in halves this way (a tile begins on a line) and wants a
+//    worse filled tile before it gains: scatter alone, 656 by 32 (85 % busy) +2 %, 272 by 16 (53 %) -2 %.  Rows that do not
+//    straddle lines lose in longer descriptors, where only the last tile is badly filled: 910 MB, 64 by 256 584 / 612, 256
+//    by 100 586 / 605, 128 by 100 569 / 582 (1152 by 8, 576 vectors, 651 / 633; 64 by 128, 512, 618 / 624).
+//  - the scatter of layers about the size of the on-die cache.  Rows that are no multiple of a line: 150 MB 656 by 64
+//    101.7 / 92.5, 80 by 256 109.4 / 97.9, 303 MB 656 by 64 207 / 184, 272 by 256 199 / 182, 405 MB 265 / 253 and 269 /
+//    260.  Rows of whole lines from 512 bytes: 303 MB 512 by 64 193 / 182, 2048 by 64 188 / 176 (with one plan for the
+//    three layers 173.6 / 174.6), 425 MB 2048 by 64 257 / 245, 546 MB 325 / 316; shorter ones 303 MB 128 by 64 197 / 200,
+//    425 MB 128 by 256 264 / 277, 256 by 256 259 / 272, 384 by 64 264 / 262, 546 MB 338 / 342.
 inline bool takes_row_map(const kvl_plan_s *plan, uint32_t row_bytes, bool pack) {
     if (plan->paired || !plan->vec16 || plan->units.empty() || plan->max_unit_rows > 4096) return false;
-    const bool lines = row_bytes % 128 == 0;
+    const bool lines = row_bytes % 128 == 0, straddle = !lines && 128 % row_bytes != 0;
     const uint64_t row = row_bytes / 16, largest = plan->max_unit_rows * row;
     const uint64_t t = tile_threads(largest), tiles = (largest + (lines ? 0 : 7) + t - 1) / t;
     const double average = (double)plan->hit_tokens * (double)row / (double)plan->units.size();
     const double busy = average / (double)(tiles * t);
-    if (average < 200 || busy < (pack || lines ? 0.91 : 0.80)) return true;
+    if (average < 200 || busy < (!straddle && largest >= 768 ? 0.66 : pack || lines ? 0.91 : 0.80)) return true;
     if (pack || row_bytes < 48) return false;
     const uint64_t mb = plan->payload_bytes >> 20;
-    return lines ? mb >= 256 && mb < 576 : plan->payload_bytes > kPlainReadBackBytes && mb < 432;
+    return lines ? row_bytes >= 512 && mb >= 256 && mb < 576 : plan->payload_bytes > kPlainReadBackBytes && mb < 432;
 }
 
 // Cut [0, n_units) of one plane into chunks of at most chunk_bytes.

@@ -309,6 +309,33 @@ static int check_row_map_split() {
     return 0;
 }
 
+// Shapes on either side of the lines between the row map and the tiles; with the map the call measured faster, or not.
+static int check_row_map_rule() {
+    const struct { uint32_t row, bs, mb; bool gather, scatter; } shapes[] = {
+        {1152, 1, 900, true, true}, {1152, 4, 900, true, true}, {2048, 1, 900, true, true}, {2048, 2, 900, false, false},
+        {64, 64, 900, true, true}, {64, 128, 900, true, true}, {1152, 8, 900, true, true}, {64, 256, 900, false, false},
+        {80, 256, 900, true, false}, {128, 50, 900, true, true}, {128, 100, 900, false, false}, {256, 100, 900, false, false},
+        {192, 64, 900, true, true}, {272, 16, 900, true, true}, {144, 256, 900, true, false}, {1152, 64, 900, false, false},
+        // scatters of layers about the size of the on-die cache
+        {656, 64, 100, false, false}, {656, 64, 140, false, true}, {656, 100, 400, false, true}, {656, 64, 440, false, false},
+        {272, 256, 300, false, true}, {1152, 64, 250, false, false}, {1152, 64, 300, false, true}, {512, 64, 300, false, true},
+        {2048, 64, 560, false, true}, {2048, 64, 600, false, false}, {128, 64, 300, false, false}, {256, 256, 420, false, false},
+        {384, 64, 540, false, false}};
+    for (const auto &q : shapes) {
+        const uint64_t n = ((uint64_t)q.mb << 20) / (q.bs * q.row);
+        kvl_plan_s p = made(n, q.bs, q.row);
+        p.layout.block_tokens = q.bs;
+        p.hit_tokens = n * q.bs;
+        p.payload_bytes = p.hit_tokens * q.row;
+        if (takes_row_map(&p, q.row, true) != q.gather || takes_row_map(&p, q.row, false) != q.scatter) {
+            std::printf("%u-byte rows by %u, %u MB: gather %d scatter %d\n", q.row, q.bs, q.mb, takes_row_map(&p, q.row, true), takes_row_map(&p, q.row, false));
+            return 1;
+        }
+        p.d_units = nullptr;
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, int (*)()> checks = {
         {"move_shapes", check_move_shapes},
@@ -320,6 +347,7 @@ int main(int argc, char **argv) {
         {"cached_arrays", check_cached_arrays},
         {"ceiling_policies", check_ceiling_policies},
         {"row_map_split", check_row_map_split},
+        {"row_map_rule", check_row_map_rule},
     };
     if (argc != 2 || !checks.count(argv[1])) {
         for (const auto &c : checks) std::printf("%s\n", c.first.c_str());

@@ -85,11 +85,11 @@ def test_small_descriptors_by_the_row_map(row, bs, kind, x_off):
     hop_at(W.tiny(970 + row + bs, 5, bs, (row,), 300, 50 * bs, kind=kind), x_off, block_threads=64)
 
 
-@pytest.mark.parametrize("row,mb", [(656, 118), (1152, 280)])
-def test_layers_about_the_size_of_the_on_die_cache(row, mb):
-    """Whole blocks whose scatter takes the row map for the size of the layer."""
+@pytest.mark.parametrize("bs,row,mb", [(64, 656, 118), (64, 1152, 280), (100, 656, 118), (64, 256, 280)])
+def test_layers_about_the_size_of_the_on_die_cache(bs, row, mb):
+    """Whole blocks whose scatter takes the row map for the size of the layer (256-byte rows: the tiles)."""
     tokens = (mb << 20) // row // 3
-    hop_at(_uniform(3, tokens, 64, row))
+    hop_at(_uniform(3, tokens, bs, row))
 
 
 def _uniform(requests, tokens, bs, row):
