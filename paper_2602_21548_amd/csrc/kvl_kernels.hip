@@ -419,7 +419,8 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
         a.tile_end[p] = (uint32_t)std::min<uint64_t>(tpu, UINT32_MAX);
     }
     if (a.n_units * widest > (uint64_t)INT32_MAX || tpu > (uint64_t)INT32_MAX) return KVL_ERANGE;
-    const uint32_t cap = plan->tuning.max_groups ? plan->tuning.max_groups
+    // (a cap that was asked for is meant for each plane, see kvl_tuning_t)
+    const uint32_t cap = plan->tuning.max_groups ? (uint32_t)std::min<uint64_t>((uint64_t)plan->tuning.max_groups * P, UINT32_MAX)
                                                  : (far_host ? (vec ? kHostSideGroups : 2 * kHostSideGroups) : 0u);
     On on(plan, stream);
     // the tiles of all planes are numbered with 32 bits: descriptors that have more go in several launches

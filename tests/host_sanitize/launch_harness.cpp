@@ -100,6 +100,13 @@ static int check_full_block_planes() {
     launches.clear();
     REQUIRE(kvl::fullblock_launch(&p, true, 1ull << 44, 4 * 64 * 2048, 0, 5, 1005, kPlanes, nullptr) == KVL_OK);
     REQUIRE(launches.size() == 1 && groups(launches[0]) == 1000 * 128);
+    for (uint32_t cap : {10u, UINT32_MAX}) {                // at most so many workgroups for each plane
+        launches.clear();
+        p.tuning.max_groups = cap;
+        REQUIRE(kvl::fullblock_launch(&p, true, 1ull << 44, 4 * 64 * 2048, 0, 5, 1005, kPlanes, nullptr) == KVL_OK);
+        REQUIRE(launches.size() == 1 && groups(launches[0]) == (cap == 10 ? 40 : 1000 * 128));
+    }
+    p.tuning.max_groups = 0;
     p.max_unit_rows = 64 * 64;
     REQUIRE(kvl::fullblock_launch(&p, true, 1ull << 44, 4 * 64 * 2048, 0, 0, 20000000, kPlanes, nullptr) == KVL_ERANGE);
     p.d_units = nullptr;
