@@ -527,7 +527,9 @@ struct FullBlockArgs {
 // the pool nt loads and sc1 stores, which leave the layer there for whoever reads it next; out of it nt loads and
 // sc1+nt stores).  Both directions in turn, 64-token blocks of 61 layers, us a layer, against plain loads with sc1+nt
 // stores one way and nt loads with plain stores the other: 1152-byte rows, 101 MB a layer, 89 -> 63; 221 MB 185 -> 142;
-// 1.8 GB 1388 -> 1305; 656-byte rows, 58 MB, 59 -> 46.  Across the host link the old ones stay (the link is the bound).
+// 1.8 GB 1388 -> 1305; 656-byte rows, 58 MB, 59 -> 46.  Across the host link the old ones stay for whole vectors (the link
+// is the bound); at byte addresses the new ones are ahead there too (out of the pool, new / old: 741-byte rows by 64, 40 MB,
+// 706 / 727; 57 by 16, 20 MB, 382 / 426; 132 by 1, 8 MB, 255 / 425; into it level).
 template <bool TO_POOL, bool VEC, int VPT, bool NTL, int SP>
 __device__ __forceinline__ void fullblock_tile(const FullBlockArgs &a, uint32_t tiles_per_unit, uint32_t tile_index) {
     const uint32_t u_idx = tile_index / tiles_per_unit;

@@ -191,6 +191,9 @@ static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, co
 //     and read back with plain loads (132-byte rows by 64, three layers in turn, hop of 40 MB: 29.4 us against 33.0
 //     with non-temporal accesses throughout), a larger one passes it by (100 MB 76.7 -> 72.0, 180 MB 131.6 -> 123.2,
 //     1 GB 710 -> 704).  Across the host link the former (741-byte rows, 80 MB in and out, 2857 us against 2987).
+//   across the host link: tiles on few workgroups (kHostSideGroups); a flat launch has as many as ever, since few of them
+//     would not keep the link busy with small descriptors (in / out, flat and tiled: 132 by 1, 8 MB, 149 / 153 and 684 /
+//     255; 36 by 2, 40 MB, 716 / 743 and 6870 / 3109; 132 by 16, 40 MB, 726 / 736 and 793 / 750).
 static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uint32_t planes, bool far_host,
                        const On &on) {
     const uint64_t unit_bytes = (uint64_t)plan->max_unit_rows * a.row_elems[a.plane_begin];

@@ -20,8 +20,8 @@ CASES = [
     ("tiny-random", lambda: W.tiny(201, 6, 16, (48,), 64, 90)),
     ("tiny-runs-2planes", lambda: W.tiny(202, 7, 4, (32, 16), 200, 60, kind="runs")),
     ("tiny-contig", lambda: W.tiny(203, 5, 8, (16,), 100, 120, kind="contiguous")),
-    ("tiny-oddrow", lambda: W.tiny(204, 4, 3, (5,), 60, 40)),              # byte fallback kernel
-    ("tiny-row-mult-of-4", lambda: W.tiny(205, 4, 8, (36,), 60, 100)),     # byte fallback kernel
+    ("tiny-oddrow", lambda: W.tiny(204, 4, 3, (5,), 60, 40)),              # rows below a vector
+    ("tiny-row-mult-of-4", lambda: W.tiny(205, 4, 8, (36,), 60, 100)),     # vectors at byte addresses
     ("tiny-3planes", lambda: W.tiny(206, 5, 16, (16, 656, 64), 40, 150)),
     ("tiny-4planes-single-tokens", lambda: W.tiny(214, 8, 1, (16, 32, 48, 2048), 64, 5)),   # KVL_MAX_PLANES, bs = 1
     ("cfg1", lambda: W.config(1)),

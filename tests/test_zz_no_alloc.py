@@ -69,7 +69,7 @@ def test_shapes_ranges_and_streams():
         (W.config(2, n_requests=7, token_scale=1 / 32), 0),                       # two planes
         (W.config(4, n_requests=12, token_scale=1 / 32), 0),                      # 656-byte rows, fragmented tables
         (W.tiny(232, 9, 1, (1152,), 3000, 300), 0),                               # token-granular: the flat kernel
-        (W.tiny(233, 4, 3, (5,), 60, 40), 0),                                     # odd rows: the byte kernel
+        (W.tiny(233, 4, 3, (5,), 60, 40), 0),                                     # rows below a vector
         (W.tiny(234, 7, 4, (32, 16), 200, 60, kind="runs"), K.KVL_NO_MERGE),
         (W.from_trace(32, 6), K.KVL_TOKENS_APPEND),
         (W.from_trace(32, 6), K.KVL_TOKENS_ALL),
