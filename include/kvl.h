@@ -152,8 +152,8 @@ int kvl_plan_tuned(const kvl_layout_t *layout, const kvl_request_t *requests, ui
 /* Frees the plan.  The call does not wait for the device: kernels enqueued with the
  * plan may still be running or queued.  Every launch made with a plan carries
  * an event (one per stream, that of the stream's last launch).  The plan's device descriptor
- * array is retired with those events and goes back to a small cache inside the library (at most
- * 16 buffers / 1 GiB, from which later plans are served without a device allocation) only when
+ * array is retired with those events and goes back to a cache inside the library (at most
+ * 256 buffers / 1 GiB, from which later plans are served without a device allocation) only when
  * they have fired.  The default stream, which cannot go away, is followed by the next launch that
  * the library makes there instead: that one carries an event for the arrays of all plans used there
  * and destroyed before it, which go back when it has finished.

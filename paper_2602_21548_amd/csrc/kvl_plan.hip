@@ -88,7 +88,9 @@ std::vector<std::pair<hipEvent_t, int>> g_map_events;   // spare events that oth
 std::vector<PooledLane> g_lanes;
 uint64_t g_retirements = 0;
 std::atomic<unsigned> g_waiting{0};     // retired arrays with default_stream and without passed
-constexpr size_t kCacheEntries = 16;
+// As many as an engine's plans that the device has not come to yet: what is beyond is freed, which waits for the device (61
+// layers of 137 MB a batch, 16 arrays, some of them of other sizes: 5110 us a batch, none of it beside the host's work; 4935)
+constexpr size_t kCacheEntries = 256;
 constexpr size_t kCacheBytes = 1u << 30;        // never keep more than this much idle (see map_fits_cache)
 constexpr size_t kSpareEvents = 256;
 constexpr size_t kPooledLanes = 16;

@@ -248,6 +248,21 @@ static int check_cached_arrays() {
         }
         REQUIRE(fake::mallocs == 2 && fake::frees == 0);
     }
+    // an engine that queues forty batches ahead, after plans of other sizes: nothing is freed, and nothing new allocated
+    // for the next forty
+    kvl_release_cached_memory();
+    for (uint32_t tokens : {100u, 20000u, 40000u, 80000u, 160000u}) kvl_plan_destroy(plan_of_blocks(tokens, 64, 1152, KVL_GATHER));
+    fake::frees = 0;
+    for (int round = 0; round < 2; ++round) {
+        fake::mallocs = 0;
+        for (int batch = 0; batch < 40; ++batch) {
+            kvl_plan_t *p = plan_of_blocks(10000, 64, 1152, KVL_GATHER);
+            REQUIRE(p && !p->d_row_map && pack(p, nullptr) == KVL_OK);
+            kvl_plan_destroy(p);
+        }
+        REQUIRE(fake::frees == 0 && fake::mallocs == (round ? 1 : 40));        // (the last one waits for a launch after it)
+        fake::finish(&fake::null_stream);
+    }
     kvl_release_cached_memory();
     fake::mallocs = fake::frees = 0;
     for (int batch = 0; batch < 2; ++batch) {               // 200 M rows in two million descriptors: no map of 800 MB beside 32
