@@ -149,7 +149,7 @@ void keep_or_free(const CachedBuffer &b) {
     (void)hipFree(b.ptr);
 }
 
-// nobody reads on the default stream what it held so far
+// Wait for what the default stream holds (false: it may not be waited for).
 bool wait_for_default_stream(int device) {
     int current = device;
     (void)hipGetDevice(&current);

@@ -253,14 +253,14 @@ static int check_cached_arrays() {
     kvl_release_cached_memory();
     for (uint32_t tokens : {100u, 20000u, 40000u, 80000u, 160000u}) kvl_plan_destroy(plan_of_blocks(tokens, 64, 1152, KVL_GATHER));
     fake::frees = 0;
-    for (int round = 0; round < 2; ++round) {
+    for (int again = 0; again < 2; ++again) {
         fake::mallocs = 0;
         for (int batch = 0; batch < 40; ++batch) {
             kvl_plan_t *p = plan_of_blocks(10000, 64, 1152, KVL_GATHER);
             REQUIRE(p && !p->d_row_map && pack(p, nullptr) == KVL_OK);
             kvl_plan_destroy(p);
         }
-        REQUIRE(fake::frees == 0 && fake::mallocs == (round ? 1 : 40));        // (the last one waits for a launch after it)
+        REQUIRE(fake::frees == 0 && fake::mallocs == (again ? 1 : 40));        // (the last one waits for a launch after it)
         fake::finish(&fake::null_stream);
     }
     kvl_release_cached_memory();
