@@ -466,7 +466,12 @@ __device__ __forceinline__ void copy_any(uintptr_t src, uintptr_t dst, uint32_t 
 }
 
 // Tiled: a tile is blockDim vectors; one workgroup per tile, or (WALK) gridDim.x of them walking over n_tiles.
-template <bool PACK, bool NTL, int SP, bool WALK>
+// Tiles begin on 128-byte lines of the destination, or (SRC) of the source: then every line of the source is read by one
+// wavefront alone.  A line that the on-die cache holds is taken out of it by a non-temporal load, so that a line shared by
+// two wavefronts is fetched from memory by the second; the stores of the two meet in the L2 instead (they must not be
+// written through: hops of 304 MB, 1026-byte rows by 64, us: gather and scatter on lines of the destination 209, of the
+// source with nt stores out of the scatter 195, with sc1+nt ones 219).
+template <bool PACK, bool NTL, int SP, bool SRC, bool WALK>
 __global__ void __launch_bounds__(1024) kvl_any_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t n_tiles) {
     cunits_t units = (cunits_t)(uintptr_t)(a.units + a.unit_begin);
     const uint32_t p = a.plane_begin + blockIdx.y;
@@ -479,12 +484,8 @@ __global__ void __launch_bounds__(1024) kvl_any_tile_kernel(const CopyArgs a, ui
         const uintptr_t pool = pool_base + (uint64_t)u->pool_row * row;
         const uintptr_t xfer = xfer_base + (uint64_t)u->xfer_row * row;
         const uintptr_t dst = PACK ? xfer : pool;
-        // tiles start on a line of the destination, or, where a gather's stores pass the cache by (SP == 1), of the
-        // source (300 MB and 1 GB of 1026-byte rows, hop, 236 -> 233 and 706 -> 693 us; 657-byte rows, 180 MB, 135 -> 131;
-        // for the scatter, and with stores that stay in the cache, the source's lines lose 2-10 %)
-        const uintptr_t line = PACK && SP == 1 ? pool : dst;
-        copy_any<NTL, SP>(PACK ? pool : xfer, dst, u->n_rows * row, (uint32_t)line & 127u,
-                          tile * blockDim.x + threadIdx.x);
+        const uintptr_t src = PACK ? pool : xfer;
+        copy_any<NTL, SP>(src, dst, u->n_rows * row, (uint32_t)(SRC ? src : dst) & 127u, tile * blockDim.x + threadIdx.x);
         if (!WALK) return;
     }
 }

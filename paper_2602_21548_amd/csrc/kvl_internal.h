@@ -64,10 +64,13 @@ void set_hip_error(hipError_t e);
 constexpr uint32_t kDefaultUnitBytes = 128u << 10;
 constexpr uint32_t kDefaultBlockThreads = 256;
 constexpr uint32_t kHostSideGroups = 64;    // workgroups of a kernel whose far side is host memory (see kvl_tile_walk_kernel)
-constexpr uint32_t kAnyFlatWindows = 288;   // rows that are no multiple of 16 bytes: largest descriptor, in vectors, dealt out flat
-// Rows that are no multiple of 16 bytes: up to this payload the on-die cache holds the layer from the gather's stores to
-// the scatter's loads, beside what else passes through it.
-constexpr uint64_t kCachedLayerBytes = 64u << 20;
+// Rows that are no multiple of 16 bytes (launch_any says why): the largest descriptor, in vectors, dealt out flat in a hop,
+// and in moves and across the host link;
+constexpr uint32_t kAnyFlatWindows = 160, kAnyFlatLinesWindows = 256, kAnyFlatPastWindows = 288;
+// up to which payload the on-die cache holds the layer from the gather's stores to the scatter's loads, beside two other
+// layers' in turn (256 MB hold three of 85 MB), and up to which it pays to read each line out of it once.
+// (Dealt out flat, 26 by 16, 73 MB, passing by / kept 81 / 85.)
+constexpr uint64_t kCachedFlatBytes = 64u << 20, kCachedLayerBytes = 76u << 20, kReadOnceBytes = 640u << 20;
 constexpr uint32_t kNumVariants = 512;       // explicit variants are 1 .. kNumVariants
 bool valid_block_threads(uint32_t t);
 

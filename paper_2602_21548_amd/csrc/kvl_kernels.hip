@@ -174,23 +174,39 @@ static void launch_rows(dim3 g, dim3 b, const On &s, const CopyArgs &a, const ui
     else KVL_LAUNCH((kvl_rows_kernel<PACK, NTL, SP, 0>), g, b, s, a, map, row_begin, n_vecs);
 }
 
-template <bool PACK, bool NTL, int SP>
+template <bool PACK, bool NTL, int SP, bool SRC>
 static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t x, uint32_t n_tiles) {
     if (flat) KVL_LAUNCH((kvl_any_flat_kernel<PACK, NTL, SP>), g, b, s, a, x);
-    else if (walk) KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, true>), g, b, s, a, x, n_tiles);
-    else KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, false>), g, b, s, a, x, n_tiles);
+    else if (walk) KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, SRC, true>), g, b, s, a, x, n_tiles);
+    else KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, SRC, false>), g, b, s, a, x, n_tiles);
 }
 
 // Rows or addresses that are not multiples of 16 bytes (the planes of a launch have one row size).
-//   flat or tiled: a descriptor of up to kAnyFlatWindows vectors leaves too much of its last 256-lane tile
-//     idle (300 MB hops: 132-byte rows by 16, 133 vectors, 250 -> 220 us flat; 260 by 16, 261 vectors, two
-//     tiles, 309 -> 225); beyond it a tile per 256 lanes is the better (132 by 64, 530 vectors: 215 against
-//     245 flat).  A flat workgroup has 1024 lanes (1026-byte rows by 1: 361 us at 256, 329 at 512, 324), a
-//     tile of a descriptor below two 256-lane tiles 128 (1026 by 4: 377 us at 256, 286 at 128).
-//   cache policy: a layer that the on-die cache holds from the gather to the scatter is written with sc1 stores
-//     and read back with plain loads (132-byte rows by 64, three layers in turn, hop of 40 MB: 29.4 us against 33.0
-//     with non-temporal accesses throughout), a larger one passes it by (100 MB 76.7 -> 72.0, 180 MB 131.6 -> 123.2,
-//     1 GB 710 -> 704).  Across the host link the former (741-byte rows, 80 MB in and out, 2857 us against 2987).
+//   cache policy and lines of the tiles, by the payload.  Up to kCachedLayerBytes the on-die cache holds a layer from the
+//     gather to the scatter: the gather writes with sc1 stores and the scatter reads with plain loads.  Up to kReadOnceBytes
+//     both lay their tiles on the source's lines, so that the scatter's non-temporal loads take each line out of the cache
+//     once (see kvl_any_tile_kernel), and the scatter stores with nt.  Larger layers pass the cache by, both ways, and the
+//     scatter's tiles lie on the destination's lines.  The gather's tiles lie on its source's always.  Hops, three layers in
+//     turn, us, passing by / read once / kept (gather on the destination's lines): 1026-byte rows by 64, 77 MB 56 / 50 / 50,
+//     100 MB 72 / 64 / 74, 242 MB 167 / 148 / 170, 494 MB 342 / 332 / 355, 666 MB 461 / 456 / 477, 924 MB 636 / 642 / -;
+//     333 by 64, 85 MB 69 / 61 / 60, 206 MB 161 / 143 / 156, 655 MB 519 / 490 / 540.  With one layer again and again the
+//     kept form would be 2-5 % ahead up to 240 MB, with four it is 15 % behind from 77 MB.  Kept, the gather on its
+//     source's lines: 333 by 64, 39 MB, 29.2 -> 27.5; 99 by 64, 22 MB, 21.3 -> 19.3.
+//     Across the host link as kept (741-byte rows, 80 MB in and out, 2857 us against 2987 passing by).
+//   flat or tiled: a descriptor of up to kAnyFlatWindows vectors leaves too much of its last tile idle (150 MB hops, flat /
+//     tiled: 300-byte rows by 8, 151 windows, 111 / 114; 90 by 32, 181 windows, 119 / 107; 153 by 24, 231 windows, 117 / 104).
+//     Blocks of whole lines go better flat, once they are not kept (200 by 16, 201 windows, 31 MB 27 / 25, 147 MB 108 / 113; 70 by 64,
+//     281 windows, 142 MB, 111 / 104).
+//     Where the largest is more than half again the average, most tiles' workgroups would find nothing to do, and narrow ones
+//     are many: flat up to kAnyFlatPastWindows (104 by 16, a chance pair merged here and there, 209 windows, 348 MB, gather
+//     157 flat, 210 tiled).  A flat workgroup has 1024 lanes (1026-byte rows by 1: 361 us at 256, 329 at 512, 324).
+//   lanes of a tile: a gather's 64, which idle least (132 by 64, 275 MB, 103 us with 256, 99 with 128, 94 with 64; 333 by 64,
+//     196 MB, 69 / 64 / 63; 1026 by 64, 181 MB, 57 / 58 / 58); a scatter's 256, whose wavefronts share fewer lines at the
+//     ends of tiles, or 128 where that leaves an eighth of the lanes fewer without work (256 / 128: 132 by 64 107 / 103, 333
+//     by 16 54 / 49, 47 by 128 46 / 42; but 333 by 64, 8 % fewer, 73 / 77, 1115 by 16 45 / 48).  Past the cache 256 or, for
+//     short descriptors, by the same rule (gather of 153 by 24, 948 MB, 256 / 128: 348 / 385).
+//   moves (150 MB of 90-byte rows by 32: flat 54, tiled with 256 / 128 lanes 53 / 59) and the host link: flat up to
+//     kAnyFlatPastWindows, tiles of 256 lanes, 128 below two such tiles (1026 by 4: 377 us at 256, 286 at 128).
 //   across the host link: tiles on few workgroups (kHostSideGroups); a flat launch has as many as ever, since few of them
 //     would not keep the link busy with small descriptors (in / out, flat and tiled: 132 by 1, 8 MB, 149 / 153 and 684 /
 //     255; 36 by 2, 40 MB, 716 / 743 and 6870 / 3109; 132 by 16, 40 MB, 726 / 736 and 793 / 750).
@@ -198,17 +214,31 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
                        const On &on) {
     const uint64_t unit_bytes = (uint64_t)plan->max_unit_rows * a.row_elems[a.plane_begin];
     const uint64_t windows = (unit_bytes + 30) / 16;       // 16-byte windows a span of that size can touch
-    const bool flat = windows <= kAnyFlatWindows;
+    const bool hop = !plan->paired && !far_host;
+    const bool alike = 2ull * plan->max_unit_rows * plan->units.size() <= 3 * plan->hit_tokens;
+    const bool lines = (uint64_t)plan->layout.block_tokens * a.row_elems[a.plane_begin] % 128 == 0 && plan->payload_bytes > kCachedFlatBytes;
+    const bool flat = windows <= (!hop || !alike ? kAnyFlatPastWindows : lines ? kAnyFlatLinesWindows : kAnyFlatWindows);
+    const bool kept = far_host || (!plan->paired && plan->payload_bytes <= (flat ? kCachedFlatBytes : kCachedLayerBytes));
+    const bool once = hop && !kept && plan->payload_bytes <= kReadOnceBytes;
+    const uint64_t spanned = unit_bytes + 127;              // with the lanes before its first byte on the line
+    auto tiles_of = [spanned](uint64_t lanes) { return (spanned + 16 * lanes - 1) / (16 * lanes); };
     uint32_t threads = plan->tuning.block_threads;
-    if (!plan->threads_chosen) threads = flat ? 1024 : unit_bytes + 127 <= 2 * 256 * 16 ? 128 : 256;
+    if (!plan->threads_chosen) {
+        const bool is_short = spanned <= 2 * 256 * 16;
+        const double busy_128 = (double)spanned / (2048.0 * (double)tiles_of(128)), busy_256 = (double)spanned / (4096.0 * (double)tiles_of(256));
+        const bool halve = busy_128 - busy_256 > 0.125;
+        if (flat) threads = 1024;
+        else if (!hop) threads = is_short ? 128 : 256;
+        else if (pack && (kept || once)) threads = 64;
+        else threads = halve && (is_short || kept || once) ? 128 : 256;
+    }
     uint64_t cap = plan->tuning.max_groups;
     if (!cap && far_host) cap = 2 * kHostSideGroups;       // (one vector per lane: see kHostSideGroups)
-    const uint64_t per_unit = (unit_bytes + 127 + 16ull * threads - 1) / (16ull * threads);
+    const uint64_t per_unit = tiles_of(threads);
     uint64_t per_launch = flat ? ((1ull << 32) - threads) / windows : (uint64_t)INT32_MAX / per_unit;
     if (flat && plan->tuning.max_groups)
         per_launch = std::min<uint64_t>(per_launch, (uint64_t)plan->tuning.max_groups * threads / windows);
     per_launch = std::max<uint64_t>(1, per_launch);
-    const bool kept = far_host || (plan->payload_bytes <= kCachedLayerBytes && !plan->paired);
     for (uint64_t first = 0; first < a.n_units; first += per_launch) {
         CopyArgs part = a;
         part.unit_begin = a.unit_begin + (uint32_t)first;
@@ -217,14 +247,16 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
         bool walk = false;
         const uint32_t groups = flat ? (uint32_t)((part.n_units * windows + threads - 1) / threads)
                                      : launch_groups(tiles, threads, (uint32_t)cap, &walk);
-        const uint32_t x = (uint32_t)(flat ? windows : per_unit);
+        const uint32_t x = (uint32_t)(flat ? windows : per_unit), n_tiles = (uint32_t)tiles;
         dim3 grid(groups, planes), block(threads);
         if (pack) {
-            if (kept) launch_any_one<true, true, 2>(flat, walk, grid, block, on, part, x, (uint32_t)tiles);
-            else launch_any_one<true, true, 1>(flat, walk, grid, block, on, part, x, (uint32_t)tiles);
+            if (far_host) launch_any_one<true, true, 2, false>(flat, walk, grid, block, on, part, x, n_tiles);
+            else if (kept || (once && !flat)) launch_any_one<true, true, 2, true>(flat, walk, grid, block, on, part, x, n_tiles);
+            else launch_any_one<true, true, 1, true>(flat, walk, grid, block, on, part, x, n_tiles);
         } else {
-            if (kept) launch_any_one<false, false, 3>(flat, walk, grid, block, on, part, x, (uint32_t)tiles);
-            else launch_any_one<false, true, 1>(flat, walk, grid, block, on, part, x, (uint32_t)tiles);
+            if (kept) launch_any_one<false, false, 3, false>(flat, walk, grid, block, on, part, x, n_tiles);
+            else if (once) launch_any_one<false, true, 1, true>(flat, walk, grid, block, on, part, x, n_tiles);
+            else launch_any_one<false, true, 1, false>(flat, walk, grid, block, on, part, x, n_tiles);
         }
     }
 }

@@ -75,6 +75,17 @@ def test_odd_rows_of_layers_that_pass_the_cache_by(bs, row, tuning, x_off, pool_
     hop_at(w, x_off, pool_off, **tuning)
 
 
+# layers that the on-die cache holds in part: both tiles begin on the source's lines, the gather's have 64 lanes, the scatter's
+# 256 or 128; beyond that they pass the cache by.  161 windows are the first that are tiled; spans of one line and two tiles
+@pytest.mark.parametrize("bs,row,mb,tuning", [(64, 333, 78, {}), (16, 333, 78, {}), (64, 132, 78, dict(max_groups=999)), (1, 2547, 78, {}),
+                                              (8, 1009, 78, dict(block_threads=512)), (64, 1026, 642, {})])
+@pytest.mark.parametrize("x_off,pool_off", [(0, 0), (13, 19)])
+def test_odd_rows_of_layers_that_are_read_once(bs, row, mb, tuning, x_off, pool_off):
+    w = _uniform(3, (mb << 20) // row // 3, bs, row)
+    assert oracle.payload_bytes(w.hit, w.layout.row_bytes) > (mb - 2) << 20
+    hop_at(w, x_off, pool_off, **tuning)
+
+
 # rows of 1, 15, 16, 31, 32, 63, 64, 65 and 72 vectors (how many rows a wavefront's 64 vectors can touch changes at
 # 16, 32 and 64), one to a few to a block, with and without chance neighbours merged into longer descriptors
 @pytest.mark.parametrize("row", [16, 240, 256, 496, 512, 1008, 1024, 1040, 1152])
