@@ -86,16 +86,14 @@ inline uint32_t launch_groups(uint64_t work, uint32_t threads, uint32_t cap, boo
 }
 
 // Rows that are no multiple of a 128-byte line: up to this payload the scatter reads the transfer buffer with plain
-// loads (the on-die cache still has it, beside two other layers' in turn), beyond it with non-temporal ones, up to 432 MB
-// by the row map, which reads each line once.  Hops, plain / non-temporal: 656-byte rows by 64, 80 MB 49 / 51, 99 MB 69 / 62,
-// 1 GB 771 / 748; 1040 by 64, 104 MB, 71 / 64; 576-byte rows, 1 GB, 745 / 702.  (With one or two layers in turn the plain loads would do to 112 MB,
-// 2 % ahead there: 99 MB 60.4 / 61.8.)
+// loads (the on-die cache still has it), beyond it with non-temporal ones (64-token blocks of 656-byte rows, hop:
+// 100 MB 63 us against 73; 140 MB 107 against 104; 1 GB 771 against 748; 576-byte rows, 1 GB, 745 against 702).
 // From some GB up the plain loads, with a gather that stores past the cache, are ahead again.  Hops, us, gather sc1 and
 // scatter nt / sc1 and plain / sc1+nt and plain, in turn (runs of one form within 0.1-0.7 %): 656-byte rows 2.5 GB 1668 /
 // 1697 / 1674, 5 GB 3377 / 3386 / 3363, 12 GB 8151 / 8125 / 8081; 1040-byte rows 6 GB 3715 / 3719 / 3696, 12 GB 7706 /
 // 7696 / 7662; 2064-byte rows 12 GB 7914 / 7921 / 7875.  (Again and again by itself the gather would lose 5 % so: its
 // reference stream 6.13 TB/s in turn with the scatter's, 5.83 alone.)
-constexpr uint64_t kPlainReadBackBytes = 80u << 20, kPassByBytes = 4ull << 30;
+constexpr uint64_t kPlainReadBackBytes = 112u << 20, kPassByBytes = 4ull << 30;
 
 // Tiles of a launch by descriptors: the default workgroup, halved where that leaves clearly fewer lanes without
 // work (32-token blocks of 656-byte rows are 5.1 tiles of 256 lanes: 5.1 TB/s; 10.3 tiles of 128 lanes: 5.8).
