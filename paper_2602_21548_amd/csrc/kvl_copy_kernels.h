@@ -181,12 +181,11 @@ __global__ void __launch_bounds__(1024) kvl_unpack_kernel(const CopyArgs a) {
 // operations: the hardware keeps the memory system busy by the sheer number of
 // resident wavefronts rather than by unrolling.
 template <bool PACK, int VPT, bool NTL, int SP>
-__device__ __forceinline__ void tile_body(const CopyArgs &a, uint32_t tiles_per_unit, uint32_t align_dst,
+__device__ __forceinline__ void tile_body(const CopyArgs &a, uint32_t p, uint32_t tiles_per_unit, uint32_t align_dst,
                                           uint32_t tile_index) {
     const uint32_t u_idx = tile_index / tiles_per_unit;
     const uint32_t tile = tile_index - u_idx * tiles_per_unit;
     const kvl_unit_t u = a.units[a.unit_begin + u_idx];
-    const uint32_t p = a.plane_begin + blockIdx.y;
     const uint32_t row = a.row_elems[p];
     const uint32_t n = u.n_rows * row;
     const uintptr_t pool = a.pool[p] + (uint64_t)u.pool_row * row * 16u;
@@ -217,13 +216,13 @@ __device__ __forceinline__ void tile_body(const CopyArgs &a, uint32_t tiles_per_
 template <int VPT, bool NTL, int SP>
 __global__ void __launch_bounds__(1024) kvl_pack_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit,
                                                              uint32_t align_dst) {
-    tile_body<true, VPT, NTL, SP>(a, tiles_per_unit, align_dst, blockIdx.x);
+    tile_body<true, VPT, NTL, SP>(a, a.plane_begin + blockIdx.y, tiles_per_unit, align_dst, blockIdx.x);
 }
 
 template <int VPT, bool NTL, int SP>
 __global__ void __launch_bounds__(1024) kvl_unpack_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit,
                                                                uint32_t align_dst) {
-    tile_body<false, VPT, NTL, SP>(a, tiles_per_unit, align_dst, blockIdx.x);
+    tile_body<false, VPT, NTL, SP>(a, a.plane_begin + blockIdx.y, tiles_per_unit, align_dst, blockIdx.x);
 }
 
 // Thin form of the tiled kernels: a fixed, small number of workgroups, each walking over
@@ -235,7 +234,7 @@ template <bool PACK, int VPT, bool NTL, int SP>
 __global__ void __launch_bounds__(1024) kvl_tile_walk_kernel(const CopyArgs a, uint32_t tiles_per_unit,
                                                              uint32_t align_dst, uint32_t n_tiles) {
     for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x)
-        tile_body<PACK, VPT, NTL, SP>(a, tiles_per_unit, align_dst, t);
+        tile_body<PACK, VPT, NTL, SP>(a, a.plane_begin + blockIdx.y, tiles_per_unit, align_dst, t);
 }
 
 // Pipelined form of the tiled kernels: a fixed grid that fills the machine once (every
@@ -386,13 +385,12 @@ __global__ void __launch_bounds__(1024) kvl_flat_kernel(const CopyArgs a, uint32
 typedef const uint32_t __attribute__((address_space(4))) *cmap_t;
 
 template <bool PACK, bool NTL, int SP, int K>
-__global__ void __launch_bounds__(1024) kvl_rows_kernel(const CopyArgs a, const uint32_t *row_map, uint32_t row_begin,
-                                                        uint32_t n_vecs) {
-    const uint32_t p = a.plane_begin + blockIdx.y;
+__device__ __forceinline__ void rows_body(const CopyArgs &a, uint32_t p, const uint32_t *row_map, uint32_t row_begin,
+                                          uint32_t n_vecs, uint32_t group) {
     const uint32_t row = a.row_elems[p];
     const uintptr_t xfer = a.xfer[p] + (uint64_t)row_begin * row * 16u;
     const uint32_t lead = (uint32_t)(xfer >> 4) & 7u;
-    const uint32_t pos = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t pos = group * blockDim.x + threadIdx.x;
     const uint32_t g = pos - lead;
     if (pos < lead || g >= n_vecs) return;
     cmap_t map = (cmap_t)(uintptr_t)(row_map + row_begin);
@@ -422,6 +420,45 @@ __global__ void __launch_bounds__(1024) kvl_rows_kernel(const CopyArgs a, const 
     gsrc_t src = (gsrc_t)(PACK ? pool : xfer + (uint64_t)g * 16u);
     gdst_t dst = (gdst_t)(PACK ? xfer + (uint64_t)g * 16u : pool);
     store16<SP>(dst, load16<NTL>(src));
+}
+
+template <bool PACK, bool NTL, int SP, int K>
+__global__ void __launch_bounds__(1024) kvl_rows_kernel(const CopyArgs a, const uint32_t *row_map, uint32_t row_begin,
+                                                        uint32_t n_vecs) {
+    rows_body<PACK, NTL, SP, K>(a, a.plane_begin + blockIdx.y, row_map, row_begin, n_vecs, blockIdx.x);
+}
+
+// Planes of unlike rows in one launch, the workgroups of one plane after those of the other, each plane with its own number:
+// a launch of its own costs a narrow plane more than its bytes do, on the host and between the kernels.  By tiles or by the
+// row map, with the cache policies of the kernels above.  Planes of 1024 and 128 bytes by 64, us, apart / at once: hop 3 MB
+// 23.3 / 17.6, 105 MB 66.3 / 62.5, 330 MB 200 / 194; move 3 MB 11.5 / 9.0; 512, 16 and 128 bytes, hop 28 MB 30.1 / 21.2.
+struct PlanesArgs {
+    uint32_t group_end[KVL_MAX_PLANES];        // workgroups up to and with this plane
+    uint32_t per_unit[KVL_MAX_PLANES];         // tiles of a descriptor
+    uint32_t align_dst[KVL_MAX_PLANES];        // the destination's spans may begin off a line
+    uint32_t plain[KVL_MAX_PLANES];            // scatter by tiles: plain loads
+    uint32_t row_begin, n_rows;                // transfer rows of the launch's descriptors
+};
+
+// SP: the stores of a gather or a move (a scatter's are sc1+nt, by the row map off lines nt)
+template <bool PACK, int SP, bool ROWS>
+__global__ void __launch_bounds__(1024) kvl_planes_kernel(const CopyArgs a, const PlanesArgs pl, const uint32_t *row_map) {
+    uint32_t p = a.plane_begin;
+#pragma unroll
+    for (uint32_t q = 0; q + 1 < KVL_MAX_PLANES; ++q) p += blockIdx.x >= pl.group_end[q] ? 1u : 0u;
+    const uint32_t group = blockIdx.x - (p > a.plane_begin ? pl.group_end[p - 1] : 0u);
+    const uint32_t row = a.row_elems[p];
+    const uint32_t n_vecs = pl.n_rows * row;
+    if (!ROWS) {
+        if (!PACK && pl.plain[p]) tile_body<PACK, 1, false, 3>(a, p, pl.per_unit[p], pl.align_dst[p], group);
+        else tile_body<PACK, 1, true, PACK ? SP : 3>(a, p, pl.per_unit[p], pl.align_dst[p], group);
+    } else if (PACK || row % 8 == 0) {
+        if (row >= 64) rows_body<PACK, true, PACK ? SP : 3, 2>(a, p, row_map, pl.row_begin, n_vecs, group);
+        else rows_body<PACK, true, PACK ? SP : 3, 0>(a, p, row_map, pl.row_begin, n_vecs, group);
+    } else {
+        if (row >= 64) rows_body<PACK, true, 1, 2>(a, p, row_map, pl.row_begin, n_vecs, group);
+        else rows_body<PACK, true, 1, 0>(a, p, row_map, pl.row_begin, n_vecs, group);
+    }
 }
 
 // Rows or addresses that are not multiples of 16 bytes.  The vector unit takes 16-byte accesses at any

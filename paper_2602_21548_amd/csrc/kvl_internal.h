@@ -71,6 +71,11 @@ constexpr uint32_t kAnyFlatWindows = 160, kAnyFlatLinesWindows = 256, kAnyFlatPa
 // layers' in turn (256 MB hold three of 85 MB), and up to which it pays to read each line out of it once.
 // (Dealt out flat, 26 by 16, 73 MB, passing by / kept 81 / 85.)
 constexpr uint64_t kCachedFlatBytes = 64u << 20, kCachedLayerBytes = 76u << 20, kReadOnceBytes = 640u << 20;
+// Up to this payload planes of unlike rows share a launch (kvl_planes_kernel): beyond it a launch of their own is less than a
+// hundredth of their time, and each plane better off in the form that suits it (hops apart / at once, 2048- and 656-byte
+// rows by 16, 285 MB 176 / 177, 631 MB 412 / 412; 1024 and 128 by 24, 873 MB, 557 / 565; moves 512 and 528 by 128, 289 MB
+// 91.0 / 89.9, 591 MB 181 / 183).
+constexpr uint64_t kPlanesAtOnceBytes = 384u << 20;
 constexpr uint32_t kNumVariants = 512;       // explicit variants are 1 .. kNumVariants
 bool valid_block_threads(uint32_t t);
 

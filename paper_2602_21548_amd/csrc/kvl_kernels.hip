@@ -261,17 +261,88 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
     }
 }
 
+// Planes of unlike rows in one launch: 16-byte vectors on this device, in layers of up to kPlanesAtOnceBytes.  All planes by
+// the row map where one of them would take it (made, and not awaited by a stream under capture), else all by tiles, of
+// whose lanes no plane may idle half.  False: they go apart.
+static bool launch_planes(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uint32_t plane_end, const On &on) {
+    const uint32_t begin = a.plane_begin;
+    if (plan->tuning.variant || plan->tuning.max_groups || plan->threads_chosen || plan->payload_bytes > kPlanesAtOnceBytes)
+        return false;
+    const double average = (double)plan->hit_tokens / (double)plan->units.size();
+    bool lines = true, by_rows = false;
+    uint32_t widest = 0, threads = 0;
+    for (uint32_t p = begin; p < plane_end; ++p) {
+        lines = lines && plan->layout.row_bytes[p] % 128 == 0;
+        by_rows = by_rows || takes_row_map(plan, plan->layout.row_bytes[p], pack);
+        widest = std::max(widest, a.row_elems[p]);
+    }
+    if (by_rows) {
+        if (!plan->d_row_map || !row_map_ready(plan, on.stream)) return false;
+        threads = kDefaultBlockThreads;
+    } else {
+        threads = plan->paired ? (lines ? move_threads(plan, 128) : kDefaultBlockThreads)
+                               : tile_threads((uint64_t)plan->max_unit_rows * widest);
+    }
+    const kvl_unit_t &first = plan->units[a.unit_begin], &last = plan->units[a.unit_begin + a.n_units - 1];
+    PlanesArgs pl{};
+    pl.row_begin = first.xfer_row;
+    pl.n_rows = by_rows ? last.xfer_row + last.n_rows - first.xfer_row : 0;
+    uint64_t groups = 0;
+    for (uint32_t p = 0; p < KVL_MAX_PLANES; ++p) {
+        pl.group_end[p] = UINT32_MAX;
+        if (p < begin || p >= plane_end) continue;
+        const uint64_t row = a.row_elems[p];
+        const bool dst_lines = plan->layout.row_bytes[p] % 128 == 0 && (pack ? a.xfer[p] : a.pool[p]) % 128 == 0;
+        pl.align_dst[p] = dst_lines ? 0u : 1u;
+        const uint64_t tiles = (plan->max_unit_rows * row + (dst_lines ? 0 : 7) + threads - 1) / threads;
+        if (!by_rows && average * (double)row < 0.5 * (double)(tiles * threads)) return false;
+        pl.per_unit[p] = (uint32_t)tiles;
+        pl.plain[p] = plan->layout.row_bytes[p] % 128 != 0 && plan->payload_bytes <= kPlainReadBackBytes ? 1u : 0u;
+        groups += by_rows ? (pl.n_rows * row + 7 + threads - 1) / threads : a.n_units * tiles;
+        if (groups > kMaxLanesPerLaunch / threads || groups > (uint64_t)INT32_MAX) return false;
+        pl.group_end[p] = (uint32_t)groups;
+    }
+    const dim3 grid((uint32_t)groups), block(threads);
+    const uint32_t *map = plan->d_row_map;
+    if (plan->paired) KVL_LAUNCH((kvl_planes_kernel<true, 3, false>), grid, block, on, a, pl, map);
+    else if (pack && by_rows) KVL_LAUNCH((kvl_planes_kernel<true, 2, true>), grid, block, on, a, pl, map);
+    else if (pack) KVL_LAUNCH((kvl_planes_kernel<true, 2, false>), grid, block, on, a, pl, map);
+    else if (by_rows) KVL_LAUNCH((kvl_planes_kernel<false, 3, true>), grid, block, on, a, pl, map);
+    else KVL_LAUNCH((kvl_planes_kernel<false, 3, false>), grid, block, on, a, pl, map);
+    return true;
+}
+
 int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_t unit_end,
                  uint32_t plane_begin, uint32_t plane_end,
                  void *const *pool_planes, const uintptr_t *xfer_plane, hipStream_t stream, bool far_host) {
     if (unit_end <= unit_begin || plane_end <= plane_begin) return KVL_OK;
     if (!plan->d_units || unit_end > plan->units.size() || plane_end > plan->layout.n_planes)
         return KVL_EINVAL;
-    // Planes of different row sizes go in launches of their own: one launch gives every plane the
-    // tile count of the widest, and a narrow plane's workgroups would mostly find nothing to do
-    // (K/V-style planes of 1024 and 128 bytes in one launch: 2.8 TB/s; apart: 6 TB/s and more).
-    for (uint32_t p = plane_begin + 1; p < plane_end; ++p) {
-        if (plan->layout.row_bytes[p] == plan->layout.row_bytes[plane_begin]) continue;
+    int rc_dev = check_device(plan);
+    if (rc_dev != KVL_OK) return rc_dev;
+    CopyArgs a{};
+    a.units = plan->d_units;
+    a.unit_begin = unit_begin;
+    a.n_units = unit_end - unit_begin;
+    a.plane_begin = plane_begin;
+    bool vec = plan->vec16, unlike = false;
+    for (uint32_t p = plane_begin; p < plane_end; ++p) {
+        if (!pool_planes[p]) return KVL_EINVAL;
+        a.pool[p] = reinterpret_cast<uintptr_t>(pool_planes[p]);
+        a.xfer[p] = xfer_plane[p];
+        vec = vec && (a.pool[p] % 16 == 0) && (a.xfer[p] % 16 == 0);
+        unlike = unlike || plan->layout.row_bytes[p] != plan->layout.row_bytes[plane_begin];
+    }
+    for (uint32_t p = plane_begin; p < plane_end; ++p)
+        a.row_elems[p] = vec ? plan->layout.row_bytes[p] / 16 : plan->layout.row_bytes[p];
+    // Planes of different row sizes share a launch in which each has its own number of workgroups, or go in launches of
+    // their own: with the tile count of the widest for every plane a narrow plane's workgroups would mostly find nothing
+    // to do (K/V-style planes of 1024 and 128 bytes that way: 2.8 TB/s; apart: 6 TB/s and more).
+    if (unlike) {
+        if (vec && !far_host) {
+            On on(plan, stream);
+            if (launch_planes(plan, pack, a, plane_end, on)) return on.made();
+        }
         for (uint32_t q = plane_begin; q < plane_end;) {
             uint32_t e = q + 1;
             while (e < plane_end && plan->layout.row_bytes[e] == plan->layout.row_bytes[q]) ++e;
@@ -281,22 +352,6 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         }
         return KVL_OK;
     }
-    int rc_dev = check_device(plan);
-    if (rc_dev != KVL_OK) return rc_dev;
-    CopyArgs a{};
-    a.units = plan->d_units;
-    a.unit_begin = unit_begin;
-    a.n_units = unit_end - unit_begin;
-    a.plane_begin = plane_begin;
-    bool vec = plan->vec16;
-    for (uint32_t p = plane_begin; p < plane_end; ++p) {
-        if (!pool_planes[p]) return KVL_EINVAL;
-        a.pool[p] = reinterpret_cast<uintptr_t>(pool_planes[p]);
-        a.xfer[p] = xfer_plane[p];
-        vec = vec && (a.pool[p] % 16 == 0) && (a.xfer[p] % 16 == 0);
-    }
-    for (uint32_t p = plane_begin; p < plane_end; ++p)
-        a.row_elems[p] = vec ? plan->layout.row_bytes[p] / 16 : plan->layout.row_bytes[p];
 
     uint32_t threads = plan->tuning.block_threads;
     // default: tiled, one vector per lane; cache policies as measured (see the top of kvl_copy_kernels.h)

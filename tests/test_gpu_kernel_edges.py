@@ -96,6 +96,26 @@ def test_small_descriptors_by_the_row_map(row, bs, kind, x_off):
     hop_at(W.tiny(970 + row + bs, 5, bs, (row,), 300, 50 * bs, kind=kind), x_off, block_threads=64)
 
 
+# planes of unlike rows in one launch, by tiles (rows of whole lines, and not; the plain loads of odd lines) or by the row map
+# (rows below and from 64 vectors), with a plane repeated; tiles of one wavefront in moves; a range of transfer rows
+@pytest.mark.parametrize("bs,rows", [(64, (1024, 128)), (64, (512, 16, 128)), (16, (2048, 656)), (64, (656, 1040)), (1, (1152, 128)),
+                                     (3, (16, 1040, 64, 1024)), (128, (128, 2048, 128)), (2, (1008, 1024))])
+@pytest.mark.parametrize("x_off", [0, 48])
+def test_planes_of_unlike_rows_at_once(bs, rows, x_off):
+    for kind in ("runs", "random"):
+        w = W.tiny(1160 + bs + sum(rows), 6, bs, rows, 150, 20 * bs, kind=kind)
+        hop_at(w, x_off)
+        src = W.fill_pool(w, 0, "src")
+        want = W.sentinel_pool(w, "dst")
+        oracle.unpack(bs, rows, w.hit, w.dst.tables, oracle.pack(bs, rows, w.hit, w.src.tables, src), want)
+        pair = K.kvl_plan_pair(dev_plan(w, "src", K.KVL_GATHER), dev_plan(w, "dst", K.KVL_SCATTER))
+        d_src, d_dst = planes_to_dev(src), planes_to_dev(W.sentinel_pool(w, "dst"))
+        K.kvl_move_layer(pair, d_src, d_dst)
+        torch.cuda.synchronize()
+        for a, b in zip(d_dst, want):
+            assert same_bytes(to_host(a), b)
+
+
 @pytest.mark.parametrize("bs,row,mb", [(64, 656, 118), (64, 1152, 280), (100, 656, 118), (64, 256, 280)])
 def test_layers_about_the_size_of_the_on_die_cache(bs, row, mb):
     """Whole blocks whose scatter takes the row map for the size of the layer (256-byte rows: the tiles)."""
