@@ -565,10 +565,13 @@ struct FullBlockArgs {
 // the pool nt loads and sc1 stores, which leave the layer there for whoever reads it next; out of it nt loads and
 // sc1+nt stores).  Both directions in turn, 64-token blocks of 61 layers, us a layer, against plain loads with sc1+nt
 // stores one way and nt loads with plain stores the other: 1152-byte rows, 101 MB a layer, 89 -> 63; 221 MB 185 -> 142;
-// 1.8 GB 1388 -> 1305; 656-byte rows, 58 MB, 59 -> 46.  Across the host link the old ones stay for whole vectors (the link
+// 1.8 GB 1388 -> 1305; 656-byte rows, 58 MB, 59 -> 46.  SRC (one vector per lane): tiles begin on 128-byte lines of the
+// source, which a non-temporal load then takes out of the cache once (kvl_any_tile_kernel): blocks that begin off a line,
+// both directions, 336-byte rows by 100, 43 MB, 35.6 -> 31.2; at byte addresses, where they began on lines of the
+// destination, with nt stores out of the pool (763 by 64, 52 MB, 40.2 -> 35.7).  Across the host link the old ones stay for whole vectors (the link
 // is the bound); at byte addresses the new ones are ahead there too (out of the pool, new / old: 741-byte rows by 64, 40 MB,
 // 706 / 727; 57 by 16, 20 MB, 382 / 426; 132 by 1, 8 MB, 255 / 425; into it level).
-template <bool TO_POOL, bool VEC, int VPT, bool NTL, int SP>
+template <bool TO_POOL, bool VEC, int VPT, bool NTL, int SP, bool SRC>
 __device__ __forceinline__ void fullblock_tile(const FullBlockArgs &a, uint32_t tiles_per_unit, uint32_t tile_index) {
     const uint32_t u_idx = tile_index / tiles_per_unit;
     uint32_t tile = tile_index - u_idx * tiles_per_unit;
@@ -585,9 +588,14 @@ __device__ __forceinline__ void fullblock_tile(const FullBlockArgs &a, uint32_t 
     const uint64_t in_pool = (uint64_t)pool_row * row;
     const uint64_t in_blocks = (uint64_t)u->block_index * a.fb_elems + a.layer_plane_off[p] + (uint64_t)within * row;
     if (VEC) {
-        if (first >= n) return;
         gsrc_t src = TO_POOL ? (gsrc_t)a.blocks + in_blocks : (gsrc_t)a.pool[p] + in_pool;
         gdst_t dst = TO_POOL ? (gdst_t)a.pool[p] + in_pool : (gdst_t)a.blocks + in_blocks;
+        if (SRC) {
+            const uint32_t lead = (uint32_t)((uintptr_t)src >> 4) & 7u;
+            if (first >= lead && first - lead < n) store16<SP>(dst + (first - lead), load16<NTL>(src + (first - lead)));
+            return;
+        }
+        if (first >= n) return;
         v4u v[VPT];
 #pragma unroll
         for (int k = 0; k < VPT; ++k) {
@@ -601,17 +609,17 @@ __device__ __forceinline__ void fullblock_tile(const FullBlockArgs &a, uint32_t 
         }
     } else {
         const uintptr_t pool = a.pool[p] + in_pool, blocks = a.blocks + in_blocks;
-        const uintptr_t dst = TO_POOL ? pool : blocks;
-        copy_any<NTL, SP>(TO_POOL ? blocks : pool, dst, n, (uint32_t)dst & 127u, first);
+        const uintptr_t src = TO_POOL ? blocks : pool, dst = TO_POOL ? pool : blocks;
+        copy_any<NTL, SP>(src, dst, n, (uint32_t)(SRC ? src : dst) & 127u, first);
     }
 }
 
 // gridDim.x workgroups walk over the n_tiles tiles (one tile each when there are as many).
-template <bool TO_POOL, bool VEC, int VPT, bool NTL, int SP>
+template <bool TO_POOL, bool VEC, int VPT, bool NTL, int SP, bool SRC>
 __global__ void __launch_bounds__(256) kvl_fullblock_kernel(const FullBlockArgs a, uint32_t tiles_per_unit,
                                                             uint32_t n_tiles) {
     for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x)
-        fullblock_tile<TO_POOL, VEC, VPT, NTL, SP>(a, tiles_per_unit, t);
+        fullblock_tile<TO_POOL, VEC, VPT, NTL, SP, SRC>(a, tiles_per_unit, t);
 }
 
 // Reference streams for measuring what the memory can do (kvl_ceiling_kernel): the tiled form

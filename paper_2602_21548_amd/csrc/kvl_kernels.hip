@@ -496,19 +496,48 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
         a.layer_plane_off[p] = (layer_off + plane_off) / e;
         plane_off += bs * plan->layout.row_bytes[p];
     }
-    const uint32_t threads = 256;
     // across the host link: two vectors per lane on few workgroups (as the copy kernels do, see launch_units)
     const uint32_t vpt = far_host && vec ? 2 : 1;
-    const uint64_t per_tile = (uint64_t)threads * vpt * (vec ? 1 : 16);
-    // (a span off the 16-byte grid is laid out from the 128-byte line below its start)
-    uint64_t tpu = 0, widest = 0;
+    // vectors of a descriptor's plane, with those before it on its first line (none where every descriptor begins on a line:
+    // whole blocks of whole lines, or rows of whole lines)
+    const bool whole = !(plan->flags & KVL_TOKENS_APPEND) && plan->units.size() == plan->blocks_touched;
+    bool lines = base % 128 == 0 && block_pitch % 128 == 0 && layer_off % 128 == 0;
+    for (uint32_t p = 0; p < P; ++p) {
+        const uint64_t row = plan->layout.row_bytes[p];
+        lines = lines && reinterpret_cast<uintptr_t>(pool_planes[p]) % 128 == 0 && (row % 128 == 0 || (whole && bs * row % 128 == 0));
+    }
+    uint64_t vectors[KVL_MAX_PLANES] = {}, most = 0;
+    for (uint32_t p = 0; p < P; ++p) {
+        const uint64_t bytes = (uint64_t)plan->max_unit_rows * plan->layout.row_bytes[p];
+        vectors[p] = (bytes + (lines || vpt == 2 ? 0 : vec ? 112 : 127) + 15) / 16;
+        most = std::max(most, (bytes + (vec ? 0 : 127) + 4096 * vpt - 1) / (4096 * vpt));
+    }
+    // Lanes of a tile: 256, or fewer where that leaves clearly fewer without work.  Both directions, us, 256 / 128 / 64 lanes
+    // (share of the lanes busy): 336-byte rows by 16, 31 MB, 27.9 / 24.1 / 24.3 (.67 .89 .89); 496 by 1, 9 MB, 30.9 / 20.9 /
+    // 16.9 (.14 .28 .56); 48 by 100, 31 MB, 32.8 / 28.1 / 26.9 (.60 .80 .96); 2064 by 1, 45.4 / 48.4 / 42.6 (.53 .53 .71);
+    // 333 by 100, 59 MB, 49.0 / 50.4 / 52.7 (.91 .96 .99); 132 by 32, 28 MB, 30.5 / 23.5 / 22.4 (.53 .71 .85); 132 and 64 by
+    // 64, 28 MB, 23.4 / 24.5 / 22.2 (.63 .78 .89).
+    uint32_t threads = 256;
+    if (!far_host) {
+        auto busy = [&](uint64_t t) {
+            uint64_t work = 0, lanes = 0;
+            for (uint32_t p = 0; p < P; ++p) {
+                work += vectors[p];
+                lanes += (vectors[p] + t - 1) / t * t;
+            }
+            return (double)work / (double)lanes;
+        };
+        if (busy(128) > busy(threads) + 0.07) threads = 128;
+        if (busy(64) > busy(threads) + 0.09) threads = 64;
+    }
+    uint64_t tpu = 0;
     for (uint32_t p = 0; p < KVL_MAX_PLANES; ++p) {
-        const uint64_t tiles = p < P ? ((uint64_t)plan->max_unit_rows * a.row_elems[p] + (vec ? 0 : 127) + per_tile - 1) / per_tile : 0;
-        widest = std::max(widest, tiles);
+        const uint64_t tiles = (vectors[p] + (uint64_t)threads * vpt - 1) / ((uint64_t)threads * vpt);
         tpu += tiles;
         a.tile_end[p] = (uint32_t)std::min<uint64_t>(tpu, UINT32_MAX);
     }
-    if (a.n_units * widest > (uint64_t)INT32_MAX || tpu > (uint64_t)INT32_MAX) return KVL_ERANGE;
+    // (the limit is that of tiles of 256 lanes, whatever their lanes are)
+    if (a.n_units * most > (uint64_t)INT32_MAX || tpu > (uint64_t)INT32_MAX) return KVL_ERANGE;
     // (a cap that was asked for is meant for each plane, see kvl_tuning_t)
     const uint32_t cap = plan->tuning.max_groups ? (uint32_t)std::min<uint64_t>((uint64_t)plan->tuning.max_groups * P, UINT32_MAX)
                                                  : (far_host ? (vec ? kHostSideGroups : 2 * kHostSideGroups) : 0u);
@@ -523,13 +552,15 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
 #define KVL_FB_LAUNCH(...) \
         KVL_LAUNCH((kvl_fullblock_kernel<__VA_ARGS__>), grid, block, on, a, (uint32_t)tpu, n_tiles)
         if (to_pool) {
-            if (!vec) KVL_FB_LAUNCH(true, false, 1, true, 2);
-            else if (far_host) KVL_FB_LAUNCH(true, true, 2, false, 3);
-            else KVL_FB_LAUNCH(true, true, 1, true, 2);
+            if (!vec && far_host) KVL_FB_LAUNCH(true, false, 1, true, 2, false);
+            else if (!vec) KVL_FB_LAUNCH(true, false, 1, true, 2, true);
+            else if (far_host) KVL_FB_LAUNCH(true, true, 2, false, 3, false);
+            else KVL_FB_LAUNCH(true, true, 1, true, 2, true);
         } else {
-            if (!vec) KVL_FB_LAUNCH(false, false, 1, true, 3);
-            else if (far_host) KVL_FB_LAUNCH(false, true, 2, true, 0);
-            else KVL_FB_LAUNCH(false, true, 1, true, 3);
+            if (!vec && far_host) KVL_FB_LAUNCH(false, false, 1, true, 3, false);
+            else if (!vec) KVL_FB_LAUNCH(false, false, 1, true, 1, true);
+            else if (far_host) KVL_FB_LAUNCH(false, true, 2, true, 0, false);
+            else KVL_FB_LAUNCH(false, true, 1, true, 3, true);
         }
         a.units += a.n_units;
     }

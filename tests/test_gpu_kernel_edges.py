@@ -188,6 +188,34 @@ def test_full_blocks_planes_and_tiles(bs, rows, off, where):
         assert same_bytes(to_host(a), b), "load differs from the oracle"
 
 
+# tiles of 256, 128 and 64 lanes that begin on lines of the source: spans of whole vectors that begin on a line and off it (the
+# last tile holds what the first leaves free: 249, 250 and 256 vectors), and at byte addresses, one wavefront and a byte beyond
+@pytest.mark.parametrize("bs,rows", [(16, (336,)), (1, (496,)), (100, (48,)), (3, (1328,)), (1, (3984,)), (1, (4000,)), (1, (4096, 128)), (100, (336,)),
+                                     (1, (897,)), (1, (898,)), (1, (1921,)), (100, (46,)), (16, (35,)), (24, (763, 5))])
+@pytest.mark.parametrize("first", ["hit", "append"])
+def test_full_blocks_on_lines_of_the_source(bs, rows, first):
+    L, layer = 3, 1
+    w = W.tiny(1200 + bs + sum(rows), 7, bs, rows, 160, 9 * bs, kind="random", n_layers=L)
+    flag, lo, n = (0, np.zeros_like(w.hit), w.hit) if first == "hit" else (K.KVL_TOKENS_APPEND, w.hit, w.app)
+    g, s = dev_plan(w, "src", K.KVL_GATHER | K.KVL_NO_MERGE | flag), dev_plan(w, "dst", K.KVL_SCATTER | K.KVL_NO_MERGE | flag)
+    fb, count = g.fullblock_geometry()
+    src = W.fill_pool(w, layer, "src")
+    want = np.full(fb * count, 0x5A, dtype=np.uint8)
+    oracle.pool_to_fullblocks(bs, L, rows, lo, n, w.src.tables, layer, src, want)
+    want_pool = W.sentinel_pool(w, "dst")
+    oracle.fullblocks_to_pool(bs, L, rows, lo, n, w.dst.tables, layer, want, want_pool)
+    buf = torch.full((fb * count + GUARD,), 0x5A, dtype=torch.uint8, device="cuda")
+    d_src, d_dst = planes_to_dev(src), planes_to_dev(W.sentinel_pool(w, "dst"))
+    K.kvl_pool_to_fullblocks_layer(g, d_src, layer, buf[:fb * count])
+    K.kvl_fullblocks_to_pool_layer(s, buf[:fb * count], layer, d_dst)
+    torch.cuda.synchronize()
+    got = to_host(buf)
+    assert same_bytes(got[:fb * count], want), "persist differs from the oracle"
+    assert np.all(got[fb * count:] == 0x5A)
+    for a, b in zip(d_dst, want_pool):
+        assert same_bytes(to_host(a), b), "load differs from the oracle"
+
+
 # a move's own workgroups: 64 lanes, 128, and 1024 flat; descriptors around one wavefront and one workgroup
 @pytest.mark.parametrize("bs,rows", [(1, (16,)), (1, (1152,)), (1, (656, 128)), (2, (1024,)), (1, (2048,)), (1, (2064,)), (16, (1152, 656)),
                                      (64, (656,)), (3, (37,)), (64, (132, 132))])
