@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libkvl.so: argument marshalling only.
+"""Thin binding of libkvl.so: argument marshalling only, by ctypes and, for the calls made once a layer, by a module of
+their own (_native, csrc/kvl_python.cpp) that takes the calls in which nothing is out of the ordinary.
 
 Every step of the load path runs inside the library's HIP kernels and host
 code; this module turns Python objects (NumPy block tables, torch tensors used
@@ -171,6 +172,20 @@ _lib = _load()
 LIB_PATH = _build.LIB
 
 
+def _load_native():
+    """The module with the per-layer calls, or None where it cannot be built (no compiler, no Python headers)."""
+    try:
+        if not os.path.exists(_build.NATIVE):
+            _build.build_native()
+        from . import _native
+    except (ImportError, OSError, RuntimeError):
+        return None
+    return _native
+
+
+_native = _load_native()
+
+
 def _check(rc: int, what: str) -> None:
     if rc != KVL_OK:
         raise KvlError(rc, what)
@@ -180,6 +195,24 @@ def _check(rc: int, what: str) -> None:
 # (2.8 us of a 13 us call; 0.2 us this way), where this torch has the two accessors.
 _current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+if _native is not None and _current_raw_stream is not None and _current_device is not None:
+    _native.setup(torch.Tensor, np.ndarray, _current_raw_stream, _current_device, torch.cuda.is_initialized,
+                  *(C.cast(getattr(_lib, f), C.c_void_p).value
+                    for f in ("kvl_pack_layer", "kvl_unpack_layer", "kvl_move_layer", "kvl_fullblocks_to_pool_layer",
+                              "kvl_pool_to_fullblocks_layer")))
+    os.register_at_fork(after_in_child=_native.forked)
+    # (these return what the library returned, or 1 for a call that is the general path's)
+    _fast_pack, _fast_unpack, _fast_move = _native.pack_layer, _native.unpack_layer, _native.move_layer
+    _fast_to_pool, _fast_to_blocks = _native.fullblocks_to_pool_layer, _native.pool_to_fullblocks_layer
+else:
+    _native = None
+
+    def _not_taken(*_args):
+        return 1
+
+    _fast_pack = _fast_unpack = _fast_move = _fast_to_pool = _fast_to_blocks = _not_taken
 
 
 def _stream_handle(stream) -> Optional[int]:
@@ -202,7 +235,7 @@ def _dev(t: torch.Tensor, what: str) -> int:
     return t.data_ptr()
 
 
-class Plan:
+class Plan(_native.PlanBase if _native is not None else object):
     """Owner of a kvl_plan_t*."""
 
     def __init__(self, handle: int, layout: kvl_layout_t, flags: int):
@@ -214,9 +247,13 @@ class Plan:
         self._plane_bytes = tuple(int(layout.pool_blocks) * int(layout.block_tokens) * int(layout.row_bytes[p])
                                   for p in range(self.n_planes))
         self._pointers = C.c_void_p * self.n_planes
+        if _native is not None:
+            self._set(handle or 0, self._plane_bytes)
 
     def destroy(self) -> None:
         if self._h:
+            if _native is not None:
+                self._clear()
             _lib.kvl_plan_destroy(self._h)
             self._h = C.c_void_p(None)
 
@@ -318,8 +355,12 @@ def _requests(hit, app, tables: Sequence[np.ndarray]):
     n = int(hit.shape[0])
     if len(tables) != n or app.shape[0] != n:
         raise ValueError("hit, app and tables must have one entry per request")
-    keep = [np.ascontiguousarray(np.asarray(t, dtype=np.int32)) for t in tables]
     reqs = (kvl_request_t * max(1, n))()
+    if _native is not None:
+        keep = list(tables)
+        if _native.requests(hit, app, keep, reqs):
+            return reqs, n, keep
+    keep = [np.ascontiguousarray(np.asarray(t, dtype=np.int32)) for t in tables]
     for r in range(n):
         reqs[r].hit_tokens = int(hit[r])
         reqs[r].append_tokens = int(app[r])
@@ -356,6 +397,9 @@ def _plane_ptrs(plan: Plan, planes: Sequence[torch.Tensor], what: str):
 
 def kvl_pack_layer(plan: Plan, pool_planes: Sequence[torch.Tensor], xfer: torch.Tensor, stream=None) -> None:
     """xfer: a device tensor, or a pinned host tensor (the kernel then writes it over the host link)."""
+    rc = _fast_pack(plan, pool_planes, xfer, stream)
+    if rc <= 0:
+        return _check(rc, "kvl_pack_layer")
     arr = _plane_ptrs(plan, pool_planes, "kvl_pack_layer pool")
     if isinstance(xfer, torch.Tensor) and not xfer.is_cuda:
         ptr = _pinned(xfer, "xfer", 0)
@@ -372,11 +416,16 @@ def kvl_plan_pair(gather: Plan, scatter: Plan) -> Plan:
     p = Plan(out.value, gather.layout, gather.flags)
     p.dst_layout = scatter.layout
     p._dst_plane_bytes = scatter._plane_bytes
+    if _native is not None:
+        p._set_dst(scatter._plane_bytes)
     return p
 
 
 def kvl_move_layer(paired: Plan, src_pool_planes: Sequence[torch.Tensor],
                    dst_pool_planes: Sequence[torch.Tensor], stream=None) -> None:
+    rc = _fast_move(paired, src_pool_planes, dst_pool_planes, stream)
+    if rc <= 0:
+        return _check(rc, "kvl_move_layer")
     src = _plane_ptrs(paired, src_pool_planes, "kvl_move_layer source pool")
     if len(dst_pool_planes) != paired.n_planes:
         raise ValueError("kvl_move_layer: wrong number of destination planes")
@@ -391,6 +440,9 @@ def kvl_move_layer(paired: Plan, src_pool_planes: Sequence[torch.Tensor],
 
 def kvl_unpack_layer(plan: Plan, xfer: torch.Tensor, pool_planes: Sequence[torch.Tensor], stream=None) -> None:
     """xfer: a device tensor, or a pinned host tensor (the kernel then reads it over the host link)."""
+    rc = _fast_unpack(plan, xfer, pool_planes, stream)
+    if rc <= 0:
+        return _check(rc, "kvl_unpack_layer")
     arr = _plane_ptrs(plan, pool_planes, "kvl_unpack_layer pool")
     if isinstance(xfer, torch.Tensor) and not xfer.is_cuda:
         ptr = _pinned(xfer, "xfer", 0)
@@ -464,6 +516,9 @@ def _dev_or_pinned(t: torch.Tensor, what: str) -> int:
 def kvl_fullblocks_to_pool_layer(plan: Plan, full_blocks: torch.Tensor, layer: int,
                                  pool_planes: Sequence[torch.Tensor], stream=None) -> None:
     """full_blocks: a device tensor or a pinned host tensor holding the plan's Full Blocks."""
+    rc = _fast_to_pool(plan, full_blocks, layer, pool_planes, stream)
+    if rc <= 0:
+        return _check(rc, "kvl_fullblocks_to_pool_layer")
     arr = _plane_ptrs(plan, pool_planes, "kvl_fullblocks_to_pool_layer pool")
     _check(_lib.kvl_fullblocks_to_pool_layer(plan.handle, _dev_or_pinned(full_blocks, "full_blocks"),
                                              _nbytes(full_blocks), layer, arr, _stream_handle(stream)),
@@ -505,6 +560,9 @@ def kvl_h2d_fullblocks_layer(plan: Plan, full_blocks: torch.Tensor, layer: int, 
 
 def kvl_pool_to_fullblocks_layer(plan: Plan, pool_planes: Sequence[torch.Tensor], layer: int,
                                  full_blocks: torch.Tensor, stream=None) -> None:
+    rc = _fast_to_blocks(plan, pool_planes, layer, full_blocks, stream)
+    if rc <= 0:
+        return _check(rc, "kvl_pool_to_fullblocks_layer")
     arr = _plane_ptrs(plan, pool_planes, "kvl_pool_to_fullblocks_layer pool")
     _check(_lib.kvl_pool_to_fullblocks_layer(plan.handle, arr, layer, _dev_or_pinned(full_blocks, "full_blocks"),
                                              _nbytes(full_blocks), _stream_handle(stream)),

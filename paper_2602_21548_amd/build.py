@@ -4,11 +4,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libkvl.so")
+NATIVE = os.path.join(_HERE, "_native.so")
 SOURCES = ["kvl_plan.hip", "kvl_kernels.hip", "kvl_h2d.hip", "kvl_stream.hip", "kvl_noalloc.hip", "kvl_sched.cpp"]
 
 
@@ -17,6 +19,23 @@ def hipcc() -> str:
         if c and (os.path.isabs(c) and os.path.exists(c) or not os.path.isabs(c)):
             return c
     return "hipcc"
+
+
+def build_native(verbose: bool = False) -> str:
+    """Compile the module with the per-layer calls of the binding (host code only; always rebuilds)."""
+    tmp = NATIVE + f".tmp{os.getpid()}"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
+           "-Wno-missing-field-initializers", "-I" + os.path.join(_ROOT, "include"),
+           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "kvl_python.cpp"), "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        if os.path.exists(tmp):
+            os.unlink(tmp)
+        raise RuntimeError("the binding's module does not compile:\n" + res.stderr)
+    os.replace(tmp, NATIVE)
+    return NATIVE
 
 
 def build(verbose: bool = False) -> str:
@@ -41,6 +60,8 @@ def build(verbose: bool = False) -> str:
     if verbose and err.strip():
         print(err, file=sys.stderr)
     os.replace(tmp, LIB)
+    if os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        build_native(verbose)       # (without Python's headers the binding marshals by ctypes alone)
     return LIB
 
 
