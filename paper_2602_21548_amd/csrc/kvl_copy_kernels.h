@@ -175,21 +175,20 @@ __global__ void __launch_bounds__(1024) kvl_unpack_kernel(const CopyArgs a) {
     units_body<false, WAVE, U, NTL, SP>(a);
 }
 
-// Tiled form: the grid is (descriptors x tiles_per_unit, planes); a workgroup
-// takes tile `t` of its descriptor and each lane moves VPT vectors.  With one
-// vector per lane there is no loop and no dependency between a lane's memory
-// operations: the hardware keeps the memory system busy by the sheer number of
-// resident wavefronts rather than by unrolling.
+// One descriptor in one scalar load (field by field the compiler fetches them one after the other, each as late as it can).
+typedef const v4u __attribute__((address_space(4), aligned(4))) *cunit_vec_t;
+__device__ __forceinline__ kvl_unit_t fetch_unit(const kvl_unit_t *units, uint32_t i) {
+    const v4u d = *((cunit_vec_t)(uintptr_t)units + i);
+    return kvl_unit_t{d.x, d.y, d.z, d.w};
+}
+
+// A tile of a descriptor: `threads` lanes move VPT vectors each.
 template <bool PACK, int VPT, bool NTL, int SP>
-__device__ __forceinline__ void tile_body(const CopyArgs &a, uint32_t p, uint32_t tiles_per_unit, uint32_t align_dst,
-                                          uint32_t tile_index) {
-    const uint32_t u_idx = tile_index / tiles_per_unit;
-    const uint32_t tile = tile_index - u_idx * tiles_per_unit;
-    const kvl_unit_t u = a.units[a.unit_begin + u_idx];
-    const uint32_t row = a.row_elems[p];
+__device__ __forceinline__ void tile_span(const kvl_unit_t u, uintptr_t pool_base, uintptr_t xfer_base, uint32_t row, uint32_t tile,
+                                          uint32_t threads, uint32_t align_dst) {
     const uint32_t n = u.n_rows * row;
-    const uintptr_t pool = a.pool[p] + (uint64_t)u.pool_row * row * 16u;
-    const uintptr_t xfer = a.xfer[p] + (uint64_t)u.xfer_row * row * 16u;
+    const uintptr_t pool = pool_base + (uint64_t)u.pool_row * row * 16u;
+    const uintptr_t xfer = xfer_base + (uint64_t)u.xfer_row * row * 16u;
     gsrc_t src = (gsrc_t)(PACK ? pool : xfer);
     gdst_t dst = (gdst_t)(PACK ? xfer : pool);
     // With rows that are not multiples of 128 bytes a span starts anywhere in a
@@ -198,31 +197,81 @@ __device__ __forceinline__ void tile_body(const CopyArgs &a, uint32_t p, uint32_
     // whole lines (its load may straddle them, which costs far less): the first
     // `lead` lanes of the first tile idle.
     const uint32_t lead = align_dst ? ((uint32_t)((PACK ? xfer : pool) >> 4) & 7u) : 0u;
-    const uint32_t first = tile * (blockDim.x * VPT);
+    const uint32_t first = tile * (threads * VPT);
     if (first >= n + lead) return;      // this tile lies beyond the descriptor's end
     v4u v[VPT];
 #pragma unroll
     for (int k = 0; k < VPT; ++k) {
-        const uint32_t pos = first + k * blockDim.x + threadIdx.x;
+        const uint32_t pos = first + k * threads + threadIdx.x;
         if (pos >= lead && pos - lead < n) v[k] = load16<NTL>(src + (pos - lead));
     }
 #pragma unroll
     for (int k = 0; k < VPT; ++k) {
-        const uint32_t pos = first + k * blockDim.x + threadIdx.x;
+        const uint32_t pos = first + k * threads + threadIdx.x;
         if (pos >= lead && pos - lead < n) store16<SP>(dst + (pos - lead), v[k]);
     }
 }
 
-template <int VPT, bool NTL, int SP>
-__global__ void __launch_bounds__(1024) kvl_pack_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit,
-                                                             uint32_t align_dst) {
-    tile_body<true, VPT, NTL, SP>(a, a.plane_begin + blockIdx.y, tiles_per_unit, align_dst, blockIdx.x);
+// Tiled form: the grid is (descriptors x tiles_per_unit, planes); a workgroup
+// takes tile `t` of its descriptor and each lane moves VPT vectors.  With one
+// vector per lane there is no loop and no dependency between a lane's memory
+// operations: the hardware keeps the memory system busy by the sheer number of
+// resident wavefronts rather than by unrolling.
+//
+// A wavefront lives for one load and one store, so what it waits for before them counts: the descriptor is found without
+// a division (`magic` and the shift in `how`, see TileDivisor), fetched in one load, and the arguments are scalars, which the
+// hardware puts into registers before the wavefront starts (-amdgpu-kernarg-preload-count).  Hops, 1152-byte rows by 64, us,
+// four scalar loads one after the other / so: 11 MB 9.9 / 9.3, 22 MB 16.3 / 15.7, 80 MB 47.8 / 46.9.
+struct TileMore {                       // planes after the first of a launch
+    uintptr_t pool[KVL_MAX_PLANES - 1], xfer[KVL_MAX_PLANES - 1];
+};
+#define KVL_TILE_PARAMS                                                                                            \
+    const kvl_unit_t *units, uintptr_t pool, uintptr_t xfer, uint32_t row, uint32_t tiles_per_unit, uint32_t magic, \
+        uint32_t how, uint32_t threads
+
+template <bool PACK, int VPT, bool NTL, int SP>
+__device__ __forceinline__ void tile_group(KVL_TILE_PARAMS) {
+    const uint32_t b = blockIdx.x;
+    const uint32_t u_idx = magic ? (uint32_t)(((uint64_t)b * magic) >> 32) >> (how >> 1) : b;
+    tile_span<PACK, VPT, NTL, SP>(fetch_unit(units, u_idx), pool, xfer, row, b - u_idx * tiles_per_unit, threads, how & 1u);
 }
 
 template <int VPT, bool NTL, int SP>
-__global__ void __launch_bounds__(1024) kvl_unpack_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit,
-                                                               uint32_t align_dst) {
-    tile_body<false, VPT, NTL, SP>(a, a.plane_begin + blockIdx.y, tiles_per_unit, align_dst, blockIdx.x);
+__global__ void __launch_bounds__(1024) kvl_pack_tile_kernel(KVL_TILE_PARAMS, const TileMore more) {
+    if (blockIdx.y) {
+        pool = more.pool[blockIdx.y - 1];
+        xfer = more.xfer[blockIdx.y - 1];
+    }
+    tile_group<true, VPT, NTL, SP>(units, pool, xfer, row, tiles_per_unit, magic, how, threads);
+}
+
+template <int VPT, bool NTL, int SP>
+__global__ void __launch_bounds__(1024) kvl_unpack_tile_kernel(KVL_TILE_PARAMS, const TileMore more) {
+    if (blockIdx.y) {
+        pool = more.pool[blockIdx.y - 1];
+        xfer = more.xfer[blockIdx.y - 1];
+    }
+    tile_group<false, VPT, NTL, SP>(units, pool, xfer, row, tiles_per_unit, magic, how, threads);
+}
+
+// The same where a layer fills the machine many times over, its arguments and descriptors fetched one after the other: the
+// wavefronts of a workgroup then start their loads apart, which the memory takes better from neighbouring spans.  Hops of
+// contiguous blocks, us, so / by the form above: 656-byte rows by 64, 4.1 GB 2551 / 2792; 1280-byte rows by 128, 2.3 GB 1460 / 1485.
+template <bool PACK, int VPT, bool NTL, int SP>
+__device__ __forceinline__ void late_tile(const CopyArgs &a, uint32_t tiles_per_unit, uint32_t align_dst, uint32_t t) {
+    const uint32_t u_idx = t / tiles_per_unit, p = a.plane_begin + blockIdx.y;
+    tile_span<PACK, VPT, NTL, SP>(a.units[a.unit_begin + u_idx], a.pool[p], a.xfer[p], a.row_elems[p], t - u_idx * tiles_per_unit, blockDim.x,
+                                  align_dst);
+}
+
+template <int VPT, bool NTL, int SP>
+__global__ void __launch_bounds__(1024) kvl_pack_late_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t align_dst) {
+    late_tile<true, VPT, NTL, SP>(a, tiles_per_unit, align_dst, blockIdx.x);
+}
+
+template <int VPT, bool NTL, int SP>
+__global__ void __launch_bounds__(1024) kvl_unpack_late_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t align_dst) {
+    late_tile<false, VPT, NTL, SP>(a, tiles_per_unit, align_dst, blockIdx.x);
 }
 
 // Thin form of the tiled kernels: a fixed, small number of workgroups, each walking over
@@ -233,8 +282,8 @@ __global__ void __launch_bounds__(1024) kvl_unpack_tile_kernel(const CopyArgs a,
 template <bool PACK, int VPT, bool NTL, int SP>
 __global__ void __launch_bounds__(1024) kvl_tile_walk_kernel(const CopyArgs a, uint32_t tiles_per_unit,
                                                              uint32_t align_dst, uint32_t n_tiles) {
-    for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x)
-        tile_body<PACK, VPT, NTL, SP>(a, a.plane_begin + blockIdx.y, tiles_per_unit, align_dst, t);
+    // (with the descriptor in one load a streamed load of eight layers takes 15.01 ms, so 14.87)
+    for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) late_tile<PACK, VPT, NTL, SP>(a, tiles_per_unit, align_dst, t);
 }
 
 // Pipelined form of the tiled kernels: a fixed grid that fills the machine once (every
@@ -385,12 +434,11 @@ __global__ void __launch_bounds__(1024) kvl_flat_kernel(const CopyArgs a, uint32
 typedef const uint32_t __attribute__((address_space(4))) *cmap_t;
 
 template <bool PACK, bool NTL, int SP, int K>
-__device__ __forceinline__ void rows_body(const CopyArgs &a, uint32_t p, const uint32_t *row_map, uint32_t row_begin,
-                                          uint32_t n_vecs, uint32_t group) {
-    const uint32_t row = a.row_elems[p];
-    const uintptr_t xfer = a.xfer[p] + (uint64_t)row_begin * row * 16u;
+__device__ __forceinline__ void rows_body(const uint32_t *row_map, uintptr_t pool_base, uintptr_t xfer_base, uint32_t row,
+                                          uint32_t row_begin, uint32_t n_vecs, uint32_t group, uint32_t threads) {
+    const uintptr_t xfer = xfer_base + (uint64_t)row_begin * row * 16u;
     const uint32_t lead = (uint32_t)(xfer >> 4) & 7u;
-    const uint32_t pos = group * blockDim.x + threadIdx.x;
+    const uint32_t pos = group * threads + threadIdx.x;
     const uint32_t g = pos - lead;
     if (pos < lead || g >= n_vecs) return;
     cmap_t map = (cmap_t)(uintptr_t)(row_map + row_begin);
@@ -416,16 +464,20 @@ __device__ __forceinline__ void rows_body(const CopyArgs &a, uint32_t p, const u
         }
         off -= skip;
     }
-    const uintptr_t pool = a.pool[p] + ((uint64_t)pool_row * row + off) * 16u;
+    const uintptr_t pool = pool_base + ((uint64_t)pool_row * row + off) * 16u;
     gsrc_t src = (gsrc_t)(PACK ? pool : xfer + (uint64_t)g * 16u);
     gdst_t dst = (gdst_t)(PACK ? xfer + (uint64_t)g * 16u : pool);
     store16<SP>(dst, load16<NTL>(src));
 }
 
 template <bool PACK, bool NTL, int SP, int K>
-__global__ void __launch_bounds__(1024) kvl_rows_kernel(const CopyArgs a, const uint32_t *row_map, uint32_t row_begin,
-                                                        uint32_t n_vecs) {
-    rows_body<PACK, NTL, SP, K>(a, a.plane_begin + blockIdx.y, row_map, row_begin, n_vecs, blockIdx.x);
+__global__ void __launch_bounds__(1024) kvl_rows_kernel(const uint32_t *row_map, uintptr_t pool, uint32_t row_begin, uint32_t n_vecs,
+                                                        uintptr_t xfer, uint32_t row, uint32_t threads, const TileMore more) {
+    if (blockIdx.y) {
+        pool = more.pool[blockIdx.y - 1];
+        xfer = more.xfer[blockIdx.y - 1];
+    }
+    rows_body<PACK, NTL, SP, K>(row_map, pool, xfer, row, row_begin, n_vecs, blockIdx.x, threads);
 }
 
 // Planes of unlike rows in one launch, the workgroups of one plane after those of the other, each plane with its own number:
@@ -450,14 +502,16 @@ __global__ void __launch_bounds__(1024) kvl_planes_kernel(const CopyArgs a, cons
     const uint32_t row = a.row_elems[p];
     const uint32_t n_vecs = pl.n_rows * row;
     if (!ROWS) {
-        if (!PACK && pl.plain[p]) tile_body<PACK, 1, false, 3>(a, p, pl.per_unit[p], pl.align_dst[p], group);
-        else tile_body<PACK, 1, true, PACK ? SP : 3>(a, p, pl.per_unit[p], pl.align_dst[p], group);
+        const uint32_t u_idx = group / pl.per_unit[p], tile = group - u_idx * pl.per_unit[p];
+        const kvl_unit_t u = fetch_unit(a.units, a.unit_begin + u_idx);
+        if (!PACK && pl.plain[p]) tile_span<PACK, 1, false, 3>(u, a.pool[p], a.xfer[p], row, tile, blockDim.x, pl.align_dst[p]);
+        else tile_span<PACK, 1, true, PACK ? SP : 3>(u, a.pool[p], a.xfer[p], row, tile, blockDim.x, pl.align_dst[p]);
     } else if (PACK || row % 8 == 0) {
-        if (row >= 64) rows_body<PACK, true, PACK ? SP : 3, 2>(a, p, row_map, pl.row_begin, n_vecs, group);
-        else rows_body<PACK, true, PACK ? SP : 3, 0>(a, p, row_map, pl.row_begin, n_vecs, group);
+        if (row >= 64) rows_body<PACK, true, PACK ? SP : 3, 2>(row_map, a.pool[p], a.xfer[p], row, pl.row_begin, n_vecs, group, blockDim.x);
+        else rows_body<PACK, true, PACK ? SP : 3, 0>(row_map, a.pool[p], a.xfer[p], row, pl.row_begin, n_vecs, group, blockDim.x);
     } else {
-        if (row >= 64) rows_body<PACK, true, 1, 2>(a, p, row_map, pl.row_begin, n_vecs, group);
-        else rows_body<PACK, true, 1, 0>(a, p, row_map, pl.row_begin, n_vecs, group);
+        if (row >= 64) rows_body<PACK, true, 1, 2>(row_map, a.pool[p], a.xfer[p], row, pl.row_begin, n_vecs, group, blockDim.x);
+        else rows_body<PACK, true, 1, 0>(row_map, a.pool[p], a.xfer[p], row, pl.row_begin, n_vecs, group, blockDim.x);
     }
 }
 
@@ -502,28 +556,40 @@ __device__ __forceinline__ void copy_any(uintptr_t src, uintptr_t dst, uint32_t 
     }
 }
 
-// Tiled: a tile is blockDim vectors; one workgroup per tile, or (WALK) gridDim.x of them walking over n_tiles.
+// Tiled: a tile is blockDim vectors; one workgroup per tile, or (the walk) gridDim.x of them walking over n_tiles.
 // Tiles begin on 128-byte lines of the destination, or (SRC) of the source: then every line of the source is read by one
 // wavefront alone.  A line that the on-die cache holds is taken out of it by a non-temporal load, so that a line shared by
 // two wavefronts is fetched from memory by the second; the stores of the two meet in the L2 instead (they must not be
 // written through: hops of 304 MB, 1026-byte rows by 64, us: gather and scatter on lines of the destination 209, of the
 // source with nt stores out of the scatter 195, with sc1+nt ones 219).
-template <bool PACK, bool NTL, int SP, bool SRC, bool WALK>
-__global__ void __launch_bounds__(1024) kvl_any_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t n_tiles) {
-    cunits_t units = (cunits_t)(uintptr_t)(a.units + a.unit_begin);
+template <bool PACK, bool NTL, int SP, bool SRC>
+__device__ __forceinline__ void any_span(const kvl_unit_t u, uintptr_t pool_base, uintptr_t xfer_base, uint32_t row, uint32_t k) {
+    const uintptr_t pool = pool_base + (uint64_t)u.pool_row * row;
+    const uintptr_t xfer = xfer_base + (uint64_t)u.xfer_row * row;
+    const uintptr_t src = PACK ? pool : xfer, dst = PACK ? xfer : pool;
+    copy_any<NTL, SP>(src, dst, u.n_rows * row, (uint32_t)(SRC ? src : dst) & 127u, k);
+}
+
+template <bool PACK, bool NTL, int SP, bool SRC>
+__global__ void __launch_bounds__(1024) kvl_any_tile_kernel(KVL_TILE_PARAMS, const TileMore more) {
+    if (blockIdx.y) {
+        pool = more.pool[blockIdx.y - 1];
+        xfer = more.xfer[blockIdx.y - 1];
+    }
+    const uint32_t b = blockIdx.x;
+    const uint32_t u_idx = magic ? (uint32_t)(((uint64_t)b * magic) >> 32) >> (how >> 1) : b;
+    any_span<PACK, NTL, SP, SRC>(fetch_unit(units, u_idx), pool, xfer, row, (b - u_idx * tiles_per_unit) * threads + threadIdx.x);
+}
+
+template <bool PACK, bool NTL, int SP, bool SRC>
+__global__ void __launch_bounds__(1024) kvl_any_walk_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t n_tiles) {
     const uint32_t p = a.plane_begin + blockIdx.y;
     const uint32_t row = a.row_elems[p];
-    const uintptr_t pool_base = a.pool[p], xfer_base = a.xfer[p];
+    const uintptr_t pool = a.pool[p], xfer = a.xfer[p];
     for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         const uint32_t u_idx = t / tiles_per_unit;
-        const uint32_t tile = t - u_idx * tiles_per_unit;
-        cunits_t u = units + u_idx;
-        const uintptr_t pool = pool_base + (uint64_t)u->pool_row * row;
-        const uintptr_t xfer = xfer_base + (uint64_t)u->xfer_row * row;
-        const uintptr_t dst = PACK ? xfer : pool;
-        const uintptr_t src = PACK ? pool : xfer;
-        copy_any<NTL, SP>(src, dst, u->n_rows * row, (uint32_t)(SRC ? src : dst) & 127u, tile * blockDim.x + threadIdx.x);
-        if (!WALK) return;
+        any_span<PACK, NTL, SP, SRC>(fetch_unit(a.units, a.unit_begin + u_idx), pool, xfer, row,
+                                     (t - u_idx * tiles_per_unit) * blockDim.x + threadIdx.x);
     }
 }
 

@@ -88,31 +88,66 @@ static void launch_span_variant(uint32_t v, dim3 g, dim3 b, const On &s, const C
     }
 }
 
+// The descriptor of workgroup b is (b * magic >> 32) >> shift, exactly, for every b below 2^31: with l = ceil(log2 d) the
+// number m = ceil(2^(31+l) / d) fits 32 bits and exceeds 2^(31+l) / d by less than 2^l / d, which b / 2^(31+l) makes less than
+// 1 / d.  (d == 1: magic 0, the workgroup's own number.)
+struct TileDivisor {
+    uint32_t magic = 0, shift = 0;
+    explicit TileDivisor(uint32_t d) {
+        if (d < 2) return;
+        uint32_t l = 1;
+        while ((1ull << l) < d) ++l;
+        magic = (uint32_t)(((1ull << (31 + l)) + d - 1) / d);
+        shift = l - 1;
+    }
+};
+
+static TileMore more_planes(const CopyArgs &a, uint32_t planes) {
+    TileMore more{};
+    for (uint32_t q = 1; q < planes; ++q) {
+        more.pool[q - 1] = a.pool[a.plane_begin + q];
+        more.xfer[q - 1] = a.xfer[a.plane_begin + q];
+    }
+    return more;
+}
+
 // n_tiles != 0: the launch has fewer workgroups than tiles and they walk over them
 template <bool PACK, int VPT, bool NTL, int SP>
 static void launch_tile_one(dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t tpu, uint32_t al,
-                            uint32_t n_tiles) {
-    if (n_tiles) KVL_LAUNCH((kvl_tile_walk_kernel<PACK, VPT, NTL, SP>), g, b, s, a, tpu, al, n_tiles);
-    else if (PACK) KVL_LAUNCH((kvl_pack_tile_kernel<VPT, NTL, SP>), g, b, s, a, tpu, al);
-    else KVL_LAUNCH((kvl_unpack_tile_kernel<VPT, NTL, SP>), g, b, s, a, tpu, al);
+                            uint32_t n_tiles, bool late) {
+    if (n_tiles) {
+        KVL_LAUNCH((kvl_tile_walk_kernel<PACK, VPT, NTL, SP>), g, b, s, a, tpu, al, n_tiles);
+        return;
+    }
+    if (late) {
+        if (PACK) KVL_LAUNCH((kvl_pack_late_tile_kernel<VPT, NTL, SP>), g, b, s, a, tpu, al);
+        else KVL_LAUNCH((kvl_unpack_late_tile_kernel<VPT, NTL, SP>), g, b, s, a, tpu, al);
+        return;
+    }
+    const TileDivisor d(tpu);
+    const uint32_t p = a.plane_begin, how = d.shift << 1 | al;
+    const TileMore more = more_planes(a, g.y);
+    const kvl_unit_t *units = a.units + a.unit_begin;
+    if (PACK) KVL_LAUNCH((kvl_pack_tile_kernel<VPT, NTL, SP>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], tpu, d.magic, how, b.x, more);
+    else KVL_LAUNCH((kvl_unpack_tile_kernel<VPT, NTL, SP>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], tpu, d.magic, how, b.x, more);
 }
 
 template <bool PACK, int VPT, bool NTL>
 static void launch_tile_sp(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t tpu,
-                           uint32_t al, uint32_t n_tiles) {
+                           uint32_t al, uint32_t n_tiles, bool late) {
     switch ((v >> 3) & 3u) {
-        case 0: launch_tile_one<PACK, VPT, NTL, 0>(g, b, s, a, tpu, al, n_tiles); break;
-        case 1: launch_tile_one<PACK, VPT, NTL, 1>(g, b, s, a, tpu, al, n_tiles); break;
-        case 2: launch_tile_one<PACK, VPT, NTL, 2>(g, b, s, a, tpu, al, n_tiles); break;
-        default: launch_tile_one<PACK, VPT, NTL, 3>(g, b, s, a, tpu, al, n_tiles); break;
+        case 0: launch_tile_one<PACK, VPT, NTL, 0>(g, b, s, a, tpu, al, n_tiles, late); break;
+        case 1: launch_tile_one<PACK, VPT, NTL, 1>(g, b, s, a, tpu, al, n_tiles, late); break;
+        case 2: launch_tile_one<PACK, VPT, NTL, 2>(g, b, s, a, tpu, al, n_tiles, late); break;
+        default: launch_tile_one<PACK, VPT, NTL, 3>(g, b, s, a, tpu, al, n_tiles, late); break;
     }
 }
 
 template <bool PACK, int VPT>
 static void launch_tile_variant(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t tpu,
-                                uint32_t al, uint32_t n_tiles) {
-    if (v & 4u) launch_tile_sp<PACK, VPT, true>(v, g, b, s, a, tpu, al, n_tiles);
-    else launch_tile_sp<PACK, VPT, false>(v, g, b, s, a, tpu, al, n_tiles);
+                                uint32_t al, uint32_t n_tiles, bool late) {
+    if (v & 4u) launch_tile_sp<PACK, VPT, true>(v, g, b, s, a, tpu, al, n_tiles, late);
+    else launch_tile_sp<PACK, VPT, false>(v, g, b, s, a, tpu, al, n_tiles, late);
 }
 
 template <bool PACK, bool NTL>
@@ -167,18 +202,26 @@ static void launch_flat_variant(uint32_t v, dim3 g, dim3 b, const On &s, const C
 template <bool PACK, bool NTL, int SP>
 static void launch_rows(dim3 g, dim3 b, const On &s, const CopyArgs &a, const uint32_t *map, uint32_t row_begin,
                         uint32_t n_vecs) {
-    const uint32_t row = a.row_elems[a.plane_begin];
-    if (row >= 64) KVL_LAUNCH((kvl_rows_kernel<PACK, NTL, SP, 2>), g, b, s, a, map, row_begin, n_vecs);
-    else if (row >= 32) KVL_LAUNCH((kvl_rows_kernel<PACK, NTL, SP, 3>), g, b, s, a, map, row_begin, n_vecs);
-    else if (row >= 16) KVL_LAUNCH((kvl_rows_kernel<PACK, NTL, SP, 5>), g, b, s, a, map, row_begin, n_vecs);
-    else KVL_LAUNCH((kvl_rows_kernel<PACK, NTL, SP, 0>), g, b, s, a, map, row_begin, n_vecs);
+    const uint32_t p = a.plane_begin, row = a.row_elems[p];
+    const TileMore more = more_planes(a, g.y);
+#define KVL_ROWS(K) KVL_LAUNCH((kvl_rows_kernel<PACK, NTL, SP, K>), g, b, s, map, a.pool[p], row_begin, n_vecs, a.xfer[p], row, b.x, more)
+    if (row >= 64) KVL_ROWS(2);
+    else if (row >= 32) KVL_ROWS(3);
+    else if (row >= 16) KVL_ROWS(5);
+    else KVL_ROWS(0);
+#undef KVL_ROWS
 }
 
 template <bool PACK, bool NTL, int SP, bool SRC>
 static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t x, uint32_t n_tiles) {
     if (flat) KVL_LAUNCH((kvl_any_flat_kernel<PACK, NTL, SP>), g, b, s, a, x);
-    else if (walk) KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, SRC, true>), g, b, s, a, x, n_tiles);
-    else KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, SRC, false>), g, b, s, a, x, n_tiles);
+    else if (walk) KVL_LAUNCH((kvl_any_walk_kernel<PACK, NTL, SP, SRC>), g, b, s, a, x, n_tiles);
+    else {
+        const TileDivisor d(x);
+        const uint32_t p = a.plane_begin;
+        KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, SRC>), g, b, s, a.units + a.unit_begin, a.pool[p], a.xfer[p], a.row_elems[p], x,
+                   d.magic, d.shift << 1, b.x, more_planes(a, g.y));
+    }
 }
 
 // Rows or addresses that are not multiples of 16 bytes (the planes of a launch have one row size).
@@ -446,13 +489,14 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         bool walk = false;
         const uint32_t groups = launch_groups(blocks, threads, cap, &walk);
         const uint32_t n_tiles = walk ? (uint32_t)blocks : 0u;
+        const bool late = plan->payload_bytes > kQuickStartBytes;
         dim3 grid(groups, plane_end - plane_begin);
         if (pack) {
-            if (vpt == 2) launch_tile_variant<true, 2>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles);
-            else launch_tile_variant<true, 1>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles);
+            if (vpt == 2) launch_tile_variant<true, 2>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles, late);
+            else launch_tile_variant<true, 1>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles, late);
         } else {
-            if (vpt == 2) launch_tile_variant<false, 2>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles);
-            else launch_tile_variant<false, 1>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles);
+            if (vpt == 2) launch_tile_variant<false, 2>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles, late);
+            else launch_tile_variant<false, 1>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles, late);
         }
     } else {
         const uint32_t per_wg = (v & 3u) == 1u ? threads / 64 : 1;

@@ -299,6 +299,27 @@ static int check_ceiling_policies() {
     return 0;
 }
 
+// A tile's descriptor by multiplication is the quotient, for every workgroup number that a launch can have (around multiples of
+// the divisor, at both ends).
+static int check_tile_divisor() {
+    std::vector<uint32_t> divisors = {2147483647u, 2147483646u, 1073741825u, 1073741824u, 1431655765u, 715827883u};
+    for (uint32_t d = 1; d < 5000; ++d) divisors.push_back(d);
+    for (uint32_t k = 12; k < 31; ++k)
+        for (int e = -1; e <= 1; ++e) divisors.push_back((1u << k) + e);
+    for (uint32_t d : divisors) {
+        const TileDivisor t(d);
+        const uint32_t last = 2147483647u / d;
+        for (uint32_t q : {0u, 1u, 2u, 3u, last / 3, last / 2, last - (last > 0), last})
+            for (int e = -1; e <= 1; ++e) {
+                const int64_t b = (int64_t)q * d + e;
+                if (b < 0 || b > 2147483647) continue;
+                const uint32_t got = t.magic ? (uint32_t)(((uint64_t)b * t.magic) >> 32) >> t.shift : (uint32_t)b;
+                REQUIRE(got == (uint32_t)b / d);
+            }
+    }
+    return 0;
+}
+
 // Row-map launches beyond 2^32 lanes: in parts that follow one another and leave out no row.
 static uint64_t g_rows_covered;
 static bool g_rows_right;
@@ -369,6 +390,7 @@ int main(int argc, char **argv) {
         {"cached_arrays", check_cached_arrays},
         {"ceiling_policies", check_ceiling_policies},
         {"row_map_split", check_row_map_split},
+        {"tile_divisor", check_tile_divisor},
         {"row_map_rule", check_row_map_rule},
     };
     if (argc != 2 || !checks.count(argv[1])) {

@@ -123,8 +123,8 @@ def test_layers_about_the_size_of_the_on_die_cache(bs, row, mb):
     hop_at(_uniform(3, tokens, bs, row))
 
 
-def _uniform(requests, tokens, bs, row):
-    w = W.tiny(981, requests, bs, (row,), requests * (tokens // bs + 4), tokens, allow_zero_hit=False)
+def _uniform(requests, tokens, bs, *rows):
+    w = W.tiny(981, requests, bs, rows, requests * (tokens // bs + 4), tokens, allow_zero_hit=False)
     w.hit[:] = [tokens - 5 * r for r in range(requests)]
     w.app[:] = 3
     nb = [(int(h) + 3 + bs - 1) // bs for h in w.hit]
@@ -214,6 +214,16 @@ def test_full_blocks_on_lines_of_the_source(bs, rows, first):
     assert np.all(got[fb * count:] == 0x5A)
     for a, b in zip(d_dst, want_pool):
         assert same_bytes(to_host(a), b), "load differs from the oracle"
+
+
+# layers around a gibibyte, beyond which the tiles start late, with an odd number of tiles to a descriptor, tiles on lines and
+# off them, and a second plane
+@pytest.mark.parametrize("bs,rows", [(64, (656,)), (40, (2048, 2048))])
+@pytest.mark.parametrize("mb", [1023, 1026])
+def test_tiles_of_layers_around_a_gibibyte(bs, rows, mb):
+    w = _uniform(2, (mb << 20) // sum(rows) // 2, bs, *rows)
+    assert (oracle.payload_bytes(w.hit, w.layout.row_bytes) > 1 << 30) == (mb > 1024)
+    hop_at(w, 0)
 
 
 # a move's own workgroups: 64 lanes, 128, and 1024 flat; descriptors around one wavefront and one workgroup
