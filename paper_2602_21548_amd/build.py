@@ -42,7 +42,7 @@ def build(verbose: bool = False) -> str:
     """Compile every source for gfx950 and link the shared library (always rebuilds)."""
     cmd = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-mllvm", "-amdgpu-kernarg-preload-count=14",       # scalar arguments of kernels in registers (see kvl_pack_tile_kernel)
+           "-mllvm", "-amdgpu-kernarg-preload-count=14",       # scalar arguments of kernels in registers (see kvl_pack_quick_tile_kernel)
            "-Wall", "-Wextra", "-Wno-unused-command-line-argument",
            "-I" + os.path.join(_ROOT, "include"), "-I" + CSRC]
     cmd += [os.path.join(CSRC, s) for s in SOURCES]

@@ -237,7 +237,7 @@ __device__ __forceinline__ void tile_group(KVL_TILE_PARAMS) {
 }
 
 template <int VPT, bool NTL, int SP>
-__global__ void __launch_bounds__(1024) kvl_pack_tile_kernel(KVL_TILE_PARAMS, const TileMore more) {
+__global__ void __launch_bounds__(1024) kvl_pack_quick_tile_kernel(KVL_TILE_PARAMS, const TileMore more) {
     if (blockIdx.y) {
         pool = more.pool[blockIdx.y - 1];
         xfer = more.xfer[blockIdx.y - 1];
@@ -246,7 +246,7 @@ __global__ void __launch_bounds__(1024) kvl_pack_tile_kernel(KVL_TILE_PARAMS, co
 }
 
 template <int VPT, bool NTL, int SP>
-__global__ void __launch_bounds__(1024) kvl_unpack_tile_kernel(KVL_TILE_PARAMS, const TileMore more) {
+__global__ void __launch_bounds__(1024) kvl_unpack_quick_tile_kernel(KVL_TILE_PARAMS, const TileMore more) {
     if (blockIdx.y) {
         pool = more.pool[blockIdx.y - 1];
         xfer = more.xfer[blockIdx.y - 1];
@@ -265,12 +265,12 @@ __device__ __forceinline__ void late_tile(const CopyArgs &a, uint32_t tiles_per_
 }
 
 template <int VPT, bool NTL, int SP>
-__global__ void __launch_bounds__(1024) kvl_pack_late_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t align_dst) {
+__global__ void __launch_bounds__(1024) kvl_pack_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t align_dst) {
     late_tile<true, VPT, NTL, SP>(a, tiles_per_unit, align_dst, blockIdx.x);
 }
 
 template <int VPT, bool NTL, int SP>
-__global__ void __launch_bounds__(1024) kvl_unpack_late_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t align_dst) {
+__global__ void __launch_bounds__(1024) kvl_unpack_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t align_dst) {
     late_tile<false, VPT, NTL, SP>(a, tiles_per_unit, align_dst, blockIdx.x);
 }
 

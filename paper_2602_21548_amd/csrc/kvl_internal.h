@@ -71,7 +71,7 @@ constexpr uint32_t kAnyFlatWindows = 160, kAnyFlatLinesWindows = 256, kAnyFlatPa
 // layers' in turn (256 MB hold three of 85 MB), and up to which it pays to read each line out of it once.
 // (Dealt out flat, 26 by 16, 73 MB, passing by / kept 81 / 85.)
 constexpr uint64_t kCachedFlatBytes = 64u << 20, kCachedLayerBytes = 76u << 20, kReadOnceBytes = 640u << 20;
-// Above this payload the tiles start late (kvl_pack_late_tile_kernel).  Hops of contiguous blocks, us, early / late: 2048 + 2048-byte
+// Above this payload the tiles start late (kvl_pack_tile_kernel).  Hops of contiguous blocks, us, early / late: 2048 + 2048-byte
 // rows by 64, 765 MB 436 / 440, 1.0 GB 575 / 580; 656 by 64, 181 MB 104.8 / 106.7, 1.1 GB 734 / 734, 4.1 GB 2792 / 2551; 1280 by
 // 128, 1.1 GB 713 / 711, 2.3 GB 1485 / 1460.
 constexpr uint64_t kQuickStartBytes = 1ull << 30;

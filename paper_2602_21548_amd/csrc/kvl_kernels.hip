@@ -120,16 +120,16 @@ static void launch_tile_one(dim3 g, dim3 b, const On &s, const CopyArgs &a, uint
         return;
     }
     if (late) {
-        if (PACK) KVL_LAUNCH((kvl_pack_late_tile_kernel<VPT, NTL, SP>), g, b, s, a, tpu, al);
-        else KVL_LAUNCH((kvl_unpack_late_tile_kernel<VPT, NTL, SP>), g, b, s, a, tpu, al);
+        if (PACK) KVL_LAUNCH((kvl_pack_tile_kernel<VPT, NTL, SP>), g, b, s, a, tpu, al);
+        else KVL_LAUNCH((kvl_unpack_tile_kernel<VPT, NTL, SP>), g, b, s, a, tpu, al);
         return;
     }
     const TileDivisor d(tpu);
     const uint32_t p = a.plane_begin, how = d.shift << 1 | al;
     const TileMore more = more_planes(a, g.y);
     const kvl_unit_t *units = a.units + a.unit_begin;
-    if (PACK) KVL_LAUNCH((kvl_pack_tile_kernel<VPT, NTL, SP>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], tpu, d.magic, how, b.x, more);
-    else KVL_LAUNCH((kvl_unpack_tile_kernel<VPT, NTL, SP>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], tpu, d.magic, how, b.x, more);
+    if (PACK) KVL_LAUNCH((kvl_pack_quick_tile_kernel<VPT, NTL, SP>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], tpu, d.magic, how, b.x, more);
+    else KVL_LAUNCH((kvl_unpack_quick_tile_kernel<VPT, NTL, SP>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], tpu, d.magic, how, b.x, more);
 }
 
 template <bool PACK, int VPT, bool NTL>
