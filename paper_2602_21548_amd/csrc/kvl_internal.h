@@ -67,6 +67,8 @@ constexpr uint32_t kHostSideGroups = 64;    // workgroups of a kernel whose far 
 // Rows that are no multiple of 16 bytes (launch_any says why): the largest descriptor, in vectors, dealt out flat in a hop,
 // and in moves and across the host link;
 constexpr uint32_t kAnyFlatWindows = 160, kAnyFlatLinesWindows = 256, kAnyFlatPastWindows = 288;
+// of a capped launch, the lanes from which narrow workgroups pay (half of what the machine holds);
+constexpr uint64_t kCappedLanes = 1u << 18;
 // up to which payload the on-die cache holds the layer from the gather's stores to the scatter's loads, beside two other
 // layers' in turn (256 MB hold three of 85 MB), and up to which it pays to read each line out of it once.
 // (Dealt out flat, 26 by 16, 73 MB, passing by / kept 81 / 85.)

@@ -247,7 +247,11 @@ static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, co
 //     196 MB, 69 / 64 / 63; 1026 by 64, 181 MB, 57 / 58 / 58); a scatter's 256, whose wavefronts share fewer lines at the
 //     ends of tiles, or 128 where that leaves an eighth of the lanes fewer without work (256 / 128: 132 by 64 107 / 103, 333
 //     by 16 54 / 49, 47 by 128 46 / 42; but 333 by 64, 8 % fewer, 73 / 77, 1115 by 16 45 / 48).  Past the cache 256 or, for
-//     short descriptors, by the same rule (gather of 153 by 24, 948 MB, 256 / 128: 348 / 385).
+//     short descriptors, by the same rule (gather of 153 by 24, 948 MB, 256 / 128: 348 / 385).  Under a cap on the workgroups
+//     they are widened until kCappedLanes are at work, which is what keeps the memory busy (gather with 64 / 256: 132 by 64,
+//     254 MB, 512 workgroups 384 / 157, 4096 85 / 110; 333 by 64, 50 MB, 1024 42.4 / 20.4, 4096 19.6 / 20.8), and where 256
+//     lanes are not enough descriptors go flat, in workgroups of 1024, up to kAnyFlatPastWindows (hops, flat / tiled with 256:
+//     1026 by 4, 24 MB, 64 workgroups 140 / 251, 512 32.9 / 40.8, 1024 28.4 / 28.2).
 //   moves (150 MB of 90-byte rows by 32: flat 54, tiled with 256 / 128 lanes 53 / 59) and the host link: flat up to
 //     kAnyFlatPastWindows, tiles of 256 lanes, 128 below two such tiles (1026 by 4: 377 us at 256, 286 at 128).
 //   across the host link: tiles on few workgroups (kHostSideGroups); a flat launch has as many as ever, since few of them
@@ -260,11 +264,14 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
     const bool hop = !plan->paired && !far_host;
     const bool alike = 2ull * plan->max_unit_rows * plan->units.size() <= 3 * plan->hit_tokens;
     const bool lines = (uint64_t)plan->layout.block_tokens * a.row_elems[a.plane_begin] % 128 == 0 && plan->payload_bytes > kCachedFlatBytes;
-    const bool flat = windows <= (!hop || !alike ? kAnyFlatPastWindows : lines ? kAnyFlatLinesWindows : kAnyFlatWindows);
+    const bool thin = plan->tuning.max_groups && plan->tuning.max_groups < kCappedLanes / 256;
+    const bool flat = windows <= (!hop || !alike || thin ? kAnyFlatPastWindows : lines ? kAnyFlatLinesWindows : kAnyFlatWindows);
     const bool kept = far_host || (!plan->paired && plan->payload_bytes <= (flat ? kCachedFlatBytes : kCachedLayerBytes));
     const bool once = hop && !kept && plan->payload_bytes <= kReadOnceBytes;
     const uint64_t spanned = unit_bytes + 127;              // with the lanes before its first byte on the line
     auto tiles_of = [spanned](uint64_t lanes) { return (spanned + 16 * lanes - 1) / (16 * lanes); };
+    uint64_t cap = plan->tuning.max_groups;
+    if (!cap && far_host) cap = 2 * kHostSideGroups;       // (one vector per lane: see kHostSideGroups)
     uint32_t threads = plan->tuning.block_threads;
     if (!plan->threads_chosen) {
         const bool is_short = spanned <= 2 * 256 * 16;
@@ -274,9 +281,9 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
         else if (!hop) threads = is_short ? 128 : 256;
         else if (pack && (kept || once)) threads = 64;
         else threads = halve && (is_short || kept || once) ? 128 : 256;
+        if (hop && cap && a.n_units * tiles_of(threads) > cap)
+            while (threads < 256 && cap * threads < kCappedLanes) threads *= 2;
     }
-    uint64_t cap = plan->tuning.max_groups;
-    if (!cap && far_host) cap = 2 * kHostSideGroups;       // (one vector per lane: see kHostSideGroups)
     const uint64_t per_unit = tiles_of(threads);
     uint64_t per_launch = flat ? ((1ull << 32) - threads) / windows : (uint64_t)INT32_MAX / per_unit;
     if (flat && plan->tuning.max_groups)

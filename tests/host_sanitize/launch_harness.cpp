@@ -113,6 +113,51 @@ static int check_full_block_planes() {
     return 0;
 }
 
+// A plan of `n` descriptors of `rows` rows each, as whole blocks have them.
+static kvl_plan_s alike(uint64_t n, uint32_t rows, uint32_t row, uint32_t planes = 1) {
+    kvl_plan_s p = made(n, rows, row, planes);
+    p.layout.block_tokens = rows;
+    for (uint64_t k = 0; k < n; ++k) p.units[k] = kvl_unit_t{(uint32_t)(k * rows), (uint32_t)(k * rows), rows, (uint32_t)k};
+    p.hit_tokens = n * rows;
+    p.payload_bytes = p.hit_tokens * row * planes;
+    p.blocks_touched = n;
+    return p;
+}
+
+// Odd rows: narrow workgroups are for launches that fill the machine.  Where a cap keeps them below that, they are wide.
+static int check_capped_odd_rows() {
+    const struct { uint32_t cap, pack, unpack; } shapes[] = {{0, 64, 128}, {64, 256, 256}, {1023, 256, 256}, {2047, 256, 256}, {2048, 128, 128}, {4095, 128, 128},
+                                                             {4096, 64, 128}, {UINT32_MAX, 64, 128}};
+    for (const auto &q : shapes)
+        for (bool gather : {true, false}) {
+            kvl_plan_s p = alike(30000, 64, 132);           // 254 MB, 529 vectors each
+            p.tuning.max_groups = q.cap;
+            uintptr_t xfer[KVL_MAX_PLANES] = {1ull << 44};
+            launches.clear();
+            REQUIRE(launch_units(&p, gather, 0, 30000, 0, 1, kPlanes, xfer, nullptr) == KVL_OK);
+            const bool walks = q.cap && q.cap != UINT32_MAX;
+            REQUIRE(launches.size() == 1 && is(launches[0], walks ? "kvl_any_walk_kernel" : "kvl_any_tile_kernel"));
+            REQUIRE(launches[0].block.x == (gather ? q.pack : q.unpack) && (!walks || groups(launches[0]) == q.cap));
+            launches.clear();                               // fewer tiles than the cap allows: as without one
+            if (q.cap != 64) {
+                REQUIRE(launch_units(&p, gather, 0, 100, 0, 1, kPlanes, xfer, nullptr) == KVL_OK);
+                REQUIRE(launches[0].block.x == (gather ? 64 : 128) && is(launches[0], "kvl_any_tile_kernel"));
+            }
+            p.d_units = nullptr;
+        }
+    // too few for 256 lanes each: flat, as without lines to lay tiles on
+    for (uint32_t cap : {1023u, 1024u}) {
+        kvl_plan_s p = alike(5000, 4, 1026);                // 258 windows
+        p.tuning.max_groups = cap;
+        uintptr_t xfer[KVL_MAX_PLANES] = {1ull << 44};
+        launches.clear();
+        REQUIRE(launch_units(&p, true, 0, 5000, 0, 1, kPlanes, xfer, nullptr) == KVL_OK);
+        for (const fake::Launch &l : launches) REQUIRE(is(l, cap < 1024 ? "kvl_any_flat_kernel" : "kvl_any_walk_kernel") && groups(l) <= cap);
+        p.d_units = nullptr;
+    }
+    return 0;
+}
+
 // kvl_plan enqueues the making of the row map and waits for nothing that runs on the device, whoever answers for the
 // plan's lifetime; the array of a plan dropped before its map was made comes back when the map's kernel has run.
 static int check_caller_syncs() {
@@ -383,6 +428,7 @@ int main(int argc, char **argv) {
     const std::map<std::string, int (*)()> checks = {
         {"move_shapes", check_move_shapes},
         {"full_block_planes", check_full_block_planes},
+        {"capped_odd_rows", check_capped_odd_rows},
         {"caller_syncs", check_caller_syncs},
         {"row_map_under_capture", check_row_map_under_capture},
         {"row_map_on_two_streams", check_row_map_on_two_streams},
