@@ -581,6 +581,21 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
         if (busy(128) > busy(threads) + 0.07) threads = 128;
         if (busy(64) > busy(threads) + 0.09) threads = 64;
     }
+    // (a cap that was asked for is meant for each plane, see kvl_tuning_t)
+    const uint32_t cap = plan->tuning.max_groups ? (uint32_t)std::min<uint64_t>((uint64_t)plan->tuning.max_groups * P, UINT32_MAX)
+                                                 : (far_host ? (vec ? kHostSideGroups : 2 * kHostSideGroups) : 0u);
+    auto tiles_of = [&](uint64_t lanes) {
+        uint64_t n = 0;
+        for (uint32_t p = 0; p < P; ++p) n += (vectors[p] + lanes * vpt - 1) / (lanes * vpt);
+        return n;
+    };
+    // Under a cap on the workgroups they are widened until more than kCappedLanes are at work, or a quarter of them where
+    // that makes no fewer tiles (the other wavefronts then only fetch descriptors ahead).  Load + persist of four layers, us, 64
+    // or 128 / 256 lanes: 132-byte rows by 64, 33 MB, 64 workgroups 2911 / 919, 1024 225 / 116, 4096 106.6 / 100.0 (128 lanes
+    // 100.9); 336 by 16, 32 MB, 512 224 / 179, 4096 95.7 / 107; 496 by 1, 9 MB, 64 1509 / 1413, 1024 129 / 140, 4096 61 / 88.
+    while (threads < 256 && cap && a.n_units * tiles_of(threads) > cap &&
+           (uint64_t)cap * threads <= (tiles_of(2 * threads) < tiles_of(threads) ? kCappedLanes : kCappedLanes / 4))
+        threads *= 2;
     uint64_t tpu = 0;
     for (uint32_t p = 0; p < KVL_MAX_PLANES; ++p) {
         const uint64_t tiles = (vectors[p] + (uint64_t)threads * vpt - 1) / ((uint64_t)threads * vpt);
@@ -589,9 +604,6 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
     }
     // (the limit is that of tiles of 256 lanes, whatever their lanes are)
     if (a.n_units * most > (uint64_t)INT32_MAX || tpu > (uint64_t)INT32_MAX) return KVL_ERANGE;
-    // (a cap that was asked for is meant for each plane, see kvl_tuning_t)
-    const uint32_t cap = plan->tuning.max_groups ? (uint32_t)std::min<uint64_t>((uint64_t)plan->tuning.max_groups * P, UINT32_MAX)
-                                                 : (far_host ? (vec ? kHostSideGroups : 2 * kHostSideGroups) : 0u);
     On on(plan, stream);
     // the tiles of all planes are numbered with 32 bits: descriptors that have more go in several launches
     const uint32_t n_all = a.n_units, per_launch = (uint32_t)(INT32_MAX / tpu);

@@ -158,6 +158,24 @@ static int check_capped_odd_rows() {
     return 0;
 }
 
+// Full Blocks likewise: 64-lane workgroups for 132-byte rows by 64 without a cap, under one as wide as it takes.
+static int check_capped_full_blocks() {
+    const struct { uint32_t cap, block; } shapes[] = {{0, 64}, {64, 256}, {1024, 256}, {2048, 256}, {2049, 128}, {4096, 128}, {4097, 64}};
+    for (const auto &q : shapes)
+        for (bool to_pool : {true, false}) {
+            kvl_plan_s p = alike(4000, 64, 132);
+            p.tuning.max_groups = q.cap;
+            launches.clear();
+            REQUIRE(fullblock_launch(&p, to_pool, 1ull << 44, 64 * 132, 0, 0, 4000, kPlanes, nullptr) == KVL_OK);
+            REQUIRE(launches.size() == 1 && launches[0].block.x == q.block && (!q.cap || groups(launches[0]) == q.cap));
+            launches.clear();                               // fewer tiles than the cap allows
+            REQUIRE(fullblock_launch(&p, to_pool, 1ull << 44, 64 * 132, 0, 0, 7, kPlanes, nullptr) == KVL_OK);
+            REQUIRE(launches[0].block.x == 64 && groups(launches[0]) <= 64);
+            p.d_units = nullptr;
+        }
+    return 0;
+}
+
 // kvl_plan enqueues the making of the row map and waits for nothing that runs on the device, whoever answers for the
 // plan's lifetime; the array of a plan dropped before its map was made comes back when the map's kernel has run.
 static int check_caller_syncs() {
@@ -429,6 +447,7 @@ int main(int argc, char **argv) {
         {"move_shapes", check_move_shapes},
         {"full_block_planes", check_full_block_planes},
         {"capped_odd_rows", check_capped_odd_rows},
+        {"capped_full_blocks", check_capped_full_blocks},
         {"caller_syncs", check_caller_syncs},
         {"row_map_under_capture", check_row_map_under_capture},
         {"row_map_on_two_streams", check_row_map_on_two_streams},
