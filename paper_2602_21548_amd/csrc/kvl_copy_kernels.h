@@ -492,8 +492,13 @@ struct PlanesArgs {
     uint32_t row_begin, n_rows;                // transfer rows of the launch's descriptors
 };
 
-// SP: the stores of a gather or a move (a scatter's are sc1+nt, by the row map off lines nt)
-template <bool PACK, int SP, bool ROWS>
+// SP: the stores of a gather or a move (a scatter's are sc1+nt, by the row map off lines nt).  ROWS: 0 by tiles; else by the row
+// map, the entries of rows of 16 to 63 vectors by a vector load per lane (1), or through the scalar cache as kvl_rows_kernel has
+// them (2).  The latter is better in a scatter of a layer beyond the on-die cache (512- and 16-byte rows by 256, scatter, us, 1 /
+// 2: 289 MB 99.7 / 92.1, 367 MB 121.9 / 113.8; 512 and 128 by 8, 402 MB, 134.8 / 128.4; 200 MB 59.0 / 59.3), or of one that is
+// read by nt loads, off the lines (304 and 80 by 4, 218 MB, 71.8 / 69.0; 656 and 128 by 64, 186 MB, 62.4 / 60.4); not in a gather
+// (349 MB 103.7 / 104.6, 219 MB of 512 and 128 66.7 / 68.8).
+template <bool PACK, int SP, int ROWS>
 __global__ void __launch_bounds__(1024) kvl_planes_kernel(const CopyArgs a, const PlanesArgs pl, const uint32_t *row_map) {
     uint32_t p = a.plane_begin;
 #pragma unroll
@@ -501,18 +506,27 @@ __global__ void __launch_bounds__(1024) kvl_planes_kernel(const CopyArgs a, cons
     const uint32_t group = blockIdx.x - (p > a.plane_begin ? pl.group_end[p - 1] : 0u);
     const uint32_t row = a.row_elems[p];
     const uint32_t n_vecs = pl.n_rows * row;
+    constexpr int kMid = ROWS == 2 ? 3 : 0, kShort = ROWS == 2 ? 5 : 0;        // rows of 32 to 63 and of 16 to 31 vectors
+#define KVL_PLANE_ROWS(POLICY, K) \
+    rows_body<PACK, true, POLICY, K>(row_map, a.pool[p], a.xfer[p], row, pl.row_begin, n_vecs, group, blockDim.x)
     if (!ROWS) {
         const uint32_t u_idx = group / pl.per_unit[p], tile = group - u_idx * pl.per_unit[p];
         const kvl_unit_t u = fetch_unit(a.units, a.unit_begin + u_idx);
         if (!PACK && pl.plain[p]) tile_span<PACK, 1, false, 3>(u, a.pool[p], a.xfer[p], row, tile, blockDim.x, pl.align_dst[p]);
         else tile_span<PACK, 1, true, PACK ? SP : 3>(u, a.pool[p], a.xfer[p], row, tile, blockDim.x, pl.align_dst[p]);
     } else if (PACK || row % 8 == 0) {
-        if (row >= 64) rows_body<PACK, true, PACK ? SP : 3, 2>(row_map, a.pool[p], a.xfer[p], row, pl.row_begin, n_vecs, group, blockDim.x);
-        else rows_body<PACK, true, PACK ? SP : 3, 0>(row_map, a.pool[p], a.xfer[p], row, pl.row_begin, n_vecs, group, blockDim.x);
+        constexpr int kPolicy = PACK ? SP : 3;
+        if (row >= 64) KVL_PLANE_ROWS(kPolicy, 2);
+        else if (ROWS == 2 && row >= 32) KVL_PLANE_ROWS(kPolicy, kMid);
+        else if (ROWS == 2 && row >= 16) KVL_PLANE_ROWS(kPolicy, kShort);
+        else KVL_PLANE_ROWS(kPolicy, 0);
     } else {
-        if (row >= 64) rows_body<PACK, true, 1, 2>(row_map, a.pool[p], a.xfer[p], row, pl.row_begin, n_vecs, group, blockDim.x);
-        else rows_body<PACK, true, 1, 0>(row_map, a.pool[p], a.xfer[p], row, pl.row_begin, n_vecs, group, blockDim.x);
+        if (row >= 64) KVL_PLANE_ROWS(1, 2);
+        else if (ROWS == 2 && row >= 32) KVL_PLANE_ROWS(1, kMid);
+        else if (ROWS == 2 && row >= 16) KVL_PLANE_ROWS(1, kShort);
+        else KVL_PLANE_ROWS(1, 0);
     }
+#undef KVL_PLANE_ROWS
 }
 
 // Rows or addresses that are not multiples of 16 bytes.  The vector unit takes 16-byte accesses at any

@@ -319,12 +319,13 @@ static bool launch_planes(const kvl_plan_t *plan, bool pack, const CopyArgs &a, 
     if (plan->tuning.variant || plan->tuning.max_groups || plan->threads_chosen || plan->payload_bytes > kPlanesAtOnceBytes)
         return false;
     const double average = (double)plan->hit_tokens / (double)plan->units.size();
-    bool lines = true, by_rows = false;
+    bool lines = true, by_rows = false, askew = false;
     uint32_t widest = 0, threads = 0;
     for (uint32_t p = begin; p < plane_end; ++p) {
         lines = lines && plan->layout.row_bytes[p] % 128 == 0;
         by_rows = by_rows || takes_row_map(plan, plan->layout.row_bytes[p], pack);
         widest = std::max(widest, a.row_elems[p]);
+        askew = askew || (a.row_elems[p] >= 16 && a.row_elems[p] < 64 && a.row_elems[p] % 8 != 0);
     }
     if (by_rows) {
         if (!plan->d_row_map || !row_map_ready(plan, on.stream)) return false;
@@ -354,11 +355,12 @@ static bool launch_planes(const kvl_plan_t *plan, bool pack, const CopyArgs &a, 
     }
     const dim3 grid((uint32_t)groups), block(threads);
     const uint32_t *map = plan->d_row_map;
-    if (plan->paired) KVL_LAUNCH((kvl_planes_kernel<true, 3, false>), grid, block, on, a, pl, map);
-    else if (pack && by_rows) KVL_LAUNCH((kvl_planes_kernel<true, 2, true>), grid, block, on, a, pl, map);
-    else if (pack) KVL_LAUNCH((kvl_planes_kernel<true, 2, false>), grid, block, on, a, pl, map);
-    else if (by_rows) KVL_LAUNCH((kvl_planes_kernel<false, 3, true>), grid, block, on, a, pl, map);
-    else KVL_LAUNCH((kvl_planes_kernel<false, 3, false>), grid, block, on, a, pl, map);
+    if (plan->paired) KVL_LAUNCH((kvl_planes_kernel<true, 3, 0>), grid, block, on, a, pl, map);
+    else if (pack && by_rows) KVL_LAUNCH((kvl_planes_kernel<true, 2, 1>), grid, block, on, a, pl, map);
+    else if (pack) KVL_LAUNCH((kvl_planes_kernel<true, 2, 0>), grid, block, on, a, pl, map);
+    else if (by_rows && plan->payload_bytes > (askew ? kPlainReadBackBytes : kPlanesCachedBytes)) KVL_LAUNCH((kvl_planes_kernel<false, 3, 2>), grid, block, on, a, pl, map);
+    else if (by_rows) KVL_LAUNCH((kvl_planes_kernel<false, 3, 1>), grid, block, on, a, pl, map);
+    else KVL_LAUNCH((kvl_planes_kernel<false, 3, 0>), grid, block, on, a, pl, map);
     return true;
 }
 

@@ -383,6 +383,41 @@ static int check_tile_divisor() {
     return 0;
 }
 
+// A plan of `n` descriptors of `rows` rows in planes of unlike rows; with a row map, made, if `map`.
+static uint32_t g_map;
+static kvl_plan_s unlike(uint64_t n, uint32_t rows, std::vector<uint32_t> row_bytes, bool map) {
+    kvl_plan_s p = alike(n, rows, row_bytes[0], (uint32_t)row_bytes.size());
+    p.payload_bytes = 0;
+    for (size_t q = 0; q < row_bytes.size(); ++q) {
+        p.layout.row_bytes[q] = row_bytes[q];
+        p.payload_bytes += p.hit_tokens * row_bytes[q];
+    }
+    if (map) p.d_row_map = &g_map;
+    return p;
+}
+
+// Planes of unlike rows by the row map: beyond what the on-die cache holds the scatter looks its rows up through the scalar cache.
+static int check_planes_by_rows() {
+    const struct { uint32_t wide, narrow, rows, mib, mode; } shapes[] = {
+        {512, 16, 256, 230, 1}, {512, 16, 256, 240, 2}, {512, 128, 8, 230, 1}, {512, 128, 8, 380, 2}, {656, 128, 1, 110, 1}, {656, 128, 1, 114, 2},
+        {304, 80, 4, 200, 2}, {1152, 128, 1, 230, 1}, {1152, 128, 1, 240, 2}};
+    for (const auto &q : shapes)
+        for (bool gather : {true, false}) {
+            const uint64_t n = ((uint64_t)q.mib << 20) / (q.rows * (q.wide + q.narrow));
+            kvl_plan_s p = unlike(n, q.rows, {q.wide, q.narrow}, true);
+            uintptr_t xfer[KVL_MAX_PLANES] = {1ull << 44, 1ull << 45};
+            launches.clear();
+            REQUIRE(launch_units(&p, gather, 0, (uint32_t)n, 0, 2, kPlanes, xfer, nullptr) == KVL_OK);
+            const std::string mode = gather ? "<true, 2, 1>" : q.mode == 2 ? "<false, 3, 2>" : "<false, 3, 1>";
+            if (launches.size() != 1 || !is(launches[0], ("kvl_planes_kernel" + mode).c_str())) {
+                std::printf("%u + %u by %u, %u MiB: %s\n", q.wide, q.narrow, q.rows, q.mib, launches[0].kernel.c_str());
+                return 1;
+            }
+            p.d_units = nullptr;
+        }
+    return 0;
+}
+
 // Row-map launches beyond 2^32 lanes: in parts that follow one another and leave out no row.
 static uint64_t g_rows_covered;
 static bool g_rows_right;
@@ -454,6 +489,7 @@ int main(int argc, char **argv) {
         {"default_stream", check_default_stream},
         {"cached_arrays", check_cached_arrays},
         {"ceiling_policies", check_ceiling_policies},
+        {"planes_by_rows", check_planes_by_rows},
         {"row_map_split", check_row_map_split},
         {"tile_divisor", check_tile_divisor},
         {"row_map_rule", check_row_map_rule},
