@@ -82,7 +82,9 @@ constexpr uint64_t kQuickStartBytes = 1ull << 30;
 // rows by 16, 285 MB 176 / 177, 631 MB 412 / 412; 1024 and 128 by 24, 873 MB, 557 / 565; moves 512 and 528 by 128, 289 MB
 // 91.0 / 89.9, 591 MB 181 / 183).
 constexpr uint64_t kPlanesAtOnceBytes = 384u << 20;
-// and beyond this one a scatter of theirs by the row map fetches its entries as kvl_rows_kernel does (see kvl_planes_kernel),
+// Up to these, by tiles, whatever lanes suit each plane (see launch_planes):
+constexpr uint64_t kPlanesAlikeBytes = 128u << 20, kPlanesUnlikeBytes = 60u << 20;
+// Beyond this one a scatter of theirs by the row map fetches its entries as kvl_rows_kernel does (see kvl_planes_kernel),
 // or beyond kPlainReadBackBytes where rows of 16 to 63 vectors are off the lines.
 constexpr uint64_t kPlanesCachedBytes = 236u << 20;
 constexpr uint32_t kNumVariants = 512;       // explicit variants are 1 .. kNumVariants

@@ -314,6 +314,15 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
 // Planes of unlike rows in one launch: 16-byte vectors on this device, in layers of up to kPlanesAtOnceBytes.  All planes by
 // the row map where one of them would take it (made, and not awaited by a stream under capture), else all by tiles, of
 // whose lanes no plane may idle half.  False: they go apart.
+//   lanes of the tiles: a gather's and a scatter's as the widest plane has them; a move's 64 where the descriptors are alike
+//     and begin on lines, else 128 where that leaves clearly fewer idle over all planes (moves, us, 256 / 128: 656- and
+//     336-byte rows by 40 in runs, 199 MB, 75.0 / 67.7; 272 and 144 by 48, 205 MB, 73.4 / 69.5; 656 and 128 by 16 at random,
+//     20 MB, 10.9 / 8.5).
+//   in larger layers a plane's own lanes are worth more than the launch: they go apart where the descriptors are alike and
+//     the common lanes are more in all (kPlanesAlikeBytes; hops, together / apart: 256 and 128 by 100, 150 MB 92.3 / 90.5,
+//     333 MB 220.1 / 212.8; 656 and 336 by 64, 91 MB 61.5 / 63.6, 302 MB 189.0 / 183.9), or where they are not alike and a
+//     plane would have another width (kPlanesUnlikeBytes; moves in runs: 512 and 256 by 4, 45 MB 21.7 / 22.2, 64 MB 30.0 /
+//     29.0, 299 MB 134.2 / 119.7; 256 and 128 by 16, 60 MB 25.1 / 26.6, 200 MB 80.0 / 76.6).
 static bool launch_planes(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uint32_t plane_end, const On &on) {
     const uint32_t begin = a.plane_begin;
     if (plan->tuning.variant || plan->tuning.max_groups || plan->threads_chosen || plan->payload_bytes > kPlanesAtOnceBytes)
@@ -331,8 +340,32 @@ static bool launch_planes(const kvl_plan_t *plan, bool pack, const CopyArgs &a, 
         if (!plan->d_row_map || !row_map_ready(plan, on.stream)) return false;
         threads = kDefaultBlockThreads;
     } else {
-        threads = plan->paired ? (lines ? move_threads(plan, 128) : kDefaultBlockThreads)
-                               : tile_threads((uint64_t)plan->max_unit_rows * widest);
+        auto lanes = [&](uint32_t p, uint64_t t) { return (plan->max_unit_rows * (uint64_t)a.row_elems[p] + t - 1) / t * t; };
+        auto apart = [&](uint32_t p) {          // the lanes that the plane would have by itself
+            return plan->paired ? move_threads(plan, plan->layout.row_bytes[p]) : tile_threads((uint64_t)plan->max_unit_rows * a.row_elems[p]);
+        };
+        const bool alike = 2ull * plan->max_unit_rows * plan->units.size() <= 3 * plan->hit_tokens;
+        if (!plan->paired) {
+            threads = tile_threads((uint64_t)plan->max_unit_rows * widest);
+        } else {
+            double vectors = 0, of_256 = 0, of_128 = 0;
+            for (uint32_t p = begin; p < plane_end; ++p) {
+                vectors += (double)plan->max_unit_rows * a.row_elems[p];
+                of_256 += (double)lanes(p, 256);
+                of_128 += (double)lanes(p, 128);
+            }
+            threads = lines && alike ? 64 : vectors / of_128 - vectors / of_256 > 0.07 ? 128 : kDefaultBlockThreads;
+        }
+        if (plan->payload_bytes > (alike ? kPlanesAlikeBytes : kPlanesUnlikeBytes)) {
+            double shared = 0, own = 0;
+            bool same = true;
+            for (uint32_t p = begin; p < plane_end; ++p) {
+                shared += (double)lanes(p, threads);
+                own += (double)lanes(p, apart(p));
+                same = same && apart(p) == threads;
+            }
+            if (alike ? shared > 1.03 * own : !same) return false;
+        }
     }
     const kvl_unit_t &first = plan->units[a.unit_begin], &last = plan->units[a.unit_begin + a.n_units - 1];
     PlanesArgs pl{};

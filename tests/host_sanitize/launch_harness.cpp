@@ -418,6 +418,97 @@ static int check_planes_by_rows() {
     return 0;
 }
 
+// Planes of unlike rows by tiles: together, with which lanes, or apart.  `average` rows of a descriptor whose largest has `rows`.
+static int check_planes_lanes() {
+    const struct { bool move; uint32_t wide, narrow, rows; double average; uint32_t mib, together, lanes; } shapes[] = {
+        {false, 1024, 128, 64, 64, 380, 1, 256}, {false, 1024, 128, 64, 64, 386, 0, 0}, {false, 256, 128, 100, 100, 120, 1, 256},
+        {false, 256, 128, 100, 100, 200, 0, 0}, {false, 656, 336, 64, 64, 120, 1, 256}, {false, 656, 336, 64, 64, 300, 0, 0},
+        {false, 1152, 640, 16, 16, 100, 1, 128}, {true, 1024, 128, 64, 64, 380, 1, 64}, {true, 512, 256, 8, 4.2, 45, 1, 128},
+        {true, 512, 256, 8, 4.2, 64, 0, 0}, {true, 512, 1024, 4, 2.6, 300, 0, 0}, {true, 656, 336, 40, 25, 200, 1, 128},
+        {true, 656, 336, 64, 64, 100, 1, 256}, {true, 656, 336, 64, 64, 350, 0, 0}, {true, 272, 144, 48, 48, 300, 1, 128},
+        {true, 656, 128, 16, 10, 20, 1, 128}, {true, 256, 128, 16, 10.1, 40, 1, 128}, {true, 256, 128, 16, 10.1, 80, 0, 0}};
+    for (const auto &q : shapes) {
+        const uint64_t n = (uint64_t)(((uint64_t)q.mib << 20) / (q.average * (q.wide + q.narrow)));
+        kvl_plan_s p = unlike(n, q.rows, {q.wide, q.narrow}, false);
+        p.paired = q.move;
+        p.hit_tokens = (uint64_t)(n * q.average);
+        p.payload_bytes = p.hit_tokens * (q.wide + q.narrow);
+        uintptr_t to[KVL_MAX_PLANES] = {1ull << 44, 1ull << 45};
+        for (bool gather : {true, false}) {
+            if (!gather && (q.move || takes_row_map(&p, q.wide, false) || takes_row_map(&p, q.narrow, false))) continue;
+            launches.clear();
+            REQUIRE(launch_units(&p, gather, 0, (uint32_t)n, 0, 2, kPlanes, to, nullptr) == KVL_OK);
+            const bool together = launches.size() == 1 && is(launches[0], "kvl_planes_kernel");
+            if (together != (q.together != 0) || (together && launches[0].block.x != q.lanes) || (!together && launches.size() != 2)) {
+                std::printf("%s of %u + %u by %u (%.1f), %u MiB: %zu launches, %u lanes\n", q.move ? "move" : gather ? "gather" : "scatter", q.wide,
+                            q.narrow, q.rows, q.average, q.mib, launches.size(), launches[0].block.x);
+                return 1;
+            }
+        }
+        p.d_units = nullptr;
+    }
+    return 0;
+}
+
+// What the shared launch tells its workgroups covers every vector of its planes and descriptors once and no others, for ranges
+// of both that begin anywhere.  (The workgroup's part follows kvl_planes_kernel.)
+static uint64_t g_vectors[KVL_MAX_PLANES];
+static uint32_t g_first_row;
+static int check_planes_layout() {
+    fake::watch = [](const fake::Launch &l, void **args) {
+        if (!is(l, "kvl_planes_kernel")) return;
+        const CopyArgs &a = *(const CopyArgs *)args[0];
+        const PlanesArgs &pl = *(const PlanesArgs *)args[1];
+        const bool rows = l.kernel.find(", 0>") == std::string::npos;
+        g_first_row = pl.row_begin;
+        for (uint32_t b = 0; b < l.grid.x; ++b) {
+            uint32_t p = a.plane_begin;
+            for (uint32_t q = 0; q + 1 < KVL_MAX_PLANES; ++q) p += b >= pl.group_end[q] ? 1u : 0u;
+            const uint32_t group = b - (p > a.plane_begin ? pl.group_end[p - 1] : 0u), row = a.row_elems[p];
+            const uintptr_t at = a.xfer[p] + (uint64_t)pl.row_begin * row * 16;
+            const uint64_t span = rows ? (uint64_t)pl.n_rows * row : 64 * row;      // (64 rows to a descriptor)
+            const uint64_t lead = rows ? (at >> 4) & 7 : pl.align_dst[p] ? 7 : 0;
+            if (!rows && group / pl.per_unit[p] >= a.n_units) g_vectors[p] = ~0ull;
+            const uint64_t tile = rows ? group : group % pl.per_unit[p];
+            for (uint64_t k = tile * l.block.x; k < (tile + 1) * l.block.x; ++k) g_vectors[p] += k >= lead && k - lead < span ? 1 : 0;
+        }
+    };
+    for (bool map : {false, true})
+        for (uint32_t begin : {0u, 1u, 2u})
+            for (uint32_t first : {0u, 7u, 99u}) {
+                kvl_plan_s p = unlike(100, map ? 5 : 64, {1152, 1040, 1024, 2048}, map);
+                uintptr_t xfer[KVL_MAX_PLANES] = {1ull << 44, (1ull << 45) + 48, (1ull << 46) + 16, 1ull << 47};
+                for (uint64_t &v : g_vectors) v = 0;
+                launches.clear();
+                REQUIRE(launch_units(&p, true, first, 100, begin, 4, kPlanes, xfer, nullptr) == KVL_OK);
+                REQUIRE(launches.size() == 1 && is(launches[0], map ? "kvl_planes_kernel<true, 2, 1>" : "kvl_planes_kernel<true, 2, 0>"));
+                REQUIRE(g_first_row == first * p.max_unit_rows);
+                for (uint32_t q = 0; q < 4; ++q)
+                    REQUIRE(g_vectors[q] == (q < begin ? 0 : (uint64_t)(100 - first) * p.max_unit_rows * (p.layout.row_bytes[q] / 16)));
+                p.d_units = nullptr;
+            }
+    fake::watch = nullptr;
+    // a map that is still being made is not waited for in a capture: the planes go apart, by their descriptors
+    fake::Stream capturing, map_stream;
+    map_stream.queued = 1;
+    fake::Event made_by{&map_stream, 1};
+    kvl_plan_s p = unlike(100, 5, {1152, 1040}, true);
+    p.map_pending = true;
+    p.map_event = reinterpret_cast<hipEvent_t>(&made_by);
+    uintptr_t xfer[KVL_MAX_PLANES] = {1ull << 44, 1ull << 45};
+    fake::begin_capture(capturing);
+    launches.clear();
+    REQUIRE(launch_units(&p, true, 0, 100, 0, 2, kPlanes, xfer, fake::handle(capturing)) == KVL_OK);
+    REQUIRE(launches.size() == 2 && is(launches[0], "kvl_pack_quick_tile_kernel") && is(launches[1], "kvl_pack_quick_tile_kernel"));
+    fake::finish(&map_stream);
+    launches.clear();
+    REQUIRE(launch_units(&p, true, 0, 100, 0, 2, kPlanes, xfer, fake::handle(capturing)) == KVL_OK);
+    REQUIRE(launches.size() == 1 && is(launches[0], "kvl_planes_kernel<true, 2, 1>") && !fake::capture_broken && fake::waits.empty());
+    fake::end_capture(capturing);
+    p.d_units = nullptr;
+    return 0;
+}
+
 // Row-map launches beyond 2^32 lanes: in parts that follow one another and leave out no row.
 static uint64_t g_rows_covered;
 static bool g_rows_right;
@@ -490,6 +581,8 @@ int main(int argc, char **argv) {
         {"cached_arrays", check_cached_arrays},
         {"ceiling_policies", check_ceiling_policies},
         {"planes_by_rows", check_planes_by_rows},
+        {"planes_lanes", check_planes_lanes},
+        {"planes_layout", check_planes_layout},
         {"row_map_split", check_row_map_split},
         {"tile_divisor", check_tile_divisor},
         {"row_map_rule", check_row_map_rule},
