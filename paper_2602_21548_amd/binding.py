@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from typing import List, Optional, Sequence
 
 import numpy as np
@@ -173,12 +174,13 @@ LIB_PATH = _build.LIB
 
 
 def _load_native():
-    """The module with the per-layer calls, or None where it cannot be built (no compiler, no Python headers)."""
+    """The module with the per-layer calls, or None, with a warning, where it cannot be built (no compiler, no Python headers)."""
     try:
         if not os.path.exists(_build.NATIVE):
             _build.build_native()
         from . import _native
-    except (ImportError, OSError, RuntimeError):
+    except (ImportError, OSError, RuntimeError) as e:
+        warnings.warn(f"per-layer calls go by ctypes, which takes twice as long on the host: {e}", RuntimeWarning)
         return None
     return _native
 

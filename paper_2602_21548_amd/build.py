@@ -5,6 +5,7 @@ import os
 import subprocess
 import sys
 import sysconfig
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
@@ -61,8 +62,11 @@ def build(verbose: bool = False) -> str:
     if verbose and err.strip():
         print(err, file=sys.stderr)
     os.replace(tmp, LIB)
-    if os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
-        build_native(verbose)       # (without Python's headers the binding marshals by ctypes alone)
+    # without a host compiler or Python's headers the binding marshals by ctypes alone
+    try:
+        build_native(verbose)
+    except (OSError, RuntimeError) as e:
+        warnings.warn(f"built without the module of the per-layer calls, which take twice as long on the host so: {e}", RuntimeWarning)
     return LIB
 
 

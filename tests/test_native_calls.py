@@ -1,6 +1,7 @@
 """The binding's module for the per-layer calls: it takes what is plainly in order and leaves the rest to the general path,
 whose results and errors stay what they are."""
 import gc
+import os
 
 import numpy as np
 import pytest
@@ -10,6 +11,7 @@ import kvl_workloads as W
 import oracle
 import paper_2602_21548_amd as K
 from paper_2602_21548_amd import binding as B
+from paper_2602_21548_amd import build as kvl_build
 
 NOT_TAKEN = 1
 
@@ -77,6 +79,28 @@ def test_what_is_not_in_order_is_left_to_the_general_path():
         plan.handle
     del plan
     gc.collect()
+
+
+@pytest.fixture
+def elsewhere(tmp_path, monkeypatch):
+    """Built files in a directory of the test's own; the library by a stand-in for hipcc that makes an empty file."""
+    hipcc = tmp_path / "hipcc"
+    hipcc.write_text('#!/bin/sh\nwhile [ "$1" != -o ]; do shift; done\n: > "$2"\n')
+    hipcc.chmod(0o755)
+    monkeypatch.setattr(kvl_build, "hipcc", lambda: str(hipcc))
+    monkeypatch.setattr(kvl_build, "LIB", str(tmp_path / "libkvl.so"))
+    monkeypatch.setattr(kvl_build, "NATIVE", str(tmp_path / os.path.basename(kvl_build.NATIVE)))
+    return tmp_path
+
+
+@pytest.mark.parametrize("compiler", ["/nonexistent/g++", "/bin/false"])
+def test_the_library_is_built_without_a_host_compiler(elsewhere, monkeypatch, compiler):
+    monkeypatch.setenv("CXX", compiler)
+    with pytest.warns(RuntimeWarning, match="module"):
+        assert kvl_build.build() == kvl_build.LIB
+    assert os.path.exists(kvl_build.LIB) and not os.path.exists(kvl_build.NATIVE)
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        assert B._load_native() is None
 
 
 @pytest.mark.gpu
