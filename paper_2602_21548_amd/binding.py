@@ -11,6 +11,7 @@ built, importing fails.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 import warnings
 from typing import List, Optional, Sequence
@@ -176,13 +177,16 @@ LIB_PATH = _build.LIB
 def _load_native():
     """The module with the per-layer calls, or None, with a warning, where it cannot be built (no compiler, no Python headers)."""
     try:
-        if not os.path.exists(_build.NATIVE):
+        if not _build.native_is_current():
             _build.build_native()
-        from . import _native
+        # by its path: a module of this name for another interpreter may lie beside it
+        spec = importlib.util.spec_from_file_location(__package__ + "._native", _build.NATIVE)
+        native = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(native)
     except (ImportError, OSError, RuntimeError) as e:
         warnings.warn(f"per-layer calls go by ctypes, which takes twice as long on the host: {e}", RuntimeWarning)
         return None
-    return _native
+    return native
 
 
 _native = _load_native()

@@ -1,6 +1,7 @@
 """Build libkvl.so (HIP, gfx950) in-tree with hipcc.  Run as a module or call build()."""
 from __future__ import annotations
 
+import hashlib
 import os
 import subprocess
 import sys
@@ -11,7 +12,9 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libkvl.so")
-NATIVE = os.path.join(_HERE, "_native.so")
+# for this interpreter alone: the module is laid out by its headers
+NATIVE = os.path.join(_HERE, "_native" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
+NATIVE_SOURCES = [os.path.join(_ROOT, "include", "kvl.h"), os.path.join(CSRC, "kvl_python.cpp")]
 SOURCES = ["kvl_plan.hip", "kvl_kernels.hip", "kvl_h2d.hip", "kvl_stream.hip", "kvl_noalloc.hip", "kvl_sched.cpp"]
 
 
@@ -22,11 +25,30 @@ def hipcc() -> str:
     return "hipcc"
 
 
+def native_key() -> str:
+    """What the binding's module is built from (its marker is in the built file)."""
+    digest = hashlib.sha256()
+    for path in NATIVE_SOURCES:
+        with open(path, "rb") as f:
+            digest.update(f.read())
+    return "kvl-native-" + digest.hexdigest()[:24]
+
+
+def native_is_current() -> bool:
+    """Whether the binding's module is there and was built from the present sources (found without loading it)."""
+    if not os.path.exists(NATIVE):
+        return False
+    if not all(os.path.exists(path) for path in NATIVE_SOURCES):
+        return True             # nothing to compare it with
+    with open(NATIVE, "rb") as f:
+        return native_key().encode() in f.read()
+
+
 def build_native(verbose: bool = False) -> str:
     """Compile the module with the per-layer calls of the binding (host code only; always rebuilds)."""
     tmp = NATIVE + f".tmp{os.getpid()}"
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
-           "-Wno-missing-field-initializers", "-I" + os.path.join(_ROOT, "include"),
+           "-Wno-missing-field-initializers", f'-DKVL_NATIVE_KEY="{native_key()}"', "-I" + os.path.join(_ROOT, "include"),
            "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "kvl_python.cpp"), "-o", tmp]
     if verbose:
         print(" ".join(cmd), flush=True)

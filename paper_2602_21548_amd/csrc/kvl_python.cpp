@@ -351,7 +351,8 @@ PyMethodDef module_methods[] = {
     {nullptr, nullptr, 0, nullptr},
 };
 
-PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, module_methods, nullptr, nullptr, nullptr, nullptr};
+// (found in the file by build.py, which takes no module built from other sources: the calls above go by raw addresses)
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", "The per-layer calls of the binding (" KVL_NATIVE_KEY ")", -1, module_methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 

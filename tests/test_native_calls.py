@@ -2,6 +2,8 @@
 whose results and errors stay what they are."""
 import gc
 import os
+import shutil
+import sysconfig
 
 import numpy as np
 import pytest
@@ -99,6 +101,22 @@ def test_the_library_is_built_without_a_host_compiler(elsewhere, monkeypatch, co
     with pytest.warns(RuntimeWarning, match="module"):
         assert kvl_build.build() == kvl_build.LIB
     assert os.path.exists(kvl_build.LIB) and not os.path.exists(kvl_build.NATIVE)
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        assert B._load_native() is None
+
+
+def test_the_module_is_built_for_this_interpreter_and_from_the_present_sources(elsewhere, monkeypatch):
+    assert kvl_build.NATIVE.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    if not shutil.which(os.environ.get("CXX", "g++")):
+        pytest.skip("no host compiler")
+    kvl_build.build_native()
+    assert kvl_build.native_is_current()
+    header = elsewhere / "kvl.h"
+    with open(kvl_build.NATIVE_SOURCES[0], "rb") as f:
+        header.write_bytes(f.read() + b"\n")
+    monkeypatch.setattr(kvl_build, "NATIVE_SOURCES", [str(header)] + kvl_build.NATIVE_SOURCES[1:])
+    assert not kvl_build.native_is_current()        # built from another header: as good as not there
+    monkeypatch.setenv("CXX", "/nonexistent/g++")
     with pytest.warns(RuntimeWarning, match="ctypes"):
         assert B._load_native() is None
 
