@@ -362,11 +362,10 @@ def _requests(hit, app, tables: Sequence[np.ndarray]):
     if len(tables) != n or app.shape[0] != n:
         raise ValueError("hit, app and tables must have one entry per request")
     reqs = (kvl_request_t * max(1, n))()
-    if _native is not None:
-        keep = list(tables)
-        if _native.requests(hit, app, keep, reqs):
-            return reqs, n, keep
-    keep = [np.ascontiguousarray(np.asarray(t, dtype=np.int32)) for t in tables]
+    keep = list(tables)         # (gone through once: it may not allow a second time)
+    if _native is not None and _native.requests(hit, app, keep, reqs):
+        return reqs, n, keep
+    keep = [np.ascontiguousarray(np.asarray(t, dtype=np.int32)) for t in keep]
     for r in range(n):
         reqs[r].hit_tokens = int(hit[r])
         reqs[r].append_tokens = int(app[r])

@@ -25,7 +25,7 @@ def _plan(w, flags=K.KVL_GATHER | K.KVL_HOST_ONLY, tables=None, hit=None, app=No
 
 
 # lists, other integer types, strided and two-dimensional tables, an empty one, a tuple of tables
-@pytest.mark.parametrize("form", ["as-is", "int64", "lists", "strided", "two-dimensional", "tuple", "mixed"])
+@pytest.mark.parametrize("form", ["as-is", "int64", "lists", "strided", "two-dimensional", "tuple", "mixed", "iterator"])
 def test_requests_in_every_form_give_the_same_plan(form):
     w = W.tiny(7, 6, 16, (64,), 90, 200, kind="runs")
     w.hit[2] = w.app[2] = 0
@@ -46,6 +46,18 @@ def test_requests_in_every_form_give_the_same_plan(form):
         tables = tuple(tables)
     elif form == "mixed":
         tables[1] = tables[1].tolist()
+    elif form == "iterator":
+        class Once:
+            def __init__(self, items):
+                self.n, self.left = len(items), iter(items)
+
+            def __len__(self):
+                return self.n
+
+            def __iter__(self):
+                return self.left
+
+        tables = Once([t.astype(np.int64) for t in tables])
     got = _plan(w, tables=tables, hit=hit, app=app).units()
     assert np.array_equal(got, want)
 
