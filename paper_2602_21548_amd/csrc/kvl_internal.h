@@ -73,10 +73,13 @@ constexpr uint64_t kCappedLanes = 1u << 18;
 // layers' in turn (256 MB hold three of 85 MB), and up to which it pays to read each line out of it once.
 // (Dealt out flat, 26 by 16, 73 MB, passing by / kept 81 / 85.)
 constexpr uint64_t kCachedFlatBytes = 64u << 20, kCachedLayerBytes = 76u << 20, kReadOnceBytes = 640u << 20;
+// The same for blocks of whole lines in several planes (gather, scatter), and up to which one the scatter's tiles are halved.
+constexpr uint64_t kReadOnceManyBytes = 572u << 20, kScatterOnceManyBytes = 400u << 20, kHalveBytes = 336u << 20;
 // Above this payload the tiles start late (kvl_pack_tile_kernel).  Hops of contiguous blocks, us, early / late: 2048 + 2048-byte
 // rows by 64, 765 MB 436 / 440, 1.0 GB 575 / 580; 656 by 64, 181 MB 104.8 / 106.7, 1.1 GB 734 / 734, 4.1 GB 2792 / 2551; 1280 by
 // 128, 1.1 GB 713 / 711, 2.3 GB 1485 / 1460.
 constexpr uint64_t kQuickStartBytes = 1ull << 30;
+constexpr uint32_t kLateTileBytes = 32u << 10;
 // Up to this payload planes of unlike rows share a launch (kvl_planes_kernel): beyond it a launch of their own is less than a
 // hundredth of their time, and each plane better off in the form that suits it (hops apart / at once, 2048- and 656-byte
 // rows by 16, 285 MB 176 / 177, 631 MB 412 / 412; 1024 and 128 by 24, 873 MB, 557 / 565; moves 512 and 528 by 128, 289 MB

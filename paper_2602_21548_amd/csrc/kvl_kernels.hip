@@ -236,6 +236,11 @@ static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, co
 //     kept form would be 2-5 % ahead up to 240 MB, with four it is 15 % behind from 77 MB.  Kept, the gather on its
 //     source's lines: 333 by 64, 39 MB, 29.2 -> 27.5; 99 by 64, 22 MB, 21.3 -> 19.3.
 //     Across the host link as kept (741-byte rows, 80 MB in and out, 2857 us against 2987 passing by).
+//     Several planes of blocks of whole lines, none of which is nearly all of the layer: read once up to kReadOnceManyBytes, by
+//     the scatter up to kScatterOnceManyBytes where the descriptors are single blocks or two (hops, random tables, before the
+//     source's lines / on them / so: 132 and 132 by 64, 493 MB 356 / 367 / 346, 663 MB 484 / 506 / 473; 132 and 260 by 64, 592
+//     MB 430 / 449 / 432; 72 and 72 by 128, 607 MB 436 / 466 / 433); past the cache their gather starts late from
+//     kLateTileBytes on (516 and 516 by 64, 867 MB 623 / 647 / 626; in one plane the early start is 1 % ahead).
 //   flat or tiled: a descriptor of up to kAnyFlatWindows vectors leaves too much of its last tile idle (150 MB hops, flat /
 //     tiled: 300-byte rows by 8, 151 windows, 111 / 114; 90 by 32, 181 windows, 119 / 107; 153 by 24, 231 windows, 117 / 104).
 //     Blocks of whole lines go better flat, once they are not kept (200 by 16, 201 windows, 31 MB 27 / 25, 147 MB 108 / 113; 70 by 64,
@@ -246,7 +251,8 @@ static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, co
 //   lanes of a tile: a gather's 64, which idle least (132 by 64, 275 MB, 103 us with 256, 99 with 128, 94 with 64; 333 by 64,
 //     196 MB, 69 / 64 / 63; 1026 by 64, 181 MB, 57 / 58 / 58); a scatter's 256, whose wavefronts share fewer lines at the
 //     ends of tiles, or 128 where that leaves an eighth of the lanes fewer without work (256 / 128: 132 by 64 107 / 103, 333
-//     by 16 54 / 49, 47 by 128 46 / 42; but 333 by 64, 8 % fewer, 73 / 77, 1115 by 16 45 / 48).  Past the cache 256 or, for
+//     by 16 54 / 49, 47 by 128 46 / 42; but 333 by 64, 8 % fewer, 73 / 77, 1115 by 16 45 / 48), up to kHalveBytes (scatter of 132
+//     by 64, 306 MB 115 / 112, 541 MB 211 / 226; 72 by 128, 323 MB 123.5 / 123.1, 476 MB 184 / 203).  Past the cache 256 or, for
 //     short descriptors, by the same rule (gather of 153 by 24, 948 MB, 256 / 128: 348 / 385).  Under a cap on the workgroups
 //     they are widened until kCappedLanes are at work, which is what keeps the memory busy (gather with 64 / 256: 132 by 64,
 //     254 MB, 512 workgroups 384 / 157, 4096 85 / 110; 333 by 64, 50 MB, 1024 42.4 / 20.4, 4096 19.6 / 20.8), and where 256
@@ -267,7 +273,17 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
     const bool thin = plan->tuning.max_groups && plan->tuning.max_groups < kCappedLanes / 256;
     const bool flat = windows <= (!hop || !alike || thin ? kAnyFlatPastWindows : lines ? kAnyFlatLinesWindows : kAnyFlatWindows);
     const bool kept = far_host || (!plan->paired && plan->payload_bytes <= (flat ? kCachedFlatBytes : kCachedLayerBytes));
-    const bool once = hop && !kept && plan->payload_bytes <= kReadOnceBytes;
+    // the widest plane's share of the layer, where blocks are of whole lines
+    uint64_t row_bytes = 0, widest_row = 0;
+    for (uint32_t p = 0; p < plan->layout.n_planes; ++p) {
+        row_bytes += plan->layout.row_bytes[p];
+        widest_row = std::max<uint64_t>(widest_row, plan->layout.row_bytes[p]);
+    }
+    const double share = lines ? (double)widest_row / (double)row_bytes : 1.0;
+    const bool of_blocks = plan->max_unit_rows <= 2ull * plan->layout.block_tokens && unit_bytes < (64u << 10);
+    const bool once = hop && !kept && plan->payload_bytes <= (share < 0.875 ? kReadOnceManyBytes : kReadOnceBytes);
+    const bool scatter_once = once && !(share < 0.8 && of_blocks && plan->payload_bytes > kScatterOnceManyBytes);
+    const bool late = hop && !kept && !once && share < 0.8 && of_blocks && unit_bytes >= kLateTileBytes;
     const uint64_t spanned = unit_bytes + 127;              // with the lanes before its first byte on the line
     auto tiles_of = [spanned](uint64_t lanes) { return (spanned + 16 * lanes - 1) / (16 * lanes); };
     uint64_t cap = plan->tuning.max_groups;
@@ -280,7 +296,7 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
         if (flat) threads = 1024;
         else if (!hop) threads = is_short ? 128 : 256;
         else if (pack && (kept || once)) threads = 64;
-        else threads = halve && (is_short || kept || once) ? 128 : 256;
+        else threads = halve && (is_short || kept || (scatter_once && plan->payload_bytes <= kHalveBytes)) ? 128 : 256;
         if (hop && cap && a.n_units * tiles_of(threads) > cap)
             while (threads < 256 && cap * threads < kCappedLanes) threads *= 2;
     }
@@ -297,6 +313,7 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
         bool walk = false;
         const uint32_t groups = flat ? (uint32_t)((part.n_units * windows + threads - 1) / threads)
                                      : launch_groups(tiles, threads, (uint32_t)cap, &walk);
+        walk = walk || (late && !flat);         // (one tile to a workgroup all the same)
         const uint32_t x = (uint32_t)(flat ? windows : per_unit), n_tiles = (uint32_t)tiles;
         dim3 grid(groups, planes), block(threads);
         if (pack) {
@@ -305,7 +322,7 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
             else launch_any_one<true, true, 1, true>(flat, walk, grid, block, on, part, x, n_tiles);
         } else {
             if (kept) launch_any_one<false, false, 3, false>(flat, walk, grid, block, on, part, x, n_tiles);
-            else if (once) launch_any_one<false, true, 1, true>(flat, walk, grid, block, on, part, x, n_tiles);
+            else if (scatter_once) launch_any_one<false, true, 1, true>(flat, walk, grid, block, on, part, x, n_tiles);
             else launch_any_one<false, true, 1, false>(flat, walk, grid, block, on, part, x, n_tiles);
         }
     }

@@ -158,6 +158,48 @@ static int check_capped_odd_rows() {
     return 0;
 }
 
+// Odd rows in larger layers: policies, lines (last template argument: the source's) and lanes by the payload and the planes.
+static int check_large_odd_layers() {
+    const struct { uint32_t row, rows, planes, mib; const char *gather, *scatter; uint32_t gather_lanes, scatter_lanes; } shapes[] = {
+        {132, 64, 1, 70, "tile_kernel<true, true, 2, true>", "tile_kernel<false, false, 3, false>", 64, 128},
+        {132, 64, 1, 330, "tile_kernel<true, true, 2, true>", "tile_kernel<false, true, 1, true>", 64, 128},
+        {132, 64, 1, 340, "tile_kernel<true, true, 2, true>", "tile_kernel<false, true, 1, true>", 64, 256},
+        {132, 64, 1, 635, "tile_kernel<true, true, 2, true>", "tile_kernel<false, true, 1, true>", 64, 256},
+        {132, 64, 1, 645, "tile_kernel<true, true, 1, true>", "tile_kernel<false, true, 1, false>", 256, 256},
+        {132, 64, 2, 395, "tile_kernel<true, true, 2, true>", "tile_kernel<false, true, 1, true>", 64, 256},
+        {132, 64, 2, 405, "tile_kernel<true, true, 2, true>", "tile_kernel<false, true, 1, false>", 64, 256},
+        {132, 64, 2, 565, "tile_kernel<true, true, 2, true>", "tile_kernel<false, true, 1, false>", 64, 256},
+        {132, 64, 2, 580, "tile_kernel<true, true, 1, true>", "tile_kernel<false, true, 1, false>", 256, 256},
+        {333, 64, 2, 635, "tile_kernel<true, true, 2, true>", "tile_kernel<false, true, 1, true>", 64, 256},     // (not of whole lines)
+        {1026, 64, 2, 500, "tile_kernel<true, true, 2, true>", "tile_kernel<false, true, 1, true>", 64, 256},    // 64 KiB and more
+        {516, 64, 2, 600, "walk_kernel<true, true, 1, true>", "walk_kernel<false, true, 1, false>", 256, 256},
+        {516, 64, 1, 700, "tile_kernel<true, true, 1, true>", "tile_kernel<false, true, 1, false>", 256, 256},
+        {200, 16, 1, 70, "any_flat_kernel<true, true, 1>", "any_flat_kernel<false, true, 1>", 1024, 1024},           // 201, of whole lines
+        {300, 8, 1, 60, "any_flat_kernel<true, true, 2>", "any_flat_kernel<false, false, 3>", 1024, 1024},          // 151 windows
+        {300, 8, 1, 70, "any_flat_kernel<true, true, 1>", "any_flat_kernel<false, true, 1>", 1024, 1024},
+        {120, 32, 1, 60, "any_tile_kernel<true, true, 2, true>", "any_tile_kernel<false, false, 3, false>", 64, 256},  // 241, of whole lines
+        {120, 32, 1, 70, "any_flat_kernel<true, true, 1>", "any_flat_kernel<false, true, 1>", 1024, 1024},
+        {70, 64, 1, 70, "any_tile_kernel<true, true, 2, true>", "any_tile_kernel<false, false, 3, false>", 64, 128}};  // 281
+    for (const auto &q : shapes)
+        for (bool gather : {true, false}) {
+            const uint64_t n = ((uint64_t)q.mib << 20) / (q.rows * q.row * q.planes);
+            kvl_plan_s p = alike(n, q.rows, q.row, q.planes);
+            uintptr_t xfer[KVL_MAX_PLANES] = {1ull << 44, 1ull << 45};
+            launches.clear();
+            REQUIRE(launch_units(&p, gather, 0, (uint32_t)n, 0, q.planes, kPlanes, xfer, nullptr) == KVL_OK);
+            const uint32_t lanes = gather ? q.gather_lanes : q.scatter_lanes;
+            const bool tiled = !is(launches[0], "flat");
+            if (launches.size() != 1 || !is(launches[0], gather ? q.gather : q.scatter) || launches[0].block.x != lanes ||
+                (tiled && launches[0].grid.x != n * ((q.rows * q.row + 127 + 16 * lanes - 1) / (16 * lanes)))) {
+                std::printf("%u by %u, %u planes, %u MiB: %s, %u workgroups of %u lanes\n", q.row, q.rows, q.planes, q.mib,
+                            launches[0].kernel.c_str(), launches[0].grid.x, launches[0].block.x);
+                return 1;
+            }
+            p.d_units = nullptr;
+        }
+    return 0;
+}
+
 // Full Blocks likewise: 64-lane workgroups for 132-byte rows by 64 without a cap, under one as wide as it takes.
 static int check_capped_full_blocks() {
     const struct { uint32_t cap, block; } shapes[] = {{0, 64}, {64, 256}, {1024, 256}, {2048, 256}, {2049, 128}, {4096, 128}, {4097, 64}};
@@ -574,6 +616,7 @@ int main(int argc, char **argv) {
         {"full_block_planes", check_full_block_planes},
         {"capped_odd_rows", check_capped_odd_rows},
         {"capped_full_blocks", check_capped_full_blocks},
+        {"large_odd_layers", check_large_odd_layers},
         {"caller_syncs", check_caller_syncs},
         {"row_map_under_capture", check_row_map_under_capture},
         {"row_map_on_two_streams", check_row_map_on_two_streams},
