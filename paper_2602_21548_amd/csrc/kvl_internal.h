@@ -86,7 +86,7 @@ constexpr uint32_t kLateTileBytes = 32u << 10;
 // 91.0 / 89.9, 591 MB 181 / 183).
 constexpr uint64_t kPlanesAtOnceBytes = 384u << 20;
 // Up to these, by tiles, whatever lanes suit each plane (see launch_planes):
-constexpr uint64_t kPlanesAlikeBytes = 128u << 20, kPlanesUnlikeBytes = 60u << 20;
+constexpr uint64_t kPlanesAlikeBytes = 104u << 20, kPlanesUnlikeBytes = 60u << 20;
 // Beyond this one a scatter of theirs by the row map fetches its entries as kvl_rows_kernel does (see kvl_planes_kernel),
 // or beyond kPlainReadBackBytes where rows of 16 to 63 vectors are off the lines.
 constexpr uint64_t kPlanesCachedBytes = 236u << 20;

@@ -335,11 +335,12 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
 //     and begin on lines, else 128 where that leaves clearly fewer idle over all planes (moves, us, 256 / 128: 656- and
 //     336-byte rows by 40 in runs, 199 MB, 75.0 / 67.7; 272 and 144 by 48, 205 MB, 73.4 / 69.5; 656 and 128 by 16 at random,
 //     20 MB, 10.9 / 8.5).
-//   in larger layers a plane's own lanes are worth more than the launch: they go apart where the descriptors are alike and
-//     the common lanes are more in all (kPlanesAlikeBytes; hops, together / apart: 256 and 128 by 100, 150 MB 92.3 / 90.5,
-//     333 MB 220.1 / 212.8; 656 and 336 by 64, 91 MB 61.5 / 63.6, 302 MB 189.0 / 183.9), or where they are not alike and a
-//     plane would have another width (kPlanesUnlikeBytes; moves in runs: 512 and 256 by 4, 45 MB 21.7 / 22.2, 64 MB 30.0 /
-//     29.0, 299 MB 134.2 / 119.7; 256 and 128 by 16, 60 MB 25.1 / 26.6, 200 MB 80.0 / 76.6).
+//   in larger layers a plane's own lanes are worth more than the launch.  Where the descriptors are alike (kPlanesAlikeBytes) a
+//     hop's planes go apart if the common lanes are more in all (hops, together / apart: 256 and 128 by 100, 150 MB 92.3 /
+//     90.5, 333 MB 220 / 213; 656 and 336 by 64, 91 MB 61.5 / 63.6, 302 MB 189 / 184), a move's if one would have another
+//     width (160 and 320 by 16, 84 MB 31.5 / 32, 181 MB 66.9 / 63; 320 and 640 by 8, 132 MB 49.2 / 47); so do both where they
+//     are not alike (kPlanesUnlikeBytes; moves in runs: 512 and 256 by 4, 45 MB 21.7 / 22.2, 64 MB 30.0 / 29.0, 299 MB 134 /
+//     120; 256 and 128 by 16, 60 MB 25.1 / 26.6, 200 MB 80.0 / 76.6).
 static bool launch_planes(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uint32_t plane_end, const On &on) {
     const uint32_t begin = a.plane_begin;
     if (plan->tuning.variant || plan->tuning.max_groups || plan->threads_chosen || plan->payload_bytes > kPlanesAtOnceBytes)
@@ -381,7 +382,7 @@ static bool launch_planes(const kvl_plan_t *plan, bool pack, const CopyArgs &a, 
                 own += (double)lanes(p, apart(p));
                 same = same && apart(p) == threads;
             }
-            if (alike ? shared > 1.03 * own : !same) return false;
+            if (alike && !plan->paired ? shared > 1.03 * own : !same) return false;
         }
     }
     const kvl_unit_t &first = plan->units[a.unit_begin], &last = plan->units[a.unit_begin + a.n_units - 1];

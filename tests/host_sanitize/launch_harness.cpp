@@ -463,11 +463,11 @@ static int check_planes_by_rows() {
 // Planes of unlike rows by tiles: together, with which lanes, or apart.  `average` rows of a descriptor whose largest has `rows`.
 static int check_planes_lanes() {
     const struct { bool move; uint32_t wide, narrow, rows; double average; uint32_t mib, together, lanes; } shapes[] = {
-        {false, 1024, 128, 64, 64, 380, 1, 256}, {false, 1024, 128, 64, 64, 386, 0, 0}, {false, 256, 128, 100, 100, 120, 1, 256},
-        {false, 256, 128, 100, 100, 200, 0, 0}, {false, 656, 336, 64, 64, 120, 1, 256}, {false, 656, 336, 64, 64, 300, 0, 0},
+        {false, 1024, 128, 64, 64, 380, 1, 256}, {false, 1024, 128, 64, 64, 386, 0, 0}, {false, 256, 128, 100, 100, 100, 1, 256},
+        {false, 256, 128, 100, 100, 200, 0, 0}, {false, 656, 336, 64, 64, 100, 1, 256}, {false, 656, 336, 64, 64, 300, 0, 0},
         {false, 1152, 640, 16, 16, 100, 1, 128}, {true, 1024, 128, 64, 64, 380, 1, 64}, {true, 512, 256, 8, 4.2, 45, 1, 128},
         {true, 512, 256, 8, 4.2, 64, 0, 0}, {true, 512, 1024, 4, 2.6, 300, 0, 0}, {true, 656, 336, 40, 25, 200, 1, 128},
-        {true, 656, 336, 64, 64, 100, 1, 256}, {true, 656, 336, 64, 64, 350, 0, 0}, {true, 272, 144, 48, 48, 300, 1, 128},
+        {true, 656, 336, 64, 64, 100, 1, 256}, {true, 656, 336, 64, 64, 350, 0, 0}, {true, 272, 144, 48, 48, 100, 1, 128}, {true, 160, 320, 16, 16, 100, 1, 128}, {true, 160, 320, 16, 16, 110, 0, 0}, {false, 1152, 640, 16, 16, 240, 1, 128},
         {true, 656, 128, 16, 10, 20, 1, 128}, {true, 256, 128, 16, 10.1, 40, 1, 128}, {true, 256, 128, 16, 10.1, 80, 0, 0}};
     for (const auto &q : shapes) {
         const uint64_t n = (uint64_t)(((uint64_t)q.mib << 20) / (q.average * (q.wide + q.narrow)));
