@@ -620,7 +620,9 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
     // (share of the lanes busy): 336-byte rows by 16, 31 MB, 27.9 / 24.1 / 24.3 (.67 .89 .89); 496 by 1, 9 MB, 30.9 / 20.9 /
     // 16.9 (.14 .28 .56); 48 by 100, 31 MB, 32.8 / 28.1 / 26.9 (.60 .80 .96); 2064 by 1, 45.4 / 48.4 / 42.6 (.53 .53 .71);
     // 333 by 100, 59 MB, 49.0 / 50.4 / 52.7 (.91 .96 .99); 132 by 32, 28 MB, 30.5 / 23.5 / 22.4 (.53 .71 .85); 132 and 64 by
-    // 64, 28 MB, 23.4 / 24.5 / 22.2 (.63 .78 .89).
+    // 64, 28 MB, 23.4 / 24.5 / 22.2 (.63 .78 .89).  In several planes 64 lanes or 256 (four layers, 256 / 128 / 64: 32 and 656 by
+    // 32, 73 MB, 197 / 203 / 198 (.77 .90 .98); 1152 and 128 by 16, 169 MB, 410 / 430 / 419 (.83 1 1); 144 and 352 by 64, 139
+    // MB, 337 / 344 / 337 (.86 .97 1); 132 and 64 by 64, blocks on lines, 96 MB, 285 / 249 / 242 (.77 .88 .94)).
     uint32_t threads = 256;
     if (!far_host) {
         auto busy = [&](uint64_t t) {
@@ -631,8 +633,12 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
             }
             return (double)work / (double)lanes;
         };
-        if (busy(128) > busy(threads) + 0.07) threads = 128;
-        if (busy(64) > busy(threads) + 0.09) threads = 64;
+        if (P > 1) {
+            if (busy(64) > busy(threads) + 0.17) threads = 64;
+        } else {
+            if (busy(128) > busy(threads) + 0.07) threads = 128;
+            if (busy(64) > busy(threads) + 0.09) threads = 64;
+        }
     }
     // (a cap that was asked for is meant for each plane, see kvl_tuning_t)
     const uint32_t cap = plan->tuning.max_groups ? (uint32_t)std::min<uint64_t>((uint64_t)plan->tuning.max_groups * P, UINT32_MAX)

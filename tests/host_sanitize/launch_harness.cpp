@@ -124,6 +124,19 @@ static kvl_plan_s alike(uint64_t n, uint32_t rows, uint32_t row, uint32_t planes
     return p;
 }
 
+// A plan of `n` descriptors of `rows` rows in planes of unlike rows; with a row map, made, if `map`.
+static uint32_t g_map;
+static kvl_plan_s unlike(uint64_t n, uint32_t rows, std::vector<uint32_t> row_bytes, bool map) {
+    kvl_plan_s p = alike(n, rows, row_bytes[0], (uint32_t)row_bytes.size());
+    p.payload_bytes = 0;
+    for (size_t q = 0; q < row_bytes.size(); ++q) {
+        p.layout.row_bytes[q] = row_bytes[q];
+        p.payload_bytes += p.hit_tokens * row_bytes[q];
+    }
+    if (map) p.d_row_map = &g_map;
+    return p;
+}
+
 // Odd rows: narrow workgroups are for launches that fill the machine.  Where a cap keeps them below that, they are wide.
 static int check_capped_odd_rows() {
     const struct { uint32_t cap, pack, unpack; } shapes[] = {{0, 64, 128}, {64, 256, 256}, {1023, 256, 256}, {2047, 256, 256}, {2048, 128, 128}, {4095, 128, 128},
@@ -213,6 +226,24 @@ static int check_capped_full_blocks() {
             launches.clear();                               // fewer tiles than the cap allows
             REQUIRE(fullblock_launch(&p, to_pool, 1ull << 44, 64 * 132, 0, 0, 7, kPlanes, nullptr) == KVL_OK);
             REQUIRE(launches[0].block.x == 64 && groups(launches[0]) <= 64);
+            p.d_units = nullptr;
+        }
+    return 0;
+}
+
+// Full Blocks: lanes of a tile by what idles over the planes, 128 in a single plane alone.
+static int check_full_block_lanes() {
+    const struct { uint32_t rows, a, b, lanes; } shapes[] = {{64, 1152, 0, 256}, {16, 336, 0, 128}, {100, 48, 0, 64}, {1, 2064, 0, 64}, {16, 1152, 128, 256},
+                                                              {64, 144, 352, 256}, {32, 32, 656, 64}, {64, 132, 64, 64}, {16, 656, 128, 64}, {64, 1024, 128, 256}};
+    for (const auto &q : shapes)
+        for (bool to_pool : {true, false}) {
+            kvl_plan_s p = q.b ? unlike(2000, q.rows, {q.a, q.b}, false) : alike(2000, q.rows, q.a);
+            launches.clear();
+            REQUIRE(fullblock_launch(&p, to_pool, 1ull << 44, (uint64_t)q.rows * (q.a + q.b), 0, 0, 2000, kPlanes, nullptr) == KVL_OK);
+            if (launches.size() != 1 || launches[0].block.x != q.lanes) {
+                std::printf("%u + %u by %u: %u lanes\n", q.a, q.b, q.rows, launches[0].block.x);
+                return 1;
+            }
             p.d_units = nullptr;
         }
     return 0;
@@ -425,19 +456,6 @@ static int check_tile_divisor() {
     return 0;
 }
 
-// A plan of `n` descriptors of `rows` rows in planes of unlike rows; with a row map, made, if `map`.
-static uint32_t g_map;
-static kvl_plan_s unlike(uint64_t n, uint32_t rows, std::vector<uint32_t> row_bytes, bool map) {
-    kvl_plan_s p = alike(n, rows, row_bytes[0], (uint32_t)row_bytes.size());
-    p.payload_bytes = 0;
-    for (size_t q = 0; q < row_bytes.size(); ++q) {
-        p.layout.row_bytes[q] = row_bytes[q];
-        p.payload_bytes += p.hit_tokens * row_bytes[q];
-    }
-    if (map) p.d_row_map = &g_map;
-    return p;
-}
-
 // Planes of unlike rows by the row map: beyond what the on-die cache holds the scatter looks its rows up through the scalar cache.
 static int check_planes_by_rows() {
     const struct { uint32_t wide, narrow, rows, mib, mode; } shapes[] = {
@@ -617,6 +635,7 @@ int main(int argc, char **argv) {
         {"capped_odd_rows", check_capped_odd_rows},
         {"capped_full_blocks", check_capped_full_blocks},
         {"large_odd_layers", check_large_odd_layers},
+        {"full_block_lanes", check_full_block_lanes},
         {"caller_syncs", check_caller_syncs},
         {"row_map_under_capture", check_row_map_under_capture},
         {"row_map_on_two_streams", check_row_map_on_two_streams},

@@ -12,8 +12,9 @@ CSRC = os.path.join(ROOT, "paper_2602_21548_amd", "csrc")
 ENV = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:verify_asan_link_order=0", UBSAN_OPTIONS="halt_on_error=1")
 ENV.pop("LD_PRELOAD", None)
 
-CHECKS = ["move_shapes", "full_block_planes", "capped_odd_rows", "capped_full_blocks", "large_odd_layers", "caller_syncs", "row_map_under_capture",
-          "row_map_on_two_streams", "default_stream", "cached_arrays", "ceiling_policies", "planes_by_rows", "planes_lanes", "planes_layout", "row_map_split", "tile_divisor",
+CHECKS = ["move_shapes", "full_block_planes", "capped_odd_rows", "capped_full_blocks", "large_odd_layers", "full_block_lanes",
+          "caller_syncs", "row_map_under_capture", "row_map_on_two_streams", "default_stream", "cached_arrays",
+          "ceiling_policies", "planes_by_rows", "planes_lanes", "planes_layout", "row_map_split", "tile_divisor",
           "row_map_rule"]
 
 
