@@ -648,9 +648,11 @@ struct FullBlockArgs {
 // 1.8 GB 1388 -> 1305; 656-byte rows, 58 MB, 59 -> 46.  SRC (one vector per lane): tiles begin on 128-byte lines of the
 // source, which a non-temporal load then takes out of the cache once (kvl_any_tile_kernel): blocks that begin off a line,
 // both directions, 336-byte rows by 100, 43 MB, 35.6 -> 31.2; at byte addresses, where they began on lines of the
-// destination, with nt stores out of the pool (763 by 64, 52 MB, 40.2 -> 35.7).  Across the host link the old ones stay for whole vectors (the link
-// is the bound); at byte addresses the new ones are ahead there too (out of the pool, new / old: 741-byte rows by 64, 40 MB,
-// 706 / 727; 57 by 16, 20 MB, 382 / 426; 132 by 1, 8 MB, 255 / 425; into it level).
+// destination, with nt stores out of the pool (763 by 64, 52 MB, 40.2 -> 35.7), but for blocks that begin and end on lines of
+// both sides, where sc1+nt stores are ahead (four layers, nt / sc1+nt: 1026 by 64, 144 MB, 348 / 342; 661 by 256, 169 MB, 409 /
+// 398; 200 by 16, 98 MB, 285 / 276).  Across the host link the old ones stay for whole vectors (the link is the bound); at byte
+// addresses the new ones are ahead there too (out of the pool, new / old: 741-byte rows by 64, 40 MB, 706 / 727; 57 by 16, 20 MB,
+// 382 / 426; 132 by 1, 8 MB, 255 / 425; into it level).
 template <bool TO_POOL, bool VEC, int VPT, bool NTL, int SP, bool SRC>
 __device__ __forceinline__ void fullblock_tile(const FullBlockArgs &a, uint32_t tiles_per_unit, uint32_t tile_index) {
     const uint32_t u_idx = tile_index / tiles_per_unit;

@@ -605,9 +605,10 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
     // vectors of a descriptor's plane, with those before it on its first line (none where every descriptor begins on a line:
     // whole blocks of whole lines, or rows of whole lines)
     const bool whole = !(plan->flags & KVL_TOKENS_APPEND) && plan->units.size() == plan->blocks_touched;
-    bool lines = base % 128 == 0 && block_pitch % 128 == 0 && layer_off % 128 == 0;
+    bool lines = base % 128 == 0 && block_pitch % 128 == 0 && layer_off % 128 == 0, level = lines;
     for (uint32_t p = 0; p < P; ++p) {
         const uint64_t row = plan->layout.row_bytes[p];
+        level = level && reinterpret_cast<uintptr_t>(pool_planes[p]) % 128 == 0 && bs * row % 128 == 0;
         lines = lines && reinterpret_cast<uintptr_t>(pool_planes[p]) % 128 == 0 && (row % 128 == 0 || (whole && bs * row % 128 == 0));
     }
     uint64_t vectors[KVL_MAX_PLANES] = {}, most = 0;
@@ -680,6 +681,7 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
             else KVL_FB_LAUNCH(true, true, 1, true, 2, true);
         } else {
             if (!vec && far_host) KVL_FB_LAUNCH(false, false, 1, true, 3, false);
+            else if (!vec && level) KVL_FB_LAUNCH(false, false, 1, true, 3, false);
             else if (!vec) KVL_FB_LAUNCH(false, false, 1, true, 1, true);
             else if (far_host) KVL_FB_LAUNCH(false, true, 2, true, 0, false);
             else KVL_FB_LAUNCH(false, true, 1, true, 3, true);

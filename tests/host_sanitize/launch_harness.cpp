@@ -246,6 +246,15 @@ static int check_full_block_lanes() {
             }
             p.d_units = nullptr;
         }
+    // odd rows out of the pool: on lines of the source, or written through where every block lies on lines of both sides
+    const struct { uint32_t row, rows, off; bool lines; } odd[] = {{1026, 64, 0, true}, {200, 16, 0, true}, {1026, 64, 16, false}, {1026, 64, 1, false}, {333, 64, 0, false}};
+    for (const auto &q : odd) {
+        kvl_plan_s p = alike(2000, q.rows, q.row);
+        launches.clear();
+        REQUIRE(fullblock_launch(&p, false, (1ull << 44) + q.off, q.rows * q.row, 0, 0, 2000, kPlanes, nullptr) == KVL_OK);
+        REQUIRE(is(launches[0], q.lines ? "<false, false, 1, true, 3, false>" : "<false, false, 1, true, 1, true>"));
+        p.d_units = nullptr;
+    }
     return 0;
 }
 
