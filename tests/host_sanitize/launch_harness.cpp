@@ -192,6 +192,7 @@ static int check_large_odd_layers() {
         {300, 8, 1, 70, "any_flat_kernel<true, true, 1>", "any_flat_kernel<false, true, 1>", 1024, 1024},
         {120, 32, 1, 60, "any_tile_kernel<true, true, 2, true>", "any_tile_kernel<false, false, 3, false>", 64, 256},  // 241, of whole lines
         {120, 32, 1, 70, "any_flat_kernel<true, true, 1>", "any_flat_kernel<false, true, 1>", 1024, 1024},
+        {124, 32, 1, 70, "any_flat_kernel<true, true, 1>", "any_flat_kernel<false, true, 1>", 1024, 1024},           // 249
         {70, 64, 1, 70, "any_tile_kernel<true, true, 2, true>", "any_tile_kernel<false, false, 3, false>", 64, 128}};  // 281
     for (const auto &q : shapes)
         for (bool gather : {true, false}) {

@@ -65,14 +65,32 @@ def test_odd_rows_split_over_launches_and_walked(bs, row, tuning):
     hop_at(W.tiny(940 + row, 5, bs, (row, row, 16), 120, 20 * bs), 3, 1, **tuning)
 
 
-# layers beyond what the on-die cache holds from the gather to the scatter: other cache policies, and the gather's tiles
-# begin on the source's lines.  Tiled (one and several tiles, walked) and flat, both sides off their lines
-@pytest.mark.parametrize("bs,row,tuning", [(64, 132, {}), (64, 1026, {}), (64, 132, dict(max_groups=1000)), (16, 132, {}), (1, 8065, {}), (5, 1009, {})])
+# layers that the on-die cache keeps from the gather to the scatter (plain loads), tiled, one and several tiles, and walked; flat
+# ones pass it by already, whole lines up to 256 windows among them (200 by 16 and 124 by 32; 70 by 64, 281, is tiled)
+@pytest.mark.parametrize("bs,row,tuning", [(64, 132, {}), (64, 1026, {}), (64, 132, dict(max_groups=1000)), (16, 132, {}), (1, 8065, {}), (5, 1009, {}),
+                                           (16, 200, {}), (32, 124, {}), (64, 70, {})])
 @pytest.mark.parametrize("x_off,pool_off", [(0, 0), (13, 19)])
-def test_odd_rows_of_layers_that_pass_the_cache_by(bs, row, tuning, x_off, pool_off):
+def test_odd_rows_of_layers_that_are_kept_or_dealt_out_flat(bs, row, tuning, x_off, pool_off):
     w = _uniform(3, (70 << 20) // row // 3, bs, row)
-    assert oracle.payload_bytes(w.hit, w.layout.row_bytes) > 64 << 20
+    assert 64 << 20 < oracle.payload_bytes(w.hit, w.layout.row_bytes) < 76 << 20
     hop_at(w, x_off, pool_off, **tuning)
+
+
+# layers that pass it by: walked, by 128 lanes, by lanes that the caller chose
+@pytest.mark.parametrize("bs,row,tuning", [(64, 132, dict(max_groups=1000)), (5, 1009, {}), (64, 333, dict(block_threads=512))])
+def test_odd_rows_of_layers_that_pass_the_cache_by(bs, row, tuning):
+    w = _uniform(3, (646 << 20) // row // 3, bs, row)
+    assert oracle.payload_bytes(w.hit, w.layout.row_bytes) > 640 << 20
+    hop_at(w, 13, 19, **tuning)
+
+
+# two planes of blocks of whole lines: the scatter on the destination's lines after a gather on the source's, the limit of both,
+# and the tiles of large descriptors that start late
+@pytest.mark.parametrize("row,mb", [(132, 404), (132, 576), (516, 576)])
+def test_odd_rows_in_two_planes_of_whole_lines(row, mb):
+    w = _uniform(3, (mb << 20) // row // 6, 64, row, row)
+    assert oracle.payload_bytes(w.hit, w.layout.row_bytes) > (mb - 2) << 20
+    hop_at(w, 0, 19)
 
 
 # layers that the on-die cache holds in part: both tiles begin on the source's lines, the gather's have 64 lanes, the scatter's
@@ -99,7 +117,7 @@ def test_small_descriptors_by_the_row_map(row, bs, kind, x_off):
 # planes of unlike rows in one launch, by tiles (rows of whole lines, and not; the plain loads of odd lines) or by the row map
 # (rows below and from 64 vectors), with a plane repeated; tiles of one wavefront in moves; a range of transfer rows
 @pytest.mark.parametrize("bs,rows", [(64, (1024, 128)), (64, (512, 16, 128)), (16, (2048, 656)), (64, (656, 1040)), (1, (1152, 128)),
-                                     (3, (16, 1040, 64, 1024)), (128, (128, 2048, 128)), (2, (1008, 1024))])
+                                     (3, (16, 1040, 64, 1024)), (128, (128, 2048, 128)), (2, (1008, 1024)), (40, (656, 336))])
 @pytest.mark.parametrize("x_off", [0, 48])
 def test_planes_of_unlike_rows_at_once(bs, rows, x_off):
     for kind in ("runs", "random"):
@@ -114,6 +132,14 @@ def test_planes_of_unlike_rows_at_once(bs, rows, x_off):
         torch.cuda.synchronize()
         for a, b in zip(d_dst, want):
             assert same_bytes(to_host(a), b)
+
+
+# scatters by the row map of layers beyond the on-die cache, or off the lines: rows of 5, 8, 16, 19, 32 and 41 vectors
+@pytest.mark.parametrize("bs,rows,mb", [(8, (512, 128), 238), (100, (256, 128), 238), (4, (304, 80), 116), (1, (656, 256), 116)])
+def test_planes_of_unlike_rows_of_large_layers(bs, rows, mb):
+    w = _uniform(3, (mb << 20) // sum(rows) // 3, bs, *rows)
+    assert oracle.payload_bytes(w.hit, w.layout.row_bytes) > (mb - 2) << 20
+    hop_at(w, 48)
 
 
 @pytest.mark.parametrize("bs,row,mb", [(64, 656, 118), (64, 1152, 280), (100, 656, 118), (64, 256, 280)])

@@ -134,6 +134,90 @@ def test_the_module_is_built_for_this_interpreter_and_from_the_present_sources(e
 
 
 @pytest.mark.gpu
+def test_each_argument_out_of_order_is_left_to_the_general_path():
+    """One at a time, the others in order."""
+    assert B._native is not None, "the module is not built"
+    w = W.tiny(11, 4, 16, (64,), 90, 200, n_layers=2)
+    lay = K.make_layout(2, 16, (64,), w.src.pool_blocks)
+    flags = K.KVL_GATHER | K.KVL_SCATTER | K.KVL_NO_MERGE
+    plan = K.kvl_plan(lay, w.hit, w.app, w.src.tables, flags)
+    size, count = plan.fullblock_geometry()
+    n = w.src.pool_blocks * 16 * 64
+    pool = [torch.zeros(n, dtype=torch.uint8, device="cuda")]
+    x, fb = (torch.zeros(k, dtype=torch.uint8, device="cuda") for k in (plan.payload_bytes, size * count))
+    host = torch.zeros(plan.payload_bytes, dtype=torch.uint8)
+    two = torch.zeros((2, plan.payload_bytes), dtype=torch.uint8, device="cuda").t()
+    gone = K.kvl_plan(lay, w.hit, w.app, w.src.tables, flags)
+    gone.destroy()
+
+    class Special(torch.Tensor):
+        pass
+
+    short = [pool[0][:-1]]
+    calls = [(B._fast_pack, [plan, pool, x, None], {0: [None, gone, "p"], 1: [None, [], pool * 2, short, [None], [host], iter(pool)],
+                                                     2: [None, host, two, x.as_subclass(Special), 7], 3: ["s", 1.5]}),
+             (B._fast_unpack, [plan, x, pool, None], {0: [gone], 1: [None, host, two], 2: [None, short, pool[0]], 3: ["s"]}),
+             (B._fast_to_pool, [plan, fb, 1, pool, None], {0: [gone], 1: [None, host, two], 2: [-1, 1 << 32, True, 1.0, None], 3: [short], 4: ["s"]}),
+             (B._fast_to_blocks, [plan, pool, 1, fb, None], {0: [gone], 1: [short], 2: [-1, 1 << 32, True], 3: [None, host, two], 4: ["s"]})]
+    for call, args, bad in calls:
+        assert call(*args) == K.KVL_OK, call
+        for at, values in bad.items():
+            for v in values:
+                assert call(*args[:at], v, *args[at + 1:]) == NOT_TAKEN, (call, at, v)
+        assert call(*args[:-1]) == NOT_TAKEN
+    assert B._fast_move(plan, pool, pool, None) == NOT_TAKEN            # (not a paired plan)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [(64,), (1024, 128), (132,)])
+@pytest.mark.parametrize("where", ["device", "pinned"])
+def test_full_blocks_both_ways(rows, where, monkeypatch):
+    assert B._native is not None, "the module is not built"
+    L, layer = 3, 2
+    w = W.tiny(13, 6, 16, rows, 120, 300, n_layers=L)
+    bs = w.layout.block_tokens
+    lay = K.make_layout(L, bs, rows, w.src.pool_blocks)
+    src = W.fill_pool(w, layer, "src")
+    taken = []
+    for f in ("_fast_to_pool", "_fast_to_blocks"):
+        def spied(*a, call=getattr(B, f)):
+            rc = call(*a)
+            taken.append(rc)
+            return rc
+        monkeypatch.setattr(B, f, spied)
+    for general in (False, True):
+        if general:
+            for f in ("_fast_to_pool", "_fast_to_blocks"):
+                monkeypatch.setattr(B, f, lambda *a: NOT_TAKEN)
+        g = K.kvl_plan(lay, w.hit, w.app, w.src.tables, K.KVL_GATHER | K.KVL_NO_MERGE)
+        s = K.kvl_plan(lay, w.hit, w.app, w.dst.tables, K.KVL_SCATTER | K.KVL_NO_MERGE)
+        size, count = g.fullblock_geometry()
+        want = np.full(size * count, 0x5A, dtype=np.uint8)
+        zero = np.zeros_like(w.hit)
+        oracle.pool_to_fullblocks(bs, L, rows, zero, w.hit, w.src.tables, layer, src, want)
+        want_pool = W.sentinel_pool(w, "dst")
+        oracle.fullblocks_to_pool(bs, L, rows, zero, w.hit, w.dst.tables, layer, want, want_pool)
+        blocks = torch.full((size * count,), 0x5A, dtype=torch.uint8)
+        blocks = blocks.cuda() if where == "device" else blocks.pin_memory()
+        d_src, d_dst = ([torch.from_numpy(p).cuda() for p in side] for side in (src, W.sentinel_pool(w, "dst")))
+        torch.cuda.synchronize()
+        K.kvl_pool_to_fullblocks_layer(g, d_src, layer, blocks)
+        K.kvl_fullblocks_to_pool_layer(s, blocks, layer, d_dst)
+        torch.cuda.synchronize()
+        assert blocks.cpu().numpy().tobytes() == want.tobytes()
+        assert all(np.array_equal(p.cpu().numpy(), q) for p, q in zip(d_dst, want_pool))
+        for bad in (L, 1 << 20):
+            with pytest.raises(K.KvlError) as e:
+                K.kvl_fullblocks_to_pool_layer(s, blocks, bad, d_dst)
+            assert e.value.code == K.KVL_EINVAL
+        with pytest.raises(K.KvlError) as e:
+            K.kvl_pool_to_fullblocks_layer(g, d_src, layer, blocks[:-1].clone() if where == "device" else blocks[:-1].clone().pin_memory())
+        assert e.value.code == K.KVL_ESPACE
+    assert taken.count(0) == 2
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("rows", [(64,), (1024, 128), (132,)])
 def test_both_ways_move_the_same_bytes_and_refuse_the_same(rows, monkeypatch):
     assert B._native is not None, "the module is not built"
