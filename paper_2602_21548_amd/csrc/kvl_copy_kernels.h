@@ -572,10 +572,13 @@ __device__ __forceinline__ void copy_any(uintptr_t src, uintptr_t dst, uint32_t 
 
 // Tiled: a tile is blockDim vectors; one workgroup per tile, or (the walk) gridDim.x of them walking over n_tiles.
 // Tiles begin on 128-byte lines of the destination, or (SRC) of the source: then every line of the source is read by one
-// wavefront alone.  A line that the on-die cache holds is taken out of it by a non-temporal load, so that a line shared by
-// two wavefronts is fetched from memory by the second; the stores of the two meet in the L2 instead (they must not be
-// written through: hops of 304 MB, 1026-byte rows by 64, us: gather and scatter on lines of the destination 209, of the
-// source with nt stores out of the scatter 195, with sc1+nt ones 219).
+// wavefront alone, but for those that two descriptors share.  A line that the on-die cache holds is taken out of it by a
+// non-temporal load, so that a line shared by two wavefronts is fetched from memory by the second.  Lines of the destination
+// are shared by two wavefronts instead.  A scatter's stores to them meet in the L2, which they must not be written through for
+// (hops of 304 MB, 1026-byte rows by 64, us: gather and scatter on lines of the destination 209, of the source with nt stores
+// out of the scatter 195, with sc1+nt ones 219); a gather's are written through (sc1) all the same, because they leave the
+// layer in the on-die cache for the scatter (hops, sc1 / nt stores out of the gather: 132 by 64, 197 MB, 136 / 156; 1026 by 64,
+// 305 MB, 190 / 221).
 template <bool PACK, bool NTL, int SP, bool SRC>
 __device__ __forceinline__ void any_span(const kvl_unit_t u, uintptr_t pool_base, uintptr_t xfer_base, uint32_t row, uint32_t k) {
     const uintptr_t pool = pool_base + (uint64_t)u.pool_row * row;
@@ -595,6 +598,7 @@ __global__ void __launch_bounds__(1024) kvl_any_tile_kernel(KVL_TILE_PARAMS, con
     any_span<PACK, NTL, SP, SRC>(fetch_unit(units, u_idx), pool, xfer, row, (b - u_idx * tiles_per_unit) * threads + threadIdx.x);
 }
 
+// (With as many workgroups as tiles: the form that starts late, as kvl_pack_tile_kernel does.)
 template <bool PACK, bool NTL, int SP, bool SRC>
 __global__ void __launch_bounds__(1024) kvl_any_walk_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t n_tiles) {
     const uint32_t p = a.plane_begin + blockIdx.y;

@@ -107,6 +107,10 @@ inline uint32_t launch_groups(uint64_t work, uint32_t threads, uint32_t cap, boo
 // Rows that are no multiple of a 128-byte line: up to this payload the scatter reads the transfer buffer with plain
 // loads (the on-die cache still has it), beyond it with non-temporal ones (64-token blocks of 656-byte rows, hop:
 // 100 MB 63 us against 73; 140 MB 107 against 104; 1 GB 771 against 748; 576-byte rows, 1 GB, 745 against 702).
+// The line lies where it does for callers that use one transfer buffer again and again, as an engine does: 64-token blocks of
+// 656-byte rows, hop, plain loads / nt loads by the row map, us, one layer in a loop 96 MB 57.6 / 58.3, 117 MB 69.1 / 70.1; one
+// transfer buffer and six pools in turn 57.7 / 58.5, 69.4 / 70.2; but three or four layers in turn, each with its own transfer
+// buffer, 62.5 / 58.2 and 65.2 / 58.3, 78.7 / 70.2 and 79.1 / 70.3.
 // From some GB up the plain loads, with a gather that stores past the cache, are ahead again.  Hops, us, gather sc1 and
 // scatter nt / sc1 and plain / sc1+nt and plain, in turn (runs of one form within 0.1-0.7 %): 656-byte rows 2.5 GB 1668 /
 // 1697 / 1674, 5 GB 3377 / 3386 / 3363, 12 GB 8151 / 8125 / 8081; 1040-byte rows 6 GB 3715 / 3719 / 3696, 12 GB 7706 /

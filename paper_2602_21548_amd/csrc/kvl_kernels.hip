@@ -229,7 +229,7 @@ static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, co
 //     gather to the scatter: the gather writes with sc1 stores and the scatter reads with plain loads.  Up to kReadOnceBytes
 //     both lay their tiles on the source's lines, so that the scatter's non-temporal loads take each line out of the cache
 //     once (see kvl_any_tile_kernel), and the scatter stores with nt.  Larger layers pass the cache by, both ways, and the
-//     scatter's tiles lie on the destination's lines.  The gather's tiles lie on its source's always.  Hops, three layers in
+//     scatter's tiles lie on the destination's lines.  The gather's lie on its source's, but across the host link.  Hops, three layers in
 //     turn, us, passing by / read once / kept (gather on the destination's lines): 1026-byte rows by 64, 77 MB 56 / 50 / 50,
 //     100 MB 72 / 64 / 74, 242 MB 167 / 148 / 170, 494 MB 342 / 332 / 355, 666 MB 461 / 456 / 477, 924 MB 636 / 642 / -;
 //     333 by 64, 85 MB 69 / 61 / 60, 206 MB 161 / 143 / 156, 655 MB 519 / 490 / 540.  With one layer again and again the
