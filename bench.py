@@ -253,8 +253,8 @@ def main() -> int:
     tail = None if args.only_steps else tail_return_leg(w, lay_src, lay_dst, src, dst, stream, L, WIN)
     fused = None if args.only_steps else fused_move_leg(w, lay_src, lay_dst, src, dst, stream, L, WIN, payload)
 
-    roof_pack = roof(tile_kernel("pack", payload), pack_ms)
-    roof_unpack = roof(tile_kernel("unpack", payload), unpack_ms)
+    roof_pack = roof(tile_kernel("pack"), pack_ms)
+    roof_unpack = roof(tile_kernel("unpack"), unpack_ms)
     dominant, other = (roof_pack, roof_unpack) if pack_ms.sum() >= unpack_ms.sum() else (roof_unpack, roof_pack)
 
     out = {
@@ -296,9 +296,9 @@ def main() -> int:
     return 0
 
 
-def tile_kernel(direction: str, payload: int) -> str:
-    """The kernel that the workloads' layers go through (whole vectors, long descriptors), by the size of the layer."""
-    return f"kvl_{direction}_tile_kernel" if payload > 1 << 30 else f"kvl_{direction}_quick_tile_kernel"
+def tile_kernel(direction: str) -> str:
+    """The kernel that the workloads' layers go through (whole vectors, long descriptors)."""
+    return f"kvl_{direction}_quick_tile_kernel"
 
 
 def roofline_object(config_index: int, kernel: str, ms, payload: int, linear_ceiling: float) -> dict:
@@ -516,8 +516,8 @@ def short_hop(index: int, reps: int = 8, check: bool = True, linear_ceiling: flo
            "unpack_frac_of_hbm_peak": round(2 * payload / um / 1e6 / HBM_PEAK_GBPS, 4),
            "tokens_layers_per_s": round(T / ((pm + um) * 1e-3), 1), "verified_rows_vs_oracle": verified,
            "plan_ms": round(plan_ms, 3), "descriptors": g.n_units,
-           "roofline": {"pack": roofline_object(index, tile_kernel("pack", payload), pk, payload, linear_ceiling),
-                        "unpack": roofline_object(index, tile_kernel("unpack", payload), up, payload, linear_ceiling)}}
+           "roofline": {"pack": roofline_object(index, tile_kernel("pack"), pk, payload, linear_ceiling),
+                        "unpack": roofline_object(index, tile_kernel("unpack"), up, payload, linear_ceiling)}}
     # pool to pool in one kernel (paired plan), after the hop above has been checked
     m = K.kvl_plan_pair(g, s)
     mv = []

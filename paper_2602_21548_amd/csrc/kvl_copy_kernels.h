@@ -40,8 +40,7 @@
 // scatter (sequential reads, random writes) with sc1+nt stores and non-temporal
 // loads, plain ones where rows that are not multiples of 128 bytes make neighbouring
 // wavefronts share source lines and the layer is small enough for the on-die cache
-// still to hold them (kPlainReadBackBytes), or so large that nothing of it is held
-// (kPassByBytes; the gather's stores are sc1+nt there).  Together the policies are worth 5-15 % over plain
+// still to hold them (kPlainReadBackBytes).  Together the policies are worth 5-15 % over plain
 // loads and stores.  With rows that are not multiples of 128 bytes the tiles are
 // also lined up with the destination's cache lines (worth 5-9 % on 656-byte rows).
 #pragma once
@@ -52,7 +51,6 @@ namespace kvl {
 
 // default variant codes (see the list above) and the plain copy's policies
 constexpr uint32_t kDefaultPackCode = 2u | 4u | (2u << 3);   // tile x1, nt loads, sc1 stores
-constexpr uint32_t kDefaultPackCodePassBy = 2u | 4u | (3u << 3);  // tile x1, nt loads, sc1+nt stores
 constexpr uint32_t kDefaultUnpackCode = 2u | 4u | (3u << 3);    // tile x1, nt loads, sc1+nt stores
 constexpr uint32_t kDefaultUnpackCodeOddRows = 2u | (3u << 3);  // tile x1, plain loads, sc1+nt stores
 // A move reads one pool and writes another, both in hops, and nobody reads the result at once: it writes past the caches,
@@ -65,8 +63,8 @@ constexpr uint32_t kFlatPackCode = 128u | 4u | (2u << 3);       // flat, nt load
 constexpr uint32_t kFlatUnpackCode = 128u | 4u | (1u << 3);     // flat, nt loads, nt stores
 // The tiled form's code for a plain gather or scatter; `lines`: every row begins on a 128-byte line.
 inline uint32_t default_tile_code(bool pack, bool lines, uint64_t payload) {
-    if (pack) return lines || payload < kPassByBytes ? kDefaultPackCode : kDefaultPackCodePassBy;
-    return lines || (payload > kPlainReadBackBytes && payload < kPassByBytes) ? kDefaultUnpackCode : kDefaultUnpackCodeOddRows;
+    if (pack) return kDefaultPackCode;
+    return lines || payload > kPlainReadBackBytes ? kDefaultUnpackCode : kDefaultUnpackCodeOddRows;
 }
 constexpr bool kLinearNtLoad = true;
 constexpr int kLinearStorePolicy = 2;
@@ -182,6 +180,20 @@ __device__ __forceinline__ kvl_unit_t fetch_unit(const kvl_unit_t *units, uint32
     return kvl_unit_t{d.x, d.y, d.z, d.w};
 }
 
+// The tile that workgroup b takes.  Workgroups go round the eight XCDs, each with an L2 of its own, so taken in order the tiles of
+// a block are dealt to all of them: a line that two tiles share is read by two XCDs, and every XCD works on every page.  Here an
+// XCD takes runs of 2^shift tiles one after the other (a run is kRun*Bytes long), the runs going round the XCDs, from one round to
+// the next by one place on; the tiles behind the last whole round keep their order.  `order` is the number of tiles in whole
+// rounds, a multiple of 16, with the shift in its low bits; 0 leaves the order as it is.  Hops, us, in order / in runs: 1152-byte
+// rows by 64, 149 MB 84.9 / 82.8, contiguous 2.7 GB 1580 / 1522; 656 by 64, 186 MB 110.6 / 104.7, 11 GB 6913 / 6710, contiguous
+// 4.3 GB 2849 / 2513; 2048 + 2048 by 64, 10 GB 6080 / 5943.  Runs of 16 to 64 KB are slower than any order (73,728-byte blocks,
+// 4 GB: 2 tiles 2726, 4 2661, 16 2461, 32 2425, 64 2408, 256 2459; in order 2435).
+__host__ __device__ __forceinline__ uint32_t tile_number(uint32_t b, uint32_t order) {
+    if (b >= (order & ~15u)) return b;
+    const uint32_t shift = order & 15u, i = b >> 3, round = i >> shift;
+    return (((round << 3) | ((b + round) & 7u)) << shift) | (i & ((1u << shift) - 1u));
+}
+
 // A tile of a descriptor: `threads` lanes move VPT vectors each.
 template <bool PACK, int VPT, bool NTL, int SP>
 __device__ __forceinline__ void tile_span(const kvl_unit_t u, uintptr_t pool_base, uintptr_t xfer_base, uint32_t row, uint32_t tile,
@@ -227,11 +239,11 @@ struct TileMore {                       // planes after the first of a launch
 };
 #define KVL_TILE_PARAMS                                                                                            \
     const kvl_unit_t *units, uintptr_t pool, uintptr_t xfer, uint32_t row, uint32_t tiles_per_unit, uint32_t magic, \
-        uint32_t how, uint32_t threads
+        uint32_t how, uint32_t threads, uint32_t order
 
 template <bool PACK, int VPT, bool NTL, int SP>
 __device__ __forceinline__ void tile_group(KVL_TILE_PARAMS) {
-    const uint32_t b = blockIdx.x;
+    const uint32_t b = tile_number(blockIdx.x, order);
     const uint32_t u_idx = magic ? (uint32_t)(((uint64_t)b * magic) >> 32) >> (how >> 1) : b;
     tile_span<PACK, VPT, NTL, SP>(fetch_unit(units, u_idx), pool, xfer, row, b - u_idx * tiles_per_unit, threads, how & 1u);
 }
@@ -242,7 +254,7 @@ __global__ void __launch_bounds__(1024) kvl_pack_quick_tile_kernel(KVL_TILE_PARA
         pool = more.pool[blockIdx.y - 1];
         xfer = more.xfer[blockIdx.y - 1];
     }
-    tile_group<true, VPT, NTL, SP>(units, pool, xfer, row, tiles_per_unit, magic, how, threads);
+    tile_group<true, VPT, NTL, SP>(units, pool, xfer, row, tiles_per_unit, magic, how, threads, order);
 }
 
 template <int VPT, bool NTL, int SP>
@@ -251,27 +263,7 @@ __global__ void __launch_bounds__(1024) kvl_unpack_quick_tile_kernel(KVL_TILE_PA
         pool = more.pool[blockIdx.y - 1];
         xfer = more.xfer[blockIdx.y - 1];
     }
-    tile_group<false, VPT, NTL, SP>(units, pool, xfer, row, tiles_per_unit, magic, how, threads);
-}
-
-// The same where a layer fills the machine many times over, its arguments and descriptors fetched one after the other: the
-// wavefronts of a workgroup then start their loads apart, which the memory takes better from neighbouring spans.  Hops of
-// contiguous blocks, us, so / by the form above: 656-byte rows by 64, 4.1 GB 2551 / 2792; 1280-byte rows by 128, 2.3 GB 1460 / 1485.
-template <bool PACK, int VPT, bool NTL, int SP>
-__device__ __forceinline__ void late_tile(const CopyArgs &a, uint32_t tiles_per_unit, uint32_t align_dst, uint32_t t) {
-    const uint32_t u_idx = t / tiles_per_unit, p = a.plane_begin + blockIdx.y;
-    tile_span<PACK, VPT, NTL, SP>(a.units[a.unit_begin + u_idx], a.pool[p], a.xfer[p], a.row_elems[p], t - u_idx * tiles_per_unit, blockDim.x,
-                                  align_dst);
-}
-
-template <int VPT, bool NTL, int SP>
-__global__ void __launch_bounds__(1024) kvl_pack_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t align_dst) {
-    late_tile<true, VPT, NTL, SP>(a, tiles_per_unit, align_dst, blockIdx.x);
-}
-
-template <int VPT, bool NTL, int SP>
-__global__ void __launch_bounds__(1024) kvl_unpack_tile_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t align_dst) {
-    late_tile<false, VPT, NTL, SP>(a, tiles_per_unit, align_dst, blockIdx.x);
+    tile_group<false, VPT, NTL, SP>(units, pool, xfer, row, tiles_per_unit, magic, how, threads, order);
 }
 
 // Thin form of the tiled kernels: a fixed, small number of workgroups, each walking over
@@ -282,8 +274,13 @@ __global__ void __launch_bounds__(1024) kvl_unpack_tile_kernel(const CopyArgs a,
 template <bool PACK, int VPT, bool NTL, int SP>
 __global__ void __launch_bounds__(1024) kvl_tile_walk_kernel(const CopyArgs a, uint32_t tiles_per_unit,
                                                              uint32_t align_dst, uint32_t n_tiles) {
-    // (with the descriptor in one load a streamed load of eight layers takes 15.01 ms, so 14.87)
-    for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) late_tile<PACK, VPT, NTL, SP>(a, tiles_per_unit, align_dst, t);
+    const uint32_t p = a.plane_begin + blockIdx.y;
+    for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+        // (with the descriptor in one load a streamed load of eight layers takes 15.01 ms, so 14.87)
+        const uint32_t u_idx = t / tiles_per_unit;
+        tile_span<PACK, VPT, NTL, SP>(a.units[a.unit_begin + u_idx], a.pool[p], a.xfer[p], a.row_elems[p], t - u_idx * tiles_per_unit,
+                                      blockDim.x, align_dst);
+    }
 }
 
 // Pipelined form of the tiled kernels: a fixed grid that fills the machine once (every
@@ -472,12 +469,13 @@ __device__ __forceinline__ void rows_body(const uint32_t *row_map, uintptr_t poo
 
 template <bool PACK, bool NTL, int SP, int K>
 __global__ void __launch_bounds__(1024) kvl_rows_kernel(const uint32_t *row_map, uintptr_t pool, uint32_t row_begin, uint32_t n_vecs,
-                                                        uintptr_t xfer, uint32_t row, uint32_t threads, const TileMore more) {
+                                                        uintptr_t xfer, uint32_t row, uint32_t threads, uint32_t order,
+                                                        const TileMore more) {
     if (blockIdx.y) {
         pool = more.pool[blockIdx.y - 1];
         xfer = more.xfer[blockIdx.y - 1];
     }
-    rows_body<PACK, NTL, SP, K>(row_map, pool, xfer, row, row_begin, n_vecs, blockIdx.x, threads);
+    rows_body<PACK, NTL, SP, K>(row_map, pool, xfer, row, row_begin, n_vecs, tile_number(blockIdx.x, order), threads);
 }
 
 // Planes of unlike rows in one launch, the workgroups of one plane after those of the other, each plane with its own number:
@@ -593,18 +591,18 @@ __global__ void __launch_bounds__(1024) kvl_any_tile_kernel(KVL_TILE_PARAMS, con
         pool = more.pool[blockIdx.y - 1];
         xfer = more.xfer[blockIdx.y - 1];
     }
-    const uint32_t b = blockIdx.x;
+    const uint32_t b = tile_number(blockIdx.x, order);
     const uint32_t u_idx = magic ? (uint32_t)(((uint64_t)b * magic) >> 32) >> (how >> 1) : b;
     any_span<PACK, NTL, SP, SRC>(fetch_unit(units, u_idx), pool, xfer, row, (b - u_idx * tiles_per_unit) * threads + threadIdx.x);
 }
 
-// (With as many workgroups as tiles: the form that starts late, as kvl_pack_tile_kernel does.)
+// (With as many workgroups as tiles: a form that starts late, its arguments fetched one after the other.)
 template <bool PACK, bool NTL, int SP, bool SRC>
-__global__ void __launch_bounds__(1024) kvl_any_walk_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t n_tiles) {
+__global__ void __launch_bounds__(1024) kvl_any_walk_kernel(const CopyArgs a, uint32_t tiles_per_unit, uint32_t n_tiles, uint32_t order) {
     const uint32_t p = a.plane_begin + blockIdx.y;
     const uint32_t row = a.row_elems[p];
     const uintptr_t pool = a.pool[p], xfer = a.xfer[p];
-    for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+    for (uint32_t t = tile_number(blockIdx.x, order); t < n_tiles; t += gridDim.x) {
         const uint32_t u_idx = t / tiles_per_unit;
         any_span<PACK, NTL, SP, SRC>(fetch_unit(a.units, a.unit_begin + u_idx), pool, xfer, row,
                                      (t - u_idx * tiles_per_unit) * blockDim.x + threadIdx.x);
@@ -613,10 +611,10 @@ __global__ void __launch_bounds__(1024) kvl_any_walk_kernel(const CopyArgs a, ui
 
 // Flat, as kvl_flat_kernel: m lanes per descriptor (m = the most 16-byte windows that the largest one touches).
 template <bool PACK, bool NTL, int SP>
-__global__ void __launch_bounds__(1024) kvl_any_flat_kernel(const CopyArgs a, uint32_t m) {
+__global__ void __launch_bounds__(1024) kvl_any_flat_kernel(const CopyArgs a, uint32_t m, uint32_t order) {
     const uint32_t p = a.plane_begin + blockIdx.y;
     const uint64_t row = a.row_elems[p];
-    const uint32_t g = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t g = tile_number(blockIdx.x, order) * blockDim.x + threadIdx.x;
     const uint32_t u_idx = g / m;
     if (u_idx >= a.n_units) return;
     const kvl_unit_t u = a.units[a.unit_begin + u_idx];

@@ -75,11 +75,12 @@ constexpr uint64_t kCappedLanes = 1u << 18;
 constexpr uint64_t kCachedFlatBytes = 64u << 20, kCachedLayerBytes = 76u << 20, kReadOnceBytes = 640u << 20;
 // The same for blocks of whole lines in several planes (gather, scatter), and up to which one the scatter's tiles are halved.
 constexpr uint64_t kReadOnceManyBytes = 572u << 20, kScatterOnceManyBytes = 400u << 20, kHalveBytes = 336u << 20;
-// Above this payload the tiles start late (kvl_pack_tile_kernel).  Hops of contiguous blocks, us, early / late: 2048 + 2048-byte
-// rows by 64, 765 MB 436 / 440, 1.0 GB 575 / 580; 656 by 64, 181 MB 104.8 / 106.7, 1.1 GB 734 / 734, 4.1 GB 2792 / 2551; 1280 by
-// 128, 1.1 GB 713 / 711, 2.3 GB 1485 / 1460.
-constexpr uint64_t kQuickStartBytes = 1ull << 30;
+// Odd rows in several planes: descriptors from which the gather starts late (launch_any).
 constexpr uint32_t kLateTileBytes = 32u << 10;
+// Tiles of one plane, or of planes alike: their lanes and their order by the layer's size (hop_threads, tile_run_bytes).
+constexpr uint64_t kNarrowBytes = 28u << 20, kWaveTileBytes = 512u << 20, kLongRunBytes = 288u << 20;
+constexpr uint64_t kOrderBytes = 224u << 20, kOrderBlockBytes = 48u << 10, kMoveRunBytes = 96u << 20, kMoveLongRunBytes = 1u << 30, kRowsRunBytes = 512u << 10, kOddOrderBytes = 48u << 20;
+constexpr uint64_t kFlatOrderBytes = 160u << 20, kOnDieBytes = 256u << 20, kOddRunsAgainBytes = 400u << 20;
 // Up to this payload planes of unlike rows share a launch (kvl_planes_kernel): beyond it a launch of their own is less than a
 // hundredth of their time, and each plane better off in the form that suits it (hops apart / at once, 2048- and 656-byte
 // rows by 16, 285 MB 176 / 177, 631 MB 412 / 412; 1024 and 128 by 24, 873 MB, 557 / 565; moves 512 and 528 by 128, 289 MB
@@ -111,18 +112,50 @@ inline uint32_t launch_groups(uint64_t work, uint32_t threads, uint32_t cap, boo
 // 656-byte rows, hop, plain loads / nt loads by the row map, us, one layer in a loop 96 MB 57.6 / 58.3, 117 MB 69.1 / 70.1; one
 // transfer buffer and six pools in turn 57.7 / 58.5, 69.4 / 70.2; but three or four layers in turn, each with its own transfer
 // buffer, 62.5 / 58.2 and 65.2 / 58.3, 78.7 / 70.2 and 79.1 / 70.3.
-// From some GB up the plain loads, with a gather that stores past the cache, are ahead again.  Hops, us, gather sc1 and
-// scatter nt / sc1 and plain / sc1+nt and plain, in turn (runs of one form within 0.1-0.7 %): 656-byte rows 2.5 GB 1668 /
-// 1697 / 1674, 5 GB 3377 / 3386 / 3363, 12 GB 8151 / 8125 / 8081; 1040-byte rows 6 GB 3715 / 3719 / 3696, 12 GB 7706 /
-// 7696 / 7662; 2064-byte rows 12 GB 7914 / 7921 / 7875.  (Again and again by itself the gather would lose 5 % so: its
-// reference stream 6.13 TB/s in turn with the scatter's, 5.83 alone.)
-constexpr uint64_t kPlainReadBackBytes = 112u << 20, kPassByBytes = 4ull << 30;
+constexpr uint64_t kPlainReadBackBytes = 112u << 20;
 
 // Tiles of a launch by descriptors: the default workgroup, halved where that leaves clearly fewer lanes without
 // work (32-token blocks of 656-byte rows are 5.1 tiles of 256 lanes: 5.1 TB/s; 10.3 tiles of 128 lanes: 5.8).
 inline uint32_t tile_threads(uint64_t unit_vecs) {
     auto idle = [&](uint64_t t) { return 1.0 - (double)unit_vecs / (double)((unit_vecs + t - 1) / t * t); };
     return idle(kDefaultBlockThreads) - idle(kDefaultBlockThreads / 2) > 0.07 ? kDefaultBlockThreads / 2 : kDefaultBlockThreads;
+}
+
+// Bytes of the run of tiles that one XCD takes before the next run's turn (tile_number); 0: tile by tile.  One plan for several
+// layers and one transfer buffer, us, tile by tile / runs of 128 / 256 / 512 KiB:
+//  - hops: 656-byte rows by 64, 186 MB 120 / 107 / 105 / 105, 443 MB 286 / 267 / 264 / 266, 613 MB 393 / 378 / 378 / 381; 1152 by
+//    64, 281 MB 156.6 / 154.3 / 154.3 / 153.6, 414 MB 235.7 / 235.9 / 233.4 / 235.0, 655 MB 384 / 380 / 383 / 387.
+//  - small blocks of whole lines beyond the on-die cache lose: hops, 512 by 64, 175 MB 100.6 / 98.9 / 99.3 / 99.2, 344 MB 199 / 201 /
+//    202 / 201, 2.6 GB 1681 / 1752 / 1727 / 1727; 1024 by 8, 334 MB 195 / 198 / 196 / 199, 2.6 GB 1670 / 1749 / 1719 / 1724; but 1024 by
+//    48, 587 MB 346 / 344 / 347 / 351.
+//  - moves: 656 by 64, 613 MB 194 / 192 / 191 / 191, 3.3 GB 1078 / 1067 / 1055 / 1050; 2048 + 2048 by 64, 521 MB 157 / 153 / 154 /
+//    153; 1152 by 64, 27 MB 9.9 / 9.9 / 10.0 / 10.0, 223 MB 68.2 / 68.3 / 67.9 / 68.1, 2.7 GB 805 / 819 / 812 / 804.
+inline uint64_t tile_run_bytes(const kvl_plan_s *plan, uint32_t row_bytes) {
+    const uint64_t payload = plan->payload_bytes;
+    const bool lines = row_bytes % 128 == 0;
+    const bool small_blocks = (double)plan->hit_tokens * row_bytes < (double)kOrderBlockBytes * (double)plan->units.size();
+    if (lines && small_blocks && payload > kOrderBytes) return 0;
+    if (plan->paired) return payload > kMoveLongRunBytes ? 512u << 10 : !lines || payload > kMoveRunBytes ? 256u << 10 : 0;
+    return payload <= kLongRunBytes ? 512u << 10 : payload <= kWaveTileBytes ? 256u << 10 : 128u << 10;
+}
+
+// Lanes of a hop's tiles: 128 in small layers, one wavefront where large layers go in runs, else 256 unless that leaves more of
+// them without work.  Hops, us, 256 / 128 / 64 lanes: 1152-byte rows by 64, 12.6 MB 10.1 / 10.0 / 10.3; 656 by 64, 12.9 MB 12.0 / 11.7 /
+// 12.6, 151 MB 86.2 / - / 88.8, 1.2 GB 728.5 / - / 727.8, contiguous 4.3 GB 2528 / - / 2513; 576 by 32, 112 MB 66.5 / - / 65.8, 563 MB
+// 373 / - / 362; 80 by 256, 186 MB 109.7 / - / 107.8; tile by tile 768 by 40 (7.5 tiles of 256), 665 MB 446 / 412 / 408; 1152 by 20 (5.6),
+// 655 MB 419 / 435 / 410; 1152 by 16 (4.5), 259 MB 147.7 / 147.3 / 151.1, 655 MB 413 / 408 / 406.  Descriptors that are not alike have
+// a launch of the largest one's tiles, and wide workgroups are the fewest of those that find nothing to do.
+inline uint32_t hop_threads(const kvl_plan_s *plan, uint32_t row_bytes) {
+    const uint64_t payload = plan->payload_bytes, largest = (uint64_t)plan->max_unit_rows * (row_bytes / 16);
+    const bool alike = 2ull * plan->max_unit_rows * plan->units.size() <= 3 * plan->hit_tokens;
+    const uint64_t vecs = largest + (row_bytes % 128 ? 7 : 0);         // with those before the first on its line
+    if (!alike || plan->tuning.max_groups || plan->units.size() * (vecs / 64 + 1) > INT32_MAX) return tile_threads(largest);
+    if (payload <= kNarrowBytes) return 128;
+    const bool in_runs = tile_run_bytes(plan, row_bytes) != 0, large = payload > kWaveTileBytes;
+    if (large && in_runs) return 64;
+    const uint32_t narrow = in_runs || large ? 64 : 128;
+    auto idle = [&](uint64_t t) { return 1.0 - (double)vecs / (double)((vecs + t - 1) / t * t); };
+    return idle(kDefaultBlockThreads) - idle(narrow) > (in_runs ? 0.07 : large ? 0.03 : 0.05) ? narrow : kDefaultBlockThreads;
 }
 
 // Lanes of a move's workgroups: one wavefront where the descriptors are alike and begin on lines, else as tile_threads
@@ -163,6 +196,26 @@ inline bool takes_row_map(const kvl_plan_s *plan, uint32_t row_bytes, bool pack)
     if (pack || row_bytes < 48) return false;
     const uint64_t mb = plan->payload_bytes >> 20;
     return lines ? row_bytes >= 512 && mb >= 256 && mb < 576 : plan->payload_bytes > kPlainReadBackBytes && mb < 432;
+}
+
+// The same for a launch of one plane, or of planes alike, whose tiles go to the XCDs in runs: by rows both ways where descriptors are
+// small or tiles badly filled, and the scatter of layers a little larger than the on-die cache.
+//  - hops with one plan and one transfer buffer for several layers, us, by rows, in runs as well / by tiles in runs: 272 by 16, 98 MB
+//    60.4 / 59.9, 335 MB 207 / 225; 336 by 16, 351 MB 217 / 229; 1040 by 8, 362 MB 224 / 234; 656 by 16, 181 MB 106.8 / 104.8, 1.1 GB 779 /
+//    766; 400 by 24, 189 MB 111.1 / 109.4; lines: 1152 by 4, 324 MB, in order, 191 / 194, 873 MB 567 / 570; 1024 by 8, 1.0 GB 661 / 640.
+//  - the same with the scatter by rows, its gather by tiles: 656 by 64, 368 MB 219.2 / 215.0; 272 by 100, 335 MB 202.3 / 196.8; 1152 by 64,
+//    324 MB 181.9 / 179.8.  Each layer with a plan and a transfer buffer of its own: 656 by 64, 368 MB 222 / 230; 272 by 100, 335 MB 204 /
+//    216; 1040 by 64, 362 MB 215 / 220; 1152 by 64, 324 MB 188 / 192; but 656 by 64, 181 MB 103.6 / 102.5, 613 MB 394 / 377; 2048 + 2048 by
+//    64, 521 MB 295.4 / 294.5.
+inline bool rows_ahead(const kvl_plan_s *plan, uint32_t row_bytes, bool pack) {
+    if (plan->paired || !plan->vec16 || plan->units.empty() || plan->max_unit_rows > 4096) return false;
+    const bool lines = row_bytes % 128 == 0;
+    const uint64_t row = row_bytes / 16, largest = plan->max_unit_rows * row + (lines ? 0 : 7);
+    const uint64_t t = hop_threads(plan, row_bytes), tiles = (largest + t - 1) / t;
+    const double average = (double)plan->hit_tokens * (double)row / (double)plan->units.size();
+    if (average < (lines ? 320 : 576) || average < 0.66 * (double)(tiles * t)) return true;
+    const uint64_t mb = plan->payload_bytes >> 20;
+    return !pack && row_bytes >= (lines ? 512 : 48) && mb >= 244 && mb < (lines ? 480 : 432);
 }
 
 // Cut [0, n_units) of one plane into chunks of at most chunk_bytes.

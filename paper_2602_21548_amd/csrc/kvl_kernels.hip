@@ -102,6 +102,14 @@ struct TileDivisor {
     }
 };
 
+// How a launch's workgroups take its tiles (see tile_number).
+static uint32_t tile_order(uint64_t tiles, uint64_t tile_bytes, uint64_t run_bytes) {
+    if (run_bytes == 0) return 0;
+    uint32_t shift = 1;
+    while (shift < 12 && (tile_bytes << shift) < run_bytes) ++shift;
+    return (uint32_t)(std::min<uint64_t>(tiles, INT32_MAX) >> (shift + 3) << (shift + 3)) | shift;
+}
+
 static TileMore more_planes(const CopyArgs &a, uint32_t planes) {
     TileMore more{};
     for (uint32_t q = 1; q < planes; ++q) {
@@ -114,40 +122,36 @@ static TileMore more_planes(const CopyArgs &a, uint32_t planes) {
 // n_tiles != 0: the launch has fewer workgroups than tiles and they walk over them
 template <bool PACK, int VPT, bool NTL, int SP>
 static void launch_tile_one(dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t tpu, uint32_t al,
-                            uint32_t n_tiles, bool late) {
+                            uint32_t n_tiles, uint64_t run_bytes) {
     if (n_tiles) {
         KVL_LAUNCH((kvl_tile_walk_kernel<PACK, VPT, NTL, SP>), g, b, s, a, tpu, al, n_tiles);
         return;
     }
-    if (late) {
-        if (PACK) KVL_LAUNCH((kvl_pack_tile_kernel<VPT, NTL, SP>), g, b, s, a, tpu, al);
-        else KVL_LAUNCH((kvl_unpack_tile_kernel<VPT, NTL, SP>), g, b, s, a, tpu, al);
-        return;
-    }
     const TileDivisor d(tpu);
     const uint32_t p = a.plane_begin, how = d.shift << 1 | al;
+    const uint32_t order = tile_order(g.x, 16ull * VPT * b.x, run_bytes);
     const TileMore more = more_planes(a, g.y);
     const kvl_unit_t *units = a.units + a.unit_begin;
-    if (PACK) KVL_LAUNCH((kvl_pack_quick_tile_kernel<VPT, NTL, SP>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], tpu, d.magic, how, b.x, more);
-    else KVL_LAUNCH((kvl_unpack_quick_tile_kernel<VPT, NTL, SP>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], tpu, d.magic, how, b.x, more);
+    if (PACK) KVL_LAUNCH((kvl_pack_quick_tile_kernel<VPT, NTL, SP>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], tpu, d.magic, how, b.x, order, more);
+    else KVL_LAUNCH((kvl_unpack_quick_tile_kernel<VPT, NTL, SP>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], tpu, d.magic, how, b.x, order, more);
 }
 
 template <bool PACK, int VPT, bool NTL>
 static void launch_tile_sp(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t tpu,
-                           uint32_t al, uint32_t n_tiles, bool late) {
+                           uint32_t al, uint32_t n_tiles, uint64_t run_bytes) {
     switch ((v >> 3) & 3u) {
-        case 0: launch_tile_one<PACK, VPT, NTL, 0>(g, b, s, a, tpu, al, n_tiles, late); break;
-        case 1: launch_tile_one<PACK, VPT, NTL, 1>(g, b, s, a, tpu, al, n_tiles, late); break;
-        case 2: launch_tile_one<PACK, VPT, NTL, 2>(g, b, s, a, tpu, al, n_tiles, late); break;
-        default: launch_tile_one<PACK, VPT, NTL, 3>(g, b, s, a, tpu, al, n_tiles, late); break;
+        case 0: launch_tile_one<PACK, VPT, NTL, 0>(g, b, s, a, tpu, al, n_tiles, run_bytes); break;
+        case 1: launch_tile_one<PACK, VPT, NTL, 1>(g, b, s, a, tpu, al, n_tiles, run_bytes); break;
+        case 2: launch_tile_one<PACK, VPT, NTL, 2>(g, b, s, a, tpu, al, n_tiles, run_bytes); break;
+        default: launch_tile_one<PACK, VPT, NTL, 3>(g, b, s, a, tpu, al, n_tiles, run_bytes); break;
     }
 }
 
 template <bool PACK, int VPT>
 static void launch_tile_variant(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t tpu,
-                                uint32_t al, uint32_t n_tiles, bool late) {
-    if (v & 4u) launch_tile_sp<PACK, VPT, true>(v, g, b, s, a, tpu, al, n_tiles, late);
-    else launch_tile_sp<PACK, VPT, false>(v, g, b, s, a, tpu, al, n_tiles, late);
+                                uint32_t al, uint32_t n_tiles, uint64_t run_bytes) {
+    if (v & 4u) launch_tile_sp<PACK, VPT, true>(v, g, b, s, a, tpu, al, n_tiles, run_bytes);
+    else launch_tile_sp<PACK, VPT, false>(v, g, b, s, a, tpu, al, n_tiles, run_bytes);
 }
 
 template <bool PACK, bool NTL>
@@ -201,10 +205,11 @@ static void launch_flat_variant(uint32_t v, dim3 g, dim3 b, const On &s, const C
 
 template <bool PACK, bool NTL, int SP>
 static void launch_rows(dim3 g, dim3 b, const On &s, const CopyArgs &a, const uint32_t *map, uint32_t row_begin,
-                        uint32_t n_vecs) {
+                        uint32_t n_vecs, uint64_t run_bytes) {
     const uint32_t p = a.plane_begin, row = a.row_elems[p];
     const TileMore more = more_planes(a, g.y);
-#define KVL_ROWS(K) KVL_LAUNCH((kvl_rows_kernel<PACK, NTL, SP, K>), g, b, s, map, a.pool[p], row_begin, n_vecs, a.xfer[p], row, b.x, more)
+    const uint32_t order = tile_order(g.x, 16ull * b.x, run_bytes);
+#define KVL_ROWS(K) KVL_LAUNCH((kvl_rows_kernel<PACK, NTL, SP, K>), g, b, s, map, a.pool[p], row_begin, n_vecs, a.xfer[p], row, b.x, order, more)
     if (row >= 64) KVL_ROWS(2);
     else if (row >= 32) KVL_ROWS(3);
     else if (row >= 16) KVL_ROWS(5);
@@ -213,14 +218,16 @@ static void launch_rows(dim3 g, dim3 b, const On &s, const CopyArgs &a, const ui
 }
 
 template <bool PACK, bool NTL, int SP, bool SRC>
-static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t x, uint32_t n_tiles) {
-    if (flat) KVL_LAUNCH((kvl_any_flat_kernel<PACK, NTL, SP>), g, b, s, a, x);
-    else if (walk) KVL_LAUNCH((kvl_any_walk_kernel<PACK, NTL, SP, SRC>), g, b, s, a, x, n_tiles);
+static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t x, uint32_t n_tiles,
+                           uint64_t run_bytes) {
+    const uint32_t order = tile_order(g.x, 16ull * b.x, run_bytes);
+    if (flat) KVL_LAUNCH((kvl_any_flat_kernel<PACK, NTL, SP>), g, b, s, a, x, order);
+    else if (walk) KVL_LAUNCH((kvl_any_walk_kernel<PACK, NTL, SP, SRC>), g, b, s, a, x, n_tiles, n_tiles > g.x ? 0u : order);
     else {
         const TileDivisor d(x);
         const uint32_t p = a.plane_begin;
         KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, SRC>), g, b, s, a.units + a.unit_begin, a.pool[p], a.xfer[p], a.row_elems[p], x,
-                   d.magic, d.shift << 1, b.x, more_planes(a, g.y));
+                   d.magic, d.shift << 1, b.x, order, more_planes(a, g.y));
     }
 }
 
@@ -258,6 +265,15 @@ static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, co
 //     254 MB, 512 workgroups 384 / 157, 4096 85 / 110; 333 by 64, 50 MB, 1024 42.4 / 20.4, 4096 19.6 / 20.8), and where 256
 //     lanes are not enough descriptors go flat, in workgroups of 1024, up to kAnyFlatPastWindows (hops, flat / tiled with 256:
 //     1026 by 4, 24 MB, 64 workgroups 140 / 251, 512 32.9 / 40.8, 1024 28.4 / 28.2).
+//   order (tile_number): in runs, so that wavefronts that share a line have one L2.  Moves in runs of 256 KiB, flat hops too, from
+//     kFlatOrderBytes, tiled ones above kOddOrderBytes of 512 KiB, or 128 where the layer is a little more than the on-die cache holds.
+//     Hops, three layers in turn, us, in order / runs of 64, 128, 256, 512 KiB: 132 by 64, 70 MB 45.7 / 44.0 / 44.0 / 43.7 / 43.3, 199 MB
+//     136 / 123 / 121 / 121 / 119, 340 MB 236 / 236 / 238 / 238 / 238, 1.4 GB 1048 / 1010 / 1001 / 993 / 988; 333 by 64, 340 MB 232 / 220 /
+//     222 / 225 / 226, 793 MB 626 / 573 / 565 / 566 / 566; 1026 by 64, 279 MB 171 / 168 / 168 / 171 / 175; flat, 200 by 16, 401 MB 295 / 291 / 289 /
+//     288 / 289, 21 by 64, 75 MB 74.0 / 74.1 / 74.4 / 74.1 / 75.4.  In order stay short blocks of whole lines in one plane just beyond the
+//     cache (132 by 64, 275 MB 187 / 190 / 191 / 192 / 192; with one transfer buffer for the three 203 / 187 / 184 / 185 / 185), and small
+//     layers (132 by 64, 30 MB, one transfer buffer, 23.5 / 23.6 / 24.9 / 25.9 / 27.7).  Moves: 333 by 64, 206 MB 74.1 / 69.4 / 69.1 / 68.9 /
+//     69.2, 132 by 64, 1.9 GB 663 / 640 / 632 / 626 / 624, 292 MB 96.0 / 96.4 / 96.1 / 95.8 / 95.9.
 //   moves (150 MB of 90-byte rows by 32: flat 54, tiled with 256 / 128 lanes 53 / 59) and the host link: flat up to
 //     kAnyFlatPastWindows, tiles of 256 lanes, 128 below two such tiles (1026 by 4: 377 us at 256, 286 at 128).
 //   across the host link: tiles on few workgroups (kHostSideGroups); a flat launch has as many as ever, since few of them
@@ -300,6 +316,15 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
         if (hop && cap && a.n_units * tiles_of(threads) > cap)
             while (threads < 256 && cap * threads < kCappedLanes) threads *= 2;
     }
+    uint64_t run_bytes = 0;
+    if (plan->paired) {
+        run_bytes = 256u << 10;
+    } else if (!far_host && plan->payload_bytes > (flat ? kFlatOrderBytes : kOddOrderBytes)) {
+        const bool beyond = plan->payload_bytes > kOnDieBytes;
+        if (flat) run_bytes = 256u << 10;
+        else if (!beyond || plan->payload_bytes > kWaveTileBytes) run_bytes = 512u << 10;
+        else if (!lines || share < 0.875 || unit_bytes >= kLateTileBytes || plan->payload_bytes > kOddRunsAgainBytes) run_bytes = 128u << 10;
+    }
     const uint64_t per_unit = tiles_of(threads);
     uint64_t per_launch = flat ? ((1ull << 32) - threads) / windows : (uint64_t)INT32_MAX / per_unit;
     if (flat && plan->tuning.max_groups)
@@ -317,13 +342,13 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
         const uint32_t x = (uint32_t)(flat ? windows : per_unit), n_tiles = (uint32_t)tiles;
         dim3 grid(groups, planes), block(threads);
         if (pack) {
-            if (far_host) launch_any_one<true, true, 2, false>(flat, walk, grid, block, on, part, x, n_tiles);
-            else if (kept || (once && !flat)) launch_any_one<true, true, 2, true>(flat, walk, grid, block, on, part, x, n_tiles);
-            else launch_any_one<true, true, 1, true>(flat, walk, grid, block, on, part, x, n_tiles);
+            if (far_host) launch_any_one<true, true, 2, false>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
+            else if (kept || (once && !flat)) launch_any_one<true, true, 2, true>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
+            else launch_any_one<true, true, 1, true>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
         } else {
-            if (kept) launch_any_one<false, false, 3, false>(flat, walk, grid, block, on, part, x, n_tiles);
-            else if (scatter_once) launch_any_one<false, true, 1, true>(flat, walk, grid, block, on, part, x, n_tiles);
-            else launch_any_one<false, true, 1, false>(flat, walk, grid, block, on, part, x, n_tiles);
+            if (kept) launch_any_one<false, false, 3, false>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
+            else if (scatter_once) launch_any_one<false, true, 1, true>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
+            else launch_any_one<false, true, 1, false>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
         }
     }
 }
@@ -474,8 +499,11 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
     uint32_t widest = 0;        // vectors of the largest descriptor, over the planes of this launch
     for (uint32_t p = plane_begin; p < plane_end; ++p) widest = std::max(widest, a.row_elems[p]);
     const uint64_t unit_vecs = (uint64_t)plan->max_unit_rows * widest;
-    if (vec && !plan->threads_chosen && !plan->tuning.variant)
-        threads = plan->paired ? move_threads(plan, plan->layout.row_bytes[plane_begin]) : tile_threads(unit_vecs);
+    const uint32_t row_bytes = plan->layout.row_bytes[plane_begin];
+    const uint64_t run_bytes = far_host ? 0 : tile_run_bytes(plan, row_bytes);
+    if (vec && !plan->threads_chosen && !plan->tuning.variant) {
+        threads = plan->paired ? move_threads(plan, row_bytes) : far_host ? tile_threads(unit_vecs) : hop_threads(plan, row_bytes);
+    }
     // descriptors that fill less than half a workgroup: deal the lanes out without tiles
     if (vec && !plan->tuning.variant && unit_vecs * 2 <= plan->tuning.block_threads) {
         v = plan->paired ? kFlatMoveCode : pack ? kFlatPackCode : kFlatUnpackCode;
@@ -485,19 +513,20 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
     On on(plan, stream);
     const kvl_unit_t &u_first = plan->units[unit_begin], &u_last = plan->units[unit_end - 1];
     if (vec && !plan->tuning.variant && !plan->tuning.max_groups && !far_host && plan->d_row_map &&
-        takes_row_map(plan, plan->layout.row_bytes[plane_begin], pack) && row_map_ready(plan, stream)) {
+        rows_ahead(plan, row_bytes, pack) && row_map_ready(plan, stream)) {
         // the launch is laid out over the transfer rows of these descriptors; its lanes are numbered with 32 bits
         if (!plan->threads_chosen) threads = kDefaultBlockThreads;
         const uint64_t rows = (uint64_t)u_last.xfer_row + u_last.n_rows - u_first.xfer_row;
         const uint64_t per_launch = std::max<uint64_t>(1, ((1ull << 32) - threads - 8) / widest);
-        const bool lines = plan->layout.row_bytes[plane_begin] % 128 == 0;
+        const bool lines = row_bytes % 128 == 0;
+        const uint64_t rows_run = run_bytes && !(lines && plan->payload_bytes > kOnDieBytes) ? kRowsRunBytes : 0;
         for (uint64_t first = 0; first < rows; first += per_launch) {
             const uint32_t n = (uint32_t)(std::min<uint64_t>(per_launch, rows - first) * widest);
             const uint32_t row_begin = (uint32_t)(u_first.xfer_row + first);
             dim3 grid((uint32_t)(((uint64_t)n + 7 + threads - 1) / threads), plane_end - plane_begin);
-            if (pack) launch_rows<true, true, 2>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n);
-            else if (lines) launch_rows<false, true, 3>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n);
-            else launch_rows<false, true, 1>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n);
+            if (pack) launch_rows<true, true, 2>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
+            else if (lines) launch_rows<false, true, 3>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
+            else launch_rows<false, true, 1>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
         }
     } else if (!vec) {
         launch_any(plan, pack, a, plane_end - plane_begin, far_host, on);
@@ -549,14 +578,13 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         bool walk = false;
         const uint32_t groups = launch_groups(blocks, threads, cap, &walk);
         const uint32_t n_tiles = walk ? (uint32_t)blocks : 0u;
-        const bool late = plan->payload_bytes > kQuickStartBytes;
         dim3 grid(groups, plane_end - plane_begin);
         if (pack) {
-            if (vpt == 2) launch_tile_variant<true, 2>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles, late);
-            else launch_tile_variant<true, 1>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles, late);
+            if (vpt == 2) launch_tile_variant<true, 2>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles, run_bytes);
+            else launch_tile_variant<true, 1>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles, run_bytes);
         } else {
-            if (vpt == 2) launch_tile_variant<false, 2>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles, late);
-            else launch_tile_variant<false, 1>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles, late);
+            if (vpt == 2) launch_tile_variant<false, 2>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles, run_bytes);
+            else launch_tile_variant<false, 1>(v, grid, block, on, a, (uint32_t)tpu, al, n_tiles, run_bytes);
         }
     } else {
         const uint32_t per_wg = (v & 3u) == 1u ? threads / 64 : 1;

@@ -418,10 +418,15 @@ __global__ void __launch_bounds__(256) kvl_row_map_kernel(const kvl_unit_t *unit
 // (The bounds keep its launch below 2^32 lanes.)
 static bool wants_row_map(const kvl_plan_t *plan) {
     if (plan->units.size() >= (1u << 28) || plan->hit_tokens >= (1u << 28)) return false;
+    bool unlike = false;
+    for (uint32_t p = 1; p < plan->layout.n_planes; ++p) unlike = unlike || plan->layout.row_bytes[p] != plan->layout.row_bytes[0];
     for (uint32_t p = 0; p < plan->layout.n_planes; ++p) {
         const uint32_t row = plan->layout.row_bytes[p];
-        if ((plan->flags & KVL_GATHER) && takes_row_map(plan, row, true)) return true;
-        if ((plan->flags & KVL_SCATTER) && takes_row_map(plan, row, false)) return true;
+        for (bool pack : {true, false}) {
+            if (!(plan->flags & (pack ? KVL_GATHER : KVL_SCATTER))) continue;
+            if (rows_ahead(plan, row, pack)) return true;
+            if (unlike && plan->payload_bytes <= kPlanesAtOnceBytes && takes_row_map(plan, row, pack)) return true;
+        }
     }
     return false;
 }

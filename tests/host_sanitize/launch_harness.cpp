@@ -466,6 +466,33 @@ static int check_tile_divisor() {
     return 0;
 }
 
+// Workgroups take every tile once, whatever their number, and of the whole rounds an XCD's workgroups (every eighth) take runs of
+// neighbouring tiles in their order, every XCD as many.
+static int check_tile_order() {
+    std::vector<uint32_t> counts = {1, 7, 8, 15, 16, 17, 100003};
+    for (uint32_t shift : {1u, 5u, 7u, 9u})
+        for (uint32_t rounds : {1u, 2u, 8u, 9u})
+            for (int e = -1; e <= 1; ++e) counts.push_back((rounds * 8u << shift) + e);
+    for (uint32_t tiles : counts)
+        for (uint64_t run : {0ull, 2048ull, 128ull << 10, 256ull << 10, 512ull << 10})
+            for (uint32_t lanes : {64u, 128u, 256u, 1024u}) {
+                const uint32_t order = tile_order(tiles, 16ull * lanes, run), whole = order & ~15u, length = 1u << (order & 15u);
+                REQUIRE(whole <= tiles && (run || !order) && (!run || whole % (8 * length) == 0) && (!run || tiles - whole < 8 * length));
+                REQUIRE(!run || 16ull * lanes * length == std::max<uint64_t>(run, 32ull * lanes));
+                std::vector<uint32_t> by(tiles, UINT32_MAX);
+                for (uint32_t b = 0; b < tiles; ++b) {
+                    const uint32_t t = tile_number(b, order);
+                    REQUIRE(t < tiles && by[t] == UINT32_MAX && (b < whole || t == b));
+                    by[t] = b;
+                }
+                for (uint32_t t = 0; t < whole; ++t) REQUIRE(t % length == 0 || by[t] == by[t - 1] + 8);
+                for (uint32_t t = 0; t + 8 * length <= whole; t += length)
+                    for (uint32_t k = 1; k < 8; ++k) REQUIRE(t % (8 * length) != 0 || by[t] % 8 != by[t + k * length] % 8);
+            }
+    REQUIRE(tile_order(INT32_MAX, 1024, 128u << 10) / 8 % 128 == 0);
+    return 0;
+}
+
 // Planes of unlike rows by the row map: beyond what the on-die cache holds the scatter looks its rows up through the scalar cache.
 static int check_planes_by_rows() {
     const struct { uint32_t wide, narrow, rows, mib, mode; } shapes[] = {
@@ -658,6 +685,7 @@ int main(int argc, char **argv) {
         {"row_map_split", check_row_map_split},
         {"tile_divisor", check_tile_divisor},
         {"row_map_rule", check_row_map_rule},
+        {"tile_order", check_tile_order},
     };
     if (argc != 2 || !checks.count(argv[1])) {
         for (const auto &c : checks) std::printf("%s\n", c.first.c_str());

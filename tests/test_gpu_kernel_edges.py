@@ -253,6 +253,27 @@ def test_tiles_of_layers_around_a_gibibyte(bs, rows, mb):
 
 
 # a move's own workgroups: 64 lanes, 128, and 1024 flat; descriptors around one wavefront and one workgroup
+# tiles in runs: just below, at and above whole rounds of eight runs (of 512 KiB: 1024 tiles of 256 lanes, 2048 of 128), one plane and two
+@pytest.mark.parametrize("bs,rows", [(64, (1152,)), (64, (656,)), (32, (256, 256)), (256, (80,))])
+@pytest.mark.parametrize("mb", [4, 30])
+@pytest.mark.parametrize("more", [-1, 0, 1])
+def test_tiles_around_whole_rounds(bs, rows, mb, more):
+    vectors = bs * rows[0] // 16 + (7 if rows[0] % 128 else 0)
+    threads = 128 if mb < 28 else 256
+    tiles = -(-vectors // threads)
+    per_round = (8 << 19) // (16 * threads)
+    rounds = max(1, round(mb * 2**20 / len(rows) / (8 << 19)))
+    blocks = rounds * per_round // tiles + more
+    hop_at(_uniform(1, blocks * bs, bs, *rows), 48 if rows[0] % 128 else 128)
+
+
+# the limits of run lengths, lanes and order by the layer's size
+@pytest.mark.parametrize("bs,rows,mb", [(64, (1152,), 27), (64, (1152,), 29), (64, (1152,), 287), (64, (1152,), 289), (16, (1152,), 223),
+                                        (16, (1152,), 225), (64, (656,), 511), (64, (656,), 513), (64, (2048, 2048), 513), (40, (768,), 520)])
+def test_hops_at_the_limits_of_runs_and_lanes(bs, rows, mb):
+    hop_at(_uniform(5, (mb << 20) // 5 // sum(rows), bs, *rows))
+
+
 @pytest.mark.parametrize("bs,rows", [(1, (16,)), (1, (1152,)), (1, (656, 128)), (2, (1024,)), (1, (2048,)), (1, (2064,)), (16, (1152, 656)),
                                      (64, (656,)), (3, (37,)), (64, (132, 132))])
 def test_move_launch_shapes(bs, rows):
