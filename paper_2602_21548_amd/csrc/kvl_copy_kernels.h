@@ -51,6 +51,7 @@ namespace kvl {
 
 // default variant codes (see the list above) and the plain copy's policies
 constexpr uint32_t kDefaultPackCode = 2u | 4u | (2u << 3);   // tile x1, nt loads, sc1 stores
+constexpr uint32_t kSmallPackCode = 2u | 4u;                 // tile x1, nt loads, plain stores
 constexpr uint32_t kDefaultUnpackCode = 2u | 4u | (3u << 3);    // tile x1, nt loads, sc1+nt stores
 constexpr uint32_t kDefaultUnpackCodeOddRows = 2u | (3u << 3);  // tile x1, plain loads, sc1+nt stores
 // A move reads one pool and writes another, both in hops, and nobody reads the result at once: it writes past the caches,
@@ -63,7 +64,7 @@ constexpr uint32_t kFlatPackCode = 128u | 4u | (2u << 3);       // flat, nt load
 constexpr uint32_t kFlatUnpackCode = 128u | 4u | (1u << 3);     // flat, nt loads, nt stores
 // The tiled form's code for a plain gather or scatter; `lines`: every row begins on a 128-byte line.
 inline uint32_t default_tile_code(bool pack, bool lines, uint64_t payload) {
-    if (pack) return kDefaultPackCode;
+    if (pack) return payload <= (lines ? kSmallBytes : kSmallOffLinesBytes) ? kSmallPackCode : kDefaultPackCode;
     return lines || payload > kPlainReadBackBytes ? kDefaultUnpackCode : kDefaultUnpackCodeOddRows;
 }
 constexpr bool kLinearNtLoad = true;

@@ -77,6 +77,13 @@ constexpr uint64_t kCachedFlatBytes = 64u << 20, kCachedLayerBytes = 76u << 20, 
 constexpr uint64_t kReadOnceManyBytes = 572u << 20, kScatterOnceManyBytes = 400u << 20, kHalveBytes = 336u << 20;
 // Odd rows in several planes: descriptors from which the gather starts late (launch_any).
 constexpr uint32_t kLateTileBytes = 32u << 10;
+// Up to this payload (the second of rows off the lines) the gather's stores stay in the L2 caches, 32 MB in all, for the scatter, whose
+// tiles the same XCDs take, instead of being written through.  Hops of three layers with buffers of their own in turn, us, through /
+// so: 656-byte rows by 64, 7.8 MB 8.2 / 7.1; 80 by 256, 8.5 MB 8.4 / 7.6; 333 by 64, 7.1 MB 8.0 / 7.1, 12.1 MB 11.2 / 10.8; 1152 by 16, 8.5
+// MB 7.6 / 7.2; above they lose (1152 by 64, 10.9 MB 9.2 / 9.4, 16 MB 12.3 / 13.0, 23 MB 16.2 / 17.8; 1026 by 64, 22 MB 16.5 / 17.4), but
+// with one transfer buffer for all layers, whose lines are then written again where they lie (32 layers of 1152 by 64, 20 MB, 410 /
+// 369; a layer of 656 by 64, 9.7 MB, 8.3 / 7.3, of 333 by 64, 12.1 MB, 13.2 / 9.5).  Odd rows that are dealt out flat lose everywhere.
+constexpr uint64_t kSmallBytes = 10u << 20, kSmallOffLinesBytes = 12u << 20;
 // Tiles of one plane, or of planes alike: their lanes and their order by the layer's size (hop_threads, tile_run_bytes).
 constexpr uint64_t kNarrowBytes = 28u << 20, kWaveTileBytes = 512u << 20, kLongRunBytes = 288u << 20;
 constexpr uint64_t kOrderBytes = 224u << 20, kOrderBlockBytes = 48u << 10, kMoveRunBytes = 96u << 20, kMoveLongRunBytes = 1u << 30, kRowsRunBytes = 512u << 10, kOddOrderBytes = 48u << 20;

@@ -297,6 +297,7 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
     }
     const double share = lines ? (double)widest_row / (double)row_bytes : 1.0;
     const bool of_blocks = plan->max_unit_rows <= 2ull * plan->layout.block_tokens && unit_bytes < (64u << 10);
+    const bool small = hop && !flat && plan->payload_bytes <= kSmallOffLinesBytes;
     const bool once = hop && !kept && plan->payload_bytes <= (share < 0.875 ? kReadOnceManyBytes : kReadOnceBytes);
     const bool scatter_once = once && !(share < 0.8 && of_blocks && plan->payload_bytes > kScatterOnceManyBytes);
     const bool late = hop && !kept && !once && share < 0.8 && of_blocks && unit_bytes >= kLateTileBytes;
@@ -311,6 +312,7 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
         const bool halve = busy_128 - busy_256 > 0.125;
         if (flat) threads = 1024;
         else if (!hop) threads = is_short ? 128 : 256;
+        else if (small) threads = 128;
         else if (pack && (kept || once)) threads = 64;
         else threads = halve && (is_short || kept || (scatter_once && plan->payload_bytes <= kHalveBytes)) ? 128 : 256;
         if (hop && cap && a.n_units * tiles_of(threads) > cap)
@@ -319,7 +321,7 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
     uint64_t run_bytes = 0;
     if (plan->paired) {
         run_bytes = 256u << 10;
-    } else if (!far_host && plan->payload_bytes > (flat ? kFlatOrderBytes : kOddOrderBytes)) {
+    } else if (!far_host && (small || plan->payload_bytes > (flat ? kFlatOrderBytes : kOddOrderBytes))) {
         const bool beyond = plan->payload_bytes > kOnDieBytes;
         if (flat) run_bytes = 256u << 10;
         else if (!beyond || plan->payload_bytes > kWaveTileBytes) run_bytes = 512u << 10;
@@ -342,7 +344,8 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
         const uint32_t x = (uint32_t)(flat ? windows : per_unit), n_tiles = (uint32_t)tiles;
         dim3 grid(groups, planes), block(threads);
         if (pack) {
-            if (far_host) launch_any_one<true, true, 2, false>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
+            if (small) launch_any_one<true, true, 0, true>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
+            else if (far_host) launch_any_one<true, true, 2, false>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
             else if (kept || (once && !flat)) launch_any_one<true, true, 2, true>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
             else launch_any_one<true, true, 1, true>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
         } else {
@@ -490,7 +493,7 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         bool rows_128 = true;       // every span starts on a 128-byte line of the transfer buffer
         for (uint32_t p = plane_begin; p < plane_end; ++p)
             rows_128 = rows_128 && plan->layout.row_bytes[p] % 128 == 0;
-        v = plan->paired ? kMoveCode : default_tile_code(pack, rows_128, plan->payload_bytes);
+        v = plan->paired ? kMoveCode : default_tile_code(pack, rows_128, far_host ? std::max(plan->payload_bytes, kSmallOffLinesBytes + 1) : plan->payload_bytes);
         // across the host link: two vectors per lane, so that the few workgroups of the thin
         // form (kHostSideGroups) keep enough bytes in flight
         if (far_host) v |= 3u;
@@ -524,7 +527,8 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
             const uint32_t n = (uint32_t)(std::min<uint64_t>(per_launch, rows - first) * widest);
             const uint32_t row_begin = (uint32_t)(u_first.xfer_row + first);
             dim3 grid((uint32_t)(((uint64_t)n + 7 + threads - 1) / threads), plane_end - plane_begin);
-            if (pack) launch_rows<true, true, 2>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
+            if (pack && plan->payload_bytes <= (lines ? kSmallBytes : kSmallOffLinesBytes)) launch_rows<true, true, 0>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
+            else if (pack) launch_rows<true, true, 2>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
             else if (lines) launch_rows<false, true, 3>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
             else launch_rows<false, true, 1>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
         }
@@ -908,7 +912,7 @@ int kvl_ceiling_kernel(const kvl_ceiling_t *c, const void *src, uint64_t src_byt
     // the cache policies of the default gather and scatter of such a layer
     const uint32_t v = default_tile_code(gather, c->skew_bytes == 0 && c->block_bytes % 128 == 0, bytes);
     if (gather && v == kDefaultPackCode) KVL_CEIL(true, true, 2);
-    else if (gather) KVL_CEIL(true, true, 3);
+    else if (gather) KVL_CEIL(true, true, 0);
     else if (v == kDefaultUnpackCode) KVL_CEIL(false, true, 3);
     else KVL_CEIL(false, false, 3);
 #undef KVL_CEIL

@@ -267,6 +267,16 @@ def test_tiles_around_whole_rounds(bs, rows, mb, more):
     hop_at(_uniform(1, blocks * bs, bs, *rows), 48 if rows[0] % 128 else 128)
 
 
+# layers that the gather leaves in the L2 caches and the next larger ones, by tiles, by the row map and of odd rows
+@pytest.mark.parametrize("bs,rows,mib", [(64, (1152,), 10), (64, (656,), 12), (64, (512, 512), 10), (1, (1152,), 10), (4, (656,), 12), (64, (333,), 12),
+                                         (16, (333,), 12)])
+@pytest.mark.parametrize("more", [-20000, 20000])
+def test_layers_that_stay_in_the_l2(bs, rows, mib, more):
+    w = _uniform(3, ((mib << 20) + more) // 3 // sum(rows) + 5, bs, *rows)
+    assert (oracle.payload_bytes(w.hit, w.layout.row_bytes) < mib << 20) == (more < 0)
+    hop_at(w, 0 if rows[0] % 16 else 48)
+
+
 # the limits of run lengths, lanes and order by the layer's size
 @pytest.mark.parametrize("bs,rows,mb", [(64, (1152,), 27), (64, (1152,), 29), (64, (1152,), 287), (64, (1152,), 289), (16, (1152,), 223),
                                         (16, (1152,), 225), (64, (656,), 511), (64, (656,), 513), (64, (2048, 2048), 513), (40, (768,), 520)])
