@@ -696,6 +696,10 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
     }
     // (the limit is that of tiles of 256 lanes, whatever their lanes are)
     if (a.n_units * most > (uint64_t)INT32_MAX || tpu > (uint64_t)INT32_MAX) return KVL_ERANGE;
+    // (an order of 512 KiB is level; 128 KiB are 1 % behind)
+    const uint64_t run_bytes = far_host ? 0 : 256u << 10;
+    bool quick = vec && !far_host && a.fb_elems <= UINT32_MAX;
+    for (uint32_t p = 1; p < P; ++p) quick = quick && a.row_elems[p] == a.row_elems[0];
     On on(plan, stream);
     // the tiles of all planes are numbered with 32 bits: descriptors that have more go in several launches
     const uint32_t n_all = a.n_units, per_launch = (uint32_t)(INT32_MAX / tpu);
@@ -704,8 +708,27 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
         const uint32_t n_tiles = a.n_units * (uint32_t)tpu;
         bool walk = false;
         dim3 grid(launch_groups(n_tiles, threads, cap, &walk)), block(threads);
+        if (quick && !walk) {
+            const uint32_t per_plane = (uint32_t)tpu / P, tokens = a.block_tokens;
+            const TileDivisor d(per_plane);
+            TileMore more{};
+            for (uint32_t p = 1; p < P; ++p) {
+                more.pool[p - 1] = a.pool[p];
+                more.xfer[p - 1] = a.blocks + a.layer_plane_off[p] * 16;
+            }
+            grid = dim3(n_tiles / P, P);
+#define KVL_FB_QUICK(TO_POOL) \
+            KVL_LAUNCH((kvl_fullblock_quick_kernel<TO_POOL>), grid, block, on, a.units, a.pool[0], a.blocks + a.layer_plane_off[0] * 16, (uint32_t)a.fb_elems, \
+                       a.row_elems[0], per_plane, d.magic, d.shift << 16 | threads, tokens, UINT32_MAX / tokens, tile_order(grid.x, 16ull * threads, run_bytes), more)
+            if (to_pool) KVL_FB_QUICK(true);
+            else KVL_FB_QUICK(false);
+#undef KVL_FB_QUICK
+            a.units += a.n_units;
+            continue;
+        }
+        const uint32_t order = walk ? 0u : tile_order(n_tiles, 16ull * vpt * threads, run_bytes);
 #define KVL_FB_LAUNCH(...) \
-        KVL_LAUNCH((kvl_fullblock_kernel<__VA_ARGS__>), grid, block, on, a, (uint32_t)tpu, n_tiles)
+        KVL_LAUNCH((kvl_fullblock_kernel<__VA_ARGS__>), grid, block, on, a, (uint32_t)tpu, n_tiles, order)
         if (to_pool) {
             if (!vec && far_host) KVL_FB_LAUNCH(true, false, 1, true, 2, false);
             else if (!vec) KVL_FB_LAUNCH(true, false, 1, true, 2, true);

@@ -490,6 +490,10 @@ static int check_tile_order() {
                     for (uint32_t k = 1; k < 8; ++k) REQUIRE(t % (8 * length) != 0 || by[t] % 8 != by[t + k * length] % 8);
             }
     REQUIRE(tile_order(INT32_MAX, 1024, 128u << 10) / 8 % 128 == 0);
+    // a pool row's place in its block by multiplication is the remainder, for any 32 bits
+    for (uint32_t d : {1u, 2u, 3u, 7u, 16u, 24u, 64u, 100u, 4096u, 65535u, 1000003u, 2147483647u, 2147483648u, 4294967295u})
+        for (uint32_t n : {0u, 1u, d - 1, d, d + 1, 2147483647u, 4294967295u / d * d - 1, 4294967295u / d * d, 4294967294u, 4294967295u})
+            REQUIRE(remainder_by(n, d, UINT32_MAX / d) == n % d);
     return 0;
 }
 

@@ -214,6 +214,37 @@ def test_full_blocks_planes_and_tiles(bs, rows, off, where):
         assert same_bytes(to_host(a), b), "load differs from the oracle"
 
 
+# planes alike whose tiles go in runs: below, at and above whole rounds of eight runs (of 256 KiB), ragged last blocks
+@pytest.mark.parametrize("bs,rows,blocks", [(64, (1152,), 28), (64, (1152,), 29), (64, (2048, 2048), 16), (64, (2048, 2048), 33), (100, (336, 336), 90),
+                                            (16, (336,), 400), (1, (496,), 5000), (256, (80, 80, 80, 80), 103)])
+def test_full_blocks_of_planes_alike(bs, rows, blocks):
+    L, layer = 3, 2
+    w = W.tiny(1060 + blocks, 2, bs, rows, 2 * blocks + 5, blocks // 2 * bs, kind="random", n_layers=L, allow_zero_hit=False)
+    w.hit[:] = [blocks // 2 * bs, (blocks - blocks // 2) * bs - bs // 3]
+    w.app[:] = 0
+    nb = [-(-int(h) // bs) for h in w.hit]
+    for side, seed in ((w.src, 1), (w.dst, 2)):
+        side.tables = W.make_tables(nb, side.pool_blocks, "random", np.random.Generator(np.random.PCG64(seed)))
+    g, s = dev_plan(w, "src", K.KVL_GATHER | K.KVL_NO_MERGE), dev_plan(w, "dst", K.KVL_SCATTER | K.KVL_NO_MERGE)
+    fb, count = g.fullblock_geometry()
+    assert count == blocks
+    first = np.zeros_like(w.hit)
+    src = W.fill_pool(w, layer, "src")
+    want = np.full(fb * count, 0x5A, dtype=np.uint8)
+    oracle.pool_to_fullblocks(bs, L, rows, first, w.hit, w.src.tables, layer, src, want)
+    want_pool = W.sentinel_pool(w, "dst")
+    oracle.fullblocks_to_pool(bs, L, rows, first, w.hit, w.dst.tables, layer, want, want_pool)
+    buf = torch.full((fb * count + GUARD,), 0x5A, dtype=torch.uint8, device="cuda")
+    d_src, d_dst = planes_to_dev(src), planes_to_dev(W.sentinel_pool(w, "dst"))
+    K.kvl_pool_to_fullblocks_layer(g, d_src, layer, buf[:fb * count])
+    K.kvl_fullblocks_to_pool_layer(s, buf[:fb * count], layer, d_dst)
+    torch.cuda.synchronize()
+    got = to_host(buf)
+    assert same_bytes(got[:fb * count], want) and np.all(got[fb * count:] == 0x5A), "persist differs from the oracle"
+    for a, b in zip(d_dst, want_pool):
+        assert same_bytes(to_host(a), b), "load differs from the oracle"
+
+
 # tiles of 256, 128 and 64 lanes that begin on lines of the source: spans of whole vectors that begin on a line and off it (the
 # last tile holds what the first leaves free: 249, 250 and 256 vectors), and at byte addresses, one wavefront and a byte beyond
 @pytest.mark.parametrize("bs,rows", [(16, (336,)), (1, (496,)), (100, (48,)), (3, (1328,)), (1, (3984,)), (1, (4000,)), (1, (4096, 128)), (100, (336,)),
