@@ -404,23 +404,85 @@ __global__ void __launch_bounds__(1024) kvl_tile_pipe_kernel(const CopyArgs a, u
 // Flat form for descriptors much smaller than a workgroup: the lanes of the launch are
 // dealt to the descriptors m at a time (m = max_unit_rows * row, the vectors of the
 // largest descriptor), so lane g moves vector g mod m of descriptor g div m; a shorter
-// descriptor leaves its last lanes idle.  Every lane reads its own descriptor (lanes of
-// one descriptor read the same 16 bytes).  The launcher keeps n_units * m below 2^32.
-template <bool PACK, bool NTL, int SP>
-__global__ void __launch_bounds__(1024) kvl_flat_kernel(const CopyArgs a, uint32_t max_unit_rows) {
-    const uint32_t p = a.plane_begin + blockIdx.y;
-    const uint32_t row = a.row_elems[p];
-    const uint32_t m = max_unit_rows * row;
-    const uint32_t g = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t u_idx = g / m;
-    if (u_idx >= a.n_units) return;
-    const uint32_t off = g - u_idx * m;
-    const kvl_unit_t u = a.units[a.unit_begin + u_idx];
+// descriptor leaves its last lanes idle.  The launcher keeps n_units * m below 2^31.
+// What a wavefront waits for before its data bounds it, and the instructions for that: the arguments are in registers, the
+// division is a multiplication of the wavefront's first lane, and the descriptors that its lanes lie in, at most K, come through
+// the scalar cache (m below 16: each lane loads its own).  Against a division and a load of the descriptor per lane, us: hops,
+// 130-byte rows by 16, 31 MB 28.9 / 27.7, 207 MB 170 / 162; 82 by 24, 207 MB 193 / 175; 33 by 16, 31 MB 36.7 / 34.5; 20 by 64, 207 MB 183 /
+// 165; moves, 1152 by 1, 31 MB 12.7 / 11.6, 310 MB 109.4 / 104.8; 150 by 24, 620 MB 221 / 211.
+template <int K>
+__device__ __forceinline__ void flat_pick(const kvl_unit_t *units, uint32_t last, uint32_t u_idx, uint32_t m, uint32_t at, kvl_unit_t *u,
+                                          uint32_t *off, uint32_t *nth) {
+    kvl_unit_t d[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) d[k] = fetch_unit(units, min(u_idx + (uint32_t)k, last));
+    uint32_t skip = 0;
+    *u = d[0];
+#pragma unroll
+    for (int k = 1; k < K; ++k) {
+        const bool past = at >= (uint32_t)k * m;
+        u->pool_row = past ? d[k].pool_row : u->pool_row;
+        u->xfer_row = past ? d[k].xfer_row : u->xfer_row;
+        u->n_rows = past ? d[k].n_rows : u->n_rows;
+        skip = past ? (uint32_t)k * m : skip;
+        *nth = past ? u_idx + (uint32_t)k : *nth;
+    }
+    *off = at - skip;
+}
+
+// This lane's descriptor and its place in it; false: beyond the last descriptor.  (Descriptors of less than 63 lanes, SHORT, in kernels of
+// their own: the branches cost the others 1 %.)
+constexpr uint32_t kFlatShort = 63;
+template <bool SHORT>
+__device__ __forceinline__ bool flat_unit(const kvl_unit_t *units, uint32_t n_units, uint32_t m, uint32_t magic, uint32_t shift,
+                                          uint32_t group, uint32_t threads, kvl_unit_t *u, uint32_t *off) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t first = group * threads + __builtin_amdgcn_readfirstlane(threadIdx.x - lane);
+    if (SHORT && m < 16) {
+        const uint32_t g = first + lane, u_idx = magic ? __umulhi(g, magic) >> shift : g;
+        if (u_idx >= n_units) return false;
+        *u = units[u_idx];
+        *off = g - u_idx * m;
+        return true;
+    }
+    const uint32_t u_idx = __umulhi(first, magic) >> shift;
+    if (u_idx >= n_units) return false;
+    const uint32_t at = first - u_idx * m + lane;       // below m + 63
+    uint32_t nth = u_idx;
+    if (!SHORT) flat_pick<2>(units, n_units - 1u, u_idx, m, at, u, off, &nth);
+    else if (m >= 32) flat_pick<3>(units, n_units - 1u, u_idx, m, at, u, off, &nth);
+    else flat_pick<5>(units, n_units - 1u, u_idx, m, at, u, off, &nth);
+    return nth < n_units;
+}
+#define KVL_FLAT_PARAMS                                                                                            \
+    const kvl_unit_t *units, uintptr_t pool, uintptr_t xfer, uint32_t row, uint32_t n_units, uint32_t m, uint32_t magic, \
+        uint32_t shift, uint32_t threads, uint32_t order, const TileMore more
+
+#define KVL_FLAT_KERNELS(NAME, BODY)                                                                  \
+    template <bool PACK, bool NTL, int SP>                                                            \
+    __global__ void __launch_bounds__(1024) NAME(KVL_FLAT_PARAMS) {                                   \
+        BODY<PACK, NTL, SP, false>(units, pool, xfer, row, n_units, m, magic, shift, threads, order, more);   \
+    }                                                                                                 \
+    template <bool PACK, bool NTL, int SP>                                                            \
+    __global__ void __launch_bounds__(1024) NAME##_short(KVL_FLAT_PARAMS) {                           \
+        BODY<PACK, NTL, SP, true>(units, pool, xfer, row, n_units, m, magic, shift, threads, order, more);    \
+    }
+
+template <bool PACK, bool NTL, int SP, bool SHORT>
+__device__ __forceinline__ void flat_body(KVL_FLAT_PARAMS) {
+    if (blockIdx.y) {
+        pool = more.pool[blockIdx.y - 1];
+        xfer = more.xfer[blockIdx.y - 1];
+    }
+    kvl_unit_t u;
+    uint32_t off;
+    if (!flat_unit<SHORT>(units, n_units, m, magic, shift, tile_number(blockIdx.x, order), threads, &u, &off)) return;
     if (off >= u.n_rows * row) return;
-    gsrc_t src = (gsrc_t)((PACK ? a.pool[p] : a.xfer[p]) + (uint64_t)(PACK ? u.pool_row : u.xfer_row) * row * 16u);
-    gdst_t dst = (gdst_t)((PACK ? a.xfer[p] : a.pool[p]) + (uint64_t)(PACK ? u.xfer_row : u.pool_row) * row * 16u);
+    gsrc_t src = (gsrc_t)((PACK ? pool : xfer) + (uint64_t)(PACK ? u.pool_row : u.xfer_row) * row * 16u);
+    gdst_t dst = (gdst_t)((PACK ? xfer : pool) + (uint64_t)(PACK ? u.xfer_row : u.pool_row) * row * 16u);
     store16<SP>(dst + off, load16<NTL>(src + off));
 }
+KVL_FLAT_KERNELS(kvl_flat_kernel, flat_body)
 
 // Row-map form for descriptors of a few rows: the transfer side is dense, so the launch is laid out over it
 // (lane g moves vector g of the range, lined up with the transfer buffer's 128-byte lines) and each row's
@@ -611,19 +673,21 @@ __global__ void __launch_bounds__(1024) kvl_any_walk_kernel(const CopyArgs a, ui
 }
 
 // Flat, as kvl_flat_kernel: m lanes per descriptor (m = the most 16-byte windows that the largest one touches).
-template <bool PACK, bool NTL, int SP>
-__global__ void __launch_bounds__(1024) kvl_any_flat_kernel(const CopyArgs a, uint32_t m, uint32_t order) {
-    const uint32_t p = a.plane_begin + blockIdx.y;
-    const uint64_t row = a.row_elems[p];
-    const uint32_t g = tile_number(blockIdx.x, order) * blockDim.x + threadIdx.x;
-    const uint32_t u_idx = g / m;
-    if (u_idx >= a.n_units) return;
-    const kvl_unit_t u = a.units[a.unit_begin + u_idx];
-    const uintptr_t pool = a.pool[p] + (uint64_t)u.pool_row * row;
-    const uintptr_t xfer = a.xfer[p] + (uint64_t)u.xfer_row * row;
-    const uintptr_t dst = PACK ? xfer : pool;
-    copy_any<NTL, SP>(PACK ? pool : xfer, dst, (uint32_t)(u.n_rows * row), (uint32_t)dst & 15u, g - u_idx * m);
+template <bool PACK, bool NTL, int SP, bool SHORT>
+__device__ __forceinline__ void any_flat_body(KVL_FLAT_PARAMS) {
+    if (blockIdx.y) {
+        pool = more.pool[blockIdx.y - 1];
+        xfer = more.xfer[blockIdx.y - 1];
+    }
+    kvl_unit_t u;
+    uint32_t off;
+    if (!flat_unit<SHORT>(units, n_units, m, magic, shift, tile_number(blockIdx.x, order), threads, &u, &off)) return;
+    const uintptr_t in_pool = pool + (uint64_t)u.pool_row * row;
+    const uintptr_t in_xfer = xfer + (uint64_t)u.xfer_row * row;
+    const uintptr_t dst = PACK ? in_xfer : in_pool;
+    copy_any<NTL, SP>(PACK ? in_pool : in_xfer, dst, u.n_rows * row, (uint32_t)dst & 15u, off);
 }
+KVL_FLAT_KERNELS(kvl_any_flat_kernel, any_flat_body)
 
 // Storage layout <-> paged pool for one layer.  Same tiling as above; the far
 // side is a buffer of Full Blocks ([layer, tokens, bytes] per block), so a

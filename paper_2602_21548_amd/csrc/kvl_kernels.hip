@@ -187,20 +187,30 @@ static int compute_units(int device) {
     return cached[device];
 }
 
+template <bool PACK, bool NTL, int SP>
+static void launch_flat_one(dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t m) {
+    const uint32_t p = a.plane_begin;
+    const TileDivisor d(m);
+#define KVL_FLAT(KERNEL, M, ORDER) \
+    KVL_LAUNCH((KERNEL<PACK, NTL, SP>), g, b, s, a.units + a.unit_begin, a.pool[p], a.xfer[p], a.row_elems[p], a.n_units, M, d.magic, d.shift, b.x, ORDER, more_planes(a, g.y))
+    if (m < kFlatShort) KVL_FLAT(kvl_flat_kernel_short, m, 0u);
+    else KVL_FLAT(kvl_flat_kernel, m, 0u);
+}
+
 template <bool PACK, bool NTL>
-static void launch_flat_sp(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t mur) {
+static void launch_flat_sp(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t m) {
     switch ((v >> 3) & 3u) {
-        case 0: KVL_LAUNCH((kvl_flat_kernel<PACK, NTL, 0>), g, b, s, a, mur); break;
-        case 1: KVL_LAUNCH((kvl_flat_kernel<PACK, NTL, 1>), g, b, s, a, mur); break;
-        case 2: KVL_LAUNCH((kvl_flat_kernel<PACK, NTL, 2>), g, b, s, a, mur); break;
-        default: KVL_LAUNCH((kvl_flat_kernel<PACK, NTL, 3>), g, b, s, a, mur); break;
+        case 0: launch_flat_one<PACK, NTL, 0>(g, b, s, a, m); break;
+        case 1: launch_flat_one<PACK, NTL, 1>(g, b, s, a, m); break;
+        case 2: launch_flat_one<PACK, NTL, 2>(g, b, s, a, m); break;
+        default: launch_flat_one<PACK, NTL, 3>(g, b, s, a, m); break;
     }
 }
 
 template <bool PACK>
-static void launch_flat_variant(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t mur) {
-    if (v & 4u) launch_flat_sp<PACK, true>(v, g, b, s, a, mur);
-    else launch_flat_sp<PACK, false>(v, g, b, s, a, mur);
+static void launch_flat_variant(uint32_t v, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t m) {
+    if (v & 4u) launch_flat_sp<PACK, true>(v, g, b, s, a, m);
+    else launch_flat_sp<PACK, false>(v, g, b, s, a, m);
 }
 
 template <bool PACK, bool NTL, int SP>
@@ -221,11 +231,13 @@ template <bool PACK, bool NTL, int SP, bool SRC>
 static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t x, uint32_t n_tiles,
                            uint64_t run_bytes) {
     const uint32_t order = tile_order(g.x, 16ull * b.x, run_bytes);
-    if (flat) KVL_LAUNCH((kvl_any_flat_kernel<PACK, NTL, SP>), g, b, s, a, x, order);
+    const TileDivisor d(x);
+    const uint32_t p = a.plane_begin;
+    if (flat && x < kFlatShort) KVL_FLAT(kvl_any_flat_kernel_short, x, order);
+    else if (flat) KVL_FLAT(kvl_any_flat_kernel, x, order);
+#undef KVL_FLAT
     else if (walk) KVL_LAUNCH((kvl_any_walk_kernel<PACK, NTL, SP, SRC>), g, b, s, a, x, n_tiles, n_tiles > g.x ? 0u : order);
     else {
-        const TileDivisor d(x);
-        const uint32_t p = a.plane_begin;
         KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, SRC>), g, b, s, a.units + a.unit_begin, a.pool[p], a.xfer[p], a.row_elems[p], x,
                    d.magic, d.shift << 1, b.x, order, more_planes(a, g.y));
     }
@@ -328,7 +340,7 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
         else if (!lines || share < 0.875 || unit_bytes >= kLateTileBytes || plan->payload_bytes > kOddRunsAgainBytes) run_bytes = 128u << 10;
     }
     const uint64_t per_unit = tiles_of(threads);
-    uint64_t per_launch = flat ? ((1ull << 32) - threads) / windows : (uint64_t)INT32_MAX / per_unit;
+    uint64_t per_launch = flat ? ((1ull << 31) - threads) / windows : (uint64_t)INT32_MAX / per_unit;
     if (flat && plan->tuning.max_groups)
         per_launch = std::min<uint64_t>(per_launch, (uint64_t)plan->tuning.max_groups * threads / windows);
     per_launch = std::max<uint64_t>(1, per_launch);
@@ -535,9 +547,9 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
     } else if (!vec) {
         launch_any(plan, pack, a, plane_end - plane_begin, far_host, on);
     } else if (v & 128u) {
-        // lane indices are 32 bits: split the descriptors over launches where they would not fit
+        // lane indices are 31 bits (TileDivisor): split the descriptors over launches where they would not fit
         // (tuning.max_groups, if given, lowers the workgroups per launch further)
-        uint64_t lanes_per_launch = (1ull << 32) - threads;
+        uint64_t lanes_per_launch = (1ull << 31) - threads;
         if (plan->tuning.max_groups)
             lanes_per_launch = std::min<uint64_t>(lanes_per_launch, (uint64_t)plan->tuning.max_groups * threads);
         const uint64_t per_launch = std::max<uint64_t>(1, lanes_per_launch / std::max<uint64_t>(1, unit_vecs));
@@ -547,8 +559,8 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
             part.n_units = (uint32_t)std::min<uint64_t>(per_launch, a.n_units - first);
             const uint64_t lanes = (uint64_t)part.n_units * unit_vecs;
             dim3 grid((uint32_t)((lanes + threads - 1) / threads), plane_end - plane_begin);
-            if (pack) launch_flat_variant<true>(v, grid, block, on, part, plan->max_unit_rows);
-            else launch_flat_variant<false>(v, grid, block, on, part, plan->max_unit_rows);
+            if (pack) launch_flat_variant<true>(v, grid, block, on, part, (uint32_t)unit_vecs);
+            else launch_flat_variant<false>(v, grid, block, on, part, (uint32_t)unit_vecs);
         }
     } else if ((v & 3u) >= 2u) {
         const uint32_t vpt = (v & 3u) == 3u ? 2 : 1;

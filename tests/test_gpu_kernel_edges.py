@@ -106,6 +106,21 @@ def test_odd_rows_of_layers_that_are_read_once(bs, row, mb, tuning, x_off, pool_
 
 # rows of 1, 15, 16, 31, 32, 63, 64, 65 and 72 vectors (how many rows a wavefront's 64 vectors can touch changes at
 # 16, 32 and 64), one to a few to a block, with and without chance neighbours merged into longer descriptors
+# lanes of a descriptor around the numbers from which a wavefront's lie in at most five, three and two of them
+@pytest.mark.parametrize("row", [225, 226, 481, 482, 977, 978, 994])
+@pytest.mark.parametrize("kind", ["fragmented", "runs"])
+def test_odd_rows_dealt_out_flat(row, kind):
+    hop_at(W.tiny(1700 + row, 7, 1, (row,), 333, 40, kind=kind), 13, 19)
+
+
+@pytest.mark.parametrize("lanes", [1, 15, 16, 31, 32, 62, 63, 64, 129])
+@pytest.mark.parametrize("store", [1, 3])
+def test_vectors_dealt_out_flat(lanes, store):
+    w = W.tiny(1800 + lanes, 7, 1, (16 * lanes, 16 * lanes), 333, 40, kind="fragmented")
+    hop_at(w, 16, 32, variant=1 + (128 | 4 | store << 3))
+    hop_at(w, 16, 32, variant=1 + (128 | 4 | store << 3), max_groups=3, block_threads=64)
+
+
 @pytest.mark.parametrize("row", [16, 240, 256, 496, 512, 1008, 1024, 1040, 1152])
 @pytest.mark.parametrize("bs,kind", [(1, "runs"), (1, "random"), (3, "fragmented"), (7, "runs")])
 @pytest.mark.parametrize("x_off", [0, 48])
