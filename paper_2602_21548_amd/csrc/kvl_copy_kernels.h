@@ -53,18 +53,21 @@ namespace kvl {
 constexpr uint32_t kDefaultPackCode = 2u | 4u | (2u << 3);   // tile x1, nt loads, sc1 stores
 constexpr uint32_t kSmallPackCode = 2u | 4u;                 // tile x1, nt loads, plain stores
 constexpr uint32_t kDefaultUnpackCode = 2u | 4u | (3u << 3);    // tile x1, nt loads, sc1+nt stores
+constexpr uint32_t kNtUnpackCode = 2u | 4u | (1u << 3);         // tile x1, nt loads, nt stores (see kNtScatterBytes)
 constexpr uint32_t kDefaultUnpackCodeOddRows = 2u | (3u << 3);  // tile x1, plain loads, sc1+nt stores
 // A move reads one pool and writes another, both in hops, and nobody reads the result at once: it writes past the caches,
 // in workgroups as move_threads says.  64-token blocks, us, as the gather does it / this way: 1152-byte rows, 600 MB,
 // 218 / 199 (206 with 256 lanes), 2 GB 667 / 616; 656-byte rows, 600 MB, 213 / 196, 3 GB 1142 / 1074.  Single-token
 // blocks, flat: 1152 bytes, 600 MB, 267 -> 227 with 1024 lanes and nt stores, 656 bytes, 300 MB, 145 -> 109.
 constexpr uint32_t kMoveCode = 2u | 4u | (3u << 3);             // tile x1, nt loads, sc1+nt stores
+constexpr uint32_t kNtMoveCode = 2u | 4u | (1u << 3);           // tile x1, nt loads, nt stores (see kNtMoveBytes)
 constexpr uint32_t kFlatMoveCode = 128u | 4u | (1u << 3);       // flat, nt loads, nt stores
 constexpr uint32_t kFlatPackCode = 128u | 4u | (2u << 3);       // flat, nt loads, sc1 stores
 constexpr uint32_t kFlatUnpackCode = 128u | 4u | (1u << 3);     // flat, nt loads, nt stores
 // The tiled form's code for a plain gather or scatter; `lines`: every row begins on a 128-byte line.
 inline uint32_t default_tile_code(bool pack, bool lines, uint64_t payload) {
     if (pack) return payload <= (lines ? kSmallBytes : kSmallOffLinesBytes) ? kSmallPackCode : kDefaultPackCode;
+    if (scatter_nt(lines, payload)) return kNtUnpackCode;
     return lines || payload > kPlainReadBackBytes ? kDefaultUnpackCode : kDefaultUnpackCodeOddRows;
 }
 constexpr bool kLinearNtLoad = true;
@@ -553,7 +556,7 @@ struct PlanesArgs {
     uint32_t row_begin, n_rows;                // transfer rows of the launch's descriptors
 };
 
-// SP: the stores of a gather or a move (a scatter's are sc1+nt, by the row map off lines nt).  ROWS: 0 by tiles; else by the row
+// SP: the stores (a scatter's by the row map off lines are nt).  ROWS: 0 by tiles; else by the row
 // map, the entries of rows of 16 to 63 vectors by a vector load per lane (1), or through the scalar cache as kvl_rows_kernel has
 // them (2).  The latter is better in a scatter of a layer beyond the on-die cache (512- and 16-byte rows by 256, scatter, us, 1 /
 // 2: 289 MB 99.7 / 92.1, 367 MB 121.9 / 113.8; 512 and 128 by 8, 402 MB, 134.8 / 128.4; 200 MB 59.0 / 59.3), or of one that is
@@ -573,14 +576,13 @@ __global__ void __launch_bounds__(1024) kvl_planes_kernel(const CopyArgs a, cons
     if (!ROWS) {
         const uint32_t u_idx = group / pl.per_unit[p], tile = group - u_idx * pl.per_unit[p];
         const kvl_unit_t u = fetch_unit(a.units, a.unit_begin + u_idx);
-        if (!PACK && pl.plain[p]) tile_span<PACK, 1, false, 3>(u, a.pool[p], a.xfer[p], row, tile, blockDim.x, pl.align_dst[p]);
-        else tile_span<PACK, 1, true, PACK ? SP : 3>(u, a.pool[p], a.xfer[p], row, tile, blockDim.x, pl.align_dst[p]);
+        if (!PACK && pl.plain[p]) tile_span<PACK, 1, false, SP>(u, a.pool[p], a.xfer[p], row, tile, blockDim.x, pl.align_dst[p]);
+        else tile_span<PACK, 1, true, SP>(u, a.pool[p], a.xfer[p], row, tile, blockDim.x, pl.align_dst[p]);
     } else if (PACK || row % 8 == 0) {
-        constexpr int kPolicy = PACK ? SP : 3;
-        if (row >= 64) KVL_PLANE_ROWS(kPolicy, 2);
-        else if (ROWS == 2 && row >= 32) KVL_PLANE_ROWS(kPolicy, kMid);
-        else if (ROWS == 2 && row >= 16) KVL_PLANE_ROWS(kPolicy, kShort);
-        else KVL_PLANE_ROWS(kPolicy, 0);
+        if (row >= 64) KVL_PLANE_ROWS(SP, 2);
+        else if (ROWS == 2 && row >= 32) KVL_PLANE_ROWS(SP, kMid);
+        else if (ROWS == 2 && row >= 16) KVL_PLANE_ROWS(SP, kShort);
+        else KVL_PLANE_ROWS(SP, 0);
     } else {
         if (row >= 64) KVL_PLANE_ROWS(1, 2);
         else if (ROWS == 2 && row >= 32) KVL_PLANE_ROWS(1, kMid);

@@ -84,6 +84,18 @@ constexpr uint32_t kLateTileBytes = 32u << 10;
 // with one transfer buffer for all layers, whose lines are then written again where they lie (32 layers of 1152 by 64, 20 MB, 410 /
 // 369; a layer of 656 by 64, 9.7 MB, 8.3 / 7.3, of 333 by 64, 12.1 MB, 13.2 / 9.5).  Odd rows that are dealt out flat lose everywhere.
 constexpr uint64_t kSmallBytes = 10u << 20, kSmallOffLinesBytes = 12u << 20;
+// Between these two payloads the scatter's stores of whole lines are nt ones, which the L2 caches take up, instead of sc1+nt, which
+// wait for the memory.  Hops of three layers with buffers of their own (with one buffer), us, sc1+nt / nt: 1152-byte rows by 64, 11.9 MB 9.7 /
+// 9.3 (9.0 / 9.15), 13.9 MB 11.1 / 10.5 (10.3 / 10.3), 17 MB 12.7 / 12.1 (12.2 / 11.9), 19.6 MB 14.0 / 13.75 (13.6 / 13.3), 23.2 MB 16.0 /
+// 16.0 (15.7 / 15.65), 28.9 MB 18.9 / 19.0; 1152 by 1, by the row map, 17 MB 13.2 / 12.4.  Rows off the lines lose, and planes of unlike
+// rows (1024 and 128 by 64, 13.9 MB 12.3 / 12.6).
+constexpr uint64_t kNtScatterFromBytes = 12u << 20, kNtScatterBytes = 22u << 20;
+inline bool scatter_nt(bool lines, uint64_t payload) { return lines && payload > kNtScatterFromBytes && payload <= kNtScatterBytes; }
+// Likewise a move's stores between these two.  Moves of three pairs of pools, us, sc1+nt / nt: 656-byte rows by 64, 14.5 MB 5.7 / 5.8, 20.7 MB
+// 7.7 / 7.7, 25.8 MB 9.9 / 9.4, 33 MB 12.25 / 11.5, 46.5 MB 16.4 / 15.9, 77.5 MB 25.8 / 25.4, 134 MB 43.0 / 43.0, 207 MB 64.8 / 65.5; 1152 by 64
+// 25.8 MB 9.9 / 9.3, 33 MB 12.1 / 11.4, 77.5 MB 25.2 / 24.8, 207 MB 62.9 / 63.4.
+constexpr uint64_t kNtMoveBytes = 23u << 20, kNtMoveEndBytes = 76u << 20;
+inline bool move_nt(uint64_t payload) { return payload > kNtMoveBytes && payload <= kNtMoveEndBytes; }
 // Tiles of one plane, or of planes alike: their lanes and their order by the layer's size (hop_threads, tile_run_bytes).
 constexpr uint64_t kNarrowBytes = 28u << 20, kWaveTileBytes = 512u << 20, kLongRunBytes = 288u << 20;
 constexpr uint64_t kOrderBytes = 224u << 20, kOrderBlockBytes = 48u << 10, kMoveRunBytes = 96u << 20, kMoveLongRunBytes = 1u << 30, kRowsRunBytes = 512u << 10, kOddOrderBytes = 48u << 20;

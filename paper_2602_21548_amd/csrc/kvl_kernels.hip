@@ -446,7 +446,8 @@ static bool launch_planes(const kvl_plan_t *plan, bool pack, const CopyArgs &a, 
     }
     const dim3 grid((uint32_t)groups), block(threads);
     const uint32_t *map = plan->d_row_map;
-    if (plan->paired) KVL_LAUNCH((kvl_planes_kernel<true, 3, 0>), grid, block, on, a, pl, map);
+    if (plan->paired && move_nt(plan->payload_bytes)) KVL_LAUNCH((kvl_planes_kernel<true, 1, 0>), grid, block, on, a, pl, map);
+    else if (plan->paired) KVL_LAUNCH((kvl_planes_kernel<true, 3, 0>), grid, block, on, a, pl, map);
     else if (pack && by_rows) KVL_LAUNCH((kvl_planes_kernel<true, 2, 1>), grid, block, on, a, pl, map);
     else if (pack) KVL_LAUNCH((kvl_planes_kernel<true, 2, 0>), grid, block, on, a, pl, map);
     else if (by_rows && plan->payload_bytes > (askew ? kPlainReadBackBytes : kPlanesCachedBytes)) KVL_LAUNCH((kvl_planes_kernel<false, 3, 2>), grid, block, on, a, pl, map);
@@ -505,7 +506,8 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         bool rows_128 = true;       // every span starts on a 128-byte line of the transfer buffer
         for (uint32_t p = plane_begin; p < plane_end; ++p)
             rows_128 = rows_128 && plan->layout.row_bytes[p] % 128 == 0;
-        v = plan->paired ? kMoveCode : default_tile_code(pack, rows_128, far_host ? std::max(plan->payload_bytes, kSmallOffLinesBytes + 1) : plan->payload_bytes);
+        const uint64_t payload = far_host ? std::max(plan->payload_bytes, kNtScatterBytes + 1) : plan->payload_bytes;
+        v = plan->paired ? (move_nt(payload) ? kNtMoveCode : kMoveCode) : default_tile_code(pack, rows_128, payload);
         // across the host link: two vectors per lane, so that the few workgroups of the thin
         // form (kHostSideGroups) keep enough bytes in flight
         if (far_host) v |= 3u;
@@ -541,7 +543,7 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
             dim3 grid((uint32_t)(((uint64_t)n + 7 + threads - 1) / threads), plane_end - plane_begin);
             if (pack && plan->payload_bytes <= (lines ? kSmallBytes : kSmallOffLinesBytes)) launch_rows<true, true, 0>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
             else if (pack) launch_rows<true, true, 2>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
-            else if (lines) launch_rows<false, true, 3>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
+            else if (lines && !scatter_nt(lines, plan->payload_bytes)) launch_rows<false, true, 3>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
             else launch_rows<false, true, 1>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
         }
     } else if (!vec) {
@@ -948,6 +950,7 @@ int kvl_ceiling_kernel(const kvl_ceiling_t *c, const void *src, uint64_t src_byt
     const uint32_t v = default_tile_code(gather, c->skew_bytes == 0 && c->block_bytes % 128 == 0, bytes);
     if (gather && v == kDefaultPackCode) KVL_CEIL(true, true, 2);
     else if (gather) KVL_CEIL(true, true, 0);
+    else if (v == kNtUnpackCode) KVL_CEIL(false, true, 1);
     else if (v == kDefaultUnpackCode) KVL_CEIL(false, true, 3);
     else KVL_CEIL(false, false, 3);
 #undef KVL_CEIL

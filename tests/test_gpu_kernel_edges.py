@@ -333,7 +333,26 @@ def test_hops_at_the_limits_of_runs_and_lanes(bs, rows, mb):
 @pytest.mark.parametrize("bs,rows", [(1, (16,)), (1, (1152,)), (1, (656, 128)), (2, (1024,)), (1, (2048,)), (1, (2064,)), (16, (1152, 656)),
                                      (64, (656,)), (3, (37,)), (64, (132, 132))])
 def test_move_launch_shapes(bs, rows):
-    w = W.tiny(1080 + bs + sum(rows), 6, bs, rows, 200, 20 * bs, kind="runs" if bs % 2 else "random")
+    move_of(W.tiny(1080 + bs + sum(rows), 6, bs, rows, 200, 20 * bs, kind="runs" if bs % 2 else "random"))
+
+
+# the sizes between which scatters and moves store otherwise
+@pytest.mark.parametrize("bs,rows", [(64, (1152,)), (8, (256,)), (64, (656,)), (64, (1024, 128))])
+@pytest.mark.parametrize("mib", [12, 22])
+@pytest.mark.parametrize("more", [-20000, 20000])
+def test_hops_at_the_limits_of_the_scatters_stores(bs, rows, mib, more):
+    hop_at(_uniform(3, ((mib << 20) + more) // 3 // sum(rows) + 5, bs, *rows))
+
+
+@pytest.mark.parametrize("bs,rows", [(64, (1152,)), (64, (656,)), (64, (1024, 128))])
+@pytest.mark.parametrize("mib", [23, 76])
+@pytest.mark.parametrize("more", [-20000, 20000])
+def test_moves_at_the_limits_of_their_stores(bs, rows, mib, more):
+    move_of(_uniform(3, ((mib << 20) + more) // 3 // sum(rows) + 5, bs, *rows))
+
+
+def move_of(w):
+    bs, rows = w.layout.block_tokens, w.layout.row_bytes
     src = W.fill_pool(w, 0, "src")
     x = oracle.pack(bs, rows, w.hit, w.src.tables, src)
     want = W.sentinel_pool(w, "dst")
