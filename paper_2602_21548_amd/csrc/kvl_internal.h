@@ -98,7 +98,7 @@ constexpr uint64_t kNtMoveBytes = 23u << 20, kNtMoveEndBytes = 76u << 20;
 inline bool move_nt(uint64_t payload) { return payload > kNtMoveBytes && payload <= kNtMoveEndBytes; }
 // Tiles of one plane, or of planes alike: their lanes and their order by the layer's size (hop_threads, tile_run_bytes).
 constexpr uint64_t kNarrowBytes = 28u << 20, kWaveTileBytes = 512u << 20, kLongRunBytes = 288u << 20;
-constexpr uint64_t kOrderBytes = 224u << 20, kOrderBlockBytes = 48u << 10, kMoveRunBytes = 96u << 20, kMoveLongRunBytes = 1u << 30, kRowsRunBytes = 512u << 10, kOddOrderBytes = 48u << 20;
+constexpr uint64_t kOrderBytes = 224u << 20, kOrderBlockBytes = 48u << 10, kVeryLongRunBlockBytes = 14u << 10, kMoveRunBytes = 96u << 20, kMoveLongRunBytes = 1u << 30, kRowsRunBytes = 512u << 10, kOddOrderBytes = 48u << 20;
 constexpr uint64_t kFlatOrderBytes = 160u << 20, kOnDieBytes = 256u << 20, kOddRunsAgainBytes = 400u << 20;
 // Up to this payload planes of unlike rows share a launch (kvl_planes_kernel): beyond it a launch of their own is less than a
 // hundredth of their time, and each plane better off in the form that suits it (hops apart / at once, 2048- and 656-byte
@@ -147,14 +147,19 @@ inline uint32_t tile_threads(uint64_t unit_vecs) {
 //  - small blocks of whole lines beyond the on-die cache lose: hops, 512 by 64, 175 MB 100.6 / 98.9 / 99.3 / 99.2, 344 MB 199 / 201 /
 //    202 / 201, 2.6 GB 1681 / 1752 / 1727 / 1727; 1024 by 8, 334 MB 195 / 198 / 196 / 199, 2.6 GB 1670 / 1749 / 1719 / 1724; but 1024 by
 //    48, 587 MB 346 / 344 / 347 / 351.
+//  - short blocks off the lines in large layers like them longest: hops with buffers of their own, runs of 128 / 512 / 1024 / 2048 KiB, 400 by
+//    24, 620 MB 418 / 409 / 405 / 406, 2.6 GB 1775 / 1754 / 1746 / 1749; 176 by 64, 620 MB 419 / 411 / 408 / 407, 5.2 GB 3479 / 3466 / 3455 /
+//    3456; 272 by 64 (17 KB), 2.6 GB 1766 / 1782 / 1779 / 1785; 656 by 64, 1.0 GB 642 / 648 / 651 / 652.
 //  - moves: 656 by 64, 613 MB 194 / 192 / 191 / 191, 3.3 GB 1078 / 1067 / 1055 / 1050; 2048 + 2048 by 64, 521 MB 157 / 153 / 154 /
 //    153; 1152 by 64, 27 MB 9.9 / 9.9 / 10.0 / 10.0, 223 MB 68.2 / 68.3 / 67.9 / 68.1, 2.7 GB 805 / 819 / 812 / 804.
 inline uint64_t tile_run_bytes(const kvl_plan_s *plan, uint32_t row_bytes) {
     const uint64_t payload = plan->payload_bytes;
     const bool lines = row_bytes % 128 == 0;
-    const bool small_blocks = (double)plan->hit_tokens * row_bytes < (double)kOrderBlockBytes * (double)plan->units.size();
+    const double descriptor_bytes = (double)plan->hit_tokens * row_bytes / (double)plan->units.size();
+    const bool small_blocks = descriptor_bytes < (double)kOrderBlockBytes;
     if (lines && small_blocks && payload > kOrderBytes) return 0;
     if (plan->paired) return payload > kMoveLongRunBytes ? 512u << 10 : !lines || payload > kMoveRunBytes ? 256u << 10 : 0;
+    if (payload > kWaveTileBytes && descriptor_bytes < (double)kVeryLongRunBlockBytes) return 1u << 20;
     return payload <= kLongRunBytes ? 512u << 10 : payload <= kWaveTileBytes ? 256u << 10 : 128u << 10;
 }
 

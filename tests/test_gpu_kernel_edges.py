@@ -330,6 +330,12 @@ def test_hops_at_the_limits_of_runs_and_lanes(bs, rows, mb):
     hop_at(_uniform(5, (mb << 20) // 5 // sum(rows), bs, *rows))
 
 
+# runs of 1 MiB: short blocks off the lines, above half a GiB (64 rounds of 8 MiB and a rest)
+@pytest.mark.parametrize("bs,row", [(64, 176), (24, 400)])
+def test_short_blocks_of_large_layers_in_long_runs(bs, row):
+    hop_at(_uniform(5, (517 << 20) // 5 // row + 77, bs, row), 48)
+
+
 @pytest.mark.parametrize("bs,rows", [(1, (16,)), (1, (1152,)), (1, (656, 128)), (2, (1024,)), (1, (2048,)), (1, (2064,)), (16, (1152, 656)),
                                      (64, (656,)), (3, (37,)), (64, (132, 132))])
 def test_move_launch_shapes(bs, rows):
