@@ -706,7 +706,14 @@ struct FullBlockArgs {
     uint64_t fb_elems;                         // elements per Full Block
     uint64_t layer_plane_off[KVL_MAX_PLANES];  // element offset of (layer, plane) inside a Full Block
     uint32_t tile_end[KVL_MAX_PLANES];         // tiles of a descriptor up to and with this plane
+    uint32_t magic, shift, tokens_magic;       // division by a descriptor's tiles (TileDivisor) and by block_tokens (remainder_by)
 };
+
+// n mod d, with magic = floor((2^32 - 1) / d): the quotient by multiplication is right or one too small, for any 32 bits.
+__host__ __device__ __forceinline__ uint32_t remainder_by(uint32_t n, uint32_t d, uint32_t magic) {
+    const uint32_t r = n - (uint32_t)(((uint64_t)n * magic) >> 32) * d;
+    return r >= d ? r - d : r;
+}
 
 // A tile is VPT * blockDim vectors of a descriptor's plane; lane t takes vectors t, t + blockDim, ...  of it, all loads
 // before the first store.  VEC: whole 16-byte vectors; else any byte addresses, one vector per lane (copy_any).
@@ -722,22 +729,24 @@ struct FullBlockArgs {
 // 398; 200 by 16, 98 MB, 285 / 276).  Across the host link the old ones stay for whole vectors (the link is the bound); at byte
 // addresses the new ones are ahead there too (out of the pool, new / old: 741-byte rows by 64, 40 MB, 706 / 727; 57 by 16, 20 MB,
 // 382 / 426; 132 by 1, 8 MB, 255 / 425; into it level).
+// The descriptor comes in one load and by multiplications; both directions of four layers of 16, us, with divisions and a load of each field /
+// so: 1024- and 128-byte rows by 64, 13.7 MB 48.2 / 46.1, 51 MB 131 / 129; by 1, 26 MB 96.3 / 93.0; 132 by 64, 13.7 MB 49.5 / 47.1.
 template <bool TO_POOL, bool VEC, int VPT, bool NTL, int SP, bool SRC>
 __device__ __forceinline__ void fullblock_tile(const FullBlockArgs &a, uint32_t tiles_per_unit, uint32_t tile_index) {
-    const uint32_t u_idx = tile_index / tiles_per_unit;
+    const uint32_t u_idx = a.magic ? (uint32_t)(((uint64_t)tile_index * a.magic) >> 32) >> a.shift : tile_index;
     uint32_t tile = tile_index - u_idx * tiles_per_unit;
-    const cunits_t u = (cunits_t)(uintptr_t)a.units + u_idx;
+    const kvl_unit_t u = fetch_unit(a.units, u_idx);
     // a descriptor's tiles are those of its planes one after the other, each plane its own number of them
     uint32_t p = 0;
 #pragma unroll
     for (uint32_t q = 0; q + 1 < KVL_MAX_PLANES; ++q) p += tile >= a.tile_end[q] ? 1u : 0u;
     tile -= p ? a.tile_end[p - 1] : 0u;
-    const uint32_t row = a.row_elems[p], pool_row = u->pool_row;
-    const uint32_t n = u->n_rows * row;
+    const uint32_t row = a.row_elems[p], pool_row = u.pool_row;
+    const uint32_t n = u.n_rows * row;
     const uint32_t first = tile * (blockDim.x * VPT) + threadIdx.x;
-    const uint32_t within = pool_row % a.block_tokens;
+    const uint32_t within = remainder_by(pool_row, a.block_tokens, a.tokens_magic);
     const uint64_t in_pool = (uint64_t)pool_row * row;
-    const uint64_t in_blocks = (uint64_t)u->block_index * a.fb_elems + a.layer_plane_off[p] + (uint64_t)within * row;
+    const uint64_t in_blocks = (uint64_t)u.block_index * a.fb_elems + a.layer_plane_off[p] + (uint64_t)within * row;
     if (VEC) {
         gsrc_t src = TO_POOL ? (gsrc_t)a.blocks + in_blocks : (gsrc_t)a.pool[p] + in_pool;
         gdst_t dst = TO_POOL ? (gdst_t)a.pool[p] + in_pool : (gdst_t)a.blocks + in_blocks;
@@ -771,12 +780,6 @@ __global__ void __launch_bounds__(256) kvl_fullblock_kernel(const FullBlockArgs 
                                                             uint32_t n_tiles, uint32_t order) {
     for (uint32_t t = tile_number(blockIdx.x, order); t < n_tiles; t += gridDim.x)
         fullblock_tile<TO_POOL, VEC, VPT, NTL, SP, SRC>(a, tiles_per_unit, t);
-}
-
-// n mod d, with magic = floor((2^32 - 1) / d): the quotient by multiplication is right or one too small, for any 32 bits.
-__host__ __device__ __forceinline__ uint32_t remainder_by(uint32_t n, uint32_t d, uint32_t magic) {
-    const uint32_t r = n - (uint32_t)(((uint64_t)n * magic) >> 32) * d;
-    return r >= d ? r - d : r;
 }
 
 // Planes alike, of whole vectors in device memory: the first one's arguments in registers (`blocks`: its part of the first Full Block),

@@ -714,6 +714,10 @@ int fullblock_launch(const kvl_plan_t *plan, bool to_pool, uintptr_t base, uint6
     const uint64_t run_bytes = far_host ? 0 : 256u << 10;
     bool quick = vec && !far_host && a.fb_elems <= UINT32_MAX;
     for (uint32_t p = 1; p < P; ++p) quick = quick && a.row_elems[p] == a.row_elems[0];
+    const TileDivisor by_tiles((uint32_t)tpu);
+    a.magic = by_tiles.magic;
+    a.shift = by_tiles.shift;
+    a.tokens_magic = UINT32_MAX / a.block_tokens;
     On on(plan, stream);
     // the tiles of all planes are numbered with 32 bits: descriptors that have more go in several launches
     const uint32_t n_all = a.n_units, per_launch = (uint32_t)(INT32_MAX / tpu);
