@@ -64,9 +64,9 @@ constexpr uint32_t kNtMoveCode = 2u | 4u | (1u << 3);           // tile x1, nt l
 constexpr uint32_t kFlatMoveCode = 128u | 4u | (1u << 3);       // flat, nt loads, nt stores
 constexpr uint32_t kFlatPackCode = 128u | 4u | (2u << 3);       // flat, nt loads, sc1 stores
 constexpr uint32_t kFlatUnpackCode = 128u | 4u | (1u << 3);     // flat, nt loads, nt stores
-// The tiled form's code for a plain gather or scatter; `lines`: every row begins on a 128-byte line.
-inline uint32_t default_tile_code(bool pack, bool lines, uint64_t payload) {
-    if (pack) return payload <= (lines ? kSmallBytes : kSmallOffLinesBytes) ? kSmallPackCode : kDefaultPackCode;
+// The tiled form's code for a plain gather or scatter; `lines`: every row begins on a 128-byte line; `event`: the launch carries one.
+inline uint32_t default_tile_code(bool pack, bool lines, uint64_t payload, bool event) {
+    if (pack) return gather_stays(lines, payload, event) ? kSmallPackCode : kDefaultPackCode;
     if (scatter_nt(lines, payload)) return kNtUnpackCode;
     return lines || payload > kPlainReadBackBytes ? kDefaultUnpackCode : kDefaultUnpackCodeOddRows;
 }

@@ -77,13 +77,20 @@ constexpr uint64_t kCachedFlatBytes = 64u << 20, kCachedLayerBytes = 76u << 20, 
 constexpr uint64_t kReadOnceManyBytes = 572u << 20, kScatterOnceManyBytes = 400u << 20, kHalveBytes = 336u << 20;
 // Odd rows in several planes: descriptors from which the gather starts late (launch_any).
 constexpr uint32_t kLateTileBytes = 32u << 10;
-// Up to this payload (the second of rows off the lines) the gather's stores stay in the L2 caches, 32 MB in all, for the scatter, whose
-// tiles the same XCDs take, instead of being written through.  Hops of three layers with buffers of their own in turn, us, through /
-// so: 656-byte rows by 64, 7.8 MB 8.2 / 7.1; 80 by 256, 8.5 MB 8.4 / 7.6; 333 by 64, 7.1 MB 8.0 / 7.1, 12.1 MB 11.2 / 10.8; 1152 by 16, 8.5
-// MB 7.6 / 7.2; above they lose (1152 by 64, 10.9 MB 9.2 / 9.4, 16 MB 12.3 / 13.0, 23 MB 16.2 / 17.8; 1026 by 64, 22 MB 16.5 / 17.4), but
-// with one transfer buffer for all layers, whose lines are then written again where they lie (32 layers of 1152 by 64, 20 MB, 410 /
-// 369; a layer of 656 by 64, 9.7 MB, 8.3 / 7.3, of 333 by 64, 12.1 MB, 13.2 / 9.5).  Odd rows that are dealt out flat lose everywhere.
-constexpr uint64_t kSmallBytes = 10u << 20, kSmallOffLinesBytes = 12u << 20;
+// Above the first of these payloads and up to the second (the third of rows off the lines) the gather's stores stay in the L2 caches,
+// 32 MB in all, for the scatter, whose tiles the same XCDs take, instead of being written through; but where the launch carries an
+// event, which waits for the caches to be written back (eager hops on a stream of the caller's, 4.6 MB of 1152-byte rows by 16, us,
+// through / so: 8.50 / 9.05; 9.8 MB by 64 10.68 / 11.11).  Without one, hops of three layers with buffers of their own in turn in a HIP
+// graph, through / so: 1152 by 16, 1.0 MB 3.91 / 3.99, 2.5 MB 4.29 / 4.45, 2.9 MB 4.88 / 4.76, 3.4 MB 5.42 / 5.13, 4.2 MB 5.53 / 5.22; 1152 by
+// 64, 4.6 MB 5.73 / 5.26; 656 by 64, 2.8 MB 4.81 / 4.70, 6.6 MB 7.23 / 6.53; 333 by 64, 2.4 MB 4.79 / 4.84, 4.9 MB 6.54 / 5.98, 10.6 MB
+// 9.69 / 9.65; 1152 by 1, 2.0 MB 4.13 / 4.23, 5.9 MB 6.45 / 5.68; eager ones on the default stream are bound by the host up to 6 MB, then 1152
+// by 64, 7.5 MB 7.03 / 6.46, 9.7 MB 8.28 / 8.01.  Above they lose (1152 by 64, 10.9 MB 9.2 / 9.4, 16 MB 12.3 / 13.0; 1026 by 64, 22 MB
+// 16.5 / 17.4), but with one transfer buffer for all layers, whose lines are then written again where they lie (656 by 64, 10.6 MB
+// 8.91 / 8.10; 333 by 64, 10.8 MB 9.38 / 8.61).  Odd rows that are dealt out flat lose everywhere.
+constexpr uint64_t kSmallFromBytes = 2816u << 10, kSmallBytes = 10u << 20, kSmallOffLinesBytes = 12u << 20;
+inline bool gather_stays(bool lines, uint64_t payload, bool event) {
+    return !event && payload > kSmallFromBytes && payload <= (lines ? kSmallBytes : kSmallOffLinesBytes);
+}
 // Between these two payloads the scatter's stores of whole lines are nt ones, which the L2 caches take up, instead of sc1+nt, which
 // wait for the memory.  Hops of three layers with buffers of their own (with one buffer), us, sc1+nt / nt: 1152-byte rows by 64, 11.9 MB 9.7 /
 // 9.3 (9.0 / 9.15), 13.9 MB 11.1 / 10.5 (10.3 / 10.3), 17 MB 12.7 / 12.1 (12.2 / 11.9), 19.6 MB 14.0 / 13.75 (13.6 / 13.3), 23.2 MB 16.0 /

@@ -356,7 +356,7 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
         const uint32_t x = (uint32_t)(flat ? windows : per_unit), n_tiles = (uint32_t)tiles;
         dim3 grid(groups, planes), block(threads);
         if (pack) {
-            if (small) launch_any_one<true, true, 0, true>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
+            if (small && gather_stays(false, plan->payload_bytes, on.done != nullptr)) launch_any_one<true, true, 0, true>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
             else if (far_host) launch_any_one<true, true, 2, false>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
             else if (kept || (once && !flat)) launch_any_one<true, true, 2, true>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
             else launch_any_one<true, true, 1, true>(flat, walk, grid, block, on, part, x, n_tiles, run_bytes);
@@ -497,6 +497,7 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         return KVL_OK;
     }
 
+    On on(plan, stream);
     uint32_t threads = plan->tuning.block_threads;
     // default: tiled, one vector per lane; cache policies as measured (see the top of kvl_copy_kernels.h)
     uint32_t v;
@@ -507,7 +508,7 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         for (uint32_t p = plane_begin; p < plane_end; ++p)
             rows_128 = rows_128 && plan->layout.row_bytes[p] % 128 == 0;
         const uint64_t payload = far_host ? std::max(plan->payload_bytes, kNtScatterBytes + 1) : plan->payload_bytes;
-        v = plan->paired ? (move_nt(payload) ? kNtMoveCode : kMoveCode) : default_tile_code(pack, rows_128, payload);
+        v = plan->paired ? (move_nt(payload) ? kNtMoveCode : kMoveCode) : default_tile_code(pack, rows_128, payload, on.done != nullptr);
         // across the host link: two vectors per lane, so that the few workgroups of the thin
         // form (kHostSideGroups) keep enough bytes in flight
         if (far_host) v |= 3u;
@@ -527,7 +528,6 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
         threads = plan->paired && !plan->threads_chosen ? 1024u : plan->tuning.block_threads;
     }
     dim3 block(threads);
-    On on(plan, stream);
     const kvl_unit_t &u_first = plan->units[unit_begin], &u_last = plan->units[unit_end - 1];
     if (vec && !plan->tuning.variant && !plan->tuning.max_groups && !far_host && plan->d_row_map &&
         rows_ahead(plan, row_bytes, pack) && row_map_ready(plan, stream)) {
@@ -541,7 +541,7 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
             const uint32_t n = (uint32_t)(std::min<uint64_t>(per_launch, rows - first) * widest);
             const uint32_t row_begin = (uint32_t)(u_first.xfer_row + first);
             dim3 grid((uint32_t)(((uint64_t)n + 7 + threads - 1) / threads), plane_end - plane_begin);
-            if (pack && plan->payload_bytes <= (lines ? kSmallBytes : kSmallOffLinesBytes)) launch_rows<true, true, 0>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
+            if (pack && gather_stays(lines, plan->payload_bytes, on.done != nullptr)) launch_rows<true, true, 0>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
             else if (pack) launch_rows<true, true, 2>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
             else if (lines && !scatter_nt(lines, plan->payload_bytes)) launch_rows<false, true, 3>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
             else launch_rows<false, true, 1>(grid, dim3(threads), on, a, plan->d_row_map, row_begin, n, rows_run);
@@ -951,7 +951,7 @@ int kvl_ceiling_kernel(const kvl_ceiling_t *c, const void *src, uint64_t src_byt
         else hipLaunchKernelGGL((kvl_ceiling_pattern_kernel<2, G, N, S>), grid, block, 0, s, a);                     \
     } while (0)
     // the cache policies of the default gather and scatter of such a layer
-    const uint32_t v = default_tile_code(gather, c->skew_bytes == 0 && c->block_bytes % 128 == 0, bytes);
+    const uint32_t v = default_tile_code(gather, c->skew_bytes == 0 && c->block_bytes % 128 == 0, bytes, false);
     if (gather && v == kDefaultPackCode) KVL_CEIL(true, true, 2);
     else if (gather) KVL_CEIL(true, true, 0);
     else if (v == kNtUnpackCode) KVL_CEIL(false, true, 1);

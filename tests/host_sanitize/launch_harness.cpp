@@ -445,6 +445,39 @@ static int check_ceiling_policies() {
     return 0;
 }
 
+// Small layers: what the gather writes stays in the L2 caches where no event has to wait for it to be written back, from 2.75 MiB on.
+// By tiles, by the row map (of single rows) and of odd rows.
+static int check_small_gathers() {
+    const struct { uint32_t row, rows; uint64_t least, most; } shapes[] = {{1152, 64, 2816u << 10, 10u << 20}, {656, 64, 2816u << 10, 12u << 20},
+                                                                           {1152, 1, 2816u << 10, 10u << 20}, {656, 4, 2816u << 10, 12u << 20},
+                                                                           {333, 64, 2816u << 10, 12u << 20}};
+    for (const auto &q : shapes)
+        for (uint64_t payload : {q.least - 80000, q.least + 80000, q.most - 80000, q.most + 80000}) {
+            const uint32_t n = (uint32_t)(payload / (q.rows * q.row));
+            const bool stays = payload > q.least && payload < q.most;
+            fake::Stream own, captured;
+            uintptr_t xfer[KVL_MAX_PLANES] = {1ull << 44};
+            for (int where = 0; where < 4; ++where) {       // the default stream; the caller's, with an event and without; a capture
+                kvl_plan_s p = alike(n, q.rows, q.row);
+                p.d_row_map = &g_map;
+                if (where == 2) p.flags |= KVL_CALLER_SYNCS;
+                if (where == 3) fake::begin_capture(captured);
+                launches.clear();
+                REQUIRE(launch_units(&p, true, 0, n, 0, 1, kPlanes, xfer, where == 0 ? nullptr : fake::handle(where == 3 ? captured : own)) == KVL_OK);
+                if (where == 3) fake::end_capture(captured);
+                REQUIRE(launches.size() == 1 && launches[0].event == (where == 1));
+                REQUIRE(is(launches[0], q.row == 333 ? "kvl_any_tile_kernel" : q.rows < 64 ? "kvl_rows_kernel" : "kvl_pack_quick_tile_kernel"));
+                REQUIRE(is(launches[0], q.row == 333 || q.rows < 64 ? "<true, true, " : "<1, true, "));
+                if (!is(launches[0], stays && where != 1 ? "true, 0" : "true, 2")) {
+                    std::printf("%u by %u, %llu bytes, %d: %s\n", q.row, q.rows, (unsigned long long)payload, where, launches[0].kernel.c_str());
+                    return 1;
+                }
+                p.d_units = nullptr;
+            }
+        }
+    return 0;
+}
+
 // A tile's descriptor by multiplication is the quotient, for every workgroup number that a launch can have (around multiples of
 // the divisor, at both ends).
 static int check_tile_divisor() {
@@ -690,6 +723,7 @@ int main(int argc, char **argv) {
         {"tile_divisor", check_tile_divisor},
         {"row_map_rule", check_row_map_rule},
         {"tile_order", check_tile_order},
+        {"small_gathers", check_small_gathers},
     };
     if (argc != 2 || !checks.count(argv[1])) {
         for (const auto &c : checks) std::printf("%s\n", c.first.c_str());
