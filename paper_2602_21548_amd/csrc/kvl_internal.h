@@ -106,7 +106,7 @@ inline bool move_nt(uint64_t payload) { return payload > kNtMoveBytes && payload
 // Tiles of one plane, or of planes alike: their lanes and their order by the layer's size (hop_threads, tile_run_bytes).
 constexpr uint64_t kNarrowBytes = 28u << 20, kWaveTileBytes = 512u << 20, kLongRunBytes = 288u << 20;
 constexpr uint64_t kOrderBytes = 224u << 20, kOrderBlockBytes = 48u << 10, kVeryLongRunBlockBytes = 14u << 10, kMoveRunBytes = 96u << 20, kMoveLongRunBytes = 1u << 30, kRowsRunBytes = 512u << 10, kOddOrderBytes = 48u << 20;
-constexpr uint64_t kFlatOrderBytes = 160u << 20, kOnDieBytes = 256u << 20, kOddRunsAgainBytes = 400u << 20;
+constexpr uint64_t kFlatOrderBytes = 160u << 20, kOnDieBytes = 256u << 20;
 // Up to this payload planes of unlike rows share a launch (kvl_planes_kernel): beyond it a launch of their own is less than a
 // hundredth of their time, and each plane better off in the form that suits it (hops apart / at once, 2048- and 656-byte
 // rows by 16, 285 MB 176 / 177, 631 MB 412 / 412; 1024 and 128 by 24, 873 MB, 557 / 565; moves 512 and 528 by 128, 289 MB

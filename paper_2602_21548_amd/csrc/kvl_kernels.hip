@@ -282,10 +282,14 @@ static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, co
 //     Hops, three layers in turn, us, in order / runs of 64, 128, 256, 512 KiB: 132 by 64, 70 MB 45.7 / 44.0 / 44.0 / 43.7 / 43.3, 199 MB
 //     136 / 123 / 121 / 121 / 119, 340 MB 236 / 236 / 238 / 238 / 238, 1.4 GB 1048 / 1010 / 1001 / 993 / 988; 333 by 64, 340 MB 232 / 220 /
 //     222 / 225 / 226, 793 MB 626 / 573 / 565 / 566 / 566; 1026 by 64, 279 MB 171 / 168 / 168 / 171 / 175; flat, 200 by 16, 401 MB 295 / 291 / 289 /
-//     288 / 289, 21 by 64, 75 MB 74.0 / 74.1 / 74.4 / 74.1 / 75.4.  In order stay short blocks of whole lines in one plane just beyond the
-//     cache (132 by 64, 275 MB 187 / 190 / 191 / 192 / 192; with one transfer buffer for the three 203 / 187 / 184 / 185 / 185), and small
-//     layers (132 by 64, 30 MB, one transfer buffer, 23.5 / 23.6 / 24.9 / 25.9 / 27.7).  Moves: 333 by 64, 206 MB 74.1 / 69.4 / 69.1 / 68.9 /
-//     69.2, 132 by 64, 1.9 GB 663 / 640 / 632 / 626 / 624, 292 MB 96.0 / 96.4 / 96.1 / 95.8 / 95.9.
+//     288 / 289, 21 by 64, 75 MB 74.0 / 74.1 / 74.4 / 74.1 / 75.4.  Short blocks of whole lines in one plane just beyond the cache,
+//     where a plan serves every layer of a batch / each layer has one of its own, whose descriptors come from the memory then (in order, runs of
+//     32, of 128 KiB): 132 by 64, 280 MB 192.1, 177.1, 170.4 / 190.6, 190.8, 195.0, 330 MB 233.9, 218.1, 209.7 / 229.1, 226.3, 230.2, 390 MB 273.0,
+//     265.1, 254.7 / 274.7, 271.3, 275.6; 72 by 64, 285 MB 197.0, 179.2, 173.1 / 202.6, 203.0, 204.3; 132 by 128, 280 MB 181.8, 173.4, 167.5 / 182.3,
+//     178.9, 182.8; 200 by 64, 330 MB 231.5, 221.0, 208.1 / 231.6, 226.0, 231.3; 260 by 64, 279 MB 181.3, 172.0, 165.7 / 182.8, 179.4, 183.1; 260 by
+//     32, 355 MB 245.9, 238.6, 229.6 / 252.8, 249.7, 254.1.  In order stay small layers (132 by
+//     64, 30 MB, one transfer buffer, 23.5 / 23.6 / 24.9 / 25.9 / 27.7).  Moves: 333 by 64, 206 MB 74.1 / 69.4 / 69.1 / 68.9 / 69.2, 132 by 64, 1.9 GB
+//     663 / 640 / 632 / 626 / 624, 292 MB 96.0 / 96.4 / 96.1 / 95.8 / 95.9.
 //   moves (150 MB of 90-byte rows by 32: flat 54, tiled with 256 / 128 lanes 53 / 59) and the host link: flat up to
 //     kAnyFlatPastWindows, tiles of 256 lanes, 128 below two such tiles (1026 by 4: 377 us at 256, 286 at 128).
 //   across the host link: tiles on few workgroups (kHostSideGroups); a flat launch has as many as ever, since few of them
@@ -337,7 +341,7 @@ static void launch_any(const kvl_plan_t *plan, bool pack, const CopyArgs &a, uin
         const bool beyond = plan->payload_bytes > kOnDieBytes;
         if (flat) run_bytes = 256u << 10;
         else if (!beyond || plan->payload_bytes > kWaveTileBytes) run_bytes = 512u << 10;
-        else if (!lines || share < 0.875 || unit_bytes >= kLateTileBytes || plan->payload_bytes > kOddRunsAgainBytes) run_bytes = 128u << 10;
+        else run_bytes = 128u << 10;
     }
     const uint64_t per_unit = tiles_of(threads);
     uint64_t per_launch = flat ? ((1ull << 31) - threads) / windows : (uint64_t)INT32_MAX / per_unit;

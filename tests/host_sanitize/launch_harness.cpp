@@ -478,6 +478,39 @@ static int check_small_gathers() {
     return 0;
 }
 
+// The bytes of the run of tiles that an XCD takes in the launch being made, from its `order` argument (0: in order).
+static uint64_t g_run_bytes;
+template <int ORDER> static void watch_order(const fake::Launch &l, void **args) {
+    const uint32_t order = *(const uint32_t *)args[ORDER];
+    g_run_bytes = order & 15u ? 16ull * l.block.x << (order & 15u) : 0;
+}
+
+// Odd rows: the order of the tiles by the layer's size alone, whatever its blocks and planes are; flat ones from 160 MiB.
+static int check_odd_rows_order() {
+    const struct { uint32_t row, rows, planes, mib, run_kib; } shapes[] = {
+        {132, 64, 1, 40, 0}, {132, 64, 1, 50, 512}, {132, 64, 1, 250, 512}, {132, 64, 1, 260, 128}, {132, 64, 1, 300, 128}, {132, 64, 1, 390, 128},
+        {132, 64, 1, 410, 128}, {132, 64, 1, 500, 128}, {132, 64, 1, 520, 512}, {72, 128, 1, 300, 128}, {260, 64, 1, 340, 128}, {132, 64, 2, 300, 128},
+        {333, 64, 1, 11, 512}, {333, 64, 1, 13, 0}, {333, 64, 1, 300, 128}, {516, 64, 1, 300, 128}, {200, 16, 1, 150, 0}, {200, 16, 1, 170, 256},
+        {200, 16, 1, 600, 256}};
+    for (const auto &q : shapes)
+        for (bool gather : {true, false}) {
+            const uint64_t n = ((uint64_t)q.mib << 20) / (q.rows * q.row * q.planes);
+            kvl_plan_s p = alike(n, q.rows, q.row, q.planes);
+            uintptr_t xfer[KVL_MAX_PLANES] = {1ull << 44, 1ull << 45};
+            launches.clear();
+            fake::watch = q.row == 200 ? watch_order<9> : watch_order<8>;
+            REQUIRE(launch_units(&p, gather, 0, (uint32_t)n, 0, q.planes, kPlanes, xfer, nullptr) == KVL_OK);
+            fake::watch = nullptr;
+            REQUIRE(launches.size() == 1 && is(launches[0], q.row == 200 ? "kvl_any_flat_kernel" : "kvl_any_tile_kernel"));
+            if (g_run_bytes != q.run_kib * 1024) {
+                std::printf("%u by %u, %u planes, %u MiB: runs of %llu KiB\n", q.row, q.rows, q.planes, q.mib, (unsigned long long)g_run_bytes >> 10);
+                return 1;
+            }
+            p.d_units = nullptr;
+        }
+    return 0;
+}
+
 // A tile's descriptor by multiplication is the quotient, for every workgroup number that a launch can have (around multiples of
 // the divisor, at both ends).
 static int check_tile_divisor() {
@@ -724,6 +757,7 @@ int main(int argc, char **argv) {
         {"row_map_rule", check_row_map_rule},
         {"tile_order", check_tile_order},
         {"small_gathers", check_small_gathers},
+        {"odd_rows_order", check_odd_rows_order},
     };
     if (argc != 2 || !checks.count(argv[1])) {
         for (const auto &c : checks) std::printf("%s\n", c.first.c_str());
