@@ -996,8 +996,10 @@ def kernel_shapes_leg(index: int = 3) -> dict:
     n = g.payload_bytes
     x = torch.empty(n, dtype=torch.uint8, device=dev)
     stream = torch.cuda.Stream()
-    # (name, pack variant, unpack variant): the cache policies are those of the default throughout
+    # (name, pack variant, unpack variant): the cache policies are those of the default throughout; the default takes its
+    # tiles in runs, in workgroups of one wavefront, the explicit forms in order
     forms = [("default: tiled, one vector per lane", 0, 0),
+             ("tiled, one vector per lane, workgroups of 256 lanes, tiles in order", 23, 31),
              ("one wavefront per descriptor, 4 vectors in flight per lane", 22, 30),
              ("one wavefront per descriptor, 8 vectors in flight per lane", 54, 62),
              ("one workgroup per descriptor, 4 vectors in flight per lane", 21, 29),

@@ -28,6 +28,7 @@
 //   flat    (code bit 7, with ntl and sp only) no tiles: lane g of the launch takes vector
 //           g mod m of descriptor g div m, m = vectors of the largest descriptor; for
 //           descriptors far smaller than a workgroup (token-granular pools)
+// All of them take their tiles in order (tile_number).
 // The default is the tiled form, or the row-map form (kvl_rows_kernel, for plans that have a
 // map) where takes_row_map says so; without a map, descriptors of less than half a workgroup
 // go flat: on single-token blocks of 1152 bytes the tiled form leaves 72 % of its lanes idle.

@@ -522,7 +522,8 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
     for (uint32_t p = plane_begin; p < plane_end; ++p) widest = std::max(widest, a.row_elems[p]);
     const uint64_t unit_vecs = (uint64_t)plan->max_unit_rows * widest;
     const uint32_t row_bytes = plan->layout.row_bytes[plane_begin];
-    const uint64_t run_bytes = far_host ? 0 : tile_run_bytes(plan, row_bytes);
+    // (explicit variants take their tiles in order, so that they differ in their form alone)
+    const uint64_t run_bytes = far_host || plan->tuning.variant ? 0 : tile_run_bytes(plan, row_bytes);
     if (vec && !plan->threads_chosen && !plan->tuning.variant) {
         threads = plan->paired ? move_threads(plan, row_bytes) : far_host ? tile_threads(unit_vecs) : hop_threads(plan, row_bytes);
     }

@@ -511,6 +511,25 @@ static int check_odd_rows_order() {
     return 0;
 }
 
+// An explicit variant is its form alone: tiles of the default width in order, also where the default takes them in runs.
+static int check_variants_order() {
+    const uint32_t n = 40000;
+    for (uint32_t variant : {0u, 23u, 31u, 24u, 23u + 64u})
+        for (bool gather : {true, false}) {
+            kvl_plan_s p = alike(n, 64, 1152);              // 2.9 GB
+            p.tuning.variant = variant;
+            uintptr_t xfer[KVL_MAX_PLANES] = {1ull << 44};
+            launches.clear();
+            fake::watch = watch_order<8>;
+            REQUIRE(launch_units(&p, gather, 0, n, 0, 1, kPlanes, xfer, nullptr) == KVL_OK);
+            fake::watch = nullptr;
+            REQUIRE(launches.size() == 1 && is(launches[0], "quick_tile_kernel") && launches[0].block.x == (variant ? 256 : 64));
+            REQUIRE(g_run_bytes == (variant ? 0 : 128 * 1024));
+            p.d_units = nullptr;
+        }
+    return 0;
+}
+
 // A tile's descriptor by multiplication is the quotient, for every workgroup number that a launch can have (around multiples of
 // the divisor, at both ends).
 static int check_tile_divisor() {
@@ -758,6 +777,7 @@ int main(int argc, char **argv) {
         {"tile_order", check_tile_order},
         {"small_gathers", check_small_gathers},
         {"odd_rows_order", check_odd_rows_order},
+        {"variants_order", check_variants_order},
     };
     if (argc != 2 || !checks.count(argv[1])) {
         for (const auto &c : checks) std::printf("%s\n", c.first.c_str());
