@@ -921,7 +921,7 @@ def _time_in_turn(fns, stream, reps: int = 8, warm: int = 2):
 
 def ceilings_leg(stream, roof_pack: dict, roof_unpack: dict, config_index: int) -> dict:
     """What the memory of this machine does on reference streams that use the load and store
-    instructions and cache policies of the default kernels but no descriptors: a linear copy and
+    instructions, cache policies, workgroups and order of the default kernels but no descriptors: a linear copy and
     its read and write halves alone (4 GiB), and a copy with the access shape of cfg4 -- one
     side dense, the other hopping every 41,984 bytes to a pseudo-random block, the two sides 16
     bytes apart in their 128-byte lines -- with the block's address computed, or read from a

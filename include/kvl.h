@@ -478,8 +478,8 @@ int kvl_measure_h2d_peak(const void *pinned_host, void *dev, uint64_t bytes, uin
 int kvl_copy_linear(const void *src, void *dst, uint64_t bytes, void *stream);
 
 /* Reference streams for measuring what the memory can do, beside the kernels of the load path
- * (the benchmark's ceilings): plain device memory, the load/store instructions and cache policies
- * of the default gather and scatter of a layer of that size, no descriptors.
+ * (the benchmark's ceilings): plain device memory, the load/store instructions, cache policies,
+ * workgroups and order of the default gather and scatter of a layer of that size, no descriptors.
  *   block_bytes == 0: one linear stream of `bytes` bytes, src (+ skew_bytes) -> dst;
  *   block_bytes != 0: the access shape of a paged copy without its block tables: one side
  *     ("dense") is a linear stream, the other hops every block_bytes: block u of the dense
@@ -490,7 +490,7 @@ int kvl_copy_linear(const void *src, void *dst, uint64_t bytes, void *stream);
  *     hopping_side 0: the source hops (a gather; src holds 2^hop_blocks_log2 blocks, dst
  *     bytes + skew_bytes), 1: the destination hops (a scatter).  skew_bytes (multiple of 16, below
  *     128) shifts the dense side, so that the two sides sit differently in their 128-byte lines.
- * mode: copy, or only the reads, or only the writes of that copy.  Both pointers 128-byte
+ * mode: copy, or only the reads, or only the writes of that copy (these in order, in workgroups of 256 lanes).  Both pointers 128-byte
  * aligned; sizes are checked against the buffers (KVL_ESPACE).  What lands in dst is of no
  * use.  Enqueues on stream; the caller times it. */
 #define KVL_CEILING_COPY  0u

@@ -815,16 +815,16 @@ __global__ void __launch_bounds__(256) kvl_fullblock_quick_kernel(const kvl_unit
 struct CeilingArgs {
     uintptr_t dense, hopping;       // base addresses
     const uint32_t *table;          // optional
-    uint64_t tile_magic;            // ceil(2^40 / tiles_per_block): block of a workgroup by multiplication
+    uint32_t magic, shift, order;   // the block of a tile by multiplication (TileDivisor); the order of the tiles (tile_number)
     uint32_t n_blocks, hop_mask, mul;
-    uint32_t block_vecs, tiles_per_block, skew_vecs, n_vecs;
+    uint32_t block_vecs, tiles_per_block, skew_vecs;
 };
 
 // MODE 0: copy, 1: read only, 2: write only.  GATHER: the source hops, else the destination.
 template <int MODE, bool GATHER, bool NTL, int SP>
 __global__ void __launch_bounds__(256) kvl_ceiling_pattern_kernel(const CeilingArgs a) {
-    const uint32_t w = blockIdx.x;
-    const uint32_t u = (uint32_t)(((uint64_t)w * a.tile_magic) >> 40);
+    const uint32_t w = tile_number(blockIdx.x, a.order);
+    const uint32_t u = a.magic ? (uint32_t)(((uint64_t)w * a.magic) >> 32) >> a.shift : w;
     const uint32_t tile = w - u * a.tiles_per_block;
     const uint32_t hb = a.table ? a.table[u] : ((u * a.mul) & a.hop_mask);
     const uintptr_t hop = a.hopping + (uint64_t)hb * a.block_vecs * 16u;
@@ -847,8 +847,8 @@ __global__ void __launch_bounds__(256) kvl_ceiling_pattern_kernel(const CeilingA
 }
 
 template <int MODE, bool NTL, int SP>
-__global__ void __launch_bounds__(256) kvl_ceiling_linear_kernel(const v4u *src, v4u *dst, uint64_t n) {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256) kvl_ceiling_linear_kernel(const v4u *src, v4u *dst, uint64_t n, uint32_t order) {
+    const uint64_t i = (uint64_t)tile_number(blockIdx.x, order) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     if (MODE == 0) {
         store16<SP>((gdst_t)dst + i, load16<NTL>((gsrc_t)src + i));

@@ -147,6 +147,15 @@ inline uint32_t tile_threads(uint64_t unit_vecs) {
     return idle(kDefaultBlockThreads) - idle(kDefaultBlockThreads / 2) > 0.07 ? kDefaultBlockThreads / 2 : kDefaultBlockThreads;
 }
 
+// What the order of a layer's tiles and their lanes are chosen by.
+struct LayerShape {
+    uint64_t payload, tokens, units, max_unit_rows;     // (as in kvl_plan_s)
+    bool paired, capped;                                // a move; a cap on the workgroups
+};
+inline LayerShape shape_of(const kvl_plan_s *plan) {
+    return {plan->payload_bytes, plan->hit_tokens, plan->units.size(), plan->max_unit_rows, plan->paired, plan->tuning.max_groups != 0};
+}
+
 // Bytes of the run of tiles that one XCD takes before the next run's turn (tile_number); 0: tile by tile.  One plan for several
 // layers and one transfer buffer, us, tile by tile / runs of 128 / 256 / 512 KiB:
 //  - hops: 656-byte rows by 64, 186 MB 120 / 107 / 105 / 105, 443 MB 286 / 267 / 264 / 266, 613 MB 393 / 378 / 378 / 381; 1152 by
@@ -159,15 +168,14 @@ inline uint32_t tile_threads(uint64_t unit_vecs) {
 //    3456; 272 by 64 (17 KB), 2.6 GB 1766 / 1782 / 1779 / 1785; 656 by 64, 1.0 GB 642 / 648 / 651 / 652.
 //  - moves: 656 by 64, 613 MB 194 / 192 / 191 / 191, 3.3 GB 1078 / 1067 / 1055 / 1050; 2048 + 2048 by 64, 521 MB 157 / 153 / 154 /
 //    153; 1152 by 64, 27 MB 9.9 / 9.9 / 10.0 / 10.0, 223 MB 68.2 / 68.3 / 67.9 / 68.1, 2.7 GB 805 / 819 / 812 / 804.
-inline uint64_t tile_run_bytes(const kvl_plan_s *plan, uint32_t row_bytes) {
-    const uint64_t payload = plan->payload_bytes;
+inline uint64_t tile_run_bytes(const LayerShape &s, uint32_t row_bytes) {
     const bool lines = row_bytes % 128 == 0;
-    const double descriptor_bytes = (double)plan->hit_tokens * row_bytes / (double)plan->units.size();
+    const double descriptor_bytes = (double)s.tokens * row_bytes / (double)s.units;
     const bool small_blocks = descriptor_bytes < (double)kOrderBlockBytes;
-    if (lines && small_blocks && payload > kOrderBytes) return 0;
-    if (plan->paired) return payload > kMoveLongRunBytes ? 512u << 10 : !lines || payload > kMoveRunBytes ? 256u << 10 : 0;
-    if (payload > kWaveTileBytes && descriptor_bytes < (double)kVeryLongRunBlockBytes) return 1u << 20;
-    return payload <= kLongRunBytes ? 512u << 10 : payload <= kWaveTileBytes ? 256u << 10 : 128u << 10;
+    if (lines && small_blocks && s.payload > kOrderBytes) return 0;
+    if (s.paired) return s.payload > kMoveLongRunBytes ? 512u << 10 : !lines || s.payload > kMoveRunBytes ? 256u << 10 : 0;
+    if (s.payload > kWaveTileBytes && descriptor_bytes < (double)kVeryLongRunBlockBytes) return 1u << 20;
+    return s.payload <= kLongRunBytes ? 512u << 10 : s.payload <= kWaveTileBytes ? 256u << 10 : 128u << 10;
 }
 
 // Lanes of a hop's tiles: 128 in small layers, one wavefront where large layers go in runs, else 256 unless that leaves more of
@@ -176,13 +184,13 @@ inline uint64_t tile_run_bytes(const kvl_plan_s *plan, uint32_t row_bytes) {
 // 373 / - / 362; 80 by 256, 186 MB 109.7 / - / 107.8; tile by tile 768 by 40 (7.5 tiles of 256), 665 MB 446 / 412 / 408; 1152 by 20 (5.6),
 // 655 MB 419 / 435 / 410; 1152 by 16 (4.5), 259 MB 147.7 / 147.3 / 151.1, 655 MB 413 / 408 / 406.  Descriptors that are not alike have
 // a launch of the largest one's tiles, and wide workgroups are the fewest of those that find nothing to do.
-inline uint32_t hop_threads(const kvl_plan_s *plan, uint32_t row_bytes) {
-    const uint64_t payload = plan->payload_bytes, largest = (uint64_t)plan->max_unit_rows * (row_bytes / 16);
-    const bool alike = 2ull * plan->max_unit_rows * plan->units.size() <= 3 * plan->hit_tokens;
+inline uint32_t hop_threads(const LayerShape &s, uint32_t row_bytes) {
+    const uint64_t largest = s.max_unit_rows * (row_bytes / 16);
+    const bool alike = 2 * s.max_unit_rows * s.units <= 3 * s.tokens;
     const uint64_t vecs = largest + (row_bytes % 128 ? 7 : 0);         // with those before the first on its line
-    if (!alike || plan->tuning.max_groups || plan->units.size() * (vecs / 64 + 1) > INT32_MAX) return tile_threads(largest);
-    if (payload <= kNarrowBytes) return 128;
-    const bool in_runs = tile_run_bytes(plan, row_bytes) != 0, large = payload > kWaveTileBytes;
+    if (!alike || s.capped || s.units * (vecs / 64 + 1) > INT32_MAX) return tile_threads(largest);
+    if (s.payload <= kNarrowBytes) return 128;
+    const bool in_runs = tile_run_bytes(s, row_bytes) != 0, large = s.payload > kWaveTileBytes;
     if (large && in_runs) return 64;
     const uint32_t narrow = in_runs || large ? 64 : 128;
     auto idle = [&](uint64_t t) { return 1.0 - (double)vecs / (double)((vecs + t - 1) / t * t); };
@@ -242,7 +250,7 @@ inline bool rows_ahead(const kvl_plan_s *plan, uint32_t row_bytes, bool pack) {
     if (plan->paired || !plan->vec16 || plan->units.empty() || plan->max_unit_rows > 4096) return false;
     const bool lines = row_bytes % 128 == 0;
     const uint64_t row = row_bytes / 16, largest = plan->max_unit_rows * row + (lines ? 0 : 7);
-    const uint64_t t = hop_threads(plan, row_bytes), tiles = (largest + t - 1) / t;
+    const uint64_t t = hop_threads(shape_of(plan), row_bytes), tiles = (largest + t - 1) / t;
     const double average = (double)plan->hit_tokens * (double)row / (double)plan->units.size();
     if (average < (lines ? 320 : 576) || average < 0.66 * (double)(tiles * t)) return true;
     const uint64_t mb = plan->payload_bytes >> 20;

@@ -523,9 +523,9 @@ int launch_units(const kvl_plan_t *plan, bool pack, uint32_t unit_begin, uint32_
     const uint64_t unit_vecs = (uint64_t)plan->max_unit_rows * widest;
     const uint32_t row_bytes = plan->layout.row_bytes[plane_begin];
     // (explicit variants take their tiles in order, so that they differ in their form alone)
-    const uint64_t run_bytes = far_host || plan->tuning.variant ? 0 : tile_run_bytes(plan, row_bytes);
+    const uint64_t run_bytes = far_host || plan->tuning.variant ? 0 : tile_run_bytes(shape_of(plan), row_bytes);
     if (vec && !plan->threads_chosen && !plan->tuning.variant) {
-        threads = plan->paired ? move_threads(plan, row_bytes) : far_host ? tile_threads(unit_vecs) : hop_threads(plan, row_bytes);
+        threads = plan->paired ? move_threads(plan, row_bytes) : far_host ? tile_threads(unit_vecs) : hop_threads(shape_of(plan), row_bytes);
     }
     // descriptors that fill less than half a workgroup: deal the lanes out without tiles
     if (vec && !plan->tuning.variant && unit_vecs * 2 <= plan->tuning.block_threads) {
@@ -902,6 +902,9 @@ int kvl_ceiling_kernel(const kvl_ceiling_t *c, const void *src, uint64_t src_byt
     if (c->mode > KVL_CEILING_WRITE || c->skew_bytes % 16 || c->skew_bytes >= 128 || c->block_bytes % 16) return KVL_EINVAL;
     if (bytes % 16 || reinterpret_cast<uintptr_t>(src) % 128 || reinterpret_cast<uintptr_t>(dst) % 128) return KVL_EINVAL;
     hipStream_t s = (hipStream_t)stream;
+    // The halves of a copy alone go in order in wide workgroups: workgroups of one wavefront are launched at some 4.8 a nanosecond,
+    // which would bound them (4 GiB read or written so 4.8 TB/s, in wide ones 6.9 and 7.0; the copy has half as many for its traffic).
+    const bool halves = c->mode != KVL_CEILING_COPY;
     if (c->block_bytes == 0) {
         // one linear stream; the skew shifts the source
         if (src_bytes < bytes + c->skew_bytes || dst_bytes < bytes) return KVL_ESPACE;
@@ -910,16 +913,22 @@ int kvl_ceiling_kernel(const kvl_ceiling_t *c, const void *src, uint64_t src_byt
         if (rc != KVL_OK) return rc;
         const uint64_t n = bytes / 16, per_launch = (kMaxLanesPerLaunch / 256) * 256;
         const v4u *from = reinterpret_cast<const v4u *>(static_cast<const char *>(src) + c->skew_bytes);
+        // (as the tiles of a contiguous table's descriptors)
+        const uint32_t piece = kDefaultUnitBytes / 128;
+        const LayerShape shape{bytes, (bytes + 127) / 128, ((bytes + 127) / 128 + piece - 1) / piece, piece, false, false};
+        const uint32_t threads = halves ? kDefaultBlockThreads : hop_threads(shape, 128);
+        const uint64_t run_bytes = halves ? 0 : tile_run_bytes(shape, 128);
         for (uint64_t first = 0; first < n; first += per_launch) {
             const uint64_t m = std::min<uint64_t>(per_launch, n - first);
-            const dim3 grid((uint32_t)((m + 255) / 256)), block(256);
+            const dim3 grid((uint32_t)((m + threads - 1) / threads)), block(threads);
+            const uint32_t order = tile_order(grid.x, 16ull * threads, run_bytes);
             v4u *to = static_cast<v4u *>(dst) + first;
             if (c->mode == KVL_CEILING_COPY)
-                hipLaunchKernelGGL((kvl_ceiling_linear_kernel<0, kLinearNtLoad, kLinearStorePolicy>), grid, block, 0, s, from + first, to, m);
+                hipLaunchKernelGGL((kvl_ceiling_linear_kernel<0, kLinearNtLoad, kLinearStorePolicy>), grid, block, 0, s, from + first, to, m, order);
             else if (c->mode == KVL_CEILING_READ)
-                hipLaunchKernelGGL((kvl_ceiling_linear_kernel<1, kLinearNtLoad, kLinearStorePolicy>), grid, block, 0, s, from + first, to, m);
+                hipLaunchKernelGGL((kvl_ceiling_linear_kernel<1, kLinearNtLoad, kLinearStorePolicy>), grid, block, 0, s, from + first, to, m, order);
             else
-                hipLaunchKernelGGL((kvl_ceiling_linear_kernel<2, kLinearNtLoad, kLinearStorePolicy>), grid, block, 0, s, from + first, to, m);
+                hipLaunchKernelGGL((kvl_ceiling_linear_kernel<2, kLinearNtLoad, kLinearStorePolicy>), grid, block, 0, s, from + first, to, m, order);
             KVL_HIP(hipGetLastError());
         }
         return KVL_OK;
@@ -942,13 +951,21 @@ int kvl_ceiling_kernel(const kvl_ceiling_t *c, const void *src, uint64_t src_byt
     a.hop_mask = (uint32_t)(hop_blocks - 1);
     a.mul = 0x9e3779b1u;                    // odd
     a.block_vecs = c->block_bytes / 16;
-    a.tiles_per_block = (a.block_vecs + 7 + 255) / 256;
     a.skew_vecs = c->skew_bytes / 16;
-    a.tile_magic = ((1ull << 40) + a.tiles_per_block - 1) / a.tiles_per_block;
-    const uint64_t groups = n_blocks * a.tiles_per_block;
-    // the multiplication finds the block of every workgroup index below 2^24 * tiles_per_block exactly
-    if (groups > (1ull << 24) || groups * 256 > kMaxLanesPerLaunch) return KVL_ERANGE;
-    const dim3 grid((uint32_t)groups), block(256);
+    // a copy's tiles, lanes and order as the default kernels have them for a layer of such blocks
+    const bool lines = c->skew_bytes == 0 && c->block_bytes % 128 == 0;
+    const uint32_t row = lines ? 128 : 16, lead = lines ? 0 : 7;
+    const LayerShape shape{bytes, bytes / row, n_blocks, c->block_bytes / row, false, false};
+    const uint32_t threads = halves ? kDefaultBlockThreads : hop_threads(shape, row);
+    // (the limit is that of tiles of 256 lanes, whatever their lanes are)
+    const uint64_t most = n_blocks * ((a.block_vecs + 7 + 255) / 256);
+    if (most > (1ull << 24) || most * 256 > kMaxLanesPerLaunch) return KVL_ERANGE;
+    a.tiles_per_block = (a.block_vecs + lead + threads - 1) / threads;
+    const TileDivisor d(a.tiles_per_block);
+    a.magic = d.magic;
+    a.shift = d.shift;
+    const dim3 grid((uint32_t)(n_blocks * a.tiles_per_block)), block(threads);
+    a.order = halves ? 0 : tile_order(grid.x, 16ull * threads, tile_run_bytes(shape, row));
 #define KVL_CEIL(G, N, S)                                                                                              \
     do {                                                                                                            \
         if (c->mode == KVL_CEILING_COPY) hipLaunchKernelGGL((kvl_ceiling_pattern_kernel<0, G, N, S>), grid, block, 0, s, a); \
@@ -956,7 +973,7 @@ int kvl_ceiling_kernel(const kvl_ceiling_t *c, const void *src, uint64_t src_byt
         else hipLaunchKernelGGL((kvl_ceiling_pattern_kernel<2, G, N, S>), grid, block, 0, s, a);                     \
     } while (0)
     // the cache policies of the default gather and scatter of such a layer
-    const uint32_t v = default_tile_code(gather, c->skew_bytes == 0 && c->block_bytes % 128 == 0, bytes, false);
+    const uint32_t v = default_tile_code(gather, lines, bytes, false);
     if (gather && v == kDefaultPackCode) KVL_CEIL(true, true, 2);
     else if (gather) KVL_CEIL(true, true, 0);
     else if (v == kNtUnpackCode) KVL_CEIL(false, true, 1);

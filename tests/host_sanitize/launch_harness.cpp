@@ -421,10 +421,19 @@ static int check_cached_arrays() {
     return 0;
 }
 
-// The reference stream of a shape has the cache policies of the tiled kernels on that shape, on both sides of every line.
+// The bytes of the run of tiles that an XCD takes in the launch being made, from its `order` argument (0: in order).
+static uint64_t g_run_bytes;
+template <int ORDER> static void watch_order(const fake::Launch &l, void **args) {
+    const uint32_t order = *(const uint32_t *)args[ORDER];
+    g_run_bytes = order & 15u ? 16ull * l.block.x << (order & 15u) : 0;
+}
+
+// The reference stream of a shape has the cache policies, the tiles and the order of the tiled kernels on that shape, on both sides
+// of every line.
 static int check_ceiling_policies() {
-    for (uint32_t row : {656u, 1152u})
-        for (uint64_t payload : {100ull << 20, 200ull << 20, 5ull << 30})
+    static uint32_t tile_orders[2];
+    for (uint32_t row : {656u, 1152u, 384u})
+        for (uint64_t payload : {2ull << 20, 8ull << 20, 16ull << 20, 100ull << 20, 200ull << 20, 400ull << 20, 5ull << 30})
             for (bool gather : {true, false}) {
                 const uint32_t block = 64 * row, n = (uint32_t)(payload / block);
                 kvl_plan_s p = made(n, 64, row);
@@ -433,15 +442,33 @@ static int check_ceiling_policies() {
                 p.payload_bytes = p.hit_tokens * row;
                 uintptr_t xfer[KVL_MAX_PLANES] = {1ull << 44};
                 launches.clear();
+                fake::watch = [](const fake::Launch &l, void **args) {
+                    const bool pattern = is(l, "kvl_ceiling_pattern_kernel");
+                    tile_orders[pattern] = pattern ? ((const CeilingArgs *)args[0])->order : *(const uint32_t *)args[8];
+                };
                 REQUIRE(launch_units(&p, gather, 0, n, 0, 1, kPlanes, xfer, nullptr) == KVL_OK);
                 const kvl_ceiling_t c{KVL_CEILING_COPY, block, gather ? 0u : 1u, row % 128 ? 16u : 0u, 18};
                 REQUIRE(kvl_ceiling_kernel(&c, kPlanes[0], 1ull << 40, kPlanes[1], 1ull << 40, p.payload_bytes, nullptr, nullptr) == KVL_OK);
+                fake::watch = nullptr;
+                REQUIRE(launches[0].grid.x == launches[1].grid.x && launches[0].block.x == launches[1].block.x && tile_orders[0] == tile_orders[1]);
                 // ..._tile_kernel<vectors per lane, nt loads, store policy>, kvl_ceiling_pattern_kernel<mode, gather, nt loads, store policy>
                 const std::string &tile = launches[0].kernel, &ceiling = launches[1].kernel;
                 const std::string policy = tile.substr(tile.find(", ") + 2, tile.find('>') - tile.find(", ") - 2);
                 REQUIRE(ceiling.find(std::string("<0, ") + (gather ? "true, " : "false, ") + policy + ">") != std::string::npos);
                 p.d_units = nullptr;
             }
+    // a linear copy too; the halves of a copy alone go in order, in wide workgroups
+    const kvl_ceiling_t modes[] = {{KVL_CEILING_COPY, 0, 0, 0, 0}, {KVL_CEILING_READ, 0, 0, 0, 0}, {KVL_CEILING_WRITE, 0, 0, 0, 0}, {KVL_CEILING_READ, 64 * 1152, 0, 0, 18}};
+    for (const kvl_ceiling_t &c : modes) {
+        launches.clear();
+        const uint64_t bytes = c.block_bytes ? 50000ull * c.block_bytes : 4ull << 30;
+        fake::watch = c.block_bytes ? (decltype(fake::watch))[](const fake::Launch &, void **args) { g_run_bytes = ((const CeilingArgs *)args[0])->order; } : watch_order<3>;
+        REQUIRE(kvl_ceiling_kernel(&c, kPlanes[0], 1ull << 40, kPlanes[1], 1ull << 40, bytes, nullptr, nullptr) == KVL_OK);
+        fake::watch = nullptr;
+        const bool copy = c.mode == KVL_CEILING_COPY;
+        REQUIRE(launches.size() == 1 && launches[0].block.x == (copy ? 64 : 256) && g_run_bytes == (copy ? 128 * 1024 : 0));
+        REQUIRE(c.block_bytes || groups(launches[0]) * launches[0].block.x == bytes / 16);
+    }
     return 0;
 }
 
@@ -476,13 +503,6 @@ static int check_small_gathers() {
             }
         }
     return 0;
-}
-
-// The bytes of the run of tiles that an XCD takes in the launch being made, from its `order` argument (0: in order).
-static uint64_t g_run_bytes;
-template <int ORDER> static void watch_order(const fake::Launch &l, void **args) {
-    const uint32_t order = *(const uint32_t *)args[ORDER];
-    g_run_bytes = order & 15u ? 16ull * l.block.x << (order & 15u) : 0;
 }
 
 // Odd rows: the order of the tiles by the layer's size alone, whatever its blocks and planes are; flat ones from 160 MiB.
