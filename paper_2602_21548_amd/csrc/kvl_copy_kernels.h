@@ -460,33 +460,33 @@ __device__ __forceinline__ bool flat_unit(const kvl_unit_t *units, uint32_t n_un
 }
 #define KVL_FLAT_PARAMS                                                                                            \
     const kvl_unit_t *units, uintptr_t pool, uintptr_t xfer, uint32_t row, uint32_t n_units, uint32_t m, uint32_t magic, \
-        uint32_t shift, uint32_t threads, uint32_t order, const TileMore more
-
-#define KVL_FLAT_KERNELS(NAME, BODY)                                                                  \
-    template <bool PACK, bool NTL, int SP>                                                            \
-    __global__ void __launch_bounds__(1024) NAME(KVL_FLAT_PARAMS) {                                   \
-        BODY<PACK, NTL, SP, false>(units, pool, xfer, row, n_units, m, magic, shift, threads, order, more);   \
-    }                                                                                                 \
-    template <bool PACK, bool NTL, int SP>                                                            \
-    __global__ void __launch_bounds__(1024) NAME##_short(KVL_FLAT_PARAMS) {                           \
-        BODY<PACK, NTL, SP, true>(units, pool, xfer, row, n_units, m, magic, shift, threads, order, more);    \
-    }
+        uint32_t shift, uint32_t threads
+#define KVL_FLAT_ARGS units, pool, xfer, row, n_units, m, magic, shift, threads
 
 template <bool PACK, bool NTL, int SP, bool SHORT>
-__device__ __forceinline__ void flat_body(KVL_FLAT_PARAMS) {
+__device__ __forceinline__ void flat_body(KVL_FLAT_PARAMS, const TileMore &more) {
     if (blockIdx.y) {
         pool = more.pool[blockIdx.y - 1];
         xfer = more.xfer[blockIdx.y - 1];
     }
     kvl_unit_t u;
     uint32_t off;
-    if (!flat_unit<SHORT>(units, n_units, m, magic, shift, tile_number(blockIdx.x, order), threads, &u, &off)) return;
+    if (!flat_unit<SHORT>(units, n_units, m, magic, shift, blockIdx.x, threads, &u, &off)) return;
     if (off >= u.n_rows * row) return;
     gsrc_t src = (gsrc_t)((PACK ? pool : xfer) + (uint64_t)(PACK ? u.pool_row : u.xfer_row) * row * 16u);
     gdst_t dst = (gdst_t)((PACK ? xfer : pool) + (uint64_t)(PACK ? u.xfer_row : u.pool_row) * row * 16u);
     store16<SP>(dst + off, load16<NTL>(src + off));
 }
-KVL_FLAT_KERNELS(kvl_flat_kernel, flat_body)
+
+template <bool PACK, bool NTL, int SP>
+__global__ void __launch_bounds__(1024) kvl_flat_kernel(KVL_FLAT_PARAMS, const TileMore more) {
+    flat_body<PACK, NTL, SP, false>(KVL_FLAT_ARGS, more);
+}
+
+template <bool PACK, bool NTL, int SP>
+__global__ void __launch_bounds__(1024) kvl_flat_kernel_short(KVL_FLAT_PARAMS, const TileMore more) {
+    flat_body<PACK, NTL, SP, true>(KVL_FLAT_ARGS, more);
+}
 
 // Row-map form for descriptors of a few rows: the transfer side is dense, so the launch is laid out over it
 // (lane g moves vector g of the range, lined up with the transfer buffer's 128-byte lines) and each row's
@@ -677,7 +677,7 @@ __global__ void __launch_bounds__(1024) kvl_any_walk_kernel(const CopyArgs a, ui
 
 // Flat, as kvl_flat_kernel: m lanes per descriptor (m = the most 16-byte windows that the largest one touches).
 template <bool PACK, bool NTL, int SP, bool SHORT>
-__device__ __forceinline__ void any_flat_body(KVL_FLAT_PARAMS) {
+__device__ __forceinline__ void any_flat_body(KVL_FLAT_PARAMS, uint32_t order, const TileMore &more) {
     if (blockIdx.y) {
         pool = more.pool[blockIdx.y - 1];
         xfer = more.xfer[blockIdx.y - 1];
@@ -690,7 +690,16 @@ __device__ __forceinline__ void any_flat_body(KVL_FLAT_PARAMS) {
     const uintptr_t dst = PACK ? in_xfer : in_pool;
     copy_any<NTL, SP>(PACK ? in_pool : in_xfer, dst, u.n_rows * row, (uint32_t)dst & 15u, off);
 }
-KVL_FLAT_KERNELS(kvl_any_flat_kernel, any_flat_body)
+
+template <bool PACK, bool NTL, int SP>
+__global__ void __launch_bounds__(1024) kvl_any_flat_kernel(KVL_FLAT_PARAMS, uint32_t order, const TileMore more) {
+    any_flat_body<PACK, NTL, SP, false>(KVL_FLAT_ARGS, order, more);
+}
+
+template <bool PACK, bool NTL, int SP>
+__global__ void __launch_bounds__(1024) kvl_any_flat_kernel_short(KVL_FLAT_PARAMS, uint32_t order, const TileMore more) {
+    any_flat_body<PACK, NTL, SP, true>(KVL_FLAT_ARGS, order, more);
+}
 
 // Storage layout <-> paged pool for one layer.  Same tiling as above; the far
 // side is a buffer of Full Blocks ([layer, tokens, bytes] per block), so a

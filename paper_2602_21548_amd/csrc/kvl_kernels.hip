@@ -191,10 +191,12 @@ template <bool PACK, bool NTL, int SP>
 static void launch_flat_one(dim3 g, dim3 b, const On &s, const CopyArgs &a, uint32_t m) {
     const uint32_t p = a.plane_begin;
     const TileDivisor d(m);
-#define KVL_FLAT(KERNEL, M, ORDER) \
-    KVL_LAUNCH((KERNEL<PACK, NTL, SP>), g, b, s, a.units + a.unit_begin, a.pool[p], a.xfer[p], a.row_elems[p], a.n_units, M, d.magic, d.shift, b.x, ORDER, more_planes(a, g.y))
-    if (m < kFlatShort) KVL_FLAT(kvl_flat_kernel_short, m, 0u);
-    else KVL_FLAT(kvl_flat_kernel, m, 0u);
+    const kvl_unit_t *units = a.units + a.unit_begin;
+    const TileMore more = more_planes(a, g.y);
+#define KVL_FLAT(KERNEL) KVL_LAUNCH((KERNEL<PACK, NTL, SP>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], a.n_units, m, d.magic, d.shift, b.x, more)
+    if (m < kFlatShort) KVL_FLAT(kvl_flat_kernel_short);
+    else KVL_FLAT(kvl_flat_kernel);
+#undef KVL_FLAT
 }
 
 template <bool PACK, bool NTL>
@@ -233,14 +235,14 @@ static void launch_any_one(bool flat, bool walk, dim3 g, dim3 b, const On &s, co
     const uint32_t order = tile_order(g.x, 16ull * b.x, run_bytes);
     const TileDivisor d(x);
     const uint32_t p = a.plane_begin;
-    if (flat && x < kFlatShort) KVL_FLAT(kvl_any_flat_kernel_short, x, order);
-    else if (flat) KVL_FLAT(kvl_any_flat_kernel, x, order);
-#undef KVL_FLAT
+    const kvl_unit_t *units = a.units + a.unit_begin;
+    const TileMore more = more_planes(a, g.y);
+#define KVL_ANY_FLAT(KERNEL) KVL_LAUNCH((KERNEL<PACK, NTL, SP>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], a.n_units, x, d.magic, d.shift, b.x, order, more)
+    if (flat && x < kFlatShort) KVL_ANY_FLAT(kvl_any_flat_kernel_short);
+    else if (flat) KVL_ANY_FLAT(kvl_any_flat_kernel);
     else if (walk) KVL_LAUNCH((kvl_any_walk_kernel<PACK, NTL, SP, SRC>), g, b, s, a, x, n_tiles, n_tiles > g.x ? 0u : order);
-    else {
-        KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, SRC>), g, b, s, a.units + a.unit_begin, a.pool[p], a.xfer[p], a.row_elems[p], x,
-                   d.magic, d.shift << 1, b.x, order, more_planes(a, g.y));
-    }
+    else KVL_LAUNCH((kvl_any_tile_kernel<PACK, NTL, SP, SRC>), g, b, s, units, a.pool[p], a.xfer[p], a.row_elems[p], x, d.magic, d.shift << 1, b.x, order, more);
+#undef KVL_ANY_FLAT
 }
 
 // Rows or addresses that are not multiples of 16 bytes (the planes of a launch have one row size).
