@@ -723,7 +723,7 @@ static int check_row_map_split() {
     kvl_plan_s p = made(n, 1, row);
     static uint32_t map;
     p.d_row_map = &map;
-    REQUIRE(takes_row_map(&p, row, true));
+    REQUIRE(rows_ahead(&p, row, true));
     uintptr_t xfer[KVL_MAX_PLANES] = {(1ull << 44) + 112};              // the widest line-up
     launches.clear();
     g_rows_right = true;
@@ -747,7 +747,8 @@ static int check_row_map_split() {
     return 0;
 }
 
-// Shapes on either side of the lines between the row map and the tiles; with the map the call measured faster, or not.
+// Planes of unlike rows: shapes on either side of the lines between the row map and the tiles (takes_row_map; one plane, or planes
+// alike, go by check_tile_rules).
 static int check_row_map_rule() {
     const struct { uint32_t row, bs, mb; bool gather, scatter; } shapes[] = {
         {1152, 1, 900, true, true}, {1152, 4, 900, true, true}, {2048, 1, 900, true, true}, {2048, 2, 900, false, false},
@@ -771,6 +772,184 @@ static int check_row_map_rule() {
         }
         p.d_units = nullptr;
     }
+    return 0;
+}
+
+// Launches of one plane by the sizes: kernel (T tiles, R row map) and store policy, lanes, KiB of an XCD's run (0: in order), of the
+// gather and of the scatter, on both sides of every limit; and of moves.
+static int check_tile_rules() {
+    struct Form { char kernel; int policy; uint32_t lanes, run_kib; };
+    const struct { uint32_t row, rows, mib; Form gather, scatter; } hops[] = {
+        // stores and lanes of small layers; plain loads of the scatter up to 112 MiB ('P')
+        {1152, 64, 11, {'T', 2, 128, 512}, {'T', 3, 128, 512}}, {1152, 64, 13, {'T', 2, 128, 512}, {'T', 1, 128, 512}},
+        {1152, 64, 21, {'T', 2, 128, 512}, {'T', 1, 128, 512}}, {1152, 64, 23, {'T', 2, 128, 512}, {'T', 3, 128, 512}},
+        {1152, 1, 11, {'R', 2, 256, 512}, {'R', 3, 256, 512}}, {1152, 1, 13, {'R', 2, 256, 512}, {'R', 1, 256, 512}},
+        {1152, 64, 27, {'T', 2, 128, 512}, {'T', 3, 128, 512}}, {1152, 64, 29, {'T', 2, 256, 512}, {'T', 3, 256, 512}},
+        {656, 64, 13, {'T', 2, 128, 512}, {'P', 3, 128, 512}}, {656, 64, 111, {'T', 2, 256, 512}, {'P', 3, 256, 512}},
+        {656, 64, 113, {'T', 2, 256, 512}, {'T', 3, 256, 512}},
+        // tiles of 256 lanes badly filled: one wavefront in runs, 128 lanes in order
+        {1152, 16, 29, {'T', 2, 64, 512}, {'T', 3, 64, 512}}, {1152, 16, 223, {'T', 2, 64, 512}, {'T', 3, 64, 512}},
+        {1152, 16, 225, {'T', 2, 128, 0}, {'T', 3, 128, 0}}, {768, 40, 225, {'T', 2, 128, 0}, {'T', 3, 128, 0}},
+        // small blocks of whole lines in order from 224 MiB (48 KiB are none); rows by the map likewise beyond the on-die cache
+        {640, 64, 223, {'T', 2, 256, 512}, {'T', 3, 256, 512}}, {640, 64, 225, {'T', 2, 256, 0}, {'T', 3, 256, 0}},
+        {768, 64, 225, {'T', 2, 256, 512}, {'T', 3, 256, 512}}, {1152, 1, 223, {'R', 2, 256, 512}, {'R', 3, 256, 512}},
+        {1152, 1, 225, {'R', 2, 256, 0}, {'R', 3, 256, 0}}, {656, 4, 600, {'R', 2, 256, 512}, {'R', 1, 256, 512}},
+        // the scatter by the row map in layers a little larger than the on-die cache
+        {1152, 64, 243, {'T', 2, 256, 512}, {'T', 3, 256, 512}}, {1152, 64, 245, {'T', 2, 256, 512}, {'R', 3, 256, 512}},
+        {1152, 64, 258, {'T', 2, 256, 512}, {'R', 3, 256, 0}}, {1152, 64, 479, {'T', 2, 256, 256}, {'R', 3, 256, 0}},
+        {1152, 64, 481, {'T', 2, 256, 256}, {'T', 3, 256, 256}}, {656, 64, 243, {'T', 2, 256, 512}, {'T', 3, 256, 512}},
+        {656, 64, 245, {'T', 2, 256, 512}, {'R', 1, 256, 512}}, {656, 64, 431, {'T', 2, 256, 256}, {'R', 1, 256, 512}},
+        {656, 64, 433, {'T', 2, 256, 256}, {'T', 3, 256, 256}}, {384, 64, 300, {'T', 2, 256, 0}, {'T', 3, 256, 0}},
+        {512, 64, 300, {'T', 2, 256, 0}, {'R', 3, 256, 0}}, {32, 500, 300, {'T', 2, 256, 256}, {'T', 3, 256, 256}},
+        {48, 500, 300, {'T', 2, 256, 256}, {'R', 1, 256, 512}},
+        // longer layers, shorter runs; short blocks off the lines longest
+        {1152, 64, 287, {'T', 2, 256, 512}, {'R', 3, 256, 0}}, {1152, 64, 289, {'T', 2, 256, 256}, {'R', 3, 256, 0}},
+        {1152, 64, 511, {'T', 2, 256, 256}, {'T', 3, 256, 256}}, {1152, 64, 513, {'T', 2, 64, 128}, {'T', 3, 64, 128}},
+        {656, 64, 511, {'T', 2, 256, 256}, {'T', 3, 256, 256}}, {656, 64, 513, {'T', 2, 64, 128}, {'T', 3, 64, 128}},
+        {656, 16, 511, {'T', 2, 64, 256}, {'T', 3, 64, 256}}, {656, 16, 513, {'T', 2, 64, 1024}, {'T', 3, 64, 1024}},
+        {80, 256, 513, {'T', 2, 64, 128}, {'T', 3, 64, 128}}, {48, 256, 513, {'T', 2, 64, 1024}, {'T', 3, 64, 1024}},
+        {768, 40, 513, {'T', 2, 64, 0}, {'T', 3, 64, 0}}, {512, 64, 2000, {'T', 2, 256, 0}, {'T', 3, 256, 0}},
+        // descriptors of a few hundred vectors
+        {1152, 4, 60, {'R', 2, 256, 512}, {'R', 3, 256, 512}}, {1152, 5, 60, {'T', 2, 64, 512}, {'T', 3, 64, 512}},
+        {656, 14, 60, {'R', 2, 256, 512}, {'R', 1, 256, 512}}, {656, 15, 60, {'T', 2, 64, 512}, {'P', 3, 64, 512}},
+        {272, 16, 60, {'R', 2, 256, 512}, {'R', 1, 256, 512}}};
+    fake::watch = [](const fake::Launch &l, void **args) { is(l, "kvl_rows_kernel") ? watch_order<7>(l, args) : watch_order<8>(l, args); };
+    uintptr_t xfer[KVL_MAX_PLANES] = {1ull << 44, 1ull << 45};
+    for (const auto &q : hops)
+        for (bool gather : {true, false})
+            for (uint32_t planes : {1u, 2u}) {              // planes alike go as one does
+                const Form &f = gather ? q.gather : q.scatter;
+                const uint32_t n = (uint32_t)(((uint64_t)q.mib << 20) / (q.rows * q.row * planes));
+                kvl_plan_s p = alike(n, q.rows, q.row, planes);
+                p.d_row_map = &g_map;
+                launches.clear();
+                REQUIRE(launch_units(&p, gather, 0, n, 0, planes, kPlanes, xfer, nullptr) == KVL_OK);
+                const std::string policy = std::to_string(f.policy), tile = gather ? "kvl_pack_quick_tile_kernel<1, " : "kvl_unpack_quick_tile_kernel<1, ";
+                const std::string kernel = f.kernel == 'R' ? std::string("kvl_rows_kernel<") + (gather ? "true" : "false") + ", true, " + policy + ", "
+                                                           : tile + (f.kernel == 'P' ? "false, " : "true, ") + policy + ">";
+                if (launches.size() != 1 || !is(launches[0], kernel.c_str()) || launches[0].block.x != f.lanes || launches[0].grid.y != planes ||
+                    g_run_bytes != f.run_kib * 1024) {
+                    std::printf("%u by %u, %u MiB, %u planes, %s: %s, %u lanes, runs of %llu KiB\n", q.row, q.rows, q.mib, planes, gather ? "gather" : "scatter",
+                                launches[0].kernel.c_str(), launches[0].block.x, (unsigned long long)g_run_bytes >> 10);
+                    return 1;
+                }
+                p.d_units = nullptr;
+            }
+    const struct { uint32_t row, rows, mib, policy, lanes, run_kib; } moves[] = {
+        {1152, 64, 22, 3, 64, 0}, {1152, 64, 24, 1, 64, 0}, {1152, 64, 75, 1, 64, 0}, {1152, 64, 77, 3, 64, 0}, {1152, 64, 95, 3, 64, 0},
+        {1152, 64, 97, 3, 64, 256}, {1152, 64, 1023, 3, 64, 256}, {1152, 64, 1025, 3, 64, 512}, {656, 64, 22, 3, 256, 256}, {656, 64, 24, 1, 256, 256},
+        {656, 64, 75, 1, 256, 256}, {656, 64, 77, 3, 256, 256}, {656, 64, 1025, 3, 256, 512}, {640, 64, 223, 3, 64, 256}, {640, 64, 225, 3, 64, 0},
+        {640, 64, 1025, 3, 64, 0}, {656, 32, 300, 3, 128, 256}};
+    for (const auto &q : moves) {
+        const uint32_t n = (uint32_t)(((uint64_t)q.mib << 20) / (q.rows * q.row));
+        kvl_plan_s p = alike(n, q.rows, q.row);
+        p.paired = true;
+        launches.clear();
+        REQUIRE(launch_units(&p, true, 0, n, 0, 1, kPlanes, xfer, nullptr) == KVL_OK);
+        const std::string kernel = "kvl_pack_quick_tile_kernel<1, true, " + std::to_string(q.policy) + ">";
+        if (launches.size() != 1 || !is(launches[0], kernel.c_str()) || launches[0].block.x != q.lanes || g_run_bytes != q.run_kib * 1024) {
+            std::printf("move %u by %u, %u MiB: %s, %u lanes, runs of %llu KiB\n", q.row, q.rows, q.mib, launches[0].kernel.c_str(), launches[0].block.x,
+                        (unsigned long long)g_run_bytes >> 10);
+            return 1;
+        }
+        p.d_units = nullptr;
+    }
+    // descriptors that are not alike: wide workgroups; a cap: a walk
+    kvl_plan_s p = alike(20000, 64, 1152);
+    p.max_unit_rows = 128;
+    launches.clear();
+    REQUIRE(launch_units(&p, true, 0, 20000, 0, 1, kPlanes, xfer, nullptr) == KVL_OK && is(launches[0], "quick_tile") && launches[0].block.x == 256);
+    p.tuning.max_groups = 1000;
+    fake::watch = nullptr;
+    launches.clear();
+    REQUIRE(launch_units(&p, true, 0, 20000, 0, 1, kPlanes, xfer, nullptr) == KVL_OK && is(launches[0], "kvl_tile_walk_kernel") && groups(launches[0]) == 1000);
+    p.d_units = nullptr;
+    return 0;
+}
+
+// Flat launches, of whole vectors and of odd rows: fewer than 2^31 lanes each (a descriptor is found by a multiplication that is
+// exact up to there), the launches' descriptors following one another with none left out.
+static const kvl_unit_t *g_next;
+static bool g_flat_right;
+static int check_flat_split() {
+    fake::watch = [](const fake::Launch &l, void **args) {
+        const kvl_unit_t *units = *(const kvl_unit_t **)args[0];
+        const uint64_t n = *(uint32_t *)args[4], m = *(uint32_t *)args[5], lanes = (uint64_t)l.grid.x * l.block.x;
+        g_flat_right = g_flat_right && units == g_next && n * m <= lanes && lanes < (1ull << 31) && *(uint32_t *)args[8] == l.block.x;
+        g_next += n;
+    };
+    const struct { uint32_t n, row; bool move; const char *kernel; uint32_t launches; } shapes[] = {
+        {17000000, 2048, false, "kvl_flat_kernel<", 2}, {17000000, 2048, true, "kvl_flat_kernel<", 2}, {14000000, 2535, false, "kvl_any_flat_kernel<", 2},
+        {14000000, 2535, true, "kvl_any_flat_kernel<", 2}, {16000000, 2048, false, "kvl_flat_kernel<", 1}, {13000000, 2535, false, "kvl_any_flat_kernel<", 1},
+        {100000, 16, true, "kvl_flat_kernel_short<", 1}, {100000, 33, false, "kvl_any_flat_kernel_short<", 1}};
+    for (const auto &q : shapes) {
+        kvl_plan_s p = made(q.n, 1, q.row);
+        p.paired = q.move;
+        uintptr_t to[KVL_MAX_PLANES] = {1ull << 44};
+        for (uint32_t first : {0u, 5u}) {
+            g_flat_right = true;
+            g_next = p.d_units + first;
+            launches.clear();
+            REQUIRE(launch_units(&p, true, first, q.n, 0, 1, kPlanes, to, nullptr) == KVL_OK);
+            REQUIRE(g_flat_right && g_next == p.d_units + q.n && launches.size() == q.launches);
+            for (const fake::Launch &l : launches) REQUIRE(is(l, q.kernel));
+        }
+        p.d_units = nullptr;
+    }
+    fake::watch = nullptr;
+    return 0;
+}
+
+// Full Blocks of planes alike: a plane's tiles to a row of the grid, every plane with its own pool and its own part of the blocks.
+struct QuickArgs {
+    uintptr_t pool[KVL_MAX_PLANES], blocks[KVL_MAX_PLANES];
+    uint32_t fb_vecs, row, tiles, threads, tokens;
+};
+static QuickArgs g_quick;
+static int check_full_blocks_alike() {
+    const uint64_t base = 1ull << 44, offset = 3 * 4096;
+    const struct { uint32_t row, rows, planes, off, lanes, tiles; } shapes[] = {{1152, 64, 1, 0, 256, 18}, {1152, 64, 1, 16, 256, 19}, {2048, 64, 2, 0, 256, 32},
+                                                                                {336, 16, 1, 0, 128, 3}, {336, 100, 4, 0, 256, 9}, {80, 256, 3, 48, 256, 6}};
+    for (const auto &q : shapes)
+        for (bool to_pool : {true, false}) {
+            kvl_plan_s p = alike(3000, q.rows, q.row, q.planes);
+            const uint64_t pitch = 61ull * q.planes * q.rows * q.row;
+            fake::watch = [](const fake::Launch &, void **args) {
+                const TileMore &more = *(const TileMore *)args[11];
+                g_quick.pool[0] = *(uintptr_t *)args[1];
+                g_quick.blocks[0] = *(uintptr_t *)args[2];
+                for (uint32_t k = 1; k < KVL_MAX_PLANES; ++k) {
+                    g_quick.pool[k] = more.pool[k - 1];
+                    g_quick.blocks[k] = more.xfer[k - 1];
+                }
+                g_quick.fb_vecs = *(uint32_t *)args[3];
+                g_quick.row = *(uint32_t *)args[4];
+                g_quick.tiles = *(uint32_t *)args[5];
+                g_quick.threads = *(uint32_t *)args[7] & 0xffff;
+                g_quick.tokens = *(uint32_t *)args[8];
+                watch_order<10>(launches.back(), args);
+            };
+            launches.clear();
+            REQUIRE(fullblock_launch(&p, to_pool, base + q.off, pitch, offset, 0, 3000, kPlanes, nullptr) == KVL_OK);
+            fake::watch = nullptr;
+            if (launches.size() != 1 || !is(launches[0], to_pool ? "kvl_fullblock_quick_kernel<true>" : "kvl_fullblock_quick_kernel<false>") ||
+                launches[0].block.x != q.lanes || g_quick.threads != q.lanes || g_quick.tiles != q.tiles) {
+                std::printf("%u by %u, %u planes: %s, %u lanes, %u tiles\n", q.row, q.rows, q.planes, launches[0].kernel.c_str(), launches[0].block.x, g_quick.tiles);
+                return 1;
+            }
+            REQUIRE(launches[0].grid.x == 3000 * q.tiles && launches[0].grid.y == q.planes && g_run_bytes == 256 * 1024);
+            REQUIRE(g_quick.fb_vecs == pitch / 16 && g_quick.row == q.row / 16 && g_quick.tokens == q.rows);
+            for (uint32_t k = 0; k < q.planes; ++k)
+                REQUIRE(g_quick.pool[k] == (uintptr_t)kPlanes[k] && g_quick.blocks[k] == base + q.off + offset + (uint64_t)k * q.rows * q.row);
+            // in the general kernel: bytes off the vectors, the host link, a walk, a pitch beyond 32 bits
+            for (int other = 0; other < 4; ++other) {
+                launches.clear();
+                p.tuning.max_groups = other == 2 ? 7 : 0;
+                REQUIRE(fullblock_launch(&p, to_pool, base + (other == 0), other == 3 ? 1ull << 36 : pitch, offset, 0, 3000, kPlanes, nullptr, other == 1) == KVL_OK);
+                REQUIRE(launches.size() == 1 && is(launches[0], "kvl_fullblock_kernel<"));
+            }
+            p.d_units = nullptr;
+        }
     return 0;
 }
 
@@ -798,6 +977,9 @@ int main(int argc, char **argv) {
         {"small_gathers", check_small_gathers},
         {"odd_rows_order", check_odd_rows_order},
         {"variants_order", check_variants_order},
+        {"tile_rules", check_tile_rules},
+        {"flat_split", check_flat_split},
+        {"full_blocks_alike", check_full_blocks_alike},
     };
     if (argc != 2 || !checks.count(argv[1])) {
         for (const auto &c : checks) std::printf("%s\n", c.first.c_str());

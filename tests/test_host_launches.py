@@ -15,7 +15,8 @@ ENV.pop("LD_PRELOAD", None)
 CHECKS = ["move_shapes", "full_block_planes", "capped_odd_rows", "capped_full_blocks", "large_odd_layers", "full_block_lanes",
           "caller_syncs", "row_map_under_capture", "row_map_on_two_streams", "default_stream", "cached_arrays",
           "ceiling_policies", "planes_by_rows", "planes_lanes", "planes_layout", "row_map_split", "tile_divisor",
-          "row_map_rule", "tile_order", "small_gathers", "odd_rows_order", "variants_order"]
+          "row_map_rule", "tile_order", "small_gathers", "odd_rows_order", "variants_order",
+          "tile_rules", "flat_split", "full_blocks_alike"]
 
 
 @pytest.fixture(scope="module")
