@@ -96,7 +96,7 @@ def test_odd_rows_in_two_planes_of_whole_lines(row, mb):
 # layers that the on-die cache holds in part: both tiles begin on the source's lines, the gather's have 64 lanes, the scatter's
 # 256 or 128; beyond that they pass the cache by.  161 windows are the first that are tiled; spans of one line and two tiles
 @pytest.mark.parametrize("bs,row,mb,tuning", [(64, 333, 78, {}), (16, 333, 78, {}), (64, 132, 78, dict(max_groups=999)), (1, 2547, 78, {}),
-                                              (8, 1009, 78, dict(block_threads=512)), (64, 1026, 642, {})])
+                                              (8, 1009, 78, dict(block_threads=512)), (64, 132, 262, {}), (64, 1026, 642, {})])
 @pytest.mark.parametrize("x_off,pool_off", [(0, 0), (13, 19)])
 def test_odd_rows_of_layers_that_are_read_once(bs, row, mb, tuning, x_off, pool_off):
     w = _uniform(3, (mb << 20) // row // 3, bs, row)
@@ -104,8 +104,6 @@ def test_odd_rows_of_layers_that_are_read_once(bs, row, mb, tuning, x_off, pool_
     hop_at(w, x_off, pool_off, **tuning)
 
 
-# rows of 1, 15, 16, 31, 32, 63, 64, 65 and 72 vectors (how many rows a wavefront's 64 vectors can touch changes at
-# 16, 32 and 64), one to a few to a block, with and without chance neighbours merged into longer descriptors
 # lanes of a descriptor around the numbers from which a wavefront's lie in at most five, three and two of them
 @pytest.mark.parametrize("row", [225, 226, 481, 482, 977, 978, 994])
 @pytest.mark.parametrize("kind", ["fragmented", "runs"])
@@ -121,6 +119,8 @@ def test_vectors_dealt_out_flat(lanes, store):
     hop_at(w, 16, 32, variant=1 + (128 | 4 | store << 3), max_groups=3, block_threads=64)
 
 
+# rows of 1, 15, 16, 31, 32, 63, 64, 65 and 72 vectors (how many rows a wavefront's 64 vectors can touch changes at
+# 16, 32 and 64), one to a few to a block, with and without chance neighbours merged into longer descriptors
 @pytest.mark.parametrize("row", [16, 240, 256, 496, 512, 1008, 1024, 1040, 1152])
 @pytest.mark.parametrize("bs,kind", [(1, "runs"), (1, "random"), (3, "fragmented"), (7, "runs")])
 @pytest.mark.parametrize("x_off", [0, 48])
@@ -288,8 +288,8 @@ def test_full_blocks_on_lines_of_the_source(bs, rows, first):
         assert same_bytes(to_host(a), b), "load differs from the oracle"
 
 
-# layers around a gibibyte, beyond which the tiles start late, with an odd number of tiles to a descriptor, tiles on lines and
-# off them, and a second plane
+# layers around a gibibyte, in runs and in workgroups of one wavefront, with an odd number of tiles to a descriptor, tiles on lines
+# and off them, and a second plane
 @pytest.mark.parametrize("bs,rows", [(64, (656,)), (40, (2048, 2048))])
 @pytest.mark.parametrize("mb", [1023, 1026])
 def test_tiles_of_layers_around_a_gibibyte(bs, rows, mb):
@@ -298,19 +298,23 @@ def test_tiles_of_layers_around_a_gibibyte(bs, rows, mb):
     hop_at(w, 0)
 
 
-# a move's own workgroups: 64 lanes, 128, and 1024 flat; descriptors around one wavefront and one workgroup
-# tiles in runs: just below, at and above whole rounds of eight runs (of 512 KiB: 1024 tiles of 256 lanes, 2048 of 128), one plane and two
-@pytest.mark.parametrize("bs,rows", [(64, (1152,)), (64, (656,)), (32, (256, 256)), (256, (80,))])
-@pytest.mark.parametrize("mb", [4, 30])
+# tiles in runs: a block's tiles below, at and above whole rounds of eight runs (of 512 KiB), one plane and two, with the lanes of
+# layers up to 28 MiB (128) and beyond (256, or 64 where that leaves fewer without work)
+@pytest.mark.parametrize("bs,rows,lanes", [(64, (1152,), 256), (64, (656,), 256), (32, (256, 256), 256), (256, (80,), 64)])
+@pytest.mark.parametrize("rounds", [1, 8])
 @pytest.mark.parametrize("more", [-1, 0, 1])
-def test_tiles_around_whole_rounds(bs, rows, mb, more):
+def test_tiles_around_whole_rounds(bs, rows, lanes, rounds, more):
     vectors = bs * rows[0] // 16 + (7 if rows[0] % 128 else 0)
-    threads = 128 if mb < 28 else 256
+    threads = 128 if rounds == 1 else lanes
     tiles = -(-vectors // threads)
     per_round = (8 << 19) // (16 * threads)
-    rounds = max(1, round(mb * 2**20 / len(rows) / (8 << 19)))
+    if rounds > 1:
+        rounds //= len(rows)
     blocks = rounds * per_round // tiles + more
-    hop_at(_uniform(1, blocks * bs, bs, *rows), 48 if rows[0] % 128 else 128)
+    w = _uniform(1, blocks * bs, bs, *rows)
+    assert (oracle.payload_bytes(w.hit, w.layout.row_bytes) <= 28 << 20) == (threads == 128)
+    assert abs(blocks * tiles - rounds * per_round) <= 2 * tiles
+    hop_at(w, 48 if rows[0] % 128 else 128)
 
 
 # layers that the gather leaves in the L2 caches and the next larger ones, by tiles, by the row map and of odd rows
@@ -336,6 +340,7 @@ def test_short_blocks_of_large_layers_in_long_runs(bs, row):
     hop_at(_uniform(5, (517 << 20) // 5 // row + 77, bs, row), 48)
 
 
+# a move's own workgroups: 64 lanes, 128, and 1024 flat; descriptors around one wavefront and one workgroup
 @pytest.mark.parametrize("bs,rows", [(1, (16,)), (1, (1152,)), (1, (656, 128)), (2, (1024,)), (1, (2048,)), (1, (2064,)), (16, (1152, 656)),
                                      (64, (656,)), (3, (37,)), (64, (132, 132))])
 def test_move_launch_shapes(bs, rows):
