@@ -105,7 +105,7 @@ constexpr uint64_t kNtMoveBytes = 23u << 20, kNtMoveEndBytes = 76u << 20;
 inline bool move_nt(uint64_t payload) { return payload > kNtMoveBytes && payload <= kNtMoveEndBytes; }
 // Tiles of one plane, or of planes alike: their lanes and their order by the layer's size (hop_threads, tile_run_bytes).
 constexpr uint64_t kNarrowBytes = 28u << 20, kWaveTileBytes = 512u << 20, kLongRunBytes = 288u << 20;
-constexpr uint64_t kOrderBytes = 224u << 20, kOrderBlockBytes = 48u << 10, kVeryLongRunBlockBytes = 14u << 10, kMoveRunBytes = 96u << 20, kMoveLongRunBytes = 1u << 30, kRowsRunBytes = 512u << 10, kOddOrderBytes = 48u << 20;
+constexpr uint64_t kOrderBytes = 224u << 20, kOrderBlockBytes = 48u << 10, kVeryLongRunBlockBytes = 14u << 10, kMoveRunBytes = 96u << 20, kRowsRunBytes = 512u << 10, kOddOrderBytes = 48u << 20;
 constexpr uint64_t kFlatOrderBytes = 160u << 20, kOnDieBytes = 256u << 20;
 // Up to this payload planes of unlike rows share a launch (kvl_planes_kernel): beyond it a launch of their own is less than a
 // hundredth of their time, and each plane better off in the form that suits it (hops apart / at once, 2048- and 656-byte
@@ -166,14 +166,15 @@ inline LayerShape shape_of(const kvl_plan_s *plan) {
 //  - short blocks off the lines in large layers like them longest: hops with buffers of their own, runs of 128 / 512 / 1024 / 2048 KiB, 400 by
 //    24, 620 MB 418 / 409 / 405 / 406, 2.6 GB 1775 / 1754 / 1746 / 1749; 176 by 64, 620 MB 419 / 411 / 408 / 407, 5.2 GB 3479 / 3466 / 3455 /
 //    3456; 272 by 64 (17 KB), 2.6 GB 1766 / 1782 / 1779 / 1785; 656 by 64, 1.0 GB 642 / 648 / 651 / 652.
-//  - moves: 656 by 64, 613 MB 194 / 192 / 191 / 191, 3.3 GB 1078 / 1067 / 1055 / 1050; 2048 + 2048 by 64, 521 MB 157 / 153 / 154 /
-//    153; 1152 by 64, 27 MB 9.9 / 9.9 / 10.0 / 10.0, 223 MB 68.2 / 68.3 / 67.9 / 68.1, 2.7 GB 805 / 819 / 812 / 804.
+//  - moves of three pairs of pools: 2048 + 2048 by 64, 62 MB 20.5 / 20.5 / 20.1 / 20.25, 114 MB 36.0 / 35.4 / 35.5 / 35.5, 413 MB 126.1 / 122.1 / 122.4 /
+//    122.0, 2.8 GB 849 / 810 / 810 / 810; 512 by 256, 723 MB 219.3 / 211.7 / 211.9 / 212.0; 656 by 64, 114 MB 37.4 / 37.0 / 37.0 / 37.2, 723 MB 228.0 /
+//    225.1 / 223.5 / 224.0, 2.8 GB 894 / 879 / 867 / 866; 1152 by 64 level up to 723 MB (218.8 / 218.0 / 217.8 / 217.3), 2.8 GB 844 / 852 / 843 / 839.
 inline uint64_t tile_run_bytes(const LayerShape &s, uint32_t row_bytes) {
     const bool lines = row_bytes % 128 == 0;
     const double descriptor_bytes = (double)s.tokens * row_bytes / (double)s.units;
     const bool small_blocks = descriptor_bytes < (double)kOrderBlockBytes;
     if (lines && small_blocks && s.payload > kOrderBytes) return 0;
-    if (s.paired) return s.payload > kMoveLongRunBytes ? 512u << 10 : !lines || s.payload > kMoveRunBytes ? 256u << 10 : 0;
+    if (s.paired) return !lines || s.payload > kMoveRunBytes ? 256u << 10 : 0;
     if (s.payload > kWaveTileBytes && descriptor_bytes < (double)kVeryLongRunBlockBytes) return 1u << 20;
     return s.payload <= kLongRunBytes ? 512u << 10 : s.payload <= kWaveTileBytes ? 256u << 10 : 128u << 10;
 }

@@ -837,8 +837,8 @@ static int check_tile_rules() {
             }
     const struct { uint32_t row, rows, mib, policy, lanes, run_kib; } moves[] = {
         {1152, 64, 22, 3, 64, 0}, {1152, 64, 24, 1, 64, 0}, {1152, 64, 75, 1, 64, 0}, {1152, 64, 77, 3, 64, 0}, {1152, 64, 95, 3, 64, 0},
-        {1152, 64, 97, 3, 64, 256}, {1152, 64, 1023, 3, 64, 256}, {1152, 64, 1025, 3, 64, 512}, {656, 64, 22, 3, 256, 256}, {656, 64, 24, 1, 256, 256},
-        {656, 64, 75, 1, 256, 256}, {656, 64, 77, 3, 256, 256}, {656, 64, 1025, 3, 256, 512}, {640, 64, 223, 3, 64, 256}, {640, 64, 225, 3, 64, 0},
+        {1152, 64, 97, 3, 64, 256}, {1152, 64, 1023, 3, 64, 256}, {1152, 64, 1025, 3, 64, 256}, {656, 64, 22, 3, 256, 256}, {656, 64, 24, 1, 256, 256},
+        {656, 64, 75, 1, 256, 256}, {656, 64, 77, 3, 256, 256}, {656, 64, 1025, 3, 256, 256}, {640, 64, 223, 3, 64, 256}, {640, 64, 225, 3, 64, 0},
         {640, 64, 1025, 3, 64, 0}, {656, 32, 300, 3, 128, 256}};
     for (const auto &q : moves) {
         const uint32_t n = (uint32_t)(((uint64_t)q.mib << 20) / (q.rows * q.row));
