@@ -30,19 +30,22 @@
 //           descriptors far smaller than a workgroup (token-granular pools)
 // All of them take their tiles in order (tile_number).
 // The default is the tiled form, or the row-map form (kvl_rows_kernel, for plans that have a
-// map) where takes_row_map says so; without a map, descriptors of less than half a workgroup
-// go flat: on single-token blocks of 1152 bytes the tiled form leaves 72 % of its lanes idle.
+// map) where rows_ahead says so (for planes of unlike rows takes_row_map); without a map,
+// descriptors of less than half a workgroup go flat: on single-token blocks of 1152 bytes the tiled form in workgroups
+// of 256 lanes leaves 72 % of them idle.
 // Measured on MI355X (5.2 GB of 72 KiB blocks in random order), the tiled form
-// with one vector per lane and 256-lane workgroups is the fastest: it leaves no
+// with one vector per lane is the fastest: it leaves no
 // dependency between a lane's memory operations and lets the hardware fill the
-// memory system with resident wavefronts.  Cache policies, measured with gather
+// memory system with resident wavefronts.  Its lanes (64 in large layers) and the order of its tiles are
+// chosen by hop_threads, move_threads and tile_run_bytes.  Cache policies, measured with gather
 // and scatter alternating as they do in use: the gather (random reads,
 // sequential writes) runs best with non-temporal loads and sc1 stores; the
 // scatter (sequential reads, random writes) with sc1+nt stores and non-temporal
 // loads, plain ones where rows that are not multiples of 128 bytes make neighbouring
 // wavefronts share source lines and the layer is small enough for the on-die cache
 // still to hold them (kPlainReadBackBytes).  Together the policies are worth 5-15 % over plain
-// loads and stores.  With rows that are not multiples of 128 bytes the tiles are
+// loads and stores.  Layers of a few MB store otherwise: see gather_stays, scatter_nt and move_nt.  With rows that
+// are not multiples of 128 bytes the tiles are
 // also lined up with the destination's cache lines (worth 5-9 % on 656-byte rows).
 #pragma once
 
@@ -187,7 +190,7 @@ __device__ __forceinline__ kvl_unit_t fetch_unit(const kvl_unit_t *units, uint32
 
 // The tile that workgroup b takes.  Workgroups go round the eight XCDs, each with an L2 of its own, so taken in order the tiles of
 // a block are dealt to all of them: a line that two tiles share is read by two XCDs, and every XCD works on every page.  Here an
-// XCD takes runs of 2^shift tiles one after the other (a run is kRun*Bytes long), the runs going round the XCDs, from one round to
+// XCD takes runs of 2^shift tiles one after the other (how long: tile_run_bytes, launch_any), the runs going round the XCDs, from one round to
 // the next by one place on; the tiles behind the last whole round keep their order.  `order` is the number of tiles in whole
 // rounds, a multiple of 16, with the shift in its low bits; 0 leaves the order as it is.  Hops, us, in order / in runs: 1152-byte
 // rows by 64, 149 MB 84.9 / 82.8, contiguous 2.7 GB 1580 / 1522; 656 by 64, 186 MB 110.6 / 104.7, 11 GB 6913 / 6710, contiguous
@@ -796,6 +799,8 @@ __global__ void __launch_bounds__(256) kvl_fullblock_kernel(const FullBlockArgs 
 // the descriptor in one load, no division, tiles in runs, as in the quick tiles above.  Both directions of four layers of 16, us, before /
 // so: 1152-byte rows by 64, 10 MB a layer 42.3 / 36.9, 25 MB 74.0 / 67.6, 88 MB 218 / 207; 1152 by 16, 10 MB 43.2 / 36.2; 496 by 1, 27 MB
 // 138 / 125; 4096 by 64 (Layer Blocks 4 MiB apart), 24 MB 81.6 / 64.6, 211 MB 583 / 464.
+// In small layers, where the host's part of a call is most of it, ahead too: the eight calls of four layers of 1152 by 64 on the default stream,
+// 0.3 MB 32.1 / 26.7, 2.2 MB 32.9 / 26.0, 5.3 MB 37.7 / 30.0; in a HIP graph 0.3 MB 15.4 / 14.3, 2.2 MB 24.8 / 18.6, 4.6 MB 28.9 / 21.5.
 template <bool TO_POOL>
 __global__ void __launch_bounds__(256) kvl_fullblock_quick_kernel(const kvl_unit_t *units, uintptr_t pool, uintptr_t blocks, uint32_t fb_vecs,
                                                                   uint32_t row, uint32_t tiles_per_unit, uint32_t magic, uint32_t shift_threads,

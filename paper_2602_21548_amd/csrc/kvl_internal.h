@@ -210,8 +210,9 @@ inline uint32_t move_threads(const kvl_plan_s *plan, uint32_t row_bytes) {
     return row_bytes % 128 == 0 && alike ? 64 : tile_threads(largest);
 }
 
-// Whether a launch over planes of this row size is laid out over the transfer rows (kvl_rows_kernel) instead of over
-// the descriptors' tiles, which have the size of the largest descriptor's.  Measured on hops of one plane, 16 requests of
+// Whether a launch over planes of unlike rows, one of this size among them, is laid out over the transfer rows (launch_planes) instead
+// of over the descriptors' tiles, which have the size of the largest descriptor's.  (One plane, or planes alike, go as rows_ahead
+// says.)  Measured on hops of one plane by tiles in order, 16 requests of
 // uneven length, random tables, three layers each with its own plan and buffers in turn; us a hop, tiles / rows:
 //  - tiles that would leave lanes idle, and descriptors of less than a workgroup: by rows both ways.  1 GB, 1152-byte rows
 //    by 1 (72 vectors) 747 / 579, by 4 (1.1 tiles) 630 / 580, by 8 (2.25 tiles) 577 / 575, by 10 569 / 574; 2048 by 1 779 /
