@@ -100,7 +100,8 @@ constexpr uint64_t kNtScatterFromBytes = 12u << 20, kNtScatterBytes = 22u << 20;
 inline bool scatter_nt(bool lines, uint64_t payload) { return lines && payload > kNtScatterFromBytes && payload <= kNtScatterBytes; }
 // Likewise a move's stores between these two.  Moves of three pairs of pools, us, sc1+nt / nt: 656-byte rows by 64, 14.5 MB 5.7 / 5.8, 20.7 MB
 // 7.7 / 7.7, 25.8 MB 9.9 / 9.4, 33 MB 12.25 / 11.5, 46.5 MB 16.4 / 15.9, 77.5 MB 25.8 / 25.4, 134 MB 43.0 / 43.0, 207 MB 64.8 / 65.5; 1152 by 64
-// 25.8 MB 9.9 / 9.3, 33 MB 12.1 / 11.4, 77.5 MB 25.2 / 24.8, 207 MB 62.9 / 63.4.
+// 25.8 MB 9.9 / 9.3, 33 MB 12.1 / 11.4, 77.5 MB 25.2 / 24.8, 207 MB 62.9 / 63.4.  On a stream of the caller's and in a HIP graph 1152 by 64, 31 MB
+// 11.1 / 10.7 and 11.5 / 11.0, 400 by 16, 49 MB 18.1 / 18.05 and 43 MB 16.4 / 16.1, but 656 by 64, 25 MB 9.4 / 9.6 and 9.3 / 9.4.
 constexpr uint64_t kNtMoveBytes = 23u << 20, kNtMoveEndBytes = 76u << 20;
 inline bool move_nt(uint64_t payload) { return payload > kNtMoveBytes && payload <= kNtMoveEndBytes; }
 // Tiles of one plane, or of planes alike: their lanes and their order by the layer's size (hop_threads, tile_run_bytes).
